@@ -150,7 +150,12 @@ typedef struct {
  * short items, whenever dense_split > 1 is forced,
  * the block shape is not the kernels' or no device is present.  1 and 3
  * need the kernels' block shape (SVD_ERR_UNSUPPORTED otherwise) and a device
- * (SVD_ERR_HIP).  The split of the dense heads is still chosen and its scratch
+ * (SVD_ERR_HIP).  Where the choice is the library's, svd_attn_forward_planned may also
+ * run the layer from a table of items: one launch of work-groups, each with the
+ * (head, query tile, key range) its record in the workspace names, long items cut
+ * into chunks that a second launch merges; most layers run that way, the long
+ * D = 128 ones through the layer kernel.  svd_plan_single_launch keeps reporting
+ * the form named above.  The split of the dense heads is still chosen and its scratch
  * still part of the workspace: the FP8 forward pass and the per-group entry
  * points run such a plan group by group.
  * no_fork: 1 = grouped launches always run one after the other on the caller's
@@ -192,7 +197,9 @@ svd_status svd_plan_dense_split(const svd_plan* plan, int32_t* dense_split);
 /* How svd_attn_forward_planned runs this plan (Section 4.2, fusion of heads; plan
  * option single_launch): 1 = the layer kernel alone, 3 = the
  * layer kernel after the dense head start (plan option single_launch, or the
- * library's choice), 0 = a launch per group. */
+ * library's choice), 0 = a launch per group.  (A plan whose form the library chose may
+ * run from a table of items instead, see single_launch above; the per-group entry
+ * points and the FP8 forward pass then follow the form reported here.) */
 svd_status svd_plan_single_launch(const svd_plan* plan, int32_t* single_launch);
 
 /* Inspection of a compiled plan (host copies owned by the plan, valid until

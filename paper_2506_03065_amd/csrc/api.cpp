@@ -55,6 +55,12 @@ struct svd_plan {
   svd::LayerLaunch layer{};
   size_t counters_offset = 0;
   int n_cu = 0;
+  // the layer as one launch of a table of items (the library's choice for layers of short items), and the
+  // byte offset of its partial results in the workspace
+  bool grid = false;
+  int grid_waves = 0;
+  svd::GridTable grid_table{};
+  size_t grid_partial_offset = 0;
   ~svd_plan() {
     for (int i = 0; i < kSideStreams; ++i) {
       if (side[i]) (void)hipStreamDestroy(side[i]);
@@ -208,9 +214,41 @@ int stripe_gather_pad(const Plan& p) {
   return pad;
 }
 
+// The layer as one launch of a table of items: waves per work-group (4 = the small query tile, 8 = the large one),
+// 0 = the plan runs in its launch form as before.  Only where the caller leaves the form to the library.
+// A launch per group pays a launch, a gap and a partly filled last round for each, and forked groups the events
+// between streams; the layer kernel an atomic round trip per item and a call per segment.  With the table each
+// work-group reads its item in one load and the hardware hands the items out.  Microseconds per layer, before / small
+// tile / large tile, against the layer's key tiles per resident small work-group:
+//   D = 128   24 heads x 8,536 with text borders (35)      473 / 269 / 288
+//             28 x 13,661 (356)                            735 / 673 / 687   (before: the layer kernel)
+//             40 x 32,760 (1,395)                        2,637 / 2,570 / 2,619   (layer kernel)
+//             24 x 115,456 (7,415)                      12,490 / 12,810 / 12,700   (layer kernel)
+//   D = 64    4 x 1,024 (1)                                 82 / 16 / 19
+//             30 x 9,328 (157)                             479 / 337 / 337
+//             29 x 32,710 (965)                          1,969 / 1,908 / 1,851
+//             48 x 86,400 (3,620)                        7,283 / 7,351 / 7,232
+// Short layers take the small tile (two independent work-groups per compute unit: one's prologue runs under the
+// other's loop).  Long D = 128 layers of long items stay with the layer kernel, whose queues level the XCDs.  Long
+// D = 64 layers take the large tile (a K/V tile in LDS serves twice the rows, 3-4 % a tile) unless its lists, which
+// follow the bands less closely, hold more than that on top.
+int grid_waves(const Plan& p, const svd_plan_options* opt, int form, int n_cu) {
+  if (!svd::launch_grid || n_cu < 1) return 0;
+  if (opt && (opt->block_q || opt->block_k || opt->dense_split || opt->single_launch)) return 0;
+  const double small = svd::grid_tiles(p, svd::kernel_small_block_q(p.desc.D)), per_slot = small / (2.0 * n_cu);
+  if (form == 1) return per_slot < 2500.0 ? 4 : 0;
+  if (form != 0) return 0;
+  return p.desc.D == 64 && per_slot > 400.0 && 2.0 * svd::grid_tiles(p, p.block_q) < (per_slot > 2500.0 ? 1.06 : 1.03) * small ? 8 : 4;
+}
+
+bool add_grid_table(Plan* p, int waves, int n_cu, svd::GridTable* table) {
+  // a compute unit runs eight of the kernels' waves at a time
+  return svd::build_grid_table(p, waves * 32, 8 / waves * n_cu, stripe_gather_pad(*p), table);
+}
+
 size_t workspace_need(const Plan& p, int dense_split, int n_cu, size_t* partial_offset, std::vector<int>* text_split,
                       std::vector<size_t>* text_offset, bool single_launch = false, size_t* counters_offset = nullptr,
-                      size_t* gather_offset = nullptr) {
+                      size_t* gather_offset = nullptr, int grid_slots = 0, size_t* grid_offset = nullptr, int waves = 0) {
   size_t end = p.ws_image.size() * sizeof(int32_t);
   if (partial_offset) *partial_offset = 0;
   if (gather_offset) *gather_offset = 0;
@@ -239,6 +277,11 @@ size_t workspace_need(const Plan& p, int dense_split, int n_cu, size_t* partial_
     if (text_offset) (*text_offset)[gi] = off;
     const int items = (p.text_tokens / p.block_q) * static_cast<int>(g.heads.size()) * p.desc.B * split;
     end = off + svd::partial_floats(p.desc.D, items) * sizeof(float);
+  }
+  if (grid_slots > 0) {   // partial results of the split items of a grid launch
+    const size_t off = align_up(end, 256);
+    if (grid_offset) *grid_offset = off;
+    end = off + static_cast<size_t>(grid_slots) * svd::grid_slot_floats(p.desc.D, waves) * sizeof(float);
   }
   if (single_launch) {   // the queue positions of the layer kernel come last
     const size_t off = align_up(end, 256);
@@ -360,7 +403,10 @@ svd_status svd_plan_workspace_bytes(const svd_tensor_desc* desc, const int32_t* 
     return st;
   // (the split of the dense heads still serves the grouped launches of such a plan: the FP8 path, the per-group calls)
   const int split = native ? choose_dense_split(*desc, bq, bk, count_dense_heads(tmp), n_cu, options) : 1;
-  *bytes = workspace_need(tmp, split, native ? n_cu : 0, nullptr, nullptr, nullptr, single, nullptr);
+  svd::GridTable grid;
+  const int waves = native ? grid_waves(tmp, options, form, n_cu) : 0;
+  if (waves) add_grid_table(&tmp, waves, n_cu, &grid);
+  *bytes = workspace_need(tmp, split, native ? n_cu : 0, nullptr, nullptr, nullptr, single, nullptr, nullptr, grid.n_slots, nullptr, waves);
   return SVD_OK;
 }
 
@@ -466,10 +512,12 @@ static svd_status create_plan(svd_plan** plan, const svd_tensor_desc* desc,
   if (device_workspace) {
     const int n_cu_ws = device_compute_units();
     sp->dense_split = native ? choose_dense_split(*desc, bq, bk, count_dense_heads(sp->p), n_cu_ws, options) : 1;
+    sp->gather_pad = stripe_gather_pad(sp->p);
+    sp->grid_waves = native ? grid_waves(sp->p, options, form, n_cu_ws) : 0;
+    if (sp->grid_waves) sp->grid = add_grid_table(&sp->p, sp->grid_waves, n_cu_ws, &sp->grid_table);
     const size_t need = workspace_need(sp->p, sp->dense_split, native ? n_cu_ws : 0, &sp->partial_offset,
                                        &sp->text_split, &sp->text_partial_offset, single, &sp->counters_offset,
-                                       &sp->gather_offset);
-    sp->gather_pad = stripe_gather_pad(sp->p);
+                                       &sp->gather_offset, sp->grid_table.n_slots, &sp->grid_partial_offset, sp->grid_waves);
 
     if (workspace_bytes < need || !aligned16(device_workspace)) {
       delete sp;
@@ -494,7 +542,7 @@ static svd_status create_plan(svd_plan** plan, const svd_tensor_desc* desc,
       }
       build_layer_segments(sp);
     }
-    if (native && with_side_streams && !single && !(options && options->no_fork)) {
+    if (native && with_side_streams && !single && !sp->grid && !(options && options->no_fork)) {
       bool ok = hipEventCreateWithFlags(&sp->fork, hipEventDisableTiming) == hipSuccess;
       for (int i = 0; ok && i < kSideStreams; ++i)
         ok = hipStreamCreateWithFlags(&sp->side[i], hipStreamNonBlocking) == hipSuccess &&
@@ -786,11 +834,42 @@ static svd_status check_launchable(const svd_plan* plan, const void* q, const vo
   return SVD_OK;
 }
 
+// The stripe heads' K and V rows, gathered ahead of a launch that holds the whole layer; a: its tensors and ws.
+static svd_status gather_stripes(const svd_plan& sp, svd::AttnLaunch* launch, hipStream_t stream) {
+  for (const svd::Group& g : sp.p.groups) {
+    if (g.mode != SVD_VSTRIPE) continue;
+    svd::AttnLaunch a = *launch;
+    a.n_heads = static_cast<int>(g.heads.size());
+    a.heads = a.ws + g.ws_heads;
+    a.list_id = a.ws + g.ws_list_id;
+    a.list_table = static_cast<int>(g.ws_list_table);
+    a.gathered = reinterpret_cast<__bf16*>(static_cast<char*>(sp.p.device_workspace) + sp.gather_offset);
+    a.gather_pad = sp.gather_pad;
+    if (svd::launch_gather_kv(a, stream) != hipSuccess) return SVD_ERR_HIP;
+    launch->gathered = a.gathered;
+    launch->gather_pad = a.gather_pad;
+  }
+  return SVD_OK;
+}
+
 svd_status svd_attn_forward_planned(const svd_plan* plan, const void* q, const void* k, const void* v,
                                     void* out, void* hip_stream) {
   if (svd_status st = check_launchable(plan, q, k, v, out, static_cast<hipStream_t>(hip_stream))) return st;
   const Plan& p = plan->p;
   hipStream_t main_stream = static_cast<hipStream_t>(hip_stream);
+  if (plan->grid) {
+    svd::GridLaunch gl{};
+    gl.a = base_launch(p.desc, q, k, v, out);
+    gl.a.ws = static_cast<const int*>(p.device_workspace);
+    gl.table = static_cast<int>(plan->grid_table.table);
+    gl.waves = plan->grid_waves;
+    gl.n_blocks = plan->grid_table.n_blocks;
+    gl.merge_table = static_cast<int>(plan->grid_table.merge_table);
+    gl.n_merges = plan->grid_table.n_merges;
+    gl.partial = reinterpret_cast<float*>(static_cast<char*>(p.device_workspace) + plan->grid_partial_offset);
+    if (svd_status st = gather_stripes(*plan, &gl.a, main_stream)) return st;
+    return svd::launch_grid(gl, main_stream) == hipSuccess ? SVD_OK : SVD_ERR_HIP;
+  }
   if (plan->single_launch) {
     if (plan->dense_head_start > 0) {
       // whole rounds of the dense kernel on its 256-row tile; what is left of the dense group is in the queues
@@ -809,21 +888,8 @@ svd_status svd_attn_forward_planned(const svd_plan* plan, const void* q, const v
     svd::LayerLaunch lay = plan->layer;
     lay.a = base_launch(p.desc, q, k, v, out);
     lay.a.ws = static_cast<const int*>(p.device_workspace);
-    for (const svd::Group& g : p.groups) {
-      if (g.mode != SVD_VSTRIPE) continue;
-      // the stripe heads' K and V rows are gathered ahead of the layer kernel
-      svd::AttnLaunch a = lay.a;
-      a.n_heads = static_cast<int>(g.heads.size());
-      a.heads = lay.a.ws + g.ws_heads;
-      a.list_id = lay.a.ws + g.ws_list_id;
-      a.list_table = static_cast<int>(g.ws_list_table);
-      a.gathered = reinterpret_cast<__bf16*>(static_cast<char*>(p.device_workspace) + plan->gather_offset);
-      a.gather_pad = plan->gather_pad;
-      if (svd::launch_gather_kv(a, main_stream) != hipSuccess) return SVD_ERR_HIP;
-      lay.a.gathered = a.gathered;
-      lay.a.gather_pad = a.gather_pad;
-      lay.a.skip_q_blocks = p.text_tokens / svd::layer_block_q(p.desc.D);   // text rows are items of the dense kind
-    }
+    if (svd_status st = gather_stripes(*plan, &lay.a, main_stream)) return st;
+    lay.a.skip_q_blocks = p.text_tokens / svd::layer_block_q(p.desc.D);   // text rows are items of the dense kind
     return svd::launch_layer(lay, plan->n_cu, main_stream) == hipSuccess ? SVD_OK : SVD_ERR_HIP;
   }
   // heaviest first: dense, then the band groups, the gathers, and the zero fill

@@ -6,6 +6,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "plan.h"
+
 namespace svd {
 
 // Kernel-level modes: the five modes of Section 4.2 map to three loop shapes
@@ -81,7 +83,6 @@ hipError_t launch_gather_kv(const AttnLaunch& p, hipStream_t stream);
 // dense heads are not split: the next segment fills the tail that a launch per
 // group pays for.
 constexpr int kMaxSegments = 12;
-enum { SEG_DENSE = 0, SEG_BAND = 1, SEG_GATHER = 2, SEG_PBAND = 3, SEG_ZERO = 4 };
 struct LayerSegment {
   int kind;          // SEG_*
   int n_items;       // n_q_blocks * n_heads * B - first_item
@@ -102,6 +103,19 @@ constexpr int kLayerCounterWords = 8 * kMaxSegments;   // one queue position per
 // Query rows per item of the single-launch path (the small query tile).
 int layer_block_q(int D);
 hipError_t launch_layer(const LayerLaunch& p, int n_compute_units, hipStream_t stream);
+
+// A layer of short items in one launch (see plan.h for the records of the table).
+struct GridLaunch {
+  AttnLaunch a;          // tensors, shape, strides, scale, ws, gathered, gather_pad
+  int table, n_blocks;   // word offset of the records in ws; records
+  int merge_table, n_merges;
+  int waves;             // per work-group: the small query tile's (4) or the large one's (8)
+  float* partial;        // device: slots of NW * (D / 32 * 16 + 2) * 64 floats, NW = waves of the small tile
+};
+// Floats of one slot of partial results.
+inline size_t grid_slot_floats(int D, int waves) { return static_cast<size_t>(waves) * (D / 32 * 16 + 2) * 64; }
+// (weak: the host code runs such a layer as a launch per group where this is not linked in)
+__attribute__((weak)) hipError_t launch_grid(const GridLaunch& p, hipStream_t stream);
 
 // Floats of scratch one split launch needs (n_items counts chunks).
 size_t partial_floats(int D, int n_items);

@@ -116,13 +116,32 @@ __device__ __forceinline__ const T __attribute__((address_space(4)))* uni_const(
   return (const T __attribute__((address_space(4)))*)(uintptr_t)(((unsigned long long)hi << 32) | lo);
 }
 
-// One item = one tile of BR query rows of one head (and, for split dense launches,
-// one chunk of the key range): everything a work-group does between picking the
-// item and storing its rows.  smem: 4 * BC * D * 2 bytes of LDS, 16-byte aligned.
-// Every wave of the work-group calls it with the same item; a return leaves no
-// wave behind at a barrier (all returns are work-group uniform).
+// The band lists are read through the constant address space: the plan's
+// workspace is never written by a kernel while lists in it are read, and loads with
+// a uniform address from that space are scalar loads, which neither queue behind nor
+// wait for the tile loads in flight.
+typedef const i32x2 __attribute__((address_space(4)))* const_int2_ptr;
+
+// One item = one tile of BR query rows of one head and the key tiles it walks (for
+// a split item: one chunk of them).  Everything in it is uniform.
+struct Item {
+  int head, b, qblk;
+  int n_tiles;
+  int t_base;               // DENSE: first key tile
+  const_int2_ptr entries;   // BAND, PBAND: the item's part of the CSR list
+  const_int2_ptr runs;      // BAND, PBAND
+  const int* row_map;       // PBAND
+  int n_cols;               // GATHER: the head's columns (the keys of its gathered arrays), from the item's first tile on
+  const __bf16* gathered;   // GATHER: the head's gathered K rows from the item's first tile on; V rows follow gather_pad rows later
+  float* partial;           // split item: where its unnormalised result goes, else nullptr
+};
+
+// Everything a work-group does between picking the item and storing its rows.  smem:
+// 4 * BC * D * 2 bytes of LDS, 16-byte aligned.  Every wave of the work-group calls it
+// with the same item; a return leaves no wave behind at a barrier (all returns are
+// work-group uniform).
 template <int D, int NW, int QB, int BC, int OCC, int MODE>
-__device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item, unsigned char* const smem) {
+__device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, unsigned char* const smem) {
   constexpr bool kBand = MODE == MODE_BAND || MODE == MODE_PBAND;        // walks a CSR list of key tiles
   constexpr bool kIndirect = MODE == MODE_PBAND;   // key rows come through an index list (the row map)
   constexpr bool kGathered = MODE == MODE_GATHER;  // K and V are the group's gathered rows: a short dense head
@@ -133,7 +152,6 @@ __device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item, u
   constexpr int KB2 = BC / 32;      // 32-key blocks per tile
   constexpr int KS = D / 16;        // contraction steps of S^T = K Q^T
   constexpr int DB = D / 32;        // 32-row blocks of O^T
-  constexpr int NCH = BC * CH / NT; // chunks per thread and tile (K and V each)
   static_assert(BC * CH % NT == 0, "tile must split evenly over the threads");
   constexpr int TILE_BYTES = BC * D * 2;
   constexpr int ROW_BYTES = D * 2;
@@ -141,12 +159,10 @@ __device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item, u
   unsigned char* const sK = smem;                    // [2][BC][D] bf16, swizzled
   unsigned char* const sV = smem + 2 * TILE_BYTES;   // [2][BC][D] bf16, swizzled
 
-  const int qblk = item % p.n_q_blocks;
-  const int chunk = (item / p.n_q_blocks) % p.split;   // key-range chunk (dense launches only)
-  const int hb = item / p.n_q_blocks / p.split;
-  const int hg = hb % p.n_heads;
-  const int b = hb / p.n_heads;
-  const int head = uni(p.heads ? p.heads[hg] : hg);   // scalar: the buffer resources of K and V are built from it
+  const int qblk = it.qblk, head = it.head, b = it.b;
+  const int n_tiles = it.n_tiles, t_base = it.t_base, n_cols = it.n_cols;
+  const const_int2_ptr entries = it.entries, runs = it.runs;
+  const int* __restrict__ cols = it.row_map;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -156,53 +172,10 @@ __device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item, u
 
   const int64_t base = (int64_t)b * p.stride_b + (int64_t)head * p.stride_h;
   const __bf16* __restrict__ Q = p.q + base;
-  const __bf16* __restrict__ K = kGathered ? p.gathered + (size_t)hb * 2 * p.gather_pad * D : p.k + base;
+  const __bf16* __restrict__ K = kGathered ? it.gathered : p.k + base;
   const __bf16* __restrict__ V = kGathered ? K + (size_t)p.gather_pad * D : p.v + base;
   __bf16* __restrict__ O = p.out + base;
   const int L = p.L;
-
-  // ---- the list this head walks ----
-  int n_tiles = 0;
-  int t_base = 0;                               // DENSE: first key tile of this item's chunk
-  // The band lists are read through the constant address space: the plan's
-  // workspace is never written by a kernel, and loads with a uniform address
-  // from that space are scalar loads, which neither queue behind nor wait for
-  // the tile loads in flight.
-  typedef const i32x2 __attribute__((address_space(4)))* const_int2_ptr;
-  const_int2_ptr entries = nullptr;   // BAND
-  const_int2_ptr runs = nullptr;      // BAND
-  const int* __restrict__ cols = nullptr;      // PBAND: the row map
-  int n_cols = 0;                              // GATHER: the head's columns (the keys of its gathered arrays)
-  if (MODE == MODE_DENSE) {
-    const int n_all = (L + BC - 1) / BC;
-    t_base = chunk * n_all / p.split;
-    n_tiles = (chunk + 1) * n_all / p.split - t_base;
-  } else {
-    const int* rec = p.ws + p.list_table + 4 * p.list_id[hg];
-    if (kBand) {
-      const int* row_ptr = p.ws + rec[0];
-      const int e0 = row_ptr[qblk], e1 = row_ptr[qblk + 1];
-      entries = (const_int2_ptr)(uintptr_t)(p.ws + rec[1]) + e0;
-      runs = (const_int2_ptr)(uintptr_t)(p.ws + rec[2]);
-      n_tiles = e1 - e0;
-      if (n_tiles == 0) return;   // rows that another launch computes (text rows of a layer with a text prefix)
-      if (MODE == MODE_PBAND) cols = p.ws + rec[3];
-    } else {
-      if (qblk < p.skip_q_blocks) return;   // text rows: another launch computes them
-      n_tiles = rec[1] / BC;
-      n_cols = rec[2];
-    }
-  }
-
-  // The list pointers and counts are uniform but may have been loaded through the vector
-  // memory path: as scalars, the list reads in the loop are scalar loads, which neither
-  // queue behind nor wait for the tile loads in flight.
-  entries = uni_const(entries);
-  runs = uni_const(runs);
-  cols = uni(cols);
-  n_tiles = uni(n_tiles);
-  n_cols = uni(n_cols);
-  t_base = uni(t_base);
 
   // ---- Q fragments: B operand of S^T = K Q^T (lane: query l32, 8 of 16 d) ----
   // Q is multiplied by log2(e) / sqrt(D) here, once, and rounded back to bf16:
@@ -289,7 +262,7 @@ __device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item, u
     g_v[u] = kIndirect ? cv : (unsigned)r * stride_bytes + cv;
   }
   // buffer resources of this head's K and V (raw buffers: base, byte range, no swizzle)
-  const unsigned head_bytes = kGathered ? (unsigned)p.gather_pad * (unsigned)ROW_BYTES
+  const unsigned head_bytes = kGathered ? (unsigned)n_tiles * (unsigned)TILE_BYTES
                                         : (unsigned)(L - 1) * stride_bytes + (unsigned)ROW_BYTES;
   const __amdgpu_buffer_rsrc_t rsrc_k = __builtin_amdgcn_make_buffer_rsrc((void*)K, 0, (int)head_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsrc_v = __builtin_amdgcn_make_buffer_rsrc((void*)V, 0, (int)head_bytes, 0x00020000);
@@ -647,15 +620,16 @@ __device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item, u
 
   // ---- split launch: leave the chunk's state for the merge kernel, register by
   // register (each a coalesced 256-byte row of the wave) ----
-  if (MODE == MODE_DENSE && p.split > 1) {
-    static_assert(MODE != MODE_DENSE || QB == 1, "the split path keeps one 32-row block per wave");
+  if (MODE != MODE_PBAND && it.partial) {
+    static_assert(QB == 1, "the split path keeps one 32-row block per wave");
     typedef float __attribute__((address_space(1)))* global_float_ptr;   // global stores, not FLAT ones
-    global_float_ptr dst = (global_float_ptr)(uintptr_t)(p.partial + ((size_t)item * NW + wave) * ((DB * 16 + 2) * 64) + lane);
+    global_float_ptr dst = (global_float_ptr)(uintptr_t)(it.partial + (size_t)wave * ((DB * 16 + 2) * 64) + lane);
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int i = 0; i < 16; ++i) dst[(db * 16 + i) * 64] = o[db][0][i];
-    dst[(DB * 16) * 64] = -nm[0][0];      // reference exponent of this chunk
+    // reference exponent of this chunk; none for a row without a kept key in it (band chunks)
+    dst[(DB * 16) * 64] = kBand && thr[0] == kNegInf ? kNegInf : -nm[0][0];
     dst[(DB * 16 + 1) * 64] = l4[0][0];   // row sum relative to it
     return;
   }
@@ -681,6 +655,58 @@ __device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item, u
       }
     }
   }
+}
+
+
+// The item `item` of a launch over one group of heads (or of a segment of the layer
+// kernel): its place in the (batch entry, head, chunk, query tile) order and its list.
+template <int D, int NW, int QB, int BC, int OCC, int MODE>
+__device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item, unsigned char* const smem) {
+  constexpr bool kBand = MODE == MODE_BAND || MODE == MODE_PBAND;
+  constexpr int DB = D / 32;
+  Item it{};
+  const int qblk = item % p.n_q_blocks;
+  const int chunk = (item / p.n_q_blocks) % p.split;   // key-range chunk (dense launches only)
+  const int hb = item / p.n_q_blocks / p.split;
+  const int hg = hb % p.n_heads;
+  it.qblk = qblk;
+  it.b = hb / p.n_heads;
+  it.head = uni(p.heads ? p.heads[hg] : hg);   // scalar: the buffer resources of K and V are built from it
+  int n_tiles = 0, t_base = 0, n_cols = 0;
+  const_int2_ptr entries = nullptr, runs = nullptr;
+  const int* row_map = nullptr;
+  if (MODE == MODE_DENSE) {
+    const int n_all = (p.L + BC - 1) / BC;
+    t_base = chunk * n_all / p.split;
+    n_tiles = (chunk + 1) * n_all / p.split - t_base;
+    if (p.split > 1) it.partial = p.partial + (size_t)item * NW * ((DB * 16 + 2) * 64);
+  } else {
+    const int* rec = p.ws + p.list_table + 4 * p.list_id[hg];
+    if (kBand) {
+      const int* row_ptr = p.ws + rec[0];
+      const int e0 = row_ptr[qblk], e1 = row_ptr[qblk + 1];
+      entries = (const_int2_ptr)(uintptr_t)(p.ws + rec[1]) + e0;
+      runs = (const_int2_ptr)(uintptr_t)(p.ws + rec[2]);
+      n_tiles = e1 - e0;
+      if (n_tiles == 0) return;   // rows that another launch computes (text rows of a layer with a text prefix)
+      if (MODE == MODE_PBAND) row_map = p.ws + rec[3];
+    } else {
+      if (qblk < p.skip_q_blocks) return;   // text rows: another launch computes them
+      n_tiles = rec[1] / BC;
+      n_cols = rec[2];
+      it.gathered = p.gathered + (size_t)hb * 2 * p.gather_pad * D;
+    }
+  }
+  // The list pointers and counts are uniform but may have been loaded through the vector
+  // memory path: as scalars, the list reads in the loop are scalar loads, which neither
+  // queue behind nor wait for the tile loads in flight.
+  it.entries = uni_const(entries);
+  it.runs = uni_const(runs);
+  it.row_map = uni(row_map);
+  it.n_tiles = uni(n_tiles);
+  it.n_cols = uni(n_cols);
+  it.t_base = uni(t_base);
+  attn_body<D, NW, QB, BC, OCC, MODE>(p, it, smem);
 }
 
 
@@ -922,6 +948,92 @@ __global__ void __launch_bounds__(kLayerWaves * 64, 2) attn_layer_kernel(const L
   }
 }
 
+// ---- the layer in one launch, work-group = one item of a table ----
+
+// The loops are those of attn_fwd_kernel (same registers, no spill inside them: a work-group takes one branch of the
+// switch to its end).  What bounds short layers is everything around the loops: here one scalar load brings the item,
+// where a group's launch reads head, list record, row pointer and entries one after the other, and one launch
+// replaces up to nine.  4 heads x 1,024 tokens, D = 64: 82 us in groups, 16 us with the table.
+
+typedef const int __attribute__((address_space(4)))* const_int_ptr;
+
+template <int D, int NW, int BC>
+__global__ void __launch_bounds__(NW * 64, 2) attn_grid_kernel(const GridLaunch g) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * BC * D * 2];
+  const const_int_ptr r = (const_int_ptr)(uintptr_t)(g.a.ws + g.table) + (size_t)blockIdx.x * kGridWords;
+  if (r[0] < 0) return;
+  const int kind = r[0] & 255, t0 = r[0] >> 8;
+  Item it{};
+  it.head = r[1];
+  it.b = r[2];
+  it.qblk = r[3];
+  it.n_tiles = r[4];
+  const int list = r[5], more = r[6], last = r[7];
+  if (kind == SEG_DENSE) {
+    it.t_base = t0;
+  } else if (kind == SEG_GATHER) {
+    it.gathered = g.a.gathered + ((size_t)list + t0 * BC) * D;
+    it.n_cols = more - t0 * BC;
+  } else {
+    it.entries = (const_int2_ptr)(uintptr_t)(g.a.ws + list) + t0;
+    it.runs = (const_int2_ptr)(uintptr_t)(g.a.ws + more);
+  }
+  if (kind == SEG_PBAND) it.row_map = g.a.ws + last;
+  else if (last >= 0) it.partial = g.partial + (size_t)last * NW * ((D / 32 * 16 + 2) * 64);
+  switch (kind) {
+    case SEG_DENSE: attn_body<D, NW, 1, BC, 2, MODE_DENSE>(g.a, it, smem); break;
+    case SEG_BAND: attn_body<D, NW, 1, BC, 2, MODE_BAND>(g.a, it, smem); break;
+    case SEG_GATHER: attn_body<D, NW, 1, BC, 2, MODE_GATHER>(g.a, it, smem); break;
+    case SEG_PBAND: attn_body<D, NW, 1, BC, 2, MODE_PBAND>(g.a, it, smem); break;
+    default: {   // zero fill of kGridZeroRows rows of a skipped head
+      __bf16* O = g.a.out + (int64_t)it.b * g.a.stride_b + (int64_t)it.head * g.a.stride_h;
+      constexpr int CH = D / 8;
+      for (int c = threadIdx.x; c < kGridZeroRows * CH; c += NW * 64) {
+        const int row = it.qblk * kGridZeroRows + c / CH;
+        if (row < g.a.L) *reinterpret_cast<uint4*>(O + (int64_t)row * g.a.stride_l + (c % CH) * 8) = make_uint4(0, 0, 0, 0);
+      }
+    }
+  }
+}
+
+// Merge of the split items of a grid launch: work-group = (split query tile, slice of
+// four accumulator rows); the chunks of a tile lie in consecutive slots.
+template <int D, int NW>
+__global__ void __launch_bounds__(NW * 64) merge_chunks_kernel(const GridLaunch g) {
+  constexpr int DB = D / 32, RPS = 4;
+  const const_int_ptr r = (const_int_ptr)(uintptr_t)(g.a.ws + g.merge_table) + (size_t)blockIdx.x * kGridWords;
+  const int head = r[0], b = r[1], qblk = r[2], n_chunks = r[3], slot = r[4];
+  const int r0 = blockIdx.y * RPS;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l32 = lane & 31, half = lane >> 5;
+  float o[RPS];
+#pragma unroll
+  for (int i = 0; i < RPS; ++i) o[i] = 0.f;
+  float m = kNegInf, l = 0.f;
+#pragma unroll 2
+  for (int c = 0; c < n_chunks; ++c) {
+    const float* src = g.partial + ((size_t)(slot + c) * NW + wave) * ((DB * 16 + 2) * 64) + lane;
+    const float mc = src[(DB * 16) * 64], lc = src[(DB * 16 + 1) * 64];
+    const float m_new = fmaxf(m, mc);
+    // a chunk in which the row keeps no key (mc = -inf) adds nothing
+    const float wa = m == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m - m_new), wc = mc == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mc - m_new);
+    l = l * wa + lc * wc;
+#pragma unroll
+    for (int i = 0; i < RPS; ++i) o[i] = o[i] * wa + src[(r0 + i) * 64] * wc;
+    m = m_new;
+  }
+  const float inv = 1.0f / l;
+  const int row = qblk * (NW * 32) + wave * 32 + l32;
+  if (row < g.a.L) {
+    __bf16* dst = g.a.out + (int64_t)b * g.a.stride_b + (int64_t)head * g.a.stride_h + (int64_t)row * g.a.stride_l;
+    const int db = r0 / 16, gg = (r0 % 16) / 4;
+    const f32x2 a01 = {o[0] * inv, o[1] * inv}, a23 = {o[2] * inv, o[3] * inv};
+    const bf16x2 b01 = __builtin_convertvector(a01, bf16x2), b23 = __builtin_convertvector(a23, bf16x2);
+    const bf16x4 out4 = {b01[0], b01[1], b23[0], b23[1]};
+    *reinterpret_cast<bf16x4*>(dst + db * 32 + gg * 8 + half * 4) = out4;
+  }
+}
+
 template <int D, int NW, int QB, int BC, int OCC>
 hipError_t launch_mode(const AttnLaunch& p, int mode, hipStream_t stream) {
   const int per_xcd = (p.n_items + 7) / 8;
@@ -957,6 +1069,14 @@ hipError_t launch_band_small(const AttnLaunch& p, int mode, hipStream_t stream) 
   } else {
     return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+template <int D, int NW, int BC>
+hipError_t launch_grid_shape(const GridLaunch& p, hipStream_t stream) {
+  hipLaunchKernelGGL((attn_grid_kernel<D, NW, BC>), dim3(p.n_blocks), dim3(NW * 64), 0, stream, p);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess || p.n_merges < 1) return e;
+  hipLaunchKernelGGL((merge_chunks_kernel<D, NW>), dim3(p.n_merges, D / 8), dim3(NW * 64), 0, stream, p);
   return hipGetLastError();
 }
 
@@ -1017,6 +1137,16 @@ hipError_t launch_layer(const LayerLaunch& p, int n_compute_units, hipStream_t s
   else if (p.a.D == 64) hipLaunchKernelGGL((attn_layer_kernel<64, Tile64::BC>), grid, block, 0, stream, p);
   else return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+hipError_t launch_grid(const GridLaunch& p, hipStream_t stream) {
+  if (p.n_blocks < 1) return hipSuccess;
+  if (!p.a.ws || (p.n_merges > 0 && !p.partial)) return hipErrorInvalidValue;
+  if (p.a.D == 128 && p.waves == 4) return launch_grid_shape<128, 4, Tile128::BC>(p, stream);
+  if (p.a.D == 128 && p.waves == 8) return launch_grid_shape<128, 8, Tile128::BC>(p, stream);
+  if (p.a.D == 64 && p.waves == 4) return launch_grid_shape<64, 4, Tile64::BC>(p, stream);
+  if (p.a.D == 64 && p.waves == 8) return launch_grid_shape<64, 8, Tile64::BC>(p, stream);
+  return hipErrorInvalidValue;
 }
 
 size_t partial_floats(int D, int n_items) {

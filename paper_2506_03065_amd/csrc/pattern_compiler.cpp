@@ -7,6 +7,7 @@
 // walk, using interval arithmetic on the diagonals delta = j - i (a band pattern
 // depends on delta only) - no mask is ever materialised here.
 #include <algorithm>
+#include <cmath>
 #include <map>
 #include <set>
 #include <utility>
@@ -15,6 +16,10 @@
 
 namespace svd {
 namespace {
+
+// Grid table: what an item costs besides its key tiles (prologue, epilogue), in key tiles, and the most chunks of an item.
+constexpr double kGridItemCost = 3.0;
+constexpr int32_t kGridMaxChunks = 64;
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -148,6 +153,28 @@ size_t append(std::vector<int32_t>* img, const std::vector<int32_t>& data) {
   img->resize(at, 0);
   img->insert(img->end(), data.begin(), data.end());
   return at;
+}
+
+// Lists into the workspace image, their records into the list table at word `table`.
+void emit_band_lists(std::vector<int32_t>* img, const std::vector<BandList>& lists, size_t table) {
+  for (size_t l = 0; l < lists.size(); ++l) {
+    const BandList& bl = lists[l];
+    std::vector<int32_t> entries(bl.kv_block_idx.size() * 2);
+    for (size_t e = 0; e < bl.kv_block_idx.size(); ++e) {
+      entries[2 * e] = bl.kv_block_idx[e];
+      entries[2 * e + 1] = bl.flags[e] | (bl.run_first[e] << 1) | (bl.run_count[e] << 16);
+    }
+    const size_t rp = append(img, bl.row_ptr), en = append(img, entries), ru = append(img, bl.runs);
+    int32_t* rec = img->data() + table + l * kListRecordWords;
+    rec[0] = static_cast<int32_t>(rp);
+    rec[1] = static_cast<int32_t>(en);
+    rec[2] = static_cast<int32_t>(ru);
+    rec[3] = static_cast<int32_t>(bl.runs.size() / 2);
+    if (!bl.row_map.empty()) {
+      const size_t rm = append(img, bl.row_map);
+      (*img)[table + l * kListRecordWords + 3] = static_cast<int32_t>(rm);   // append may have moved the image
+    }
+  }
 }
 
 }  // namespace
@@ -316,6 +343,7 @@ svd_status compile_plan(const svd_tensor_desc& desc, const int32_t* strategy_tab
       }
       if (!always_large && area_small < 0.92 * area) {
         g.bands.swap(alt);
+        g.bands_large.swap(alt);
         g.block_q = block_q_small;
       } else {
         g.bands_small.swap(alt);
@@ -334,30 +362,10 @@ svd_status compile_plan(const svd_tensor_desc& desc, const int32_t* strategy_tab
     g.ws_list_id = append(&img, g.list_id);
     const size_t n_lists = g.bands.size() + g.columns.size();
     g.ws_list_table = append(&img, std::vector<int32_t>(n_lists * kListRecordWords, 0));
-    auto emit_band_lists = [&img](const std::vector<BandList>& lists, size_t table) {
-      for (size_t l = 0; l < lists.size(); ++l) {
-        const BandList& bl = lists[l];
-        std::vector<int32_t> entries(bl.kv_block_idx.size() * 2);
-        for (size_t e = 0; e < bl.kv_block_idx.size(); ++e) {
-          entries[2 * e] = bl.kv_block_idx[e];
-          entries[2 * e + 1] = bl.flags[e] | (bl.run_first[e] << 1) | (bl.run_count[e] << 16);
-        }
-        const size_t rp = append(&img, bl.row_ptr), en = append(&img, entries), ru = append(&img, bl.runs);
-        int32_t* rec = img.data() + table + l * kListRecordWords;
-        rec[0] = static_cast<int32_t>(rp);
-        rec[1] = static_cast<int32_t>(en);
-        rec[2] = static_cast<int32_t>(ru);
-        rec[3] = static_cast<int32_t>(bl.runs.size() / 2);
-        if (!bl.row_map.empty()) {
-          const size_t rm = append(&img, bl.row_map);
-          img[table + l * kListRecordWords + 3] = static_cast<int32_t>(rm);   // append may have moved the image
-        }
-      }
-    };
-    emit_band_lists(g.bands, g.ws_list_table);
+    emit_band_lists(&img, g.bands, g.ws_list_table);
     if (!g.bands_small.empty()) {
       g.ws_list_table_small = append(&img, std::vector<int32_t>(g.bands_small.size() * kListRecordWords, 0));
-      emit_band_lists(g.bands_small, g.ws_list_table_small);
+      emit_band_lists(&img, g.bands_small, g.ws_list_table_small);
     }
     for (size_t l = 0; l < g.columns.size(); ++l) {
       const ColumnList& cl = g.columns[l];
@@ -372,6 +380,168 @@ svd_status compile_plan(const svd_tensor_desc& desc, const int32_t* strategy_tab
   img.resize(align4(img.size()) + 4, 0);  // never empty, 16-byte multiple
   if (img.size() > static_cast<size_t>(INT32_MAX)) return SVD_ERR_UNSUPPORTED;
   return SVD_OK;
+}
+
+// The group's band lists on query tiles of block_q rows, nullptr: none were compiled.
+static const std::vector<BandList>* bands_on(const Group& g, int32_t block_q) {
+  if (g.block_q == block_q) return &g.bands;
+  const std::vector<BandList>& other = block_q < g.block_q ? g.bands_small : g.bands_large;
+  return other.empty() ? nullptr : &other;
+}
+
+double grid_tiles(const Plan& plan, int32_t block_q) {
+  const double n_qb = std::ceil(static_cast<double>(plan.desc.L) / block_q);
+  double tiles = 0.0;
+  for (const Group& g : plan.groups) {
+    const std::vector<BandList>* bands = bands_on(g, block_q);
+    const double text = g.mode >= SVD_DIAG ? static_cast<double>(plan.text_tokens / block_q) * plan.n_k_blocks : 0.0;
+    for (int32_t id : g.list_id) {
+      if (g.mode == SVD_DENSE) tiles += n_qb * plan.n_k_blocks;
+      else if (g.mode == SVD_VSTRIPE) tiles += n_qb * (g.columns[id].cols.size() / plan.block_k) + text;
+      else if (g.mode != SVD_SKIP && bands) tiles += (*bands)[id].kv_block_idx.size() + text;
+    }
+  }
+  return tiles * plan.desc.B;
+}
+
+bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, GridTable* out) {
+  const svd_tensor_desc& d = plan->desc;
+  const int64_t L = d.L, bk = plan->block_k;
+  const int32_t n_qb = static_cast<int32_t>(ceil_div(L, block_q));
+  const int32_t n_kb = plan->n_k_blocks;
+  const int32_t text_qb = plan->text_tokens / block_q;
+  std::vector<int32_t>& img = plan->ws_image;
+  struct Rec {
+    int32_t w[kGridWords];
+    double cost;
+  };
+  struct Segment {
+    std::vector<Rec> recs;
+    double cost = 0.0, longest = 0.0;
+    void add(const Rec& r) {
+      recs.push_back(r);
+      cost += r.cost;
+      longest = std::max(longest, r.cost);
+    }
+  };
+  std::vector<Segment> segs;
+  for (Group& g : plan->groups) {
+    Segment s, text;
+    const std::vector<BandList>* bands = bands_on(g, block_q);
+    size_t table = g.ws_list_table;
+    if (g.mode == SVD_DIAG || g.mode == SVD_MULTIDIAG) {
+      if (!bands) return false;
+      if (bands == &g.bands_small) table = g.ws_list_table_small;
+      if (bands == &g.bands_large) {
+        g.ws_list_table_large = table = append(&img, std::vector<int32_t>(g.bands_large.size() * kListRecordWords, 0));
+        emit_band_lists(&img, g.bands_large, table);
+      }
+    }
+    for (int32_t b = 0; b < d.B; ++b) {
+      for (size_t t = 0; t < g.heads.size(); ++t) {
+        const int32_t head = g.heads[t];
+        if (g.mode == SVD_SKIP) {
+          const int32_t n = static_cast<int32_t>(ceil_div(L, kGridZeroRows));
+          for (int32_t z = 0; z < n; ++z) s.add({{SEG_ZERO, head, b, z, 0, 0, 0, -1}, 0.5});
+          continue;
+        }
+        if (g.mode == SVD_DENSE) {
+          for (int32_t qb = 0; qb < n_qb; ++qb) s.add({{SEG_DENSE, head, b, qb, n_kb, 0, 0, -1}, n_kb + kGridItemCost});
+          continue;
+        }
+        for (int32_t qb = 0; qb < text_qb; ++qb) text.add({{SEG_DENSE, head, b, qb, n_kb, 0, 0, -1}, n_kb + kGridItemCost});
+        if (g.mode == SVD_VSTRIPE) {
+          const ColumnList& cl = g.columns[g.list_id[t]];
+          const int64_t first = (static_cast<int64_t>(b) * g.heads.size() + t) * 2 * gather_pad;
+          if (first + gather_pad > INT32_MAX) return false;
+          const int32_t n = static_cast<int32_t>(cl.cols.size() / bk);
+          for (int32_t qb = text_qb; qb < n_qb; ++qb)
+            s.add({{SEG_GATHER, head, b, qb, n, static_cast<int32_t>(first), cl.n_cols, -1}, n + kGridItemCost});
+          continue;
+        }
+        const BandList& bl = (*bands)[g.list_id[t]];
+        const int32_t* rec = img.data() + table + static_cast<size_t>(g.list_id[t]) * kListRecordWords;
+        for (int32_t qb = text_qb; qb < n_qb; ++qb) {
+          const int32_t e0 = bl.row_ptr[qb], n = bl.row_ptr[qb + 1] - e0;
+          const int64_t entry = static_cast<int64_t>(rec[1]) + 2 * static_cast<int64_t>(e0);
+          if (n < 1 || entry > INT32_MAX) return false;
+          s.add({{g.rearranged ? SEG_PBAND : SEG_BAND, head, b, qb, n, static_cast<int32_t>(entry), rec[2],
+                  g.rearranged ? rec[3] : -1}, n + kGridItemCost});
+        }
+      }
+    }
+    if (!s.recs.empty()) segs.push_back(std::move(s));
+    if (!text.recs.empty()) segs.push_back(std::move(text));
+  }
+  double total = 0.0;
+  for (const Segment& s : segs) total += s.cost;
+  // An item much longer than a slot's fair share of the layer keeps its slot busy after all others
+  // have finished: it is cut into chunks.  Not below 1.6 times the share: a chunk's partial results
+  // (64 KB) and the merge pass (5 us) cost more than the shorter tail gives (24 heads x 2,352 tokens,
+  // D = 128: 83 us at 0.5, 52 at 1.2, 45 at 1.6, 58 uncut).
+  const double longest = std::max(2.0, 1.6 * total / slots);
+  std::vector<int32_t> merges;
+  int64_t n_slots = 0;
+  for (Segment& s : segs) {
+    if (s.longest <= 1.25 * longest + kGridItemCost) continue;
+    std::vector<Rec> cut;
+    for (const Rec& r : s.recs) {
+      const int32_t n = r.w[4];
+      int32_t pieces = r.w[0] == SEG_PBAND || r.w[0] == SEG_ZERO || n <= 1.25 * longest
+                           ? 1 : static_cast<int32_t>(std::ceil(n / longest));
+      if (pieces > kGridMaxChunks) pieces = kGridMaxChunks;
+      if (pieces <= 1) {
+        cut.push_back(r);
+        continue;
+      }
+      for (int32_t v : {r.w[1], r.w[2], r.w[3], pieces, static_cast<int32_t>(n_slots), 0, 0, 0}) merges.push_back(v);
+      for (int32_t c = 0; c < pieces; ++c) {
+        Rec q = r;
+        const int32_t t0 = static_cast<int32_t>(static_cast<int64_t>(n) * c / pieces);
+        const int32_t t1 = static_cast<int32_t>(static_cast<int64_t>(n) * (c + 1) / pieces);
+        q.w[0] = r.w[0] | t0 << 8;
+        q.w[4] = t1 - t0;
+        q.w[7] = static_cast<int32_t>(n_slots++);
+        q.cost = t1 - t0 + kGridItemCost;
+        cut.push_back(q);
+      }
+    }
+    s = Segment();
+    for (const Rec& r : cut) s.add(r);
+  }
+  if (n_slots > INT32_MAX / 2) return false;
+  std::stable_sort(segs.begin(), segs.end(), [](const Segment& a, const Segment& b) { return a.longest > b.longest; });
+  // Work-groups are dealt to the eight XCDs in turn: record 8 * i + x is the i-th of XCD x.  Every segment is
+  // cut into eight runs of consecutive items (the query tiles of a head share their K and V in one L2), the
+  // cuts placed so that the XCDs' loads stay level; long items come first.
+  std::vector<const Rec*> queue[8];
+  double load[8] = {};
+  double goal = 0.0;
+  for (const Segment& s : segs) {
+    goal += s.cost / 8;
+    size_t at = 0;
+    for (int x = 0; x < 8; ++x)
+      while (at < s.recs.size() && (x == 7 || load[x] + 0.5 * s.recs[at].cost < goal)) {
+        load[x] += s.recs[at].cost;
+        queue[x].push_back(&s.recs[at++]);
+      }
+  }
+  size_t deepest = 0;
+  for (const auto& q : queue) deepest = std::max(deepest, q.size());
+  if (deepest * 8 > INT32_MAX / kGridWords) return false;
+  std::vector<int32_t> table(deepest * 8 * kGridWords, -1);
+  for (int x = 0; x < 8; ++x)
+    for (size_t i = 0; i < queue[x].size(); ++i)
+      std::copy(queue[x][i]->w, queue[x][i]->w + kGridWords, table.begin() + (8 * i + x) * kGridWords);
+  img.resize((img.size() + kGridWords - 1) / kGridWords * kGridWords, 0);
+  out->table = append(&img, table);
+  out->merge_table = append(&img, merges);
+  img.resize(align4(img.size()) + 4, 0);
+  if (img.size() > static_cast<size_t>(INT32_MAX)) return false;
+  out->n_blocks = static_cast<int>(deepest * 8);
+  out->n_merges = static_cast<int>(merges.size() / kGridWords);
+  out->n_slots = static_cast<int>(n_slots);
+  return true;
 }
 
 }  // namespace svd

@@ -51,10 +51,14 @@ struct Group {
   // large one: the FP8 kernels run band groups faster on the small tile whatever the band width
   std::vector<BandList> bands_small;
   int32_t n_q_blocks_small = 0;
+  // and on the large query tile when the group itself runs on the small one; in the workspace only when a
+  // grid table needs them
+  std::vector<BandList> bands_large;
   std::vector<ColumnList> columns;    // mode 4
   // word offsets into the device workspace (valid when the plan is launchable)
   size_t ws_heads = 0, ws_list_id = 0, ws_list_table = 0;
   size_t ws_list_table_small = 0;     // list records of bands_small (0: none)
+  size_t ws_list_table_large = 0;     // list records of bands_large (0: none)
 };
 
 // Per-list record in the device workspace, 4 int32 words.
@@ -92,6 +96,32 @@ struct Plan {
 svd_status compile_plan(const svd_tensor_desc& desc, const int32_t* strategy_table,
                         const svd_head_params* pattern_params, int32_t block_q, int32_t block_k,
                         int32_t text_tokens, int32_t block_q_small, Plan* plan, bool always_large = false);
+
+enum { SEG_DENSE = 0, SEG_BAND = 1, SEG_GATHER = 2, SEG_PBAND = 3, SEG_ZERO = 4 };
+
+// A layer as ONE launch of work-groups, each with one item: one record of a table in the plan
+// workspace, in the order in which the hardware hands work-groups out.  Record (kGridWords int32 words):
+//   0 kind (SEG_*) | first key tile << 8, -1: no item
+//   1 head  2 batch entry  3 query tile (SEG_ZERO: block of kGridZeroRows rows)
+//   4 key tiles to walk
+//   5 BAND, PBAND: word offset of the query tile's first list entry; GATHER: its head's first row in the gathered arrays
+//   6 BAND, PBAND: word offset of the runs; GATHER: columns of the head
+//   7 PBAND: word offset of the row map; else the item's slot of partial results, -1 = not split
+// A long item is cut into chunks of its key tiles; the chunks leave their unnormalised results in
+// consecutive slots and a second kernel merges them.  Merge record:
+//   0 head  1 batch entry  2 query tile  3 chunks  4 first slot
+constexpr int kGridWords = 8;
+constexpr int kGridZeroRows = 1024;
+struct GridTable {
+  int n_blocks = 0, n_merges = 0, n_slots = 0;   // records, merge records, slots of partial results
+  size_t table = 0, merge_table = 0;             // word offsets in the workspace
+};
+// Key tiles that a launch of the whole layer on query tiles of block_q rows walks.
+double grid_tiles(const Plan& plan, int32_t block_q);
+// Appends the records to plan->ws_image.  slots: work-groups that the device runs at a time;
+// gather_pad: rows per head in the gathered arrays of the vertical-stripe group.  False: an index
+// would not fit (nothing is appended that matters).
+bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, GridTable* out);
 
 svd_status validate_desc(const svd_tensor_desc* desc);
 

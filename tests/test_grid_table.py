@@ -1,0 +1,65 @@
+"""The whole layer from a table of items: the table on the host model of the launches (every output row
+stored once, every word inside the workspace, the chunks of cut items complete), and items of every kind
+cut into chunks on the GPU against the oracle."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_03065_amd import binding as svd
+from paper_2506_03065_amd import workloads as W
+from parity_util import check_layer, run_planned
+from test_gpu_random_layers import random_layer
+from test_host_launch_model import CSRC, ROOT, STUB, layer_text, run
+
+
+@pytest.fixture(scope="module")
+def replay(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("hip_stub_grid") / "replay")
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-omit-frame-pointer",
+           "-fno-sanitize-recover=undefined", "-I", STUB, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+           os.path.join(CSRC, "api.cpp"), os.path.join(CSRC, "pattern_compiler.cpp"),
+           *(os.path.join(STUB, f) for f in ("hip_stub.cpp", "launch_models.cpp", "grid_model.cpp", "replay.cpp")), "-o", exe]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-4000:]
+    return exe
+
+
+@pytest.mark.parametrize("cu", [8, 256])
+def test_random_layers_from_the_table(replay, tmp_path, cu):
+    layers = [layer_text(random_layer(seed)[0], 0, rounds=1, cu=cu) for seed in range(16)]
+    wl = W.small(L=900, D=128, H=6, seed=17)
+    wl.pattern_params[2] = {"half_width": 2 * 5 + 4, "rearranged": (0, 180, 5)}
+    layers.append(layer_text(wl, 0, rounds=1, cu=cu))
+    layers += [layer_text(W.small(L=L, D=D, H=5, seed=3), 0, rounds=1, cu=cu) for L in (1, 127, 128, 129, 257) for D in (64, 128)]
+    res = run(replay, tmp_path, layers)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+
+
+def test_full_size_tables(replay, tmp_path):
+    """Both query tiles: the D = 64 benchmark layer takes the large one, its lists appended for it."""
+    layers = [layer_text(W.cogvideox15(), 0, rounds=1, tensors=0), layer_text(W.wan21(), 0, rounds=1, tensors=0)]
+    res = run(replay, tmp_path, layers)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("mode", [W.DENSE, W.DIAG, W.MULTIDIAG, W.VSTRIPE])
+def test_cut_items_of_every_kind(D, mode):
+    """One head of one mode on a length that gives few query tiles: each is cut into chunks of a few key tiles, among
+    them band chunks in which some rows keep no key; keys whose logits rise make the chunks' references differ."""
+    L = 1930
+    table = np.asarray([mode], dtype=np.int32)
+    p = {W.DENSE: {}, W.DIAG: {"half_width": 700}, W.MULTIDIAG: {"half_width": 90, "offsets": (-1500, -600, 0, 640, 1400)},
+         W.VSTRIPE: {"cols": tuple(range(5, L, 2))}}[mode]
+    wl = W.Workload("cut", -1, 1, 1, L, D, 386, 5, 0, table, [p], 77)
+    q, k, v = (t.to("cuda:0") for t in W.make_qkv(wl))
+    # Up to twice N(0, 1): the specified arithmetic (bf16 pre-scaled Q, bf16 P, bf16 output, all else exact), carried out
+    # on the CPU, is off by at most 1.01e-2 here, inside the bar of 2e-2; with keys up to three times N(0, 1) it is off by
+    # 2.2e-2 by itself.
+    k = (k * torch.linspace(0.2, 2.0, L, device="cuda:0")[:, None]).to(torch.bfloat16)
+    out = run_planned(wl, q, k, v)
+    check_layer(wl, q, k, v, out)
