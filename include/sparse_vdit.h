@@ -154,7 +154,8 @@ typedef struct {
  * run the layer from a table of items: one launch of work-groups, each with the
  * (head, query tile, key range) its record in the workspace names, long items cut
  * into chunks that a second launch merges; most layers run that way, the long
- * D = 128 ones through the layer kernel.  svd_plan_single_launch keeps reporting
+ * D = 128 ones through the layer kernel, the longest D = 64 ones group by group.
+ * (svd_attn_forward_fp8 does the same, with one pre-pass for all heads.)  svd_plan_single_launch keeps reporting
  * the form named above.  The split of the dense heads is still chosen and its scratch
  * still part of the workspace: the FP8 forward pass and the per-group entry
  * points run such a plan group by group.
@@ -198,8 +199,7 @@ svd_status svd_plan_dense_split(const svd_plan* plan, int32_t* dense_split);
  * option single_launch): 1 = the layer kernel alone, 3 = the
  * layer kernel after the dense head start (plan option single_launch, or the
  * library's choice), 0 = a launch per group.  (A plan whose form the library chose may
- * run from a table of items instead, see single_launch above; the per-group entry
- * points and the FP8 forward pass then follow the form reported here.) */
+ * run from a table of items instead, see single_launch above.) */
 svd_status svd_plan_single_launch(const svd_plan* plan, int32_t* single_launch);
 
 /* Inspection of a compiled plan (host copies owned by the plan, valid until

@@ -60,6 +60,8 @@ struct svd_plan {
   bool grid = false;
   int grid_waves = 0;
   svd::GridTable grid_table{};
+  bool grid8 = false;              // the FP8 forward pass runs from a table too, on the small query tile
+  svd::GridTable grid8_table{};
   size_t grid_partial_offset = 0;
   ~svd_plan() {
     for (int i = 0; i < kSideStreams; ++i) {
@@ -231,24 +233,62 @@ int stripe_gather_pad(const Plan& p) {
 // Short layers take the small tile (two independent work-groups per compute unit: one's prologue runs under the
 // other's loop).  Long D = 128 layers of long items stay with the layer kernel, whose queues level the XCDs.  Long
 // D = 64 layers take the large tile (a K/V tile in LDS serves twice the rows, 3-4 % a tile) unless its lists, which
-// follow the bands less closely, hold more than that on top.
+// follow the bands less closely, hold more than that on top; the longest stay in groups, whose launches and tails no
+// longer count.
 int grid_waves(const Plan& p, const svd_plan_options* opt, int form, int n_cu) {
   if (!svd::launch_grid || n_cu < 1) return 0;
   if (opt && (opt->block_q || opt->block_k || opt->dense_split || opt->single_launch)) return 0;
   const double small = svd::grid_tiles(p, svd::kernel_small_block_q(p.desc.D)), per_slot = small / (2.0 * n_cu);
   if (form == 1) return per_slot < 2500.0 ? 4 : 0;
-  if (form != 0) return 0;
-  return p.desc.D == 64 && per_slot > 400.0 && 2.0 * svd::grid_tiles(p, p.block_q) < (per_slot > 2500.0 ? 1.06 : 1.03) * small ? 8 : 4;
+  if (form != 0 || (p.desc.D == 64 && per_slot > 2500.0)) return 0;
+  return p.desc.D == 64 && per_slot > 400.0 && 2.0 * svd::grid_tiles(p, p.block_q) < 1.03 * small ? 8 : 4;
 }
 
-bool add_grid_table(Plan* p, int waves, int n_cu, svd::GridTable* table) {
-  // a compute unit runs eight of the kernels' waves at a time
-  return svd::build_grid_table(p, waves * 32, 8 / waves * n_cu, stripe_gather_pad(*p), table);
+// The same for the FP8 forward pass, always on the small query tile.  It gains more, because its pre-pass is one launch
+// too (us per layer, before / now: 37 heads x 1,104, D = 128: 140 / 44; 24 x 8,536 with text borders, D = 128: 437 /
+// 248; 48 x 17,550, D = 64: 556 / 450; 48 x 86,400, D = 64, 3,620 tiles per slot: 5,372 / 5,160).  Only dense items are
+// faster on the large tile of a launch per group (by 2 to 10 %, from one card to the next), and in a long layer the
+// partly empty rounds of the groups weigh little: 40 x 75,600, D = 128, 39 % of the tiles dense, 6,880 per slot: 7,800 /
+// 7,230 to 8,040; D = 64, 85 % dense, 5,000 per slot: 6,244 / 6,348.
+bool grid_fp8(const Plan& p, const svd_plan_options* opt, int n_cu) {
+  if (!svd::launch_grid_fp8 || n_cu < 1) return false;
+  if (opt && (opt->block_q || opt->block_k || opt->dense_split || opt->single_launch)) return false;
+  double dense = 0.0;
+  const double tiles = svd::grid_tiles(p, svd::kernel_small_block_q(p.desc.D), &dense);
+  return tiles / (2.0 * n_cu) < 3000.0 || (p.desc.D == 64 && dense < 0.6 * tiles);
+}
+
+// The tables a plan gets.  A compute unit runs eight of the kernels' waves at a time.
+struct GridTables {
+  int waves = 0;                    // of the bf16 forward pass
+  bool bf16 = false, fp8 = false;
+  svd::GridTable table, table8;
+  size_t partial_bytes = 0;         // partial results of cut items (the two passes do not overlap)
+};
+GridTables add_grid_tables(Plan* p, const svd_plan_options* opt, int form, int n_cu) {
+  GridTables g;
+  const int pad = stripe_gather_pad(*p);
+  g.waves = grid_waves(*p, opt, form, n_cu);
+  if (g.waves) g.bf16 = svd::build_grid_table(p, g.waves * 32, 8 / g.waves * n_cu, pad, true, &g.table);
+  if (grid_fp8(*p, opt, n_cu)) {
+    bool stripes = false;
+    for (const svd::Group& gr : p->groups) stripes = stripes || gr.mode == SVD_VSTRIPE;
+    if (g.bf16 && g.waves == 4 && !(stripes && p->text_tokens > 0)) {
+      g.fp8 = true;   // the same items
+      g.table8 = g.table;
+    } else {
+      g.fp8 = svd::build_grid_table(p, svd::kernel_small_block_q(p->desc.D), 2 * n_cu, pad, false, &g.table8);
+    }
+  }
+  const size_t slots = g.bf16 ? static_cast<size_t>(g.table.n_slots) * svd::grid_slot_floats(p->desc.D, g.waves) : 0;
+  const size_t slots8 = g.fp8 ? static_cast<size_t>(g.table8.n_slots) * svd::grid_slot_floats(p->desc.D, 4) : 0;
+  g.partial_bytes = (slots > slots8 ? slots : slots8) * sizeof(float);
+  return g;
 }
 
 size_t workspace_need(const Plan& p, int dense_split, int n_cu, size_t* partial_offset, std::vector<int>* text_split,
                       std::vector<size_t>* text_offset, bool single_launch = false, size_t* counters_offset = nullptr,
-                      size_t* gather_offset = nullptr, int grid_slots = 0, size_t* grid_offset = nullptr, int waves = 0) {
+                      size_t* gather_offset = nullptr, size_t grid_bytes = 0, size_t* grid_offset = nullptr) {
   size_t end = p.ws_image.size() * sizeof(int32_t);
   if (partial_offset) *partial_offset = 0;
   if (gather_offset) *gather_offset = 0;
@@ -278,10 +318,10 @@ size_t workspace_need(const Plan& p, int dense_split, int n_cu, size_t* partial_
     const int items = (p.text_tokens / p.block_q) * static_cast<int>(g.heads.size()) * p.desc.B * split;
     end = off + svd::partial_floats(p.desc.D, items) * sizeof(float);
   }
-  if (grid_slots > 0) {   // partial results of the split items of a grid launch
+  if (grid_bytes > 0) {   // partial results of the cut items of a grid launch
     const size_t off = align_up(end, 256);
     if (grid_offset) *grid_offset = off;
-    end = off + static_cast<size_t>(grid_slots) * svd::grid_slot_floats(p.desc.D, waves) * sizeof(float);
+    end = off + grid_bytes;
   }
   if (single_launch) {   // the queue positions of the layer kernel come last
     const size_t off = align_up(end, 256);
@@ -403,10 +443,9 @@ svd_status svd_plan_workspace_bytes(const svd_tensor_desc* desc, const int32_t* 
     return st;
   // (the split of the dense heads still serves the grouped launches of such a plan: the FP8 path, the per-group calls)
   const int split = native ? choose_dense_split(*desc, bq, bk, count_dense_heads(tmp), n_cu, options) : 1;
-  svd::GridTable grid;
-  const int waves = native ? grid_waves(tmp, options, form, n_cu) : 0;
-  if (waves) add_grid_table(&tmp, waves, n_cu, &grid);
-  *bytes = workspace_need(tmp, split, native ? n_cu : 0, nullptr, nullptr, nullptr, single, nullptr, nullptr, grid.n_slots, nullptr, waves);
+  GridTables grid;
+  if (native) grid = add_grid_tables(&tmp, options, form, n_cu);
+  *bytes = workspace_need(tmp, split, native ? n_cu : 0, nullptr, nullptr, nullptr, single, nullptr, nullptr, grid.partial_bytes, nullptr);
   return SVD_OK;
 }
 
@@ -513,11 +552,16 @@ static svd_status create_plan(svd_plan** plan, const svd_tensor_desc* desc,
     const int n_cu_ws = device_compute_units();
     sp->dense_split = native ? choose_dense_split(*desc, bq, bk, count_dense_heads(sp->p), n_cu_ws, options) : 1;
     sp->gather_pad = stripe_gather_pad(sp->p);
-    sp->grid_waves = native ? grid_waves(sp->p, options, form, n_cu_ws) : 0;
-    if (sp->grid_waves) sp->grid = add_grid_table(&sp->p, sp->grid_waves, n_cu_ws, &sp->grid_table);
+    GridTables grid;
+    if (native) grid = add_grid_tables(&sp->p, options, form, n_cu_ws);
+    sp->grid = grid.bf16;
+    sp->grid_waves = grid.waves;
+    sp->grid_table = grid.table;
+    sp->grid8 = grid.fp8;
+    sp->grid8_table = grid.table8;
     const size_t need = workspace_need(sp->p, sp->dense_split, native ? n_cu_ws : 0, &sp->partial_offset,
                                        &sp->text_split, &sp->text_partial_offset, single, &sp->counters_offset,
-                                       &sp->gather_offset, sp->grid_table.n_slots, &sp->grid_partial_offset, sp->grid_waves);
+                                       &sp->gather_offset, grid.partial_bytes, &sp->grid_partial_offset);
 
     if (workspace_bytes < need || !aligned16(device_workspace)) {
       delete sp;
@@ -834,6 +878,21 @@ static svd_status check_launchable(const svd_plan* plan, const void* q, const vo
   return SVD_OK;
 }
 
+static svd::GridLaunch grid_launch(const svd_plan& sp, const svd::GridTable& t, int waves, const svd::AttnLaunch& a) {
+  svd::GridLaunch g{};
+  g.a = a;
+  g.a.ws = static_cast<const int*>(sp.p.device_workspace);
+  g.table = static_cast<int>(t.table);
+  g.n_blocks = t.n_blocks;
+  g.merge_table = static_cast<int>(t.merge_table);
+  g.n_merges = t.n_merges;
+  g.head_table = static_cast<int>(t.head_table);
+  g.n_heads = t.n_heads;
+  g.waves = waves;
+  g.partial = reinterpret_cast<float*>(static_cast<char*>(sp.p.device_workspace) + sp.grid_partial_offset);
+  return g;
+}
+
 // The stripe heads' K and V rows, gathered ahead of a launch that holds the whole layer; a: its tensors and ws.
 static svd_status gather_stripes(const svd_plan& sp, svd::AttnLaunch* launch, hipStream_t stream) {
   for (const svd::Group& g : sp.p.groups) {
@@ -858,15 +917,7 @@ svd_status svd_attn_forward_planned(const svd_plan* plan, const void* q, const v
   const Plan& p = plan->p;
   hipStream_t main_stream = static_cast<hipStream_t>(hip_stream);
   if (plan->grid) {
-    svd::GridLaunch gl{};
-    gl.a = base_launch(p.desc, q, k, v, out);
-    gl.a.ws = static_cast<const int*>(p.device_workspace);
-    gl.table = static_cast<int>(plan->grid_table.table);
-    gl.waves = plan->grid_waves;
-    gl.n_blocks = plan->grid_table.n_blocks;
-    gl.merge_table = static_cast<int>(plan->grid_table.merge_table);
-    gl.n_merges = plan->grid_table.n_merges;
-    gl.partial = reinterpret_cast<float*>(static_cast<char*>(p.device_workspace) + plan->grid_partial_offset);
+    svd::GridLaunch gl = grid_launch(*plan, plan->grid_table, plan->grid_waves, base_launch(p.desc, q, k, v, out));
     if (svd_status st = gather_stripes(*plan, &gl.a, main_stream)) return st;
     return svd::launch_grid(gl, main_stream) == hipSuccess ? SVD_OK : SVD_ERR_HIP;
   }
@@ -1341,27 +1392,53 @@ static svd_status check_fp8_workspace(const svd_tensor_desc& d, const void* ws8,
   return SVD_OK;
 }
 
+// The text rows of a sparse group: dense over every key.  f: the group's launch (a: its heads and lists).
+static svd_status launch_text_rows_fp8(const svd_plan& sp, const svd::Group& g, svd::Fp8Launch f, hipStream_t stream) {
+  svd::AttnLaunch& a = f.a;
+  a.split = 1;
+  a.skip_q_blocks = 0;
+  a.n_q_blocks = g.n_q_blocks;
+  a.n_items = a.n_q_blocks * a.n_heads * a.B;
+  // a stripe head's arrays hold its columns only: they are quantised once more, uncompacted
+  if (g.mode == SVD_VSTRIPE && svd::launch_quantise_kv(f, svd::MODE_DENSE, stream) != hipSuccess) return SVD_ERR_HIP;
+  svd::Fp8Launch t = f;
+  t.a = text_rows_launch(sp, g, a);
+  if (svd::launch_attention_fp8(t, svd::MODE_DENSE, stream) != hipSuccess) return SVD_ERR_HIP;
+  if (t.a.split > 1 && svd::launch_combine(t.a, stream) != hipSuccess) return SVD_ERR_HIP;
+  return SVD_OK;
+}
+
+// Tensors, group and quantised arrays of a launch.
+static svd::Fp8Launch fp8_launch(const svd_plan& sp, const svd::Group* g, const void* q, const void* k, const void* v, void* out,
+                                 void* ws8) {
+  const Plan& p = sp.p;
+  const svd_tensor_desc& d = p.desc;
+  svd::Fp8Launch f{};
+  f.a = base_launch(d, q, k, v, out);
+  f.a.ws = static_cast<const int*>(p.device_workspace);
+  if (g) {
+    f.a.n_q_blocks = g->n_q_blocks;
+    f.a.n_heads = static_cast<int>(g->heads.size());
+    f.a.n_items = f.a.n_q_blocks * f.a.n_heads * f.a.B;
+    f.a.heads = f.a.ws + g->ws_heads;
+    f.a.list_id = f.a.ws + g->ws_list_id;
+    f.a.list_table = static_cast<int>(g->ws_list_table);
+  }
+  f.Lp = svd::fp8_padded_len(d.L);
+  f.map_len = (d.L + p.block_k - 1) / p.block_k * p.block_k;
+  f.k8 = static_cast<uint8_t*>(ws8);
+  f.v8t = f.k8 + svd::fp8_scratch_bytes(d.B, d.H, d.L, d.D) / 2;
+  return f;
+}
+
 // Pre-pass plus attention of one group on `stream`.
 static svd_status launch_group_fp8(const svd_plan& sp, const svd::Group& g, const void* q, const void* k,
                                    const void* v, void* out, void* ws8, hipStream_t stream) {
   const Plan& p = sp.p;
   const svd_tensor_desc& d = p.desc;
-  const int* ws = static_cast<const int*>(p.device_workspace);
-  svd::Fp8Launch f{};
+  svd::Fp8Launch f = fp8_launch(sp, &g, q, k, v, out, ws8);
   svd::AttnLaunch& a = f.a;
-  a = base_launch(d, q, k, v, out);
-  a.n_q_blocks = g.n_q_blocks;
-  a.n_heads = static_cast<int>(g.heads.size());
-  a.n_items = a.n_q_blocks * a.n_heads * a.B;
-  a.heads = ws + g.ws_heads;
-  a.list_id = ws + g.ws_list_id;
-  a.ws = ws;
-  a.list_table = static_cast<int>(g.ws_list_table);
   if (g.mode == SVD_SKIP) return svd::launch_zero_heads(a, stream) == hipSuccess ? SVD_OK : SVD_ERR_HIP;
-  f.Lp = svd::fp8_padded_len(d.L);
-  f.map_len = (d.L + p.block_k - 1) / p.block_k * p.block_k;
-  f.k8 = static_cast<uint8_t*>(ws8);
-  f.v8t = f.k8 + svd::fp8_scratch_bytes(d.B, d.H, d.L, d.D) / 2;
   const int kmode = g.mode == SVD_DENSE ? svd::MODE_DENSE
                     : g.mode == SVD_VSTRIPE ? svd::MODE_GATHER
                     : g.rearranged ? svd::MODE_PBAND : svd::MODE_BAND;
@@ -1392,20 +1469,7 @@ static svd_status launch_group_fp8(const svd_plan& sp, const svd::Group& g, cons
     a.skip_q_blocks = p.text_tokens / (small_q ? svd::kernel_small_block_q(d.D) : p.block_q);
   if (svd::launch_attention_fp8(f, kmode, stream, small_q) != hipSuccess) return SVD_ERR_HIP;
   if (a.split > 1 && svd::launch_combine(a, stream) != hipSuccess) return SVD_ERR_HIP;
-  if (has_text_rows(p, g)) {
-    // text rows: dense over every key; a stripe head's arrays hold its columns
-    // only, so they are quantised once more, uncompacted
-    a.split = 1;
-    a.skip_q_blocks = 0;
-    a.n_q_blocks = g.n_q_blocks;
-    a.n_items = a.n_q_blocks * a.n_heads * a.B;
-    if (g.mode == SVD_VSTRIPE && svd::launch_quantise_kv(f, svd::MODE_DENSE, stream) != hipSuccess) return SVD_ERR_HIP;
-    svd::Fp8Launch t = f;
-    t.a = text_rows_launch(sp, g, a);
-    if (svd::launch_attention_fp8(t, svd::MODE_DENSE, stream) != hipSuccess) return SVD_ERR_HIP;
-    if (t.a.split > 1 && svd::launch_combine(t.a, stream) != hipSuccess) return SVD_ERR_HIP;
-  }
-  return SVD_OK;
+  return has_text_rows(p, g) ? launch_text_rows_fp8(sp, g, f, stream) : SVD_OK;
 }
 
 svd_status svd_attn_forward_fp8(const svd_plan* plan, const void* q, const void* k, const void* v, void* out,
@@ -1413,6 +1477,16 @@ svd_status svd_attn_forward_fp8(const svd_plan* plan, const void* q, const void*
   if (svd_status st = check_launchable(plan, q, k, v, out, static_cast<hipStream_t>(hip_stream))) return st;
   if (svd_status st = check_fp8_workspace(plan->p.desc, fp8_workspace, fp8_workspace_bytes)) return st;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  if (plan->grid8) {
+    svd::Fp8Launch f = fp8_launch(*plan, nullptr, q, k, v, out, fp8_workspace);
+    const svd::GridLaunch g = grid_launch(*plan, plan->grid8_table, 4, f.a);
+    f.a.partial = g.partial;
+    if (svd::launch_grid_fp8(f, g, stream) != hipSuccess) return SVD_ERR_HIP;
+    for (const svd::Group& gr : plan->p.groups)
+      if (gr.mode == SVD_VSTRIPE && has_text_rows(plan->p, gr))
+        if (svd_status st = launch_text_rows_fp8(*plan, gr, fp8_launch(*plan, &gr, q, k, v, out, fp8_workspace), stream)) return st;
+    return SVD_OK;
+  }
   // heaviest first, all on the caller's stream
   static const int order[5] = {SVD_DENSE, SVD_DIAG, SVD_MULTIDIAG, SVD_VSTRIPE, SVD_SKIP};
   for (int mode : order)

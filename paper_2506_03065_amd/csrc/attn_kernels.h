@@ -109,6 +109,7 @@ struct GridLaunch {
   AttnLaunch a;          // tensors, shape, strides, scale, ws, gathered, gather_pad
   int table, n_blocks;   // word offset of the records in ws; records
   int merge_table, n_merges;
+  int head_table, n_heads;   // FP8: word offset and number of the head records of the pre-pass
   int waves;             // per work-group: the small query tile's (4) or the large one's (8)
   float* partial;        // device: slots of NW * (D / 32 * 16 + 2) * 64 floats, NW = waves of the small tile
 };
@@ -116,6 +117,8 @@ struct GridLaunch {
 inline size_t grid_slot_floats(int D, int waves) { return static_cast<size_t>(waves) * (D / 32 * 16 + 2) * 64; }
 // (weak: the host code runs such a layer as a launch per group where this is not linked in)
 __attribute__((weak)) hipError_t launch_grid(const GridLaunch& p, hipStream_t stream);
+// The merge launch of the items cut into chunks alone (launch_grid contains it).
+hipError_t launch_grid_merge(const GridLaunch& p, hipStream_t stream);
 
 // Floats of scratch one split launch needs (n_items counts chunks).
 size_t partial_floats(int D, int n_items);

@@ -1075,7 +1075,12 @@ hipError_t launch_band_small(const AttnLaunch& p, int mode, hipStream_t stream) 
 template <int D, int NW, int BC>
 hipError_t launch_grid_shape(const GridLaunch& p, hipStream_t stream) {
   hipLaunchKernelGGL((attn_grid_kernel<D, NW, BC>), dim3(p.n_blocks), dim3(NW * 64), 0, stream, p);
-  if (hipError_t e = hipGetLastError(); e != hipSuccess || p.n_merges < 1) return e;
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  return launch_grid_merge(p, stream);
+}
+
+template <int D, int NW>
+hipError_t launch_merge_shape(const GridLaunch& p, hipStream_t stream) {
   hipLaunchKernelGGL((merge_chunks_kernel<D, NW>), dim3(p.n_merges, D / 8), dim3(NW * 64), 0, stream, p);
   return hipGetLastError();
 }
@@ -1137,6 +1142,16 @@ hipError_t launch_layer(const LayerLaunch& p, int n_compute_units, hipStream_t s
   else if (p.a.D == 64) hipLaunchKernelGGL((attn_layer_kernel<64, Tile64::BC>), grid, block, 0, stream, p);
   else return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+hipError_t launch_grid_merge(const GridLaunch& p, hipStream_t stream) {
+  if (p.n_merges < 1) return hipSuccess;
+  if (!p.a.ws || !p.partial) return hipErrorInvalidValue;
+  if (p.a.D == 128 && p.waves == 4) return launch_merge_shape<128, 4>(p, stream);
+  if (p.a.D == 128 && p.waves == 8) return launch_merge_shape<128, 8>(p, stream);
+  if (p.a.D == 64 && p.waves == 4) return launch_merge_shape<64, 4>(p, stream);
+  if (p.a.D == 64 && p.waves == 8) return launch_merge_shape<64, 8>(p, stream);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_grid(const GridLaunch& p, hipStream_t stream) {

@@ -87,25 +87,11 @@ using Int = std::integral_constant<int, N>;
 // Pre-pass.  Work-group = one group of 64 keys of one head.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(256) quantise_kv_kernel(const Fp8Launch pp, const int gather) {
+__device__ __forceinline__ void quantise_group(const Fp8Launch& pp, const int G, const int head, const int b,
+                                               const int* const cols, const int n_pad) {
   const AttnLaunch& p = pp.a;
   constexpr int SV_STRIDE = D + 8;   // bf16 elements; keeps rows 16-byte aligned
   __shared__ __attribute__((aligned(16))) __bf16 sv[64 * SV_STRIDE];
-  const int G = blockIdx.x;
-  const int hg = blockIdx.y % p.n_heads;
-  const int b = blockIdx.y / p.n_heads;
-  const int head = p.heads ? p.heads[hg] : hg;
-  const int* cols = nullptr;
-  int n_pad = pp.Lp;
-  if (gather == 1) {          // vertical-stripe head: its column list
-    const int* rec = p.ws + p.list_table + 4 * p.list_id[hg];
-    cols = p.ws + rec[0];
-    n_pad = rec[1];
-  } else if (gather == 2) {   // rearranged head: key j of the arrays is row row_map[j] of the tensors
-    const int* rec = p.ws + p.list_table + 4 * p.list_id[hg];
-    cols = p.ws + rec[3];
-    n_pad = pp.map_len;
-  }
   if (G * 64 >= n_pad) return;
   const int64_t base = (int64_t)b * p.stride_b + (int64_t)head * p.stride_h;
   const __bf16* __restrict__ K = p.k + base;
@@ -166,11 +152,56 @@ __global__ void __launch_bounds__(256) quantise_kv_kernel(const Fp8Launch pp, co
   }
 }
 
+// One launch per group of heads.
+template <int D>
+__global__ void __launch_bounds__(256) quantise_kv_kernel(const Fp8Launch pp, const int gather) {
+  const AttnLaunch& p = pp.a;
+  const int hg = blockIdx.y % p.n_heads;
+  const int b = blockIdx.y / p.n_heads;
+  const int head = p.heads ? p.heads[hg] : hg;
+  const int* cols = nullptr;
+  int n_pad = pp.Lp;
+  if (gather == 1) {          // vertical-stripe head: its column list
+    const int* rec = p.ws + p.list_table + 4 * p.list_id[hg];
+    cols = p.ws + rec[0];
+    n_pad = rec[1];
+  } else if (gather == 2) {   // rearranged head: key j of the arrays is row row_map[j] of the tensors
+    const int* rec = p.ws + p.list_table + 4 * p.list_id[hg];
+    cols = p.ws + rec[3];
+    n_pad = pp.map_len;
+  }
+  quantise_group<D>(pp, blockIdx.x, head, b, cols, n_pad);
+}
+
+// All heads of a layer that compute: head records {head, list word offset or -1, list length}.
+template <int D>
+__global__ void __launch_bounds__(256) quantise_layer_kernel(const Fp8Launch pp, const int head_table, const int n_heads) {
+  typedef const int __attribute__((address_space(4)))* const_int_ptr;
+  const const_int_ptr r = (const_int_ptr)(uintptr_t)(pp.a.ws + head_table) + (size_t)(blockIdx.y % n_heads) * kGridHeadWords;
+  const int list = r[1];
+  quantise_group<D>(pp, blockIdx.x, r[0], blockIdx.y / n_heads, list >= 0 ? pp.a.ws + list : nullptr, list >= 0 ? r[2] : pp.Lp);
+}
+
 // ---------------------------------------------------------------------------
 // Attention on the quantised arrays.
 // ---------------------------------------------------------------------------
-template <int D, int NW, int BC, int OCC, int MODE>
-__global__ void __launch_bounds__(NW * 64, OCC) attn_fwd_fp8_kernel(const Fp8Launch pp) {
+typedef const i32x2 __attribute__((address_space(4)))* const_int2_ptr;
+
+// One item: see the bf16 kernels.  Everything in it is uniform.
+struct Fp8Item {
+  int head, b, qblk;
+  int n_tiles;
+  int t_base;               // DENSE, GATHER: first key tile
+  int n_keys;               // DENSE, GATHER: keys of the head's arrays
+  const_int2_ptr entries;   // BAND, PBAND
+  const_int2_ptr runs;
+  const int* row_map;       // PBAND: row of the tensors for every position of the rearranged order
+  float* partial;           // split item: where its unnormalised result goes, else nullptr
+};
+
+// smem: 4 * BC * D bytes of LDS, 16-byte aligned.
+template <int D, int NW, int BC, int MODE>
+__device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it, unsigned char* const smem) {
   const AttnLaunch& p = pp.a;
   constexpr bool kBand = MODE == MODE_BAND || MODE == MODE_PBAND;   // walks a CSR list of key tiles
   constexpr int BR = NW * 32;        // query rows per work-group (one 32-row block per wave)
@@ -184,20 +215,13 @@ __global__ void __launch_bounds__(NW * 64, OCC) attn_fwd_fp8_kernel(const Fp8Lau
   static_assert(TILE_BYTES % (NW * 1024) == 0 && LPT >= 1, "tile must split evenly over the waves");
   static_assert(BC % 64 == 0, "key tiles are whole groups of 64");
 
-  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * TILE_BYTES];
   unsigned char* const sK = smem;                    // [2][BC][D] bytes, swizzled
   unsigned char* const sV = smem + 2 * TILE_BYTES;   // [2][G64][DB][2 halves][2][32 d][16 keys]
 
-  // ---- which tile of which head (XCD-aware: consecutive items share an XCD) ----
-  const int per_xcd = (p.n_items + 7) >> 3;
-  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (item >= p.n_items) return;
-  const int qblk = item % p.n_q_blocks;
-  const int chunk = (item / p.n_q_blocks) % p.split;
-  const int hb = item / p.n_q_blocks / p.split;
-  const int hg = hb % p.n_heads;
-  const int b = hb / p.n_heads;
-  const int head = p.heads ? p.heads[hg] : hg;
+  const int qblk = it.qblk, b = it.b, head = it.head;
+  const int n_tiles = it.n_tiles, t_base = it.t_base, n_keys = it.n_keys;
+  const const_int2_ptr entries = it.entries, runs = it.runs;
+  const int* __restrict__ row_map = it.row_map;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -210,35 +234,6 @@ __global__ void __launch_bounds__(NW * 64, OCC) attn_fwd_fp8_kernel(const Fp8Lau
   __bf16* __restrict__ O = p.out + base;
   const size_t base8 = ((size_t)b * p.H + head) * (size_t)pp.Lp * D;
   const int L = p.L;
-
-  // ---- the list this head walks ----
-  int n_tiles = 0;
-  int t_base = 0;     // DENSE: first key tile of this item's chunk
-  int n_keys = L;     // DENSE, GATHER: keys of the head's arrays
-  typedef const i32x2 __attribute__((address_space(4)))* const_int2_ptr;
-  const_int2_ptr entries = nullptr;   // BAND
-  const_int2_ptr runs = nullptr;      // BAND
-  const int* __restrict__ row_map = nullptr;   // PBAND: row of the tensors for every position of the rearranged order
-  if (MODE == MODE_DENSE) {
-    const int n_all = (L + BC - 1) / BC;
-    t_base = chunk * n_all / p.split;
-    n_tiles = (chunk + 1) * n_all / p.split - t_base;
-  } else {
-    const int* rec = p.ws + p.list_table + 4 * p.list_id[hg];
-    if (kBand) {
-      const int* row_ptr = p.ws + rec[0];
-      const int e0 = row_ptr[qblk], e1 = row_ptr[qblk + 1];
-      entries = (const_int2_ptr)(uintptr_t)(p.ws + rec[1]) + e0;
-      runs = (const_int2_ptr)(uintptr_t)(p.ws + rec[2]);
-      n_tiles = e1 - e0;
-      if (n_tiles == 0) return;   // rows that another launch computes (text rows of a layer with a text prefix)
-      if (MODE == MODE_PBAND) row_map = p.ws + rec[3];
-    } else {
-      if (qblk < p.skip_q_blocks) return;   // text rows: another launch computes them
-      n_tiles = rec[1] / BC;
-      n_keys = rec[2];
-    }
-  }
 
   // ---- Q fragments: B operand of S^T = K Q^T (lane: query l32, d = 64 ks + 32 half + 0..31) ----
   const float c_scale = p.scale_log2e * 4.0f;
@@ -687,13 +682,14 @@ __global__ void __launch_bounds__(NW * 64, OCC) attn_fwd_fp8_kernel(const Fp8Lau
   }
 
   // ---- split launch: leave the chunk's state for the merge kernel (layout of the bf16 kernel) ----
-  if (MODE == MODE_DENSE && p.split > 1) {
-    float* dst = p.partial + ((size_t)item * NW + wave) * ((DB * 16 + 2) * 64) + lane;
+  if (MODE != MODE_PBAND && it.partial) {
+    typedef float __attribute__((address_space(1)))* global_float_ptr;   // global stores, not FLAT ones
+    global_float_ptr dst = (global_float_ptr)(uintptr_t)(it.partial + (size_t)wave * ((DB * 16 + 2) * 64) + lane);
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int i = 0; i < 16; ++i) dst[(db * 16 + i) * 64] = o[db][i];
-    dst[(DB * 16) * 64] = -nm[0];
+    dst[(DB * 16) * 64] = kBand && thr == kNegInf ? kNegInf : -nm[0];   // none: the row keeps no key in this band chunk
     dst[(DB * 16 + 1) * 64] = l4[0];
     return;
   }
@@ -713,6 +709,85 @@ __global__ void __launch_bounds__(NW * 64, OCC) attn_fwd_fp8_kernel(const Fp8Lau
         const bf16x2 b23 = __builtin_convertvector(a23, bf16x2);
         const bf16x4 out4 = {b01[0], b01[1], b23[0], b23[1]};
         *reinterpret_cast<bf16x4*>(dst + db * 32 + g * 8 + half * 4) = out4;
+      }
+    }
+  }
+}
+
+// One launch per group: work-group = one item.
+template <int D, int NW, int BC, int OCC, int MODE>
+__global__ void __launch_bounds__(NW * 64, OCC) attn_fwd_fp8_kernel(const Fp8Launch pp) {
+  const AttnLaunch& p = pp.a;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * BC * D];
+  // which tile of which head (XCD-aware: consecutive items share an XCD)
+  const int per_xcd = (p.n_items + 7) >> 3;
+  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (item >= p.n_items) return;
+  Fp8Item it{};
+  it.qblk = item % p.n_q_blocks;
+  const int chunk = (item / p.n_q_blocks) % p.split;
+  const int hb = item / p.n_q_blocks / p.split;
+  const int hg = hb % p.n_heads;
+  it.b = hb / p.n_heads;
+  it.head = p.heads ? p.heads[hg] : hg;
+  it.n_keys = p.L;
+  if (MODE == MODE_DENSE) {
+    const int n_all = (p.L + BC - 1) / BC;
+    it.t_base = chunk * n_all / p.split;
+    it.n_tiles = (chunk + 1) * n_all / p.split - it.t_base;
+    if (p.split > 1) it.partial = p.partial + (size_t)item * NW * ((D / 32 * 16 + 2) * 64);
+  } else {
+    const int* rec = p.ws + p.list_table + 4 * p.list_id[hg];
+    if (MODE == MODE_BAND || MODE == MODE_PBAND) {
+      const int* row_ptr = p.ws + rec[0];
+      const int e0 = row_ptr[it.qblk], e1 = row_ptr[it.qblk + 1];
+      it.entries = (const_int2_ptr)(uintptr_t)(p.ws + rec[1]) + e0;
+      it.runs = (const_int2_ptr)(uintptr_t)(p.ws + rec[2]);
+      it.n_tiles = e1 - e0;
+      if (it.n_tiles == 0) return;   // rows that another launch computes (text rows of a layer with a text prefix)
+      if (MODE == MODE_PBAND) it.row_map = p.ws + rec[3];
+    } else {
+      if (it.qblk < p.skip_q_blocks) return;   // text rows: another launch computes them
+      it.n_tiles = rec[1] / BC;
+      it.n_keys = rec[2];
+    }
+  }
+  fp8_body<D, NW, BC, MODE>(pp, it, smem);
+}
+
+// The layer in one launch, work-group = one record of the plan's table of items (see the bf16 kernel).
+template <int D, int NW, int BC>
+__global__ void __launch_bounds__(NW * 64, 2) attn_grid_fp8_kernel(const Fp8Launch pp, const int table) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * BC * D];
+  typedef const int __attribute__((address_space(4)))* const_int_ptr;
+  const const_int_ptr r = (const_int_ptr)(uintptr_t)(pp.a.ws + table) + (size_t)blockIdx.x * kGridWords;
+  if (r[0] < 0) return;
+  const int kind = r[0] & 255, t0 = r[0] >> 8;
+  Fp8Item it{};
+  it.head = r[1];
+  it.b = r[2];
+  it.qblk = r[3];
+  it.n_tiles = r[4];
+  const int list = r[5], more = r[6], last = r[7];
+  it.t_base = t0;
+  it.n_keys = kind == SEG_GATHER ? more : pp.a.L;
+  if (kind == SEG_BAND || kind == SEG_PBAND) {
+    it.entries = (const_int2_ptr)(uintptr_t)(pp.a.ws + list) + t0;
+    it.runs = (const_int2_ptr)(uintptr_t)(pp.a.ws + more);
+  }
+  if (kind == SEG_PBAND) it.row_map = pp.a.ws + last;
+  else if (last >= 0) it.partial = pp.a.partial + (size_t)last * NW * ((D / 32 * 16 + 2) * 64);
+  switch (kind) {
+    case SEG_DENSE: fp8_body<D, NW, BC, MODE_DENSE>(pp, it, smem); break;
+    case SEG_BAND: fp8_body<D, NW, BC, MODE_BAND>(pp, it, smem); break;
+    case SEG_GATHER: fp8_body<D, NW, BC, MODE_GATHER>(pp, it, smem); break;
+    case SEG_PBAND: fp8_body<D, NW, BC, MODE_PBAND>(pp, it, smem); break;
+    default: {   // zero fill of kGridZeroRows rows of a skipped head
+      __bf16* O = pp.a.out + (int64_t)it.b * pp.a.stride_b + (int64_t)it.head * pp.a.stride_h;
+      constexpr int CH = D / 8;
+      for (int c = threadIdx.x; c < kGridZeroRows * CH; c += NW * 64) {
+        const int row = it.qblk * kGridZeroRows + c / CH;
+        if (row < pp.a.L) *reinterpret_cast<u32x4*>(O + (int64_t)row * pp.a.stride_l + (c % CH) * 8) = u32x4{0u, 0u, 0u, 0u};
       }
     }
   }
@@ -783,6 +858,26 @@ hipError_t launch_attention_fp8(const Fp8Launch& p, int mode, hipStream_t stream
   if (p.a.D == 128) return launch_mode_fp8<128, Tile128::NW, Tile128::BC, Tile128::OCC>(p, mode, stream);
   if (p.a.D == 64) return launch_mode_fp8<64, Tile64::NW, Tile64::BC, Tile64::OCC>(p, mode, stream);
   return hipErrorInvalidValue;
+}
+
+template <int D, int BC>
+static hipError_t launch_grid_fp8_shape(const Fp8Launch& p, const GridLaunch& g, hipStream_t stream) {
+  constexpr int NW = 4;
+  const dim3 heads(p.Lp / 64, g.n_heads * p.a.B);
+  if (g.n_heads > 0) hipLaunchKernelGGL(quantise_layer_kernel<D>, heads, dim3(256), 0, stream, p, g.head_table, g.n_heads);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_grid_fp8_kernel<D, NW, BC>), dim3(g.n_blocks), dim3(NW * 64), 0, stream, p, g.table);
+  return hipGetLastError();
+}
+
+hipError_t launch_grid_fp8(const Fp8Launch& p, const GridLaunch& g, hipStream_t stream) {
+  if (g.n_blocks < 1) return hipSuccess;
+  if (!p.k8 || !p.v8t || p.Lp != fp8_padded_len(p.a.L) || !p.a.ws || g.waves != 4) return hipErrorInvalidValue;
+  if (g.n_merges > 0 && !p.a.partial) return hipErrorInvalidValue;
+  hipError_t e = hipErrorInvalidValue;
+  if (p.a.D == 128) e = launch_grid_fp8_shape<128, Tile128s::BC>(p, g, stream);
+  if (p.a.D == 64) e = launch_grid_fp8_shape<64, Tile64s::BC>(p, g, stream);
+  return e == hipSuccess ? launch_grid_merge(g, stream) : e;
 }
 
 }  // namespace svd

@@ -389,13 +389,15 @@ static const std::vector<BandList>* bands_on(const Group& g, int32_t block_q) {
   return other.empty() ? nullptr : &other;
 }
 
-double grid_tiles(const Plan& plan, int32_t block_q) {
+double grid_tiles(const Plan& plan, int32_t block_q, double* dense) {
   const double n_qb = std::ceil(static_cast<double>(plan.desc.L) / block_q);
   double tiles = 0.0;
+  if (dense) *dense = 0.0;
   for (const Group& g : plan.groups) {
     const std::vector<BandList>* bands = bands_on(g, block_q);
     const double text = g.mode >= SVD_DIAG ? static_cast<double>(plan.text_tokens / block_q) * plan.n_k_blocks : 0.0;
     for (int32_t id : g.list_id) {
+      if (dense && g.mode == SVD_DENSE) *dense += n_qb * plan.n_k_blocks * plan.desc.B;
       if (g.mode == SVD_DENSE) tiles += n_qb * plan.n_k_blocks;
       else if (g.mode == SVD_VSTRIPE) tiles += n_qb * (g.columns[id].cols.size() / plan.block_k) + text;
       else if (g.mode != SVD_SKIP && bands) tiles += (*bands)[id].kv_block_idx.size() + text;
@@ -404,7 +406,7 @@ double grid_tiles(const Plan& plan, int32_t block_q) {
   return tiles * plan.desc.B;
 }
 
-bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, GridTable* out) {
+bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, bool text_of_stripes, GridTable* out) {
   const svd_tensor_desc& d = plan->desc;
   const int64_t L = d.L, bk = plan->block_k;
   const int32_t n_qb = static_cast<int32_t>(ceil_div(L, block_q));
@@ -413,50 +415,61 @@ bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, Gr
   std::vector<int32_t>& img = plan->ws_image;
   struct Rec {
     int32_t w[kGridWords];
-    double cost;
+    double cost() const { return w[0] == SEG_ZERO ? 0.5 : w[4] + kGridItemCost; }   // in key tiles
   };
   struct Segment {
     std::vector<Rec> recs;
     double cost = 0.0, longest = 0.0;
     void add(const Rec& r) {
       recs.push_back(r);
-      cost += r.cost;
-      longest = std::max(longest, r.cost);
+      cost += r.cost();
+      longest = std::max(longest, r.cost());
     }
   };
   std::vector<Segment> segs;
+  std::vector<int32_t> head_recs;
   for (Group& g : plan->groups) {
     Segment s, text;
+    s.recs.reserve(static_cast<size_t>(n_qb) * g.heads.size() * d.B);
     const std::vector<BandList>* bands = bands_on(g, block_q);
     size_t table = g.ws_list_table;
     if (g.mode == SVD_DIAG || g.mode == SVD_MULTIDIAG) {
       if (!bands) return false;
       if (bands == &g.bands_small) table = g.ws_list_table_small;
-      if (bands == &g.bands_large) {
+      if (bands == &g.bands_large && !g.ws_list_table_large) {
         g.ws_list_table_large = table = append(&img, std::vector<int32_t>(g.bands_large.size() * kListRecordWords, 0));
         emit_band_lists(&img, g.bands_large, table);
       }
+      if (bands == &g.bands_large) table = g.ws_list_table_large;
+    }
+    for (size_t t = 0; t < g.heads.size() && g.mode != SVD_SKIP; ++t) {
+      const int32_t* rec = img.data() + g.ws_list_table + static_cast<size_t>(g.list_id[t]) * kListRecordWords;
+      const bool listed = g.mode == SVD_VSTRIPE || g.rearranged;
+      head_recs.push_back(g.heads[t]);
+      head_recs.push_back(!listed ? -1 : g.rearranged ? rec[3] : rec[0]);
+      head_recs.push_back(!listed ? 0 : g.rearranged ? static_cast<int32_t>(n_kb * bk) : rec[1]);
+      head_recs.push_back(0);
     }
     for (int32_t b = 0; b < d.B; ++b) {
       for (size_t t = 0; t < g.heads.size(); ++t) {
         const int32_t head = g.heads[t];
         if (g.mode == SVD_SKIP) {
           const int32_t n = static_cast<int32_t>(ceil_div(L, kGridZeroRows));
-          for (int32_t z = 0; z < n; ++z) s.add({{SEG_ZERO, head, b, z, 0, 0, 0, -1}, 0.5});
+          for (int32_t z = 0; z < n; ++z) s.add({{SEG_ZERO, head, b, z, 0, 0, 0, -1}});
           continue;
         }
         if (g.mode == SVD_DENSE) {
-          for (int32_t qb = 0; qb < n_qb; ++qb) s.add({{SEG_DENSE, head, b, qb, n_kb, 0, 0, -1}, n_kb + kGridItemCost});
+          for (int32_t qb = 0; qb < n_qb; ++qb) s.add({{SEG_DENSE, head, b, qb, n_kb, 0, 0, -1}});
           continue;
         }
-        for (int32_t qb = 0; qb < text_qb; ++qb) text.add({{SEG_DENSE, head, b, qb, n_kb, 0, 0, -1}, n_kb + kGridItemCost});
+        for (int32_t qb = 0; qb < text_qb && (text_of_stripes || g.mode != SVD_VSTRIPE); ++qb) text.add({{SEG_DENSE, head, b, qb, n_kb, 0, 0, -1}});
         if (g.mode == SVD_VSTRIPE) {
           const ColumnList& cl = g.columns[g.list_id[t]];
           const int64_t first = (static_cast<int64_t>(b) * g.heads.size() + t) * 2 * gather_pad;
           if (first + gather_pad > INT32_MAX) return false;
           const int32_t n = static_cast<int32_t>(cl.cols.size() / bk);
           for (int32_t qb = text_qb; qb < n_qb; ++qb)
-            s.add({{SEG_GATHER, head, b, qb, n, static_cast<int32_t>(first), cl.n_cols, -1}, n + kGridItemCost});
+            s.add({{SEG_GATHER, head, b, qb, n, static_cast<int32_t>(first), cl.n_cols, -1}});
           continue;
         }
         const BandList& bl = (*bands)[g.list_id[t]];
@@ -466,7 +479,7 @@ bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, Gr
           const int64_t entry = static_cast<int64_t>(rec[1]) + 2 * static_cast<int64_t>(e0);
           if (n < 1 || entry > INT32_MAX) return false;
           s.add({{g.rearranged ? SEG_PBAND : SEG_BAND, head, b, qb, n, static_cast<int32_t>(entry), rec[2],
-                  g.rearranged ? rec[3] : -1}, n + kGridItemCost});
+                  g.rearranged ? rec[3] : -1}});
         }
       }
     }
@@ -502,7 +515,6 @@ bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, Gr
         q.w[0] = r.w[0] | t0 << 8;
         q.w[4] = t1 - t0;
         q.w[7] = static_cast<int32_t>(n_slots++);
-        q.cost = t1 - t0 + kGridItemCost;
         cut.push_back(q);
       }
     }
@@ -514,28 +526,36 @@ bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, Gr
   // Work-groups are dealt to the eight XCDs in turn: record 8 * i + x is the i-th of XCD x.  Every segment is
   // cut into eight runs of consecutive items (the query tiles of a head share their K and V in one L2), the
   // cuts placed so that the XCDs' loads stay level; long items come first.
-  std::vector<const Rec*> queue[8];
-  double load[8] = {};
-  double goal = 0.0;
+  std::vector<size_t> cuts;   // per segment: where the runs of XCD 0..6 end
+  double load[8] = {}, goal = 0.0;
+  size_t depth[8] = {};
   for (const Segment& s : segs) {
     goal += s.cost / 8;
     size_t at = 0;
-    for (int x = 0; x < 8; ++x)
-      while (at < s.recs.size() && (x == 7 || load[x] + 0.5 * s.recs[at].cost < goal)) {
-        load[x] += s.recs[at].cost;
-        queue[x].push_back(&s.recs[at++]);
-      }
+    for (int x = 0; x < 7; ++x) {
+      const size_t from = at;
+      for (; at < s.recs.size() && load[x] + 0.5 * s.recs[at].cost() < goal; ++at) load[x] += s.recs[at].cost();
+      depth[x] += at - from;
+      cuts.push_back(at);
+    }
+    for (size_t i = at; i < s.recs.size(); ++i) load[7] += s.recs[i].cost();
+    depth[7] += s.recs.size() - at;
   }
-  size_t deepest = 0;
-  for (const auto& q : queue) deepest = std::max(deepest, q.size());
+  const size_t deepest = *std::max_element(depth, depth + 8);
   if (deepest * 8 > INT32_MAX / kGridWords) return false;
-  std::vector<int32_t> table(deepest * 8 * kGridWords, -1);
-  for (int x = 0; x < 8; ++x)
-    for (size_t i = 0; i < queue[x].size(); ++i)
-      std::copy(queue[x][i]->w, queue[x][i]->w + kGridWords, table.begin() + (8 * i + x) * kGridWords);
   img.resize((img.size() + kGridWords - 1) / kGridWords * kGridWords, 0);
-  out->table = append(&img, table);
+  out->table = img.size();
+  img.resize(img.size() + deepest * 8 * kGridWords, -1);
+  for (int x = 0; x < 8; ++x) {
+    int32_t* to = img.data() + out->table + static_cast<size_t>(x) * kGridWords;
+    for (size_t n = 0; n < segs.size(); ++n) {
+      const size_t first = x ? cuts[7 * n + x - 1] : 0, end = x < 7 ? cuts[7 * n + x] : segs[n].recs.size();
+      for (size_t i = first; i < end; ++i, to += 8 * kGridWords) std::copy(segs[n].recs[i].w, segs[n].recs[i].w + kGridWords, to);
+    }
+  }
   out->merge_table = append(&img, merges);
+  out->head_table = append(&img, head_recs);
+  out->n_heads = static_cast<int>(head_recs.size() / kGridHeadWords);
   img.resize(align4(img.size()) + 4, 0);
   if (img.size() > static_cast<size_t>(INT32_MAX)) return false;
   out->n_blocks = static_cast<int>(deepest * 8);

@@ -112,16 +112,22 @@ enum { SEG_DENSE = 0, SEG_BAND = 1, SEG_GATHER = 2, SEG_PBAND = 3, SEG_ZERO = 4 
 //   0 head  1 batch entry  2 query tile  3 chunks  4 first slot
 constexpr int kGridWords = 8;
 constexpr int kGridZeroRows = 1024;
+constexpr int kGridHeadWords = 4;
 struct GridTable {
   int n_blocks = 0, n_merges = 0, n_slots = 0;   // records, merge records, slots of partial results
   size_t table = 0, merge_table = 0;             // word offsets in the workspace
+  // heads that compute, for the pre-pass of the FP8 variant: {head, word offset of the column list or row map (-1: none), its length, 0}
+  int n_heads = 0;
+  size_t head_table = 0;
 };
-// Key tiles that a launch of the whole layer on query tiles of block_q rows walks.
-double grid_tiles(const Plan& plan, int32_t block_q);
+// Key tiles that a launch of the whole layer on query tiles of block_q rows walks; *dense: those of the dense heads.
+double grid_tiles(const Plan& plan, int32_t block_q, double* dense = nullptr);
 // Appends the records to plan->ws_image.  slots: work-groups that the device runs at a time;
 // gather_pad: rows per head in the gathered arrays of the vertical-stripe group.  False: an index
 // would not fit (nothing is appended that matters).
-bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, GridTable* out);
+// text_of_stripes = false: the text rows of vertical-stripe heads are left out (the FP8 variant, whose arrays of such
+// a head hold its columns only, computes them in a launch of their own).
+bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, bool text_of_stripes, GridTable* out);
 
 svd_status validate_desc(const svd_tensor_desc* desc);
 

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "attn_kernels.h"
+#include "fp8_kernels.h"
 #include "hip_stub.h"
 
 namespace svd {
@@ -29,7 +30,29 @@ void rows(const GridLaunch& g, int b, int head, int row0, int n) {
 
 }  // namespace
 
+static void walk(const GridLaunch& g, const Fp8Launch* f8, hipStream_t stream);
+
 hipError_t launch_grid(const GridLaunch& g, hipStream_t stream) {
+  walk(g, nullptr, stream);
+  return hipSuccess;
+}
+
+// The pre-pass writes the arrays of every head that computes; the text rows of stripe heads are not in the table.
+hipError_t launch_grid_fp8(const Fp8Launch& f, const GridLaunch& g, hipStream_t stream) {
+  stub::note_launch(stream, "quantise_layer_kernel");
+  if (g.waves != 4 || f.a.partial != g.partial) stub::violation("grid fp8: waves %d", g.waves);
+  for (int h = 0; h < g.n_heads; ++h) {
+    const int* r = g.a.ws + g.head_table + h * kGridHeadWords;
+    need(r, kGridHeadWords * 4, "head record");
+    if (r[0] < 0 || r[0] >= g.a.H) stub::violation("grid fp8: head %d", r[0]);
+    if (r[1] >= 0) need(g.a.ws + r[1], (size_t)r[2] * 4, "column list or row map");
+    if (r[1] >= 0 && (r[2] > f.Lp || r[2] % 64)) stub::violation("grid fp8: list of %d keys", r[2]);
+  }
+  walk(g, &f, stream);
+  return hipSuccess;
+}
+
+static void walk(const GridLaunch& g, const Fp8Launch* f8, hipStream_t stream) {
   stub::note_launch(stream, "attn_grid_kernel");
   if (g.n_merges > 0) stub::note_launch(stream, "merge_chunks_kernel");
   const int BR = g.waves * 32, BC = g.a.D == 128 ? Tile128::BC : Tile64::BC;
@@ -55,9 +78,11 @@ hipError_t launch_grid(const GridLaunch& g, hipStream_t stream) {
     if (kind == SEG_DENSE) {
       if ((t0 + n - 1) * BC >= g.a.L) stub::violation("grid record %d: key tile past the sequence", i);
     } else if (kind == SEG_GATHER) {
-      if ((t0 + n) * BC > g.a.gather_pad || (t0 + n - 1) * BC >= r[6]) stub::violation("grid record %d: past the column list", i);
-      need(g.a.gathered + ((size_t)r[5] + t0 * BC) * g.a.D, (size_t)n * BC * g.a.D * 2, "gathered K rows");
-      need(g.a.gathered + ((size_t)r[5] + g.a.gather_pad + t0 * BC) * g.a.D, (size_t)n * BC * g.a.D * 2, "gathered V rows");
+      if (f8) {
+        if ((t0 + n) * BC > f8->Lp || (t0 + n - 1) * BC >= r[6]) stub::violation("grid record %d: past the column list", i);
+      } else if ((t0 + n) * BC > g.a.gather_pad || (t0 + n - 1) * BC >= r[6]) stub::violation("grid record %d: past the column list", i);
+      if (!f8) need(g.a.gathered + ((size_t)r[5] + t0 * BC) * g.a.D, (size_t)n * BC * g.a.D * 2, "gathered K rows");
+      if (!f8) need(g.a.gathered + ((size_t)r[5] + g.a.gather_pad + t0 * BC) * g.a.D, (size_t)n * BC * g.a.D * 2, "gathered V rows");
     } else {
       const int* e = g.a.ws + r[5] + 2 * t0;
       need(e, (size_t)n * 8, "band entries");
@@ -104,7 +129,6 @@ hipError_t launch_grid(const GridLaunch& g, hipStream_t stream) {
     rows(g, r[1], r[0], r[2] * BR, BR);
   }
   if (merged != slots.size()) stub::violation("grid: %zu slots, %zu merged", slots.size(), merged);
-  return hipSuccess;
 }
 
 }  // namespace svd

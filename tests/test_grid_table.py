@@ -11,6 +11,7 @@ import torch
 from paper_2506_03065_amd import binding as svd
 from paper_2506_03065_amd import workloads as W
 from parity_util import check_layer, run_planned
+from test_gpu_fp8 import check_layer_fp8, run_fp8
 from test_gpu_random_layers import random_layer
 from test_host_launch_model import CSRC, ROOT, STUB, layer_text, run
 
@@ -63,3 +64,5 @@ def test_cut_items_of_every_kind(D, mode):
     k = (k * torch.linspace(0.2, 2.0, L, device="cuda:0")[:, None]).to(torch.bfloat16)
     out = run_planned(wl, q, k, v)
     check_layer(wl, q, k, v, out)
+    out8, _ = run_fp8(wl, q, k, v)
+    check_layer_fp8(wl, q, k, v, out8)
