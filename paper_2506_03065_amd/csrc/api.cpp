@@ -267,9 +267,8 @@ struct GridTables {
 };
 GridTables add_grid_tables(Plan* p, const svd_plan_options* opt, int form, int n_cu) {
   GridTables g;
-  const int pad = stripe_gather_pad(*p);
   g.waves = grid_waves(*p, opt, form, n_cu);
-  if (g.waves) g.bf16 = svd::build_grid_table(p, g.waves * 32, 8 / g.waves * n_cu, pad, true, &g.table);
+  if (g.waves) g.bf16 = svd::build_grid_table(p, g.waves * 32, 8 / g.waves * n_cu, true, &g.table);
   if (grid_fp8(*p, opt, n_cu)) {
     bool stripes = false;
     for (const svd::Group& gr : p->groups) stripes = stripes || gr.mode == SVD_VSTRIPE;
@@ -277,7 +276,7 @@ GridTables add_grid_tables(Plan* p, const svd_plan_options* opt, int form, int n
       g.fp8 = true;   // the same items
       g.table8 = g.table;
     } else {
-      g.fp8 = svd::build_grid_table(p, svd::kernel_small_block_q(p->desc.D), 2 * n_cu, pad, false, &g.table8);
+      g.fp8 = svd::build_grid_table(p, svd::kernel_small_block_q(p->desc.D), 2 * n_cu, false, &g.table8);
     }
   }
   const size_t slots = g.bf16 ? static_cast<size_t>(g.table.n_slots) * svd::grid_slot_floats(p->desc.D, g.waves) : 0;
@@ -917,8 +916,7 @@ svd_status svd_attn_forward_planned(const svd_plan* plan, const void* q, const v
   const Plan& p = plan->p;
   hipStream_t main_stream = static_cast<hipStream_t>(hip_stream);
   if (plan->grid) {
-    svd::GridLaunch gl = grid_launch(*plan, plan->grid_table, plan->grid_waves, base_launch(p.desc, q, k, v, out));
-    if (svd_status st = gather_stripes(*plan, &gl.a, main_stream)) return st;
+    const svd::GridLaunch gl = grid_launch(*plan, plan->grid_table, plan->grid_waves, base_launch(p.desc, q, k, v, out));
     return svd::launch_grid(gl, main_stream) == hipSuccess ? SVD_OK : SVD_ERR_HIP;
   }
   if (plan->single_launch) {

@@ -15,7 +15,8 @@ namespace svd {
 // MODE_PBAND is the banded loop in a rearranged token order (Section 4.1.2): the
 // band lists index positions of that order and every row of q, k, v and out is
 // reached through the list's row map.
-enum { MODE_DENSE = 0, MODE_BAND = 1, MODE_GATHER = 2, MODE_PBAND = 3 };
+// MODE_COLS (grid launches only) is MODE_GATHER without its pre-pass: the loop takes key rows through the column list.
+enum { MODE_DENSE = 0, MODE_BAND = 1, MODE_GATHER = 2, MODE_PBAND = 3, MODE_COLS = 4 };
 
 // Tile shapes the kernels are instantiated for.  Query tile = NW waves x QB
 // blocks of 32 rows; key tile = BC keys.

@@ -130,20 +130,24 @@ struct Item {
   int t_base;               // DENSE: first key tile
   const_int2_ptr entries;   // BAND, PBAND: the item's part of the CSR list
   const_int2_ptr runs;      // BAND, PBAND
-  const int* row_map;       // PBAND
-  int n_cols;               // GATHER: the head's columns (the keys of its gathered arrays), from the item's first tile on
+  const int* index;         // PBAND: the row map; COLS: the column list from the item's first tile on
+  int n_cols;               // GATHER, COLS: the head's columns from the item's first tile on
   const __bf16* gathered;   // GATHER: the head's gathered K rows from the item's first tile on; V rows follow gather_pad rows later
   float* partial;           // split item: where its unnormalised result goes, else nullptr
 };
 
+// Bytes of LDS a work-group needs: two K and two V tiles, and a ring of the key rows of four
+// tiles for the modes that reach them through an index list.
+constexpr int body_lds(int D, int BC) { return 4 * BC * D * 2 + 4 * BC * 4; }
+
 // Everything a work-group does between picking the item and storing its rows.  smem:
-// 4 * BC * D * 2 bytes of LDS, 16-byte aligned.  Every wave of the work-group calls it
+// body_lds(D, BC) bytes of LDS, 16-byte aligned.  Every wave of the work-group calls it
 // with the same item; a return leaves no wave behind at a barrier (all returns are
 // work-group uniform).
 template <int D, int NW, int QB, int BC, int OCC, int MODE>
 __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, unsigned char* const smem) {
   constexpr bool kBand = MODE == MODE_BAND || MODE == MODE_PBAND;        // walks a CSR list of key tiles
-  constexpr bool kIndirect = MODE == MODE_PBAND;   // key rows come through an index list (the row map)
+  constexpr bool kIndirect = MODE == MODE_PBAND || MODE == MODE_COLS;   // key rows come through an index list
   constexpr bool kGathered = MODE == MODE_GATHER;  // K and V are the group's gathered rows: a short dense head
   constexpr int NT = NW * 64;
   constexpr int QW = QB * 32;       // query rows per wave
@@ -158,11 +162,12 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
 
   unsigned char* const sK = smem;                    // [2][BC][D] bf16, swizzled
   unsigned char* const sV = smem + 2 * TILE_BYTES;   // [2][BC][D] bf16, swizzled
+  unsigned char* const sI = smem + 4 * TILE_BYTES;   // [4][BC] key rows, slot = tile & 3 (kIndirect)
 
   const int qblk = it.qblk, head = it.head, b = it.b;
   const int n_tiles = it.n_tiles, t_base = it.t_base, n_cols = it.n_cols;
   const const_int2_ptr entries = it.entries, runs = it.runs;
-  const int* __restrict__ cols = it.row_map;
+  const int* __restrict__ cols = it.index;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -250,8 +255,8 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   typedef __attribute__((address_space(3))) void* lds_ptr;
   typedef __attribute__((address_space(1))) const void* glb_ptr;
   const unsigned stride_bytes = kGathered ? (unsigned)ROW_BYTES : (unsigned)p.stride_l * 2u;   // of a key row
-  unsigned g_k[LPT], g_v[LPT];   // DENSE, BAND, GATHER: byte offset inside the tile; PBAND: chunk offset inside the row
-  unsigned g_r[LPT];             // PBAND: 4 * row of the slab's lane inside the tile
+  unsigned g_k[LPT], g_v[LPT];   // byte offset inside the tile; kIndirect: chunk offset inside the row
+  unsigned g_r[LPT];             // kIndirect: 4 * row of the slab's lane inside the tile
 #pragma unroll
   for (int u = 0; u < LPT; ++u) {
     const int byte = (wave * LPT + u) * 1024 + lane * 16;
@@ -267,20 +272,40 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   const __amdgpu_buffer_rsrc_t rsrc_k = __builtin_amdgcn_make_buffer_rsrc((void*)K, 0, (int)head_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsrc_v = __builtin_amdgcn_make_buffer_rsrc((void*)V, 0, (int)head_bytes, 0x00020000);
   // INNER: the tile is known to lie inside [0, L) (anything but the last tile of a list)
-  auto load_tile = [&](auto is_k_tag, auto inner_tag, const int buf, const int t) {
+  // Key rows through an index list.  An index read in the loop from memory would hold up
+  // the tile load that needs it by a whole trip (and wait, in order, for every load in
+  // flight); so the indices of a tile travel to LDS one stage ahead of its K.  -1 =
+  // padding: an offset past the buffer's range, for which the hardware delivers zeros.
+  // Rearranged window of 8 heads x 75,600, D = 128: 632 us with the indices read from
+  // memory, 618 with the ring.  Column lists read this way cost the loop nothing
+  // measurable and save the pre-pass that gathers K and V rows (5-8 us ahead of the layer:
+  // 24 heads x 2,352, D = 128: 44.9 -> 40.3 us; 4 x 1,024, D = 64: 16.2 -> 13.1).
+  const __amdgpu_buffer_rsrc_t rsrc_i = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)cols, 0, (MODE == MODE_PBAND ? (L + BC - 1) / BC : n_tiles) * BC * 4, 0x00020000);
+  auto index_base = [&](const int t) { return (MODE == MODE_PBAND ? entries[t].x : t) * BC; };
+  auto load_index = [&](const int t) {
+    if (wave < BC / 64)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_i, (lds_ptr)(sI + ((t & 3) * BC + wave * 64) * 4), 4,
+                                               lane * 4 + wave * 256, index_base(t) * 4, 0, 0);
+  };
+  // FIRST: the prologue's loads, whose indices are read from memory
+  auto load_tile = [&](auto is_k_tag, auto inner_tag, const int buf, const int t, auto first_tag) {
     constexpr bool IS_K = decltype(is_k_tag)::value != 0;
     constexpr bool INNER = decltype(inner_tag)::value != 0;
+    constexpr bool FIRST = decltype(first_tag)::value != 0;
     const char* src_b = reinterpret_cast<const char*>(IS_K ? K : V);
     const __amdgpu_buffer_rsrc_t rsrc = IS_K ? rsrc_k : rsrc_v;
     unsigned char* dst = (IS_K ? sK : sV) + buf * TILE_BYTES + wave * (LPT * 1024);
     if (kIndirect) {
-      // key rows come from the row map at the tile the band list names (-1 = padding: any valid row, masked later)
-      const char* list = reinterpret_cast<const char*>(cols + entries[t].x * BC);
+      int c[LPT];
+#pragma unroll
+      for (int u = 0; u < LPT; ++u)
+        c[u] = FIRST ? *reinterpret_cast<const int*>(reinterpret_cast<const char*>(cols + index_base(t)) + g_r[u])
+                     : *reinterpret_cast<const int*>(sI + (t & 3) * (BC * 4) + g_r[u]);
 #pragma unroll
       for (int u = 0; u < LPT; ++u) {
-        int c = *reinterpret_cast<const int*>(list + g_r[u]);
-        c = c < 0 ? 0 : c;
-        const unsigned off = __umul24((unsigned)c, stride_bytes) + (IS_K ? g_k[u] : g_v[u]);
+        const unsigned at = __umul24((unsigned)c[u], stride_bytes) + (IS_K ? g_k[u] : g_v[u]);
+        const unsigned off = c[u] < 0 ? 0xfffffff0u : at;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr)(dst + u * 1024), 16, (int)off, 0, 0, 0);
       }
     } else {
@@ -510,9 +535,11 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   // ---- prologue: K(0), V(0), K(1) into LDS, scores of tile 0 ----
   f32x16 s_a[KB2][QB], s_b[KB2][QB];
   if (n_tiles > 0) {
-    load_tile(Int<1>{}, Int<0>{}, 0, 0);
-    load_tile(Int<0>{}, Int<0>{}, 0, 0);
-    if (n_tiles > 1) load_tile(Int<1>{}, Int<0>{}, 1, 1);
+    if (kIndirect && n_tiles > 1) load_index(1);
+    if (kIndirect && n_tiles > 2) load_index(2);
+    load_tile(Int<1>{}, Int<0>{}, 0, 0, Int<1>{});
+    load_tile(Int<0>{}, Int<0>{}, 0, 0, Int<1>{});
+    if (n_tiles > 1) load_tile(Int<1>{}, Int<0>{}, 1, 1, Int<1>{});
   }
   __syncthreads();
   if (n_tiles > 0) {
@@ -540,8 +567,9 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
     constexpr bool has1 = decltype(next_tag)::value != 0;
     constexpr bool INNER = decltype(inner_tag)::value != 0;
     const bool has2 = INNER || t + 2 < n_tiles;
-    if (has2) load_tile(Int<1>{}, inner_tag, PAR, t + 2);       // K(t+2) takes the place of K(t), read in the last stage
-    if (has1) load_tile(Int<0>{}, inner_tag, PAR ^ 1, t + 1);   // V(t+1) takes the place of V(t-1)
+    if (kIndirect && t + 3 < n_tiles) load_index(t + 3);
+    if (has2) load_tile(Int<1>{}, inner_tag, PAR, t + 2, Int<0>{});       // K(t+2) takes the place of K(t), read in the last stage
+    if (has1) load_tile(Int<0>{}, inner_tag, PAR ^ 1, t + 1, Int<0>{});   // V(t+1) takes the place of V(t-1)
     // partly kept tile?  band lists flag it per entry; the dense and gather loops
     // can only meet one at the very end (keys past L, padding of the column list)
     bool masked;
@@ -702,7 +730,7 @@ __device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item, u
   // queue behind nor wait for the tile loads in flight.
   it.entries = uni_const(entries);
   it.runs = uni_const(runs);
-  it.row_map = uni(row_map);
+  it.index = uni(row_map);
   it.n_tiles = uni(n_tiles);
   it.n_cols = uni(n_cols);
   it.t_base = uni(t_base);
@@ -713,7 +741,7 @@ __device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item, u
 // One launch per group: work-group = one item.
 template <int D, int NW, int QB, int BC, int OCC, int MODE>
 __global__ void __launch_bounds__(NW * 64, OCC) attn_fwd_kernel(const AttnLaunch p) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * BC * D * 2];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[body_lds(D, BC)];
   // which tile of which head (XCD-aware: consecutive items share an XCD)
   const int per_xcd = (p.n_items + 7) >> 3;
   const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
@@ -919,7 +947,7 @@ __device__ __attribute__((noinline)) void layer_segment(const AttnLaunch av, con
 
 template <int D, int BC>
 __global__ void __launch_bounds__(kLayerWaves * 64, 2) attn_layer_kernel(const LayerLaunch lp) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * BC * D * 2];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[body_lds(D, BC)];
   __shared__ int pick;
   typedef __attribute__((address_space(3))) unsigned char* lds_bytes;
   typedef __attribute__((address_space(3))) int* lds_int;
@@ -959,7 +987,7 @@ typedef const int __attribute__((address_space(4)))* const_int_ptr;
 
 template <int D, int NW, int BC>
 __global__ void __launch_bounds__(NW * 64, 2) attn_grid_kernel(const GridLaunch g) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * BC * D * 2];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[body_lds(D, BC)];
   const const_int_ptr r = (const_int_ptr)(uintptr_t)(g.a.ws + g.table) + (size_t)blockIdx.x * kGridWords;
   if (r[0] < 0) return;
   const int kind = r[0] & 255, t0 = r[0] >> 8;
@@ -972,18 +1000,18 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_grid_kernel(const GridLaunch 
   if (kind == SEG_DENSE) {
     it.t_base = t0;
   } else if (kind == SEG_GATHER) {
-    it.gathered = g.a.gathered + ((size_t)list + t0 * BC) * D;
+    it.index = g.a.ws + list + t0 * BC;
     it.n_cols = more - t0 * BC;
   } else {
     it.entries = (const_int2_ptr)(uintptr_t)(g.a.ws + list) + t0;
     it.runs = (const_int2_ptr)(uintptr_t)(g.a.ws + more);
   }
-  if (kind == SEG_PBAND) it.row_map = g.a.ws + last;
+  if (kind == SEG_PBAND) it.index = g.a.ws + last;
   else if (last >= 0) it.partial = g.partial + (size_t)last * NW * ((D / 32 * 16 + 2) * 64);
   switch (kind) {
     case SEG_DENSE: attn_body<D, NW, 1, BC, 2, MODE_DENSE>(g.a, it, smem); break;
     case SEG_BAND: attn_body<D, NW, 1, BC, 2, MODE_BAND>(g.a, it, smem); break;
-    case SEG_GATHER: attn_body<D, NW, 1, BC, 2, MODE_GATHER>(g.a, it, smem); break;
+    case SEG_GATHER: attn_body<D, NW, 1, BC, 2, MODE_COLS>(g.a, it, smem); break;
     case SEG_PBAND: attn_body<D, NW, 1, BC, 2, MODE_PBAND>(g.a, it, smem); break;
     default: {   // zero fill of kGridZeroRows rows of a skipped head
       __bf16* O = g.a.out + (int64_t)it.b * g.a.stride_b + (int64_t)it.head * g.a.stride_h;

@@ -406,7 +406,7 @@ double grid_tiles(const Plan& plan, int32_t block_q, double* dense) {
   return tiles * plan.desc.B;
 }
 
-bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, bool text_of_stripes, GridTable* out) {
+bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_stripes, GridTable* out) {
   const svd_tensor_desc& d = plan->desc;
   const int64_t L = d.L, bk = plan->block_k;
   const int32_t n_qb = static_cast<int32_t>(ceil_div(L, block_q));
@@ -465,11 +465,10 @@ bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, bo
         for (int32_t qb = 0; qb < text_qb && (text_of_stripes || g.mode != SVD_VSTRIPE); ++qb) text.add({{SEG_DENSE, head, b, qb, n_kb, 0, 0, -1}});
         if (g.mode == SVD_VSTRIPE) {
           const ColumnList& cl = g.columns[g.list_id[t]];
-          const int64_t first = (static_cast<int64_t>(b) * g.heads.size() + t) * 2 * gather_pad;
-          if (first + gather_pad > INT32_MAX) return false;
+          const int32_t list = img[g.ws_list_table + static_cast<size_t>(g.list_id[t]) * kListRecordWords];
           const int32_t n = static_cast<int32_t>(cl.cols.size() / bk);
           for (int32_t qb = text_qb; qb < n_qb; ++qb)
-            s.add({{SEG_GATHER, head, b, qb, n, static_cast<int32_t>(first), cl.n_cols, -1}});
+            s.add({{SEG_GATHER, head, b, qb, n, list, cl.n_cols, -1}});
           continue;
         }
         const BandList& bl = (*bands)[g.list_id[t]];

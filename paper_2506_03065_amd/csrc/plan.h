@@ -104,7 +104,7 @@ enum { SEG_DENSE = 0, SEG_BAND = 1, SEG_GATHER = 2, SEG_PBAND = 3, SEG_ZERO = 4 
 //   0 kind (SEG_*) | first key tile << 8, -1: no item
 //   1 head  2 batch entry  3 query tile (SEG_ZERO: block of kGridZeroRows rows)
 //   4 key tiles to walk
-//   5 BAND, PBAND: word offset of the query tile's first list entry; GATHER: its head's first row in the gathered arrays
+//   5 BAND, PBAND: word offset of the query tile's first list entry; GATHER: of the head's column list
 //   6 BAND, PBAND: word offset of the runs; GATHER: columns of the head
 //   7 PBAND: word offset of the row map; else the item's slot of partial results, -1 = not split
 // A long item is cut into chunks of its key tiles; the chunks leave their unnormalised results in
@@ -122,12 +122,11 @@ struct GridTable {
 };
 // Key tiles that a launch of the whole layer on query tiles of block_q rows walks; *dense: those of the dense heads.
 double grid_tiles(const Plan& plan, int32_t block_q, double* dense = nullptr);
-// Appends the records to plan->ws_image.  slots: work-groups that the device runs at a time;
-// gather_pad: rows per head in the gathered arrays of the vertical-stripe group.  False: an index
+// Appends the records to plan->ws_image.  slots: work-groups that the device runs at a time.  False: an index
 // would not fit (nothing is appended that matters).
 // text_of_stripes = false: the text rows of vertical-stripe heads are left out (the FP8 variant, whose arrays of such
 // a head hold its columns only, computes them in a launch of their own).
-bool build_grid_table(Plan* plan, int32_t block_q, int slots, int gather_pad, bool text_of_stripes, GridTable* out);
+bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_stripes, GridTable* out);
 
 svd_status validate_desc(const svd_tensor_desc* desc);
 

@@ -78,11 +78,11 @@ static void walk(const GridLaunch& g, const Fp8Launch* f8, hipStream_t stream) {
     if (kind == SEG_DENSE) {
       if ((t0 + n - 1) * BC >= g.a.L) stub::violation("grid record %d: key tile past the sequence", i);
     } else if (kind == SEG_GATHER) {
-      if (f8) {
-        if ((t0 + n) * BC > f8->Lp || (t0 + n - 1) * BC >= r[6]) stub::violation("grid record %d: past the column list", i);
-      } else if ((t0 + n) * BC > g.a.gather_pad || (t0 + n - 1) * BC >= r[6]) stub::violation("grid record %d: past the column list", i);
-      if (!f8) need(g.a.gathered + ((size_t)r[5] + t0 * BC) * g.a.D, (size_t)n * BC * g.a.D * 2, "gathered K rows");
-      if (!f8) need(g.a.gathered + ((size_t)r[5] + g.a.gather_pad + t0 * BC) * g.a.D, (size_t)n * BC * g.a.D * 2, "gathered V rows");
+      if ((t0 + n - 1) * BC >= r[6] || (f8 && (t0 + n) * BC > f8->Lp)) stub::violation("grid record %d: past the column list", i);
+      const int* cols = g.a.ws + r[5] + t0 * BC;
+      need(cols, (size_t)n * BC * 4, "column list");
+      for (int c = 0; c < n * BC; ++c)
+        if (cols[c] >= g.a.L || (cols[c] < 0) != (t0 * BC + c >= r[6])) stub::violation("grid record %d: column %d is %d", i, c, cols[c]);
     } else {
       const int* e = g.a.ws + r[5] + 2 * t0;
       need(e, (size_t)n * 8, "band entries");

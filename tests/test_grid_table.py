@@ -66,3 +66,21 @@ def test_cut_items_of_every_kind(D, mode):
     check_layer(wl, q, k, v, out)
     out8, _ = run_fp8(wl, q, k, v)
     check_layer_fp8(wl, q, k, v, out8)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,n_cols", [(64, 65), (64, 129), (128, 1), (128, 130)])
+def test_padding_of_the_column_list_reads_no_key(D, n_cols):
+    """A stripe head whose list ends inside a key tile: the rows that fill the tile are not rows of the tensor, so a NaN
+    in a key outside the list (row 0 among them) reaches no output."""
+    L = 700
+    cols = tuple(range(3, 3 + n_cols))
+    wl = W.Workload("pad", -1, 1, 2, L, D, 140, 5, 0, np.asarray([W.VSTRIPE, W.DIAG], dtype=np.int32),
+                    [{"cols": cols}, {"half_width": 40}], 78)
+    q, k, v = (t.to("cuda:0") for t in W.make_qkv(wl))
+    k2, v2 = k.clone(), v.clone()
+    outside = [r for r in range(L) if r not in cols]
+    k2[:, 0, outside] = float("nan")
+    v2[:, 0, outside] = float("nan")
+    out = run_planned(wl, q, k2, v2)
+    check_layer(wl, q, k, v, out)
