@@ -127,8 +127,8 @@ size_t partial_floats(int D, int n_items);
 void kernel_blocks(int D, int* block_q, int* block_k);
 // Query rows of the small tile (band modes only).
 int kernel_small_block_q(int D);
-// small_q: the launch uses the small query tile (MODE_BAND and MODE_PBAND only;
-// n_q_blocks and the lists must have been built for it).
+// small_q: the launch uses the small query tile (MODE_BAND, MODE_PBAND and unsplit
+// MODE_DENSE; n_q_blocks and the lists must have been built for it).
 hipError_t launch_attention(const AttnLaunch& p, int mode, hipStream_t stream, bool small_q = false);
 hipError_t launch_zero_heads(const AttnLaunch& p, hipStream_t stream);
 // Merges the chunks of a split dense launch (same AttnLaunch) into `out`.

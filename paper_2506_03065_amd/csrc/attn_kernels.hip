@@ -1085,12 +1085,14 @@ hipError_t launch_mode(const AttnLaunch& p, int mode, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// The band modes on the small query tile.
+// The dense and band modes on the small query tile.
 template <int D, int NW, int QB, int BC, int OCC>
-hipError_t launch_band_small(const AttnLaunch& p, int mode, hipStream_t stream) {
+hipError_t launch_small(const AttnLaunch& p, int mode, hipStream_t stream) {
   const int per_xcd = (p.n_items + 7) / 8;
   const dim3 grid(per_xcd * 8), block(NW * 64);
-  if (mode == MODE_BAND) {
+  if (mode == MODE_DENSE && p.split == 1) {   // (a merge of chunks would read them as the large tile's)
+    hipLaunchKernelGGL((attn_fwd_kernel<D, NW, QB, BC, OCC, MODE_DENSE>), grid, block, 0, stream, p);
+  } else if (mode == MODE_BAND) {
     hipLaunchKernelGGL((attn_fwd_kernel<D, NW, QB, BC, OCC, MODE_BAND>), grid, block, 0, stream, p);
   } else if (mode == MODE_PBAND) {
     hipLaunchKernelGGL((attn_fwd_kernel<D, NW, QB, BC, OCC, MODE_PBAND>), grid, block, 0, stream, p);
@@ -1134,8 +1136,8 @@ hipError_t launch_attention(const AttnLaunch& p, int mode, hipStream_t stream, b
   if (p.split < 1 || (p.split > 1 && (mode != MODE_DENSE || !p.partial))) return hipErrorInvalidValue;
   if (mode == MODE_GATHER && (!p.gathered || p.gather_pad < 1)) return hipErrorInvalidValue;
   if (small_q) {
-    if (p.D == 128) return launch_band_small<128, Tile128s::NW, Tile128s::QB, Tile128s::BC, Tile128s::OCC>(p, mode, stream);
-    if (p.D == 64) return launch_band_small<64, Tile64s::NW, Tile64s::QB, Tile64s::BC, Tile64s::OCC>(p, mode, stream);
+    if (p.D == 128) return launch_small<128, Tile128s::NW, Tile128s::QB, Tile128s::BC, Tile128s::OCC>(p, mode, stream);
+    if (p.D == 64) return launch_small<64, Tile64s::NW, Tile64s::QB, Tile64s::BC, Tile64s::OCC>(p, mode, stream);
     return hipErrorInvalidValue;
   }
   if (p.D == 128)

@@ -84,3 +84,25 @@ def test_padding_of_the_column_list_reads_no_key(D, n_cols):
     v2[:, 0, outside] = float("nan")
     out = run_planned(wl, q, k2, v2)
     check_layer(wl, q, k, v, out)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,D,H", [(1, 64, 2), (128, 128, 3), (129, 64, 3), (257, 128, 2), (1000, 64, 6), (4333, 128, 16)])
+def test_dense_entry_point_on_the_small_tile(L, D, H):
+    """Few work-groups, or a last round of large ones left nearly empty (4,333 x 16): the dense call takes the small
+    query tile; the bits are those of the large one (svd_plan with single_launch = 2, dense_split = 1)."""
+    wl = W.small(L=L, D=D, H=H, seed=21)
+    wl.strategy_table[:] = W.DENSE
+    q, k, v = (t.to("cuda:0") for t in W.make_qkv(wl))
+    out = torch.full_like(q, float("nan"))
+    svd.svd_dense_attn_forward(q, k, v, out)
+    desc = svd.desc_of(q)
+    opt = dict(single_launch=2, dense_split=1)
+    ws = torch.empty(svd.svd_plan_workspace_bytes(desc, wl.strategy_table, wl.pattern_params, **opt), dtype=torch.uint8, device="cuda:0")
+    plan = svd.svd_plan_create(desc, wl.strategy_table, wl.pattern_params, workspace=ws, **opt)
+    large = torch.full_like(q, float("nan"))
+    svd.svd_attn_forward_planned(plan, q, k, v, large)
+    torch.cuda.synchronize()
+    plan.close()
+    assert torch.equal(out.view(torch.int16), large.view(torch.int16))
+    check_layer(wl, q, k, v, out, heads=[0], rows=None if L < 2000 else np.arange(0, L, 97))
