@@ -656,8 +656,9 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int i = 0; i < 16; ++i) dst[(db * 16 + i) * 64] = o[db][0][i];
-    // reference exponent of this chunk; none for a row without a kept key in it (band chunks)
-    dst[(DB * 16) * 64] = kBand && thr[0] == kNegInf ? kNegInf : -nm[0][0];
+    // reference exponent of this chunk; none for a row without a finite logit in it (band chunks without a kept key of
+    // the row, chunks of any kind whose keys all have logits of -inf)
+    dst[(DB * 16) * 64] = thr[0] == kNegInf ? kNegInf : -nm[0][0];
     dst[(DB * 16 + 1) * 64] = l4[0][0];   // row sum relative to it
     return;
   }
@@ -780,7 +781,8 @@ __global__ void __launch_bounds__(NW * 64) combine_partials_kernel(const AttnLau
     const float* src = p.partial + (item * NW + wave) * ((DB * 16 + 2) * 64) + lane;
     const float mc = src[(DB * 16) * 64], lc = src[(DB * 16 + 1) * 64];
     const float m_new = fmaxf(m, mc);
-    const float wa = __builtin_amdgcn_exp2f(m - m_new), wc = __builtin_amdgcn_exp2f(mc - m_new);
+    // a chunk in which the row has no finite logit (mc = -inf) adds nothing
+    const float wa = m == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m - m_new), wc = mc == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mc - m_new);
     l = l * wa + lc * wc;
 #pragma unroll
     for (int r = 0; r < RPS; ++r) o[r] = o[r] * wa + src[(r0 + r) * 64] * wc;
@@ -1043,7 +1045,7 @@ __global__ void __launch_bounds__(NW * 64) merge_chunks_kernel(const GridLaunch 
     const float* src = g.partial + ((size_t)(slot + c) * NW + wave) * ((DB * 16 + 2) * 64) + lane;
     const float mc = src[(DB * 16) * 64], lc = src[(DB * 16 + 1) * 64];
     const float m_new = fmaxf(m, mc);
-    // a chunk in which the row keeps no key (mc = -inf) adds nothing
+    // a chunk in which the row has no finite logit (mc = -inf) adds nothing
     const float wa = m == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m - m_new), wc = mc == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mc - m_new);
     l = l * wa + lc * wc;
 #pragma unroll

@@ -689,7 +689,7 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int i = 0; i < 16; ++i) dst[(db * 16 + i) * 64] = o[db][i];
-    dst[(DB * 16) * 64] = kBand && thr == kNegInf ? kNegInf : -nm[0];   // none: the row keeps no key in this band chunk
+    dst[(DB * 16) * 64] = thr == kNegInf ? kNegInf : -nm[0];   // none: the row has no finite score in this chunk
     dst[(DB * 16 + 1) * 64] = l4[0];
     return;
   }

@@ -106,3 +106,32 @@ def test_dense_entry_point_on_the_small_tile(L, D, H):
     plan.close()
     assert torch.equal(out.view(torch.int16), large.view(torch.int16))
     check_layer(wl, q, k, v, out, heads=[0], rows=None if L < 2000 else np.arange(0, L, 97))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("low", [float("-inf"), torch.finfo(torch.bfloat16).min])
+@pytest.mark.parametrize("D,mode,options", [
+    (64, W.DENSE, {}), (128, W.DENSE, {}), (64, W.VSTRIPE, {}), (128, W.VSTRIPE, {}), (128, W.DIAG, {}), (64, W.MULTIDIAG, {}),
+    (64, W.DENSE, {"single_launch": 2, "dense_split": 4}), (128, W.DENSE, {"single_launch": 2, "dense_split": 4})])
+def test_a_chunk_of_minus_infinite_logits(D, mode, options, low):
+    """Keys masked with the type's lowest value or -inf: the first quarter of the keys has a logit of -inf for every
+    query, all others lie some 230 binary orders below zero.  A chunk that holds masked keys alone has no reference; taken
+    as one of 0, it would scale every other chunk's results to nothing."""
+    L = 1930
+    p = {W.DENSE: {}, W.DIAG: {"half_width": 700}, W.MULTIDIAG: {"half_width": 90, "offsets": (-1500, -600, 0, 640, 1400)},
+         W.VSTRIPE: {"cols": tuple(range(5, L, 2))}}[mode]
+    wl = W.Workload("masked", -1, 1, 1, L, D, 386, 5, 0, np.asarray([mode], dtype=np.int32), [p], 79)
+    q, k, v = (t.to("cuda:0") for t in W.make_qkv(wl))
+    # logits: D * 1 * -20 * (64 / D) / sqrt(D) * log2(e), about -230 (D = 64) and -163 (D = 128), and a spread of about one
+    # around that from the small random part (the common offset cancels in the softmax, its rounding with it)
+    q = (1.0 + 0.05 * q.float().clamp(-3, 3)).to(torch.bfloat16)
+    k = (-20.0 * 64 / D + 0.3 * k.float()).to(torch.bfloat16)
+    k[:, :, :480] = low
+    desc = svd.desc_of(q)
+    ws = torch.empty(svd.svd_plan_workspace_bytes(desc, wl.strategy_table, wl.pattern_params, **options), dtype=torch.uint8, device="cuda:0")
+    plan = svd.svd_plan_create(desc, wl.strategy_table, wl.pattern_params, workspace=ws, **options)
+    out = torch.full_like(q, float("nan"))
+    svd.svd_attn_forward_planned(plan, q, k, v, out)
+    torch.cuda.synchronize()
+    plan.close()
+    check_layer(wl, q, k, v, out)
