@@ -289,8 +289,15 @@ svd_status svd_attn_forward_group(const svd_plan* plan, int32_t group, const voi
                                   const void* v, void* out, void* hip_stream);
 
 /* One-shot form: compiles the table (or reuses the plan compiled by the previous
- * call with identical arguments and workspace) and launches.  workspace_bytes
- * must be at least svd_plan_workspace_bytes(...). */
+ * call with identical arguments and workspace), copies the lists to the workspace on
+ * hip_stream and launches.  workspace_bytes must be at least
+ * svd_plan_workspace_bytes(...).  Between calls the workspace is the caller's to use or
+ * free; calls that overlap in time need workspaces of their own.  The library keeps the
+ * lists in page-locked host memory (at most four areas of 8 MiB, for all callers) and
+ * does not wait for the copy; lists longer than that are copied and waited for.  While
+ * hip_stream is capturing, only a call that repeats the previous one's arguments is
+ * taken (SVD_ERR_HIP otherwise): its launches are recorded, the copy is not, and the
+ * workspace must keep what the previous call left in it for as long as the graph is used. */
 svd_status sparse_vdit_attn_forward(const void* q, const void* k, const void* v,
                                     const int32_t* strategy_table,
                                     const svd_head_params* pattern_params, void* out,

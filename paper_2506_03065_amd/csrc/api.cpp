@@ -358,7 +358,22 @@ svd_status check_tensors(const void* q, const void* k, const void* v, const void
   return SVD_OK;
 }
 
-// One-shot cache: the plan of the previous sparse_vdit_attn_forward call.
+// One-shot cache: the plan of the previous sparse_vdit_attn_forward call.  What outlives a call is on the host: between two
+// calls the workspace is the caller's, and a pointer that is the same again says nothing about what it points to (an
+// allocator hands freed memory out a second time).  So every call copies the plan's lists to the workspace, from
+// page-locked memory and in stream order, without waiting for it (0.02 to 3 MB for the benchmark's and smaller layers).
+// A slot of page-locked memory holds the lists of one plan; another plan takes it once the copies out of it are over.
+struct StagedLists {
+  void* host = nullptr;
+  void* device_address = nullptr;
+  size_t bytes = 0;
+  hipEvent_t copied = nullptr;   // behind the last copy out of the slot, on `stream`
+  hipStream_t stream = nullptr;
+  int device = -1;
+  bool pending = false;
+};
+constexpr int kStagedSlots = 4;                             // plans whose copies may be under way at a time
+constexpr size_t kStagedBytes = static_cast<size_t>(8) << 20;   // longer lists are copied from pageable memory, and waited for
 struct OneShot {
   std::mutex mu;
   svd_plan* plan = nullptr;
@@ -367,8 +382,88 @@ struct OneShot {
   std::vector<int32_t> flat;   // flattened parameters
   void* workspace = nullptr;
   size_t workspace_bytes = 0;
+  StagedLists slots[kStagedSlots];
+  int slot = -1;               // the plan's lists, -1: in no slot yet
+  int last_slot = 0;
 };
 OneShot g_oneshot;
+
+bool copies_over(StagedLists* s) {
+  if (s->pending && hipEventQuery(s->copied) == hipSuccess) s->pending = false;
+  (void)hipGetLastError();   // "not ready" is an answer, not an error of the launch that follows
+  return !s->pending;
+}
+
+// Puts the lists into a slot: one with no copy under way, else the one that was taken longest ago.  -1: no page-locked memory.
+int stage_lists(OneShot* c, const std::vector<int32_t>& img) {
+  const size_t bytes = img.size() * sizeof(int32_t);
+  int dev = 0;
+  if (bytes > kStagedBytes || hipGetDevice(&dev) != hipSuccess) return -1;
+  int n = (c->last_slot + 1) % kStagedSlots;
+  for (int i = 0; i < kStagedSlots; ++i) {
+    const int at = (c->last_slot + 1 + i) % kStagedSlots;
+    if (copies_over(&c->slots[at])) {
+      n = at;
+      break;
+    }
+  }
+  StagedLists& s = c->slots[n];
+  if (s.pending && hipEventSynchronize(s.copied) != hipSuccess) return -1;
+  s.pending = false;
+  if (s.copied && s.device != dev) {   // events belong to a device
+    (void)hipEventDestroy(s.copied);
+    s.copied = nullptr;
+  }
+  if (!s.copied && hipEventCreateWithFlags(&s.copied, hipEventDisableTiming) != hipSuccess) {
+    s.copied = nullptr;
+    return -1;
+  }
+  s.device = dev;
+  // a slot grows with its plans, and one that is far too large is given back
+  size_t want = static_cast<size_t>(64) << 10;
+  while (want < bytes) want *= 2;
+  if (s.host && (s.bytes < want || s.bytes > 16 * want)) {
+    (void)hipHostFree(s.host);
+    s.host = nullptr;
+  }
+  if (!s.host) {
+    if (hipHostMalloc(&s.host, want, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+      s.host = nullptr;
+      (void)hipGetLastError();
+      return -1;
+    }
+    s.bytes = want;
+  }
+  if (hipHostGetDevicePointer(&s.device_address, s.host, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    return -1;
+  }
+  std::memcpy(s.host, img.data(), bytes);
+  c->last_slot = n;
+  return n;
+}
+
+// Copies the plan's lists to its workspace, ahead of the launches that `stream` gets next.
+svd_status upload_lists(OneShot* c, hipStream_t stream) {
+  const std::vector<int32_t>& img = c->plan->p.ws_image;
+  const size_t bytes = img.size() * sizeof(int32_t);
+  void* to = c->plan->p.device_workspace;
+  if (c->slot < 0) c->slot = stage_lists(c, img);
+  if (c->slot < 0)
+    return hipMemcpyAsync(to, img.data(), bytes, hipMemcpyHostToDevice, stream) == hipSuccess &&
+                   hipStreamSynchronize(stream) == hipSuccess ? SVD_OK : SVD_ERR_HIP;
+  StagedLists& s = c->slots[c->slot];
+  // on another stream than the last time: one event covers both copies only if they are in order
+  if (s.pending && s.stream != stream && hipStreamWaitEvent(stream, s.copied, 0) != hipSuccess) return SVD_ERR_HIP;
+  if (svd::launch_copy_lists(s.device_address, to, bytes, stream) != hipSuccess) return SVD_ERR_HIP;
+  s.pending = true;
+  s.stream = stream;
+  if (hipEventRecord(s.copied, stream) != hipSuccess) {
+    s.pending = hipStreamSynchronize(stream) != hipSuccess;
+    return SVD_ERR_HIP;
+  }
+  return SVD_OK;
+}
 
 std::vector<int32_t> flatten(const svd_tensor_desc& d, const int32_t* table, const svd_head_params* pp) {
   std::vector<int32_t> f;
@@ -568,14 +663,14 @@ static svd_status compile_for(svd_plan** plan, const svd_tensor_desc* desc, cons
 }
 
 // Second half: the copy of the lists to the workspace, and what the launch form needs.  with_side_streams = false: the plan creates no streams
-// or events of its own and runs its groups one after the other on the caller's stream.
+// or events of its own and runs its groups one after the other on the caller's stream.  copy = false: the caller copies the lists.
 static svd_status attach_workspace(svd_plan* sp, const svd_plan_options* options, void* device_workspace,
-                                   size_t workspace_bytes, void* hip_stream, bool with_side_streams) {
+                                   size_t workspace_bytes, void* hip_stream, bool with_side_streams, bool copy = true) {
   if (workspace_bytes < sp->workspace_bytes || !aligned16(device_workspace)) return SVD_ERR_WORKSPACE;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (hipMemcpyAsync(device_workspace, sp->p.ws_image.data(), sp->p.ws_image.size() * sizeof(int32_t),
-                     hipMemcpyHostToDevice, stream) != hipSuccess ||
-      hipStreamSynchronize(stream) != hipSuccess)
+  if (copy && (hipMemcpyAsync(device_workspace, sp->p.ws_image.data(), sp->p.ws_image.size() * sizeof(int32_t),
+                              hipMemcpyHostToDevice, stream) != hipSuccess ||
+               hipStreamSynchronize(stream) != hipSuccess))
     return SVD_ERR_HIP;
   const svd_tensor_desc& desc = sp->p.desc;
   const bool single = sp->form != 0;
@@ -1061,19 +1156,30 @@ svd_status sparse_vdit_attn_forward(const void* q, const void* k, const void* v,
   const bool hit = g_oneshot.plan && std::memcmp(&g_oneshot.desc, desc, sizeof(*desc)) == 0 &&
                    g_oneshot.table == table && g_oneshot.flat == flat &&
                    g_oneshot.workspace == device_workspace && g_oneshot.workspace_bytes == workspace_bytes;
+  // a capture records the launches of a plan whose lists are in the workspace already; the copy is not recorded, because
+  // later calls reuse the memory it reads
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool capturing = hipStreamIsCapturing(static_cast<hipStream_t>(hip_stream), &capture) == hipSuccess &&
+                         capture != hipStreamCaptureStatusNone;
   if (!hit) {
+    if (capturing) return SVD_ERR_HIP;
     svd_plan* fresh = nullptr;
-    if (svd_status st = svd_plan_create(&fresh, desc, strategy_table, pattern_params, nullptr,
-                                        device_workspace, workspace_bytes, hip_stream))
+    if (svd_status st = compile_for(&fresh, desc, strategy_table, pattern_params, nullptr, true)) return st;
+    if (svd_status st = attach_workspace(fresh, nullptr, device_workspace, workspace_bytes, hip_stream, true, false)) {
+      delete fresh;
       return st;
+    }
     if (g_oneshot.plan) svd_plan_destroy(g_oneshot.plan);
     g_oneshot.plan = fresh;
+    g_oneshot.slot = -1;
     g_oneshot.desc = *desc;
     g_oneshot.table.swap(table);
     g_oneshot.flat.swap(flat);
     g_oneshot.workspace = device_workspace;
     g_oneshot.workspace_bytes = workspace_bytes;
   }
+  if (!capturing)
+    if (svd_status st = upload_lists(&g_oneshot, static_cast<hipStream_t>(hip_stream))) return st;
   return svd_attn_forward_planned(g_oneshot.plan, q, k, v, out, hip_stream);
 }
 

@@ -72,6 +72,10 @@ inline size_t gathered_elements(int B, int n_heads, int gather_pad, int D) {
 // Pre-pass of a vertical-stripe group: fills p.gathered from p.k, p.v through the group's column lists.
 hipError_t launch_gather_kv(const AttnLaunch& p, hipStream_t stream);
 
+// Copies lists from page-locked host memory (device address src) to a plan workspace, in stream order.  Both 16-byte
+// aligned, bytes a multiple of 16.
+hipError_t launch_copy_lists(const void* src, void* dst, size_t bytes, hipStream_t stream);
+
 // The whole layer in ONE launch (Section 4.2: heads that share a mode are fused;
 // here all groups are): a grid of resident work-groups, two of four waves per
 // compute unit, pulls items off eight work queues, one per XCD, heaviest segment

@@ -850,6 +850,15 @@ __global__ void __launch_bounds__(256) zero_heads_kernel(const AttnLaunch p) {
   }
 }
 
+// Lists from page-locked host memory to a plan workspace: bound by the reads over the bus, so every thread has one
+// 16-byte load in flight and nothing else.  A kernel and not a copy, because a copy between two kernels of a stream waits
+// for the copy engine and back: 12 heads x 1,998 x 2 (20 KB of lists), one-shot call repeated: 72 us with the copy, 58 us
+// with the kernel, 51 us without either (and wrong results once the memory has held something else).
+__global__ void __launch_bounds__(256) copy_lists_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, const unsigned n16) {
+  const unsigned i = blockIdx.x * 256u + threadIdx.x;
+  if (i < n16) dst[i] = src[i];
+}
+
 // ---- the whole layer in one launch ----
 
 __global__ void __launch_bounds__(128) reset_counters_kernel(int* counters) {
@@ -1218,6 +1227,14 @@ hipError_t launch_combine(const AttnLaunch& p, hipStream_t stream) {
   } else {
     return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_copy_lists(const void* src, void* dst, size_t bytes, hipStream_t stream) {
+  if (!src || !dst || bytes == 0 || bytes % 16 || bytes / 16 > 0x7fffffffu) return hipErrorInvalidValue;
+  const unsigned n16 = static_cast<unsigned>(bytes / 16);
+  hipLaunchKernelGGL(copy_lists_kernel, dim3((n16 + 255) / 256), dim3(256), 0, stream, static_cast<const uint4*>(src),
+                     static_cast<uint4*>(dst), n16);
   return hipGetLastError();
 }
 

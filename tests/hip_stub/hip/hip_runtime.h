@@ -17,6 +17,7 @@ typedef enum hipError_t {
   hipSuccess = 0,
   hipErrorInvalidValue = 1,
   hipErrorInvalidResourceHandle = 400,
+  hipErrorNotReady = 600,
   hipErrorStreamCaptureUnsupported = 900,
   hipErrorStreamCaptureInvalidated = 901,
   hipErrorStreamCaptureUnjoined = 904,
@@ -38,6 +39,8 @@ typedef enum hipStreamCaptureStatus {
 } hipStreamCaptureStatus;
 constexpr unsigned hipStreamNonBlocking = 1u;
 constexpr unsigned hipEventDisableTiming = 2u;
+constexpr unsigned hipHostMallocPortable = 1u;
+constexpr unsigned hipHostMallocMapped = 2u;
 
 hipError_t hipGetDevice(int* device);
 hipError_t hipDeviceGetAttribute(int* value, hipDeviceAttribute_t attr, int device);
@@ -50,5 +53,10 @@ hipError_t hipStreamIsCapturing(hipStream_t stream, hipStreamCaptureStatus* stat
 hipError_t hipEventCreateWithFlags(hipEvent_t* event, unsigned flags);
 hipError_t hipEventDestroy(hipEvent_t event);
 hipError_t hipEventRecord(hipEvent_t event, hipStream_t stream);
+hipError_t hipEventQuery(hipEvent_t event);
+hipError_t hipEventSynchronize(hipEvent_t event);
+hipError_t hipHostMalloc(void** ptr, size_t bytes, unsigned flags);
+hipError_t hipHostGetDevicePointer(void** device_ptr, void* host_ptr, unsigned flags);
+hipError_t hipHostFree(void* ptr);
 hipError_t hipStreamWaitEvent(hipStream_t stream, hipEvent_t event, unsigned flags);
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind kind, hipStream_t stream);

@@ -14,6 +14,7 @@
 #include <map>
 #include <set>
 #include <unordered_set>
+#include <vector>
 
 struct ihipStream_t {
   unsigned magic = 0x57AEA3u;
@@ -28,6 +29,7 @@ struct ihipEvent_t {
   ihipStream_t* from = nullptr;           // stream of the last record
   long seq = 0;
   bool recorded = false;
+  bool reached = false;                   // the last record is known to have been reached
 };
 
 namespace {
@@ -37,11 +39,46 @@ int g_violations = 0;
 long g_launches = 0, g_nodes = 0, g_seq = 0;
 int g_captures = 0;                        // captures in progress
 std::map<const char*, size_t> g_allocs;
+// Copies out of page-locked memory (or kernels that read it): the model makes them at once, the device at any time until an event
+// behind them is known to have been reached, so their source must not change before that.
+struct PendingCopy {
+  const char* src;
+  std::vector<char> bytes;
+  ihipStream_t* stream;
+  long seq;
+};
+std::vector<PendingCopy> g_pending;
+struct Wait { long at; ihipStream_t* from; long seq; };   // work enqueued after `at` runs behind what `from` had been given by `seq`
+std::map<ihipStream_t*, std::vector<Wait>> g_waits;
+std::map<const char*, size_t> g_pinned;
 ihipStream_t g_null_stream;               // the default stream
 
 ihipStream_t* resolve(hipStream_t s) { return s ? s : &g_null_stream; }
 bool alive(ihipStream_t* s) { return s->magic == 0x57AEA3u; }   // reads the object: ASan reports a freed one
 bool alive(ihipEvent_t* e) { return e->magic == 0xE7E27u; }
+
+bool pinned(const char* p) {
+  auto it = g_pinned.upper_bound(p);
+  if (it == g_pinned.begin()) return false;
+  --it;
+  return p < it->first + it->second;
+}
+// The copies of `stream` (nullptr: of every stream) up to `seq` are over, and with them those that `stream` has waited for.
+void copies_made(ihipStream_t* stream, long seq) {
+  for (size_t i = 0; i < g_pending.size();) {
+    const PendingCopy& c = g_pending[i];
+    if ((stream && c.stream != stream) || c.seq > seq) {
+      ++i;
+      continue;
+    }
+    if (std::memcmp(c.src, c.bytes.data(), c.bytes.size()) != 0) stub::violation("the source of a copy changed before the copy was made");
+    g_pending.erase(g_pending.begin() + i);
+  }
+  const auto it = g_waits.find(stream);
+  if (it != g_waits.end())
+    for (const Wait& w : it->second)   // (their sequence numbers descend: this ends)
+      if (w.at <= seq) copies_made(w.from, w.seq);
+}
 
 void work_on(ihipStream_t* s) {
   s->last_work = ++g_seq;
@@ -131,6 +168,12 @@ void note_launch(hipStream_t s, const char* what) {
   work_on(st);
 }
 
+void note_pinned_read(hipStream_t s, const void* src, size_t bytes) {
+  const char* c = static_cast<const char*>(src);
+  if (!pinned(c) || !pinned(c + bytes - 1)) violation("a copy reads %zu bytes that are not all page-locked", bytes);
+  g_pending.push_back({c, std::vector<char>(c, c + bytes), resolve(s), ++g_seq});
+}
+
 }  // namespace stub
 
 hipError_t hipGetDevice(int* device) {
@@ -153,6 +196,8 @@ hipError_t hipStreamDestroy(hipStream_t stream) {
   if (!stream) return hipErrorInvalidResourceHandle;
   if (!alive(stream)) stub::violation("hipStreamDestroy of a dead stream");
   if (stream->origin) stub::violation("hipStreamDestroy of a stream that is capturing");
+  copies_made(stream, g_seq);   // what it holds is finished first
+  g_waits.erase(stream);
   stream->magic = 0;
   delete stream;
   return hipSuccess;
@@ -164,6 +209,7 @@ hipError_t hipStreamSynchronize(hipStream_t stream) {
     stub::violation("hipStreamSynchronize on a capturing stream");
     return hipErrorStreamCaptureUnsupported;
   }
+  copies_made(st, g_seq);
   return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() {
@@ -200,6 +246,35 @@ hipError_t hipEventRecord(hipEvent_t event, hipStream_t stream) {
   event->from = st;
   event->seq = ++g_seq;
   event->recorded = true;
+  event->reached = false;
+  return hipSuccess;
+}
+// Never ready by itself: what the host may do early it must be able to do late.
+hipError_t hipEventQuery(hipEvent_t event) {
+  if (!event || !alive(event)) stub::violation("hipEventQuery with a dead handle");
+  return !event->recorded || event->reached ? hipSuccess : hipErrorNotReady;
+}
+hipError_t hipEventSynchronize(hipEvent_t event) {
+  if (!event || !alive(event)) stub::violation("hipEventSynchronize with a dead handle");
+  if (event->recorded && event->origin) stub::violation("hipEventSynchronize on an event of a capture");
+  if (event->recorded) copies_made(event->from, event->seq);
+  event->reached = true;
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void** ptr, size_t bytes, unsigned) {
+  if (g_captures > 0) stub::violation("hipHostMalloc while a capture is active");
+  *ptr = std::malloc(bytes);
+  g_pinned[static_cast<const char*>(*ptr)] = bytes;
+  return hipSuccess;
+}
+hipError_t hipHostGetDevicePointer(void** device_ptr, void* host_ptr, unsigned) {
+  *device_ptr = host_ptr;
+  return pinned(static_cast<const char*>(host_ptr)) ? hipSuccess : hipErrorInvalidValue;
+}
+hipError_t hipHostFree(void* ptr) {
+  copies_made(nullptr, g_seq);   // the real call waits for the device
+  g_pinned.erase(static_cast<const char*>(ptr));
+  std::free(ptr);
   return hipSuccess;
 }
 hipError_t hipStreamWaitEvent(hipStream_t stream, hipEvent_t event, unsigned) {
@@ -209,6 +284,7 @@ hipError_t hipStreamWaitEvent(hipStream_t stream, hipEvent_t event, unsigned) {
     return hipErrorInvalidResourceHandle;
   }
   if (!event->recorded) return hipSuccess;
+  if (!event->origin && !g_pending.empty()) g_waits[st].push_back({++g_seq, event->from, event->seq});
   if (event->origin) {
     ihipStream_t* o = event->origin;
     if (!alive(o) || o->origin != o) {
@@ -240,5 +316,6 @@ hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKin
   if (kind == hipMemcpyHostToDevice && !stub::in_device(dst, bytes)) stub::violation("H2D copy outside a device allocation");
   if (kind == hipMemcpyDeviceToHost && !stub::in_device(src, bytes)) stub::violation("D2H copy outside a device allocation");
   std::memcpy(dst, src, bytes);
+  if (kind == hipMemcpyHostToDevice && pinned(static_cast<const char*>(src))) stub::note_pinned_read(stream, src, bytes);
   return hipSuccess;
 }

@@ -30,6 +30,8 @@ size_t out_rows_written();
 
 // called by the launch models: the stream handle is checked, captured launches are counted
 void note_launch(hipStream_t s, const char* what);
+// a launch on s reads [src, src + bytes) of page-locked memory at some time before an event behind it is reached
+void note_pinned_read(hipStream_t s, const void* src, size_t bytes);
 void violation(const char* fmt, ...);      // prints and counts a broken rule
 int violations();
 long launches();

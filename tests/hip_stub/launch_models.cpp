@@ -273,6 +273,15 @@ hipError_t launch_layer(const LayerLaunch& p, int n_compute_units, hipStream_t s
   return hipSuccess;
 }
 
+hipError_t launch_copy_lists(const void* src, void* dst, size_t bytes, hipStream_t stream) {
+  stub::note_launch(stream, "copy_lists_kernel");
+  if (bytes % 16 || ((uintptr_t)src | (uintptr_t)dst) % 16) stub::violation("copy_lists: %zu bytes, or an address off 16", bytes);
+  if (!stub::in_device(dst, bytes)) stub::violation("copy_lists: outside every device allocation");
+  stub::note_pinned_read(stream, src, bytes);
+  std::memcpy(dst, src, bytes);
+  return hipSuccess;
+}
+
 hipError_t launch_gather_kv(const AttnLaunch& p, hipStream_t stream) {
   if (p.n_heads <= 0) return hipSuccess;
   if (!p.gathered || p.gather_pad < 1 || !p.heads || !p.list_id || !p.ws) return hipErrorInvalidValue;

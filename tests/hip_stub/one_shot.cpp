@@ -1,0 +1,93 @@
+// Sanitizer harness of the one-shot entry point: what its calls may rely on between two of them.  The workspace is the
+// caller's in between (the harness overwrites it), its address may belong to other data, and the page-locked lists of a
+// plan must not change before the copies out of them are made (the model of the runtime checks that).
+//
+//   one_shot ROUNDS
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <vector>
+
+#include "hip_stub.h"
+#include "sparse_vdit.h"
+
+namespace {
+int g_failures = 0;
+void expect(bool ok, const char* what, int status = 0) {
+  if (ok) return;
+  std::fprintf(stderr, "one-shot: %s (status %d)\n", what, status);
+  ++g_failures;
+}
+}  // namespace
+
+int main(int argc, char** argv) {
+  const int rounds = argc > 1 ? std::atoi(argv[1]) : 1;
+  stub::set_compute_units(256);
+  stub::set_tensor_checks(true);
+  constexpr int H = 5;
+  svd_tensor_desc d{};
+  d.B = 2, d.H = H, d.L = 700, d.D = 64;
+  d.stride_l = d.D, d.stride_h = int64_t(d.L) * d.D, d.stride_b = d.stride_h * H;
+  const size_t tensor = size_t(d.B) * d.stride_b * 2, n_rows = size_t(d.B) * H * d.L;
+  void* t[4];
+  for (void*& p : t) p = stub::device_alloc(tensor);
+  std::vector<int32_t> cols, offsets = {-300, 0, 300};
+  for (int c = 3; c < d.L; c += 4) cols.push_back(c);
+  svd_head_params pp[H] = {};
+  for (svd_head_params& p : pp) {
+    p.half_width = 40;
+    p.n_offsets = 3, p.offsets = offsets.data();
+    p.n_cols = int32_t(cols.size()), p.cols = cols.data();
+  }
+  const int32_t first[H] = {SVD_DENSE, SVD_SKIP, SVD_DIAG, SVD_MULTIDIAG, SVD_VSTRIPE};
+  // the largest workspace that any rotation of the table needs
+  size_t bytes = 0;
+  for (int r = 0; r < H; ++r) {
+    int32_t table[H];
+    for (int h = 0; h < H; ++h) table[h] = first[(h + r) % H];
+    size_t need = 0;
+    expect(svd_plan_workspace_bytes(&d, table, pp, nullptr, &need) == SVD_OK, "svd_plan_workspace_bytes");
+    if (need > bytes) bytes = need;
+  }
+  void* ws[2] = {stub::device_alloc(bytes), stub::device_alloc(bytes)};
+  hipStream_t streams[2] = {nullptr, stub::create_stream()};
+  auto call = [&](int rot, int w, hipStream_t s, const char* what) {
+    int32_t table[H];
+    for (int h = 0; h < H; ++h) table[h] = first[(h + rot) % H];
+    stub::new_forward();
+    const int st = sparse_vdit_attn_forward(t[0], t[1], t[2], table, pp, t[3], &d, ws[w], bytes, s);
+    expect(st == SVD_OK, what, st);
+    expect(stub::out_rows_written() == n_rows, what);
+    return st;
+  };
+  for (int i = 0; i < rounds; ++i) {
+    call(i, 0, nullptr, "a first call");
+    call(i, 0, nullptr, "the same call again");
+    for (int fill : {0x7f, 0xff, 0x00}) {
+      std::memset(ws[0], fill, bytes);   // freed and given to something else, then to the workspace again
+      call(i, 0, streams[fill == 0xff], "the same call on a workspace that was used in between");
+    }
+    for (int k = 0; k < 12; ++k) call(i + k, k & 1, streams[(k / 3) & 1], "tables, workspaces and streams in turn");
+    // under capture: the launches of a repeated call are recorded, without a copy; another table is refused
+    hipStream_t s = stub::create_stream();
+    call(i, 0, s, "the call to be captured");
+    long nodes = stub::captured_nodes();
+    stub::begin_capture(s);
+    call(i, 0, s, "a repeated call under capture");
+    expect(stub::captured_nodes() > nodes, "the capture recorded launches");
+    expect(stub::end_capture(s) == hipSuccess, "the capture ends");
+    nodes = stub::captured_nodes();
+    stub::begin_capture(s);
+    int32_t dense[H] = {};
+    const int st = sparse_vdit_attn_forward(t[0], t[1], t[2], dense, pp, t[3], &d, ws[0], bytes, s);
+    expect(st == SVD_ERR_HIP, "a new table under capture is refused", st);
+    expect(stub::captured_nodes() == nodes, "a refused call records nothing");
+    expect(stub::end_capture(s) == hipSuccess, "the capture ends");
+    stub::destroy_stream(s);
+    call(i, 0, nullptr, "a call after the capture");
+    expect(sparse_vdit_attn_forward(t[0], t[1], t[2], dense, pp, t[3], &d, ws[0], 64, nullptr) == SVD_ERR_WORKSPACE, "a small workspace");
+    call(i, 0, nullptr, "a call after a refused one");
+  }
+  std::printf("%d violations, %d failures\n", stub::violations(), g_failures);
+  return stub::violations() || g_failures ? 1 : 0;
+}
