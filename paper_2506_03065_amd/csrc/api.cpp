@@ -239,7 +239,7 @@ int stripe_gather_pad(const Plan& p) {
 // follow the bands less closely, hold more than that on top; the longest stay in groups, whose launches and tails no
 // longer count.
 int grid_waves(const Plan& p, const svd_plan_options* opt, int form, int n_cu) {
-  if (!svd::launch_grid || n_cu < 1) return 0;
+  if (n_cu < 1) return 0;
   if (opt && (opt->block_q || opt->block_k || opt->dense_split || opt->single_launch)) return 0;
   const double small = svd::grid_tiles(p, svd::kernel_small_block_q(p.desc.D)), per_slot = small / (2.0 * n_cu);
   if (form == 1) return per_slot < 2500.0 ? 4 : 0;
@@ -254,7 +254,7 @@ int grid_waves(const Plan& p, const svd_plan_options* opt, int form, int n_cu) {
 // partly empty rounds of the groups weigh little: 40 x 75,600, D = 128, 39 % of the tiles dense, 6,880 per slot: 7,800 /
 // 7,230 to 8,040; D = 64, 85 % dense, 5,000 per slot: 6,244 / 6,348.
 bool grid_fp8(const Plan& p, const svd_plan_options* opt, int n_cu) {
-  if (!svd::launch_grid_fp8 || n_cu < 1) return false;
+  if (n_cu < 1) return false;
   if (opt && (opt->block_q || opt->block_k || opt->dense_split || opt->single_launch)) return false;
   double dense = 0.0;
   const double tiles = svd::grid_tiles(p, svd::kernel_small_block_q(p.desc.D), &dense);

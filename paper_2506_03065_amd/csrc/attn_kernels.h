@@ -120,8 +120,7 @@ struct GridLaunch {
 };
 // Floats of one slot of partial results.
 inline size_t grid_slot_floats(int D, int waves) { return static_cast<size_t>(waves) * (D / 32 * 16 + 2) * 64; }
-// (weak: the host code runs such a layer as a launch per group where this is not linked in)
-__attribute__((weak)) hipError_t launch_grid(const GridLaunch& p, hipStream_t stream);
+hipError_t launch_grid(const GridLaunch& p, hipStream_t stream);
 // The merge launch of the items cut into chunks alone (launch_grid contains it).
 hipError_t launch_grid_merge(const GridLaunch& p, hipStream_t stream);
 

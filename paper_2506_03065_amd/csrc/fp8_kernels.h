@@ -43,7 +43,7 @@ hipError_t launch_quantise_kv(const Fp8Launch& p, int mode, hipStream_t stream);
 hipError_t launch_attention_fp8(const Fp8Launch& p, int mode, hipStream_t stream, bool small_q = false);
 
 // The layer from the plan's table of items: one pre-pass of all heads, one attention launch, one merge of the items cut
-// into chunks.  p.a.partial = g.partial.  Weak like launch_grid.
-__attribute__((weak)) hipError_t launch_grid_fp8(const Fp8Launch& p, const GridLaunch& g, hipStream_t stream);
+// into chunks.  p.a.partial = g.partial.
+hipError_t launch_grid_fp8(const Fp8Launch& p, const GridLaunch& g, hipStream_t stream);
 
 }  // namespace svd

@@ -2,6 +2,7 @@
 // walks the records, touches what the kernels would address, and checks that the chunks of a cut
 // item lie in consecutive slots, follow one another and are merged once.
 #include <cstdint>
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -54,6 +55,7 @@ hipError_t launch_grid_fp8(const Fp8Launch& f, const GridLaunch& g, hipStream_t 
 
 static void walk(const GridLaunch& g, const Fp8Launch* f8, hipStream_t stream) {
   stub::note_launch(stream, "attn_grid_kernel");
+  std::printf("grid: waves %d records %d merges %d fp8 %d\n", g.waves, g.n_blocks, g.n_merges, f8 ? 1 : 0);
   if (g.n_merges > 0) stub::note_launch(stream, "merge_chunks_kernel");
   const int BR = g.waves * 32, BC = g.a.D == 128 ? Tile128::BC : Tile64::BC;
   const size_t slot_floats = grid_slot_floats(g.a.D, g.waves);

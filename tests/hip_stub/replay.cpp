@@ -99,7 +99,9 @@ void run_layer(const Layer& l) {
   svd_plan_options opt{};
   opt.dense_split = l.split;
   opt.text_tokens = l.text;
-  for (int round = 0; round < l.rounds; ++round) {
+  // the library's choice of the launch form, then a launch per group
+  for (int round = 0; round < 2 * l.rounds; ++round) {
+    opt.single_launch = round < l.rounds ? 0 : 2;
     size_t bytes = 0;
     int st = svd_plan_workspace_bytes(&desc, l.table.data(), l.params.data(), &opt, &bytes);
     expect(st == SVD_OK, l, "svd_plan_workspace_bytes", st);
@@ -153,6 +155,7 @@ void run_layer(const Layer& l) {
     expect(svd_plan_destroy(plan) == SVD_OK, l, "svd_plan_destroy");
     stub::device_free(ws);
   }
+  opt.single_launch = 0;
   {
     // the same layer as ONE launch (and with the dense head start): eagerly, and under capture (refused with a text prefix)
     for (int form : {1, 3}) {

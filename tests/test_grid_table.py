@@ -1,9 +1,6 @@
 """The whole layer from a table of items: the table on the host model of the launches (every output row
 stored once, every word inside the workspace, the chunks of cut items complete), and items of every kind
 cut into chunks on the GPU against the oracle."""
-import os
-import subprocess
-
 import numpy as np
 import pytest
 import torch
@@ -13,19 +10,7 @@ from paper_2506_03065_amd import workloads as W
 from parity_util import check_layer, run_planned
 from test_gpu_fp8 import check_layer_fp8, run_fp8
 from test_gpu_random_layers import random_layer
-from test_host_launch_model import CSRC, ROOT, STUB, layer_text, run
-
-
-@pytest.fixture(scope="module")
-def replay(tmp_path_factory):
-    exe = str(tmp_path_factory.mktemp("hip_stub_grid") / "replay")
-    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-omit-frame-pointer",
-           "-fno-sanitize-recover=undefined", "-I", STUB, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-           os.path.join(CSRC, "api.cpp"), os.path.join(CSRC, "pattern_compiler.cpp"),
-           *(os.path.join(STUB, f) for f in ("hip_stub.cpp", "launch_models.cpp", "grid_model.cpp", "replay.cpp")), "-o", exe]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    assert res.returncode == 0, res.stderr[-4000:]
-    return exe
+from test_host_launch_model import layer_text, replay, run  # noqa: F401  (replay: the fixture)
 
 
 @pytest.mark.parametrize("cu", [8, 256])

@@ -4,9 +4,10 @@ tests/hip_stub/ holds a stand-in <hip/hip_runtime.h> (streams, events, stream
 capture with its fork/join rules, "device" memory that is exact-size host
 memory) and host models of every kernel launch that walk the kernels' index
 arithmetic and touch each byte a launch would address.  The harness replays,
-per layer: workspace sizing, plan creation, the bf16 and FP8 forward passes
-eagerly, on a caller stream and under a modelled capture, the per-group entry
-points, plan destruction.  It reports 256 compute units (or the count given),
+per layer, with the library's choice of the launch form and with a launch per
+group: workspace sizing, plan creation, the bf16 and FP8 forward passes eagerly,
+on a caller stream and under a modelled capture, the per-group entry points,
+plan destruction.  It reports 256 compute units (or the count given),
 so the key-range splits, the text-row launches and the fork onto plan-owned
 streams all run - none of which a box without a GPU reaches otherwise."""
 import os
@@ -29,8 +30,7 @@ def replay(tmp_path_factory):
     cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-omit-frame-pointer",
            "-fno-sanitize-recover=undefined", "-I", STUB, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
            os.path.join(CSRC, "api.cpp"), os.path.join(CSRC, "pattern_compiler.cpp"),
-           os.path.join(STUB, "hip_stub.cpp"), os.path.join(STUB, "launch_models.cpp"),
-           os.path.join(STUB, "replay.cpp"), "-o", exe]
+           *(os.path.join(STUB, f) for f in ("hip_stub.cpp", "launch_models.cpp", "grid_model.cpp", "replay.cpp")), "-o", exe]
     res = subprocess.run(cmd, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-4000:]
     return exe
@@ -115,5 +115,16 @@ def test_the_harness_sees_a_planted_shortfall(replay, tmp_path):
     the launch models report the accesses that leave it."""
     wl, split = random_layer(2)
     res = run(replay, tmp_path, [layer_text(wl, split, rounds=1)], shortfall=64)
+    assert res.returncode != 0
+    assert "outside every device allocation" in res.stderr or "AddressSanitizer" in res.stderr
+
+
+def test_the_harness_sees_a_planted_shortfall_of_a_table_with_cut_items(replay, tmp_path):
+    """The same for a layer that runs from a table of items, some of them cut: the chunks' results end the workspace."""
+    wl = W.small(L=1024, D=64, H=5, seed=0)
+    res = run(replay, tmp_path, [layer_text(wl, 0, rounds=3)])
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+    assert any(line.startswith("grid: waves 4") and int(line.split()[6]) > 0 for line in res.stdout.splitlines()), res.stdout[-2000:]
+    res = run(replay, tmp_path, [layer_text(wl, 0, rounds=1)], shortfall=64)
     assert res.returncode != 0
     assert "outside every device allocation" in res.stderr or "AddressSanitizer" in res.stderr
