@@ -66,6 +66,15 @@ def recorded_traffic(precision, workload, group):
 MODE_NAMES = {0: "dense", 1: "skip", 2: "diagonal", 3: "multi-diagonal", 4: "vertical-stripe"}
 
 
+def form_name(plan, fp8=False):
+    """How a whole forward pass of the plan runs."""
+    waves = plan.table()["fp8" if fp8 else "bf16"]
+    if waves:
+        return f"table of items, {waves}-wave work-groups"
+    return "grouped launches" if fp8 else {0: "grouped launches", 1: "layer kernel (the whole layer in one launch)",
+                                           3: "layer kernel after a dense head start"}[plan.launch_form()]
+
+
 def gpu_time_ms(fn, reps, warmup, torch):
     """Average milliseconds of fn() over reps, HIP events on the current stream."""
     for _ in range(warmup):
@@ -175,7 +184,7 @@ def run_stack(args, torch, np, svd, W, cpu_seconds=None, calib=None, dense_reps=
         peak = FP8_MFMA_PEAK_TFLOPS if fp8 else BF16_MFMA_PEAK_TFLOPS
         roofline = {"bound": "mfma", "kernel": f"{'attn_fwd_fp8_kernel' if fp8 else 'attn_fwd_kernel'}[dense group of layer 0]",
                     "achieved": round(tf0, 1), "peak": peak, "unit": "TFLOP/s", "frac": round(tf0 / peak, 4), "traffic": None}
-        if plans[0].single_launch() and not fp8:
+        if plans[0].single_launch() and not plans[0].table()["bf16"] and not fp8:
             # every layer is one launch of the layer kernel: the step is the dominant kernel, 40 times over
             tf = computed / 1e9 / ms_per_step
             roofline = {"bound": "mfma", "kernel": "attn_layer_kernel (one launch per layer, the whole step)",
@@ -199,7 +208,7 @@ def run_stack(args, torch, np, svd, W, cpu_seconds=None, calib=None, dense_reps=
         "data": "synthetic",
         "config": {"workload": "layer-stack (40 layers, Wan2.1-like shape)", "precision": args.precision, "B": wl0.B, "H": wl0.H, "L": wl0.L,
                    "D": wl0.D, "dense_heads_first_last": [dense_heads[0], dense_heads[-1]],
-                   "launch_form": "layer kernel" if plans[0].single_launch() else "grouped launches"},
+                   "launch_form": form_name(plans[0], fp8)},
         "computed_tile_tflops": round(computed / 1e9 / ms_per_step, 1),
         "computed_tile_frac_of_bf16_peak": round(computed / 1e9 / ms_per_step / BF16_MFMA_PEAK_TFLOPS, 4),
         "computed_tile_frac_of_measured_mfma_peak": round(computed / 1e9 / ms_per_step / calib["measured_mfma_peak_tflops"], 4) if calib and not fp8 else None,
@@ -313,18 +322,19 @@ def run_rearranged(args, torch, np, svd, W):
     ws8 = torch.empty(svd.svd_fp8_workspace_bytes(desc), dtype=torch.uint8, device=dev)
     ms_fused8 = gpu_time_ms(lambda: svd.svd_attn_forward_fp8(fused, q, k, v, out, ws8), args.steps, args.warmup, torch)
     tensor_bytes = q.numel() * 2
-    wd, wm = diag.work(), multi.work()
+    wd, wm, wf = diag.work(), multi.work(), fused.work()   # of the lists that each plan's pass walks
     result = {
         "metric": "position-window attention latency (multi-diagonal heads in rearranged form, rows through a row map)",
         "value": round(ms_fused, 4), "unit": "ms", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_fused, 4), "higher_is_better": False, "scaling": "weak", "vs_baseline": None,
         "dtype": "bf16", "data": "synthetic",
         "config": {"workload": "rearranged window, Wan2.1-like shape", "B": 1, "H": H, "L": L, "D": D,
-                   "frame_tokens": N, "frames": F, "position_half_width": w, "band_half_width": Wd},
+                   "frame_tokens": N, "frames": F, "position_half_width": w, "band_half_width": Wd,
+                   "launch_form": form_name(fused), "diagonal_launch_form": form_name(diag)},
         "fp8_row_map_ms": round(ms_fused8, 4),
         "copy_path_ms": round(ms, 4),
         "max_abs_diff_row_map_vs_copy_path": max_diff,
-        "row_map_tflops": round(wd["computed_flops"] / 1e9 / ms_fused, 1),
+        "row_map_tflops": round(wf["computed_flops"] / 1e9 / ms_fused, 1),
         "rearrange_one_tensor_ms": round(ms_move, 4), "rearrange_back_ms": round(ms_back, 4),
         "diagonal_on_rearranged_ms": round(ms_diag, 4),
         "diagonal_tflops": round(wd["computed_flops"] / 1e9 / ms_diag, 1),
@@ -431,7 +441,7 @@ def measure_layer(wl, args, torch, np, svd, cpu_seconds, dense_reps, calib=None)
     # ---- the same layer through the other launch form (single launch <-> grouped launches) ----
     other = None
     if not fp8:
-        alt_form = 2 if plan.single_launch() else 1      # grouped launches <-> the layer kernel
+        alt_form = 2 if plan.single_launch() or plan.table()["bf16"] else 1      # grouped launches <-> the layer kernel, or a table
         ws_alt = torch.empty(svd.svd_plan_workspace_bytes(desc, wl.strategy_table, wl.pattern_params,
                                                           single_launch=alt_form),
                              dtype=torch.uint8, device=dev)
@@ -473,7 +483,16 @@ def measure_layer(wl, args, torch, np, svd, cpu_seconds, dense_reps, calib=None)
     roofline = {"bound": "mfma", "kernel": f"{kname}[{dom['mode']} group]",
                 "achieved": dom["tflops"], "peak": peak, "unit": "TFLOP/s", "frac": round(dom["tflops"] / peak, 4),
                 "traffic": traffic, "traffic_source": traffic_source, "traffic_key": dom["mode"], "dispatches": dispatches}
-    if plan.single_launch() and not fp8:
+    table = plan.table()["fp8" if fp8 else "bf16"]
+    if table:
+        # the step is the launch of the table (FP8: behind the pre-pass of all heads); algorithmic FLOPs = its listed tiles
+        tf = work["computed_flops"] / 1e9 / ms_per_step
+        traffic, traffic_source = recorded_traffic(args.precision, wl.name, "table")
+        dispatches = [{"kernel": "attn_grid_fp8_kernel"}, {"kernel": "quantise_layer_kernel"}] if fp8 else [{"kernel": "attn_grid_kernel"}]
+        roofline = {"bound": "mfma", "kernel": " + ".join(d["kernel"] for d in reversed(dispatches)) + " (the whole step)",
+                    "achieved": round(tf, 1), "peak": peak, "unit": "TFLOP/s", "frac": round(tf / peak, 4),
+                    "traffic": traffic, "traffic_source": traffic_source, "traffic_key": "table", "dispatches": dispatches}
+    elif plan.single_launch() and not fp8:
         # the step IS the dominant kernel: the layer kernel (with the dense kernel's head start ahead of it, and
         # the 5 us fill of the queue positions); algorithmic FLOPs = the plan's listed tiles
         tf = work["computed_flops"] / 1e9 / ms_per_step
@@ -532,8 +551,7 @@ def measure_layer(wl, args, torch, np, svd, cpu_seconds, dense_reps, calib=None)
                    "text_tokens_with_dense_borders": text, "B": wl.B, "H": wl.H, "L": wl.L, "D": wl.D,
                    "block_q": svd.svd_default_blocks(wl.D)[0], "block_k": svd.svd_default_blocks(wl.D)[1],
                    "dense_split": plan.dense_split(),
-                   "launch_form": {0: "grouped launches", 1: "layer kernel (the whole layer in one launch)",
-                                   3: "layer kernel after a dense head start"}[plan.launch_form()],
+                   "launch_form": form_name(plan, fp8),
                    "heads_by_mode": {MODE_NAMES[m]: int((wl.strategy_table == m).sum()) for m in range(5)}},
         "wall_ms_per_step": round(wall_ms, 4),
         "dense_equiv_tflops": round(dense_flops / 1e9 / ms_per_step, 1),

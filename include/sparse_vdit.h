@@ -155,10 +155,12 @@ typedef struct {
  * (head, query tile, key range) its record in the workspace names, long items cut
  * into chunks that a second launch merges; most layers run that way, the long
  * D = 128 ones through the layer kernel, the longest D = 64 ones group by group.
- * (svd_attn_forward_fp8 does the same, with one pre-pass for all heads.)  svd_plan_single_launch keeps reporting
- * the form named above.  The split of the dense heads is still chosen and its scratch
- * still part of the workspace: the FP8 forward pass and the per-group entry
- * points run such a plan group by group.
+ * svd_attn_forward_fp8 may run from a table of its own, with one pre-pass for all
+ * heads, whatever the form of the bf16 pass (svd_plan_table tells which pass does;
+ * svd_plan_single_launch keeps reporting the form named above); where it does not, it
+ * runs group by group.  The split of the dense heads is chosen in any case and its
+ * scratch part of the workspace: the per-group entry points run every plan group by
+ * group.
  * no_fork: 1 = grouped launches always run one after the other on the caller's
  * stream (see svd_attn_forward_planned); 0 = the library forks them onto its own
  * streams when that fills an otherwise idle last round. */
@@ -191,21 +193,30 @@ svd_status svd_plan_create(svd_plan** plan, const svd_tensor_desc* desc,
                            size_t workspace_bytes, void* hip_stream);
 svd_status svd_plan_destroy(svd_plan* plan);
 
-/* Key-range chunks per dense query tile this plan launches (1 = no split; always
- * 1 for host-only plans). */
+/* Key-range chunks per dense query tile of this plan's launches group by group: those
+ * of the per-group entry points, and of the forward passes that run neither through the
+ * layer kernel nor from a table (1 = no split; always 1 for host-only plans). */
 svd_status svd_plan_dense_split(const svd_plan* plan, int32_t* dense_split);
 
 /* How svd_attn_forward_planned runs this plan (Section 4.2, fusion of heads; plan
  * option single_launch): 1 = the layer kernel alone, 3 = the
  * layer kernel after the dense head start (plan option single_launch, or the
  * library's choice), 0 = a launch per group.  (A plan whose form the library chose may
- * run from a table of items instead, see single_launch above.) */
+ * run from a table of items instead, see svd_plan_table.) */
 svd_status svd_plan_single_launch(const svd_plan* plan, int32_t* single_launch);
+
+/* Whether the forward passes run this plan from a table of items (see single_launch
+ * above): the waves per work-group of the attention launch of svd_attn_forward_planned
+ * (*waves) and of svd_attn_forward_fp8 (*waves_fp8), 4 = query tiles of 128 rows, 8 = of
+ * 256; 0 = not from a table (always for host-only plans).  Either may be NULL. */
+svd_status svd_plan_table(const svd_plan* plan, int32_t* waves, int32_t* waves_fp8);
 
 /* Inspection of a compiled plan (host copies owned by the plan, valid until
  * svd_plan_destroy).  Groups are ordered by ascending mode id. */
 svd_status svd_plan_num_groups(const svd_plan* plan, int32_t* n_groups);
-/* Block shape of one group's lists and launches.  block_k is the plan's; block_q
+/* Block shape of one group's lists and of its launch by the per-group entry points (a
+ * table of items walks lists on one query tile for all groups, which the plan keeps
+ * beside these).  block_k is the plan's; block_q
  * is the plan's too, except for a band group (modes 2, 3) of a plan created
  * without an explicit block shape: when its lists cover at least 8 % less area
  * with the kernels' small query tile (128 rows instead of 256: the listed tiles
@@ -245,27 +256,33 @@ svd_status svd_plan_row_map(const svd_plan* plan, int32_t group, int32_t list, i
  * with -1 to padded_len, a multiple of block_k. */
 svd_status svd_plan_column_list(const svd_plan* plan, int32_t group, int32_t list,
                                 int32_t* n_cols, int32_t* padded_len, const int32_t** cols);
-/* Work the plan launches per forward pass, summed over batch and heads:
- * computed_tiles counts block_q x block_k tiles (dense heads: all of them,
- * vertical heads: column tiles), computed_flops = 4 * D * (tile area inside
- * [0,L) x [0,L) or the column list) and kept_pairs the element-level count. */
+/* Work that svd_attn_forward_planned launches per forward pass, summed over batch and
+ * heads: computed_tiles counts tiles of the query tile that pass runs on by block_k
+ * keys (dense heads: all of them, vertical heads: column tiles), computed_flops =
+ * 4 * D * (tile area inside [0,L) x [0,L) or the column list) and kept_pairs the
+ * element-level count. */
 svd_status svd_plan_work(const svd_plan* plan, int64_t* computed_tiles, double* computed_flops,
                          double* kept_pairs);
 
-/* The same figures for one group (all its heads, all batch entries). */
+/* The same figures for svd_attn_forward_group (all heads of the group, all batch
+ * entries).  A layer that runs from a table may list other tiles than its groups do. */
 svd_status svd_plan_group_work(const svd_plan* plan, int32_t group, int64_t* computed_tiles,
                                double* computed_flops, double* kept_pairs);
 
-/* The work of the FP8 forward pass (svd_attn_forward_fp8, the Appendix B variant): its band groups always walk
+/* The work of svd_attn_forward_fp8_group (the Appendix B variant): its band groups always walk
  * small-tile lists (kept in the plan beside the lists of a group that the bf16
  * kernels run on the large tile), so their tile count and listed area can differ
- * from svd_plan_group_work.  group = -1: the whole layer. */
+ * from svd_plan_group_work.  group = -1: of svd_attn_forward_fp8, the whole layer (from a
+ * table: every head on the small query tile). */
 svd_status svd_plan_group_work_fp8(const svd_plan* plan, int32_t group, int64_t* computed_tiles,
                                    double* computed_flops);
 
-/* Forward pass of one layer with a compiled plan (Section 4.2: one fused launch
+/* Forward pass of one layer with a compiled plan.  The tensors must match the plan's
+ * descriptor.  The plan's form decides what is enqueued (plan option single_launch,
+ * svd_plan_table): one launch of a table of items and the merge of those cut into
+ * chunks, the layer kernel, or group by group (Section 4.2: one fused launch
  * per mode present in the table, heaviest group first, plus a zero fill for
- * skipped heads).  The tensors must match the plan's descriptor.  The group
+ * skipped heads).  The group
  * kernels are independent.  Normally they are enqueued one after the other on
  * hip_stream.  When the last round of work-groups of the heaviest group would
  * leave more than half of the compute units idle, the groups are instead forked
@@ -362,7 +379,7 @@ svd_status svd_plan_head_sparsity(const svd_plan* plan, double* sparsity);
 
 /* The block-level count of the same quantity, in the wording of Section 4.2 ("the
  * ratio of actual computation blocks to the total number of blocks"): 1 minus the
- * number of block_q x block_k tiles the head's launches compute over the number
+ * number of block_q x block_k tiles listed for the head over the number
  * of tiles of the map, on the tile shape of the head's group (a tile that holds
  * one kept pair counts whole, the text rows of a text prefix count as dense
  * tiles).  It depends on the tile shape; the element-level figure above is its

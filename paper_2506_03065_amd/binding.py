@@ -23,7 +23,7 @@ STATUS_NAMES = {0: "SVD_OK", 1: "SVD_ERR_NULL", 2: "SVD_ERR_SHAPE", 3: "SVD_ERR_
 SVD_DENSE, SVD_SKIP, SVD_DIAG, SVD_MULTIDIAG, SVD_VSTRIPE = range(5)
 
 EXPORTS = ["svd_default_blocks", "svd_plan_workspace_bytes", "svd_plan_create", "svd_plan_destroy",
-           "svd_plan_dense_split", "svd_plan_single_launch", "svd_plan_num_groups", "svd_plan_group_info", "svd_plan_group_rearranged", "svd_plan_group_blocks", "svd_plan_row_map", "svd_plan_band_list", "svd_plan_column_list",
+           "svd_plan_dense_split", "svd_plan_single_launch", "svd_plan_table", "svd_plan_num_groups", "svd_plan_group_info", "svd_plan_group_rearranged", "svd_plan_group_blocks", "svd_plan_row_map", "svd_plan_band_list", "svd_plan_column_list",
            "svd_plan_work", "svd_plan_group_work", "svd_plan_group_work_fp8", "svd_attn_forward_planned", "svd_attn_forward_group", "sparse_vdit_attn_forward", "sparse_vdit_attn_forward_static",
            "svd_dense_attn_forward", "svd_status_string",
            "svd_head_mse_workspace_bytes", "svd_head_mse", "svd_plan_head_sparsity", "svd_plan_head_block_sparsity", "svd_search_select",
@@ -74,6 +74,7 @@ def lib():
             "svd_plan_destroy": [vp],
             "svd_plan_dense_split": [vp, i32p],
             "svd_plan_single_launch": [vp, i32p],
+            "svd_plan_table": [vp, i32p, i32p],
             "svd_plan_num_groups": [vp, i32p],
             "svd_plan_group_info": [vp, C.c_int32, i32p, i32p, i32pp, i32pp, i32p],
             "svd_plan_group_rearranged": [vp, C.c_int32, i32p],
@@ -244,6 +245,12 @@ class Plan:
         _check(lib().svd_plan_single_launch(self.handle, C.byref(n)), "svd_plan_single_launch")
         return n.value
 
+    def table(self):
+        """Waves per work-group of the bf16 and of the FP8 pass where they run from a table of items, else 0."""
+        w, w8 = C.c_int32(), C.c_int32()
+        _check(lib().svd_plan_table(self.handle, C.byref(w), C.byref(w8)), "svd_plan_table")
+        return {"bf16": w.value, "fp8": w8.value}
+
     def single_launch(self) -> bool:
         return self.launch_form() != 0
 
@@ -292,7 +299,7 @@ class Plan:
         return {"n_cols": n.value, "cols": _copy(cols, padded.value)}
 
     def work_fp8(self, group=None):
-        """Tiles and FLOPs the FP8 forward pass computes (band groups always on the small query tile)."""
+        """Tiles and FLOPs of the FP8 forward pass, or of the FP8 launch of one group (band groups always on the small query tile)."""
         tiles, flops = C.c_int64(), C.c_double()
         _check(lib().svd_plan_group_work_fp8(self.handle, -1 if group is None else group, C.byref(tiles), C.byref(flops)),
                "svd_plan_group_work_fp8")

@@ -643,7 +643,7 @@ static svd_status compile_for(svd_plan** plan, const svd_tensor_desc* desc, cons
       GridTables grid;
       if (native) grid = add_grid_tables(&sp->p, options, sp->form, n_cu);
       sp->grid = grid.bf16;
-      sp->grid_waves = grid.waves;
+      sp->grid_waves = grid.bf16 ? grid.waves : 0;
       sp->grid_table = grid.table;
       sp->grid8 = grid.fp8;
       sp->grid8_table = grid.table8;
@@ -748,6 +748,13 @@ svd_status svd_plan_dense_split(const svd_plan* plan, int32_t* dense_split) {
 svd_status svd_plan_single_launch(const svd_plan* plan, int32_t* single_launch) {
   if (!plan || !single_launch) return SVD_ERR_NULL;
   *single_launch = plan->single_launch ? (plan->dense_head_start > 0 || plan->head_start_asked ? 3 : 1) : 0;
+  return SVD_OK;
+}
+
+svd_status svd_plan_table(const svd_plan* plan, int32_t* waves, int32_t* waves_fp8) {
+  if (!plan) return SVD_ERR_NULL;
+  if (waves) *waves = plan->grid ? plan->grid_waves : 0;
+  if (waves_fp8) *waves_fp8 = plan->grid8 ? 4 : 0;
   return SVD_OK;
 }
 
@@ -867,6 +874,29 @@ static void group_work(const Plan& p, const svd::Group& g, int64_t* tiles, doubl
   }
 }
 
+// The same of one group's items in a table of query tiles of block_q rows.  text_in_table = false: the text rows of
+// stripe heads come from a launch of their own on the plan's query tile (the FP8 pass).
+static void table_work(const Plan& p, const svd::Group& g, int32_t block_q, bool text_in_table, int64_t* tiles, double* area) {
+  const double L = p.desc.L, T = g.mode >= SVD_DIAG ? p.text_tokens : 0;
+  const int64_t n_qb = (p.desc.L + block_q - 1) / block_q, text_qb = static_cast<int64_t>(T) / block_q;
+  const std::vector<svd::BandList>* bands = svd::bands_on(g, block_q);
+  for (int32_t id : g.list_id) {
+    const bool stripe = g.mode == SVD_VSTRIPE;
+    if (g.mode == SVD_DENSE) {
+      *tiles += n_qb * p.n_k_blocks;
+      *area += L * L;
+    } else if (stripe) {
+      *tiles += (n_qb - text_qb) * static_cast<int64_t>(g.columns[id].cols.size() / p.block_k);
+      *area += (L - T) * g.columns[id].n_cols;
+    } else if (g.mode != SVD_SKIP && bands) {
+      *tiles += static_cast<int64_t>((*bands)[id].kv_block_idx.size());
+      *area += (*bands)[id].tile_area;
+    }
+    *tiles += (stripe && !text_in_table ? static_cast<int64_t>(T) / p.block_q : text_qb) * p.n_k_blocks;
+    *area += T * L;
+  }
+}
+
 svd_status svd_plan_work(const svd_plan* plan, int64_t* computed_tiles, double* computed_flops,
                          double* kept_pairs) {
   if (!plan) return SVD_ERR_NULL;
@@ -874,6 +904,11 @@ svd_status svd_plan_work(const svd_plan* plan, int64_t* computed_tiles, double* 
   int64_t tiles = 0;
   double area = 0.0, pairs = 0.0;
   for (const svd::Group& g : p.groups) group_work(p, g, &tiles, &area, &pairs);
+  if (plan->grid) {
+    tiles = 0;
+    area = 0.0;
+    for (const svd::Group& g : p.groups) table_work(p, g, plan->grid_waves * 32, true, &tiles, &area);
+  }
   if (computed_tiles) *computed_tiles = tiles * p.desc.B;
   if (computed_flops) *computed_flops = 4.0 * p.desc.D * area * p.desc.B;
   if (kept_pairs) *kept_pairs = pairs * p.desc.B;
@@ -888,7 +923,8 @@ svd_status svd_plan_group_work_fp8(const svd_plan* plan, int32_t group, int64_t*
   int64_t tiles = 0;
   double area = 0.0, pairs = 0.0;
   for (int32_t gi = 0; gi < static_cast<int32_t>(p.groups.size()); ++gi)
-    if (group < 0 || gi == group) group_work(p, p.groups[gi], &tiles, &area, &pairs, true);
+    if (group < 0 && plan->grid8) table_work(p, p.groups[gi], svd::kernel_small_block_q(p.desc.D), false, &tiles, &area);
+    else if (group < 0 || gi == group) group_work(p, p.groups[gi], &tiles, &area, &pairs, true);
   if (computed_tiles) *computed_tiles = tiles * p.desc.B;
   if (computed_flops) *computed_flops = 4.0 * p.desc.D * area * p.desc.B;
   return SVD_OK;

@@ -382,8 +382,7 @@ svd_status compile_plan(const svd_tensor_desc& desc, const int32_t* strategy_tab
   return SVD_OK;
 }
 
-// The group's band lists on query tiles of block_q rows, nullptr: none were compiled.
-static const std::vector<BandList>* bands_on(const Group& g, int32_t block_q) {
+const std::vector<BandList>* bands_on(const Group& g, int32_t block_q) {
   if (g.block_q == block_q) return &g.bands;
   const std::vector<BandList>& other = block_q < g.block_q ? g.bands_small : g.bands_large;
   return other.empty() ? nullptr : &other;

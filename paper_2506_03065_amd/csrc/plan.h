@@ -120,6 +120,8 @@ struct GridTable {
   int n_heads = 0;
   size_t head_table = 0;
 };
+// The group's band lists on query tiles of block_q rows, nullptr: none were compiled.
+const std::vector<BandList>* bands_on(const Group& g, int32_t block_q);
 // Key tiles that a launch of the whole layer on query tiles of block_q rows walks; *dense: those of the dense heads.
 double grid_tiles(const Plan& plan, int32_t block_q, double* dense = nullptr);
 // Appends the records to plan->ws_image.  slots: work-groups that the device runs at a time.  False: an index

@@ -76,6 +76,7 @@ static void walk(const GridLaunch& g, const Fp8Launch* f8, hipStream_t stream) {
       rows(g, b, head, qblk * kGridZeroRows, kGridZeroRows);
       continue;
     }
+    stub::note_tiles(n);
     if (qblk * BR >= g.a.L || n < 1) stub::violation("grid record %d: query tile %d, %d key tiles", i, qblk, n);
     if (kind == SEG_DENSE) {
       if ((t0 + n - 1) * BC >= g.a.L) stub::violation("grid record %d: key tile past the sequence", i);

@@ -104,8 +104,14 @@ void set_compute_units(int n) { g_cu = n; }
 
 namespace {
 std::unordered_set<const void*> g_out_rows;
+long g_tiles = 0;
 }
-void new_forward() { g_out_rows.clear(); }
+void new_forward() {
+  g_out_rows.clear();
+  g_tiles = 0;
+}
+void note_tiles(long n) { g_tiles += n; }
+long tiles_walked() { return g_tiles; }
 void note_out_row(const void* row) {
   if (!g_out_rows.insert(row).second) violation("an output row is stored twice in one forward pass (launch %ld)", launches());
 }

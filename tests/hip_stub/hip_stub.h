@@ -27,6 +27,8 @@ hipError_t end_capture(hipStream_t s);     // hipErrorStreamCaptureUnjoined when
 void new_forward();
 void note_out_row(const void* row);
 size_t out_rows_written();
+void note_tiles(long n);                   // key tiles that a table launch of this pass walks
+long tiles_walked();
 
 // called by the launch models: the stream handle is checked, captured launches are counted
 void note_launch(hipStream_t s, const char* what);

@@ -124,6 +124,17 @@ void run_layer(const Layer& l) {
       expect(st == SVD_OK, l, fp8 ? "eager fp8 forward" : "eager forward", st);
       if (l.tensors && st == SVD_OK)
         expect(stub::out_rows_written() == static_cast<size_t>(l.B) * l.H * l.L, l, "every output row stored exactly once");
+      int32_t waves[2] = {0, 0};
+      svd_plan_table(plan, &waves[0], &waves[1]);
+      expect(!(waves[fp8] && opt.single_launch == 2), l, "a launch per group where it is asked for");
+      bool stripes = false;
+      for (int32_t m : l.table) stripes = stripes || m == SVD_VSTRIPE;
+      if (waves[fp8] && (l.tensors || !fp8) && !(fp8 && stripes && l.text)) {   // (there the text rows are another launch)
+        int64_t tiles = 0;
+        if (fp8) svd_plan_group_work_fp8(plan, -1, &tiles, nullptr);
+        else svd_plan_work(plan, &tiles, nullptr, nullptr);
+        expect(tiles == stub::tiles_walked(), l, "the plan reports the key tiles that its table walks");
+      }
       stub::new_forward();
       hipStream_t side = stub::create_stream();
       st = call(side);      // warm-up on the capture stream
