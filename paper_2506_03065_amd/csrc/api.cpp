@@ -234,17 +234,35 @@ int stripe_gather_pad(const Plan& p) {
 //             29 x 32,710 (965)                          1,969 / 1,908 / 1,851
 //             48 x 86,400 (3,620)                        7,283 / 7,351 / 7,232
 // Short layers take the small tile (two independent work-groups per compute unit: one's prologue runs under the
-// other's loop).  Long D = 128 layers of long items stay with the layer kernel, whose queues level the XCDs.  Long
+// other's loop).  Long D = 128 layers of long items stay with the layer kernel, whose queues level the XCDs.  So do
+// long ones made of dense heads, whose items the layer kernel runs 4 to 6 % faster on its large tile.  Before / table at
+// D = 128, by dense tiles per slot and their share, two cards (which differ by up to 4 % here):
+//   0 of 2,500, no dense heads                           1.02 (one card)
+//   500 to 730 of 1,435 to 1,880 (0.33 to 0.38)          0.99 to 1.04
+//   410 to 505 of 550 to 620 (0.75 to 0.81)              1.01 to 1.04
+//   560 to 680 of 630 to 820 (0.78 to 0.90)              0.96 to 1.00
+//   830 to 1,700 of 1,000 to 1,950 (0.58 to 0.92)        0.95 to 1.03, most of them 0.96 to 0.98
+// Whole dense items that do not come out even keep a few slots busy after all others have finished, which the split of
+// the dense heads in a launch per group or the larger units of the layer kernel avoid: 4 heads with one dense,
+// D = 64, 66,000 tokens (258 items in 256 slots, 1.6 times the even load) 1,324 / 1,535; D = 128, 38,400 tokens (300 in
+// 512, 1.3 times) 853 / 964.  At 233 tiles per slot and 1.4 times the load the table still wins (481 / 435).  Long
 // D = 64 layers take the large tile (a K/V tile in LDS serves twice the rows, 3-4 % a tile) unless its lists, which
 // follow the bands less closely, hold more than that on top; the longest stay in groups, whose launches and tails no
 // longer count.
 int grid_waves(const Plan& p, const svd_plan_options* opt, int form, int n_cu) {
   if (n_cu < 1) return 0;
   if (opt && (opt->block_q || opt->block_k || opt->dense_split || opt->single_launch)) return 0;
-  const double small = svd::grid_tiles(p, svd::kernel_small_block_q(p.desc.D)), per_slot = small / (2.0 * n_cu);
-  if (form == 1) return per_slot < 2500.0 ? 4 : 0;
-  if (form != 0 || (p.desc.D == 64 && per_slot > 2500.0)) return 0;
-  return p.desc.D == 64 && per_slot > 400.0 && 2.0 * svd::grid_tiles(p, p.block_q) < 1.03 * small ? 8 : 4;
+  const int small_q = svd::kernel_small_block_q(p.desc.D);
+  double dense = 0.0;
+  const double small = svd::grid_tiles(p, small_q, &dense), slots = 2.0 * n_cu, per_slot = small / slots;
+  if (form != 0 && form != 1) return 0;
+  if ((form == 1 || p.desc.D == 64) && per_slot > 2500.0) return 0;
+  if (form == 1 && dense > 550.0 * slots && dense > 0.45 * small) return 0;
+  const int waves = p.desc.D == 64 && per_slot > 400.0 && 2.0 * svd::grid_tiles(p, p.block_q) < 1.03 * small ? 8 : 4;
+  const double dense_items = std::ceil(static_cast<double>(p.desc.L) / (32 * waves)) * count_dense_heads(p) * p.desc.B;
+  const double dense_rounds = std::ceil(dense_items / (8 / waves * n_cu));
+  if (per_slot > 300.0 && dense_rounds * p.n_k_blocks > 1.3 * per_slot) return 0;
+  return waves;
 }
 
 // The same for the FP8 forward pass, always on the small query tile.  It gains more, because its pre-pass is one launch

@@ -225,6 +225,9 @@ void run_layer(const Layer& l) {
       int32_t form = -1;
       svd_plan_single_launch(plan, &form);
       std::printf("layer %s: the library's launch form is %d\n", l.name.c_str(), form);
+      int32_t waves = -1, waves8 = -1;
+      svd_plan_table(plan, &waves, &waves8);
+      std::printf("layer %s: table waves %d, fp8 %d\n", l.name.c_str(), waves, waves8);
       stub::new_forward();
       st = svd_attn_forward_planned(plan, q, k, v, out, nullptr);
       expect(st == SVD_OK, l, "forward with the library's choice of the launch form", st);

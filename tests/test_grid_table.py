@@ -24,11 +24,74 @@ def test_random_layers_from_the_table(replay, tmp_path, cu):
     assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
 
 
+def tables_of(res):
+    """{(waves, cut items)} of the bf16 tables that the harness walked."""
+    words = [line.split() for line in res.stdout.splitlines() if line.startswith("grid:")]
+    return {(int(w[2]), int(w[6]) > 0) for w in words if w[8] == "0"}
+
+
+def large_tile_layer(L, n_dense, diag_w, B=1):
+    """D = 64 with enough key tiles for eight-wave work-groups: dense heads, a wide band (a group on the 256-row tile), a
+    narrow multi-diagonal band (a group on the 128-row tile, whose lists on the large one are appended for the table), a
+    stripe head, a skipped one."""
+    table = np.asarray([W.DENSE] * n_dense + [W.DIAG, W.MULTIDIAG, W.VSTRIPE, W.SKIP], dtype=np.int32)
+    params = [{}] * n_dense + [{"half_width": diag_w}, {"half_width": 60, "offsets": tuple(i * (L // 3) for i in (-2, -1, 0, 1, 2))},
+                               {"cols": tuple(range(1, L, 7))}, {}]
+    return W.Workload("large-tile", -1, B, n_dense + 4, L, 64, L, 1, 0, table, params, 81)
+
+
+def cut_text_layer():
+    """Long text rows (903 key tiles) over heads whose other items are short: eight waves, and the text items are cut."""
+    T = 256
+    return W.Workload("cut-text", -1, 1, 4, 115456, 64, 3600, 32, T, np.asarray([W.DIAG] * 4, dtype=np.int32),
+                      [{"half_width": 3500, "text_tokens": T}] * 4, 82)
+
+
 def test_full_size_tables(replay, tmp_path):
-    """Both query tiles: the D = 64 benchmark layer takes the large one, its lists appended for it."""
+    """The two longest benchmark layers keep their other forms in bf16; long D = 64 layers of 400 to 2,500 key tiles per
+    resident work-group take the large query tile, some of them with cut items."""
     layers = [layer_text(W.cogvideox15(), 0, rounds=1, tensors=0), layer_text(W.wan21(), 0, rounds=1, tensors=0)]
     res = run(replay, tmp_path, layers)
     assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+    assert tables_of(res) == set()
+    res = run(replay, tmp_path, [layer_text(large_tile_layer(20011, 9, 5000), 0, rounds=1, tensors=0)])
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+    assert tables_of(res) == {(8, False)}
+    res = run(replay, tmp_path, [layer_text(cut_text_layer(), 0, rounds=1, tensors=0)])
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+    assert tables_of(res) == {(8, True)}
+
+
+def test_eight_wave_table_stores_every_row_once(replay, tmp_path):
+    """The large query tile with the tensors checked (four compute units make a small layer long)."""
+    res = run(replay, tmp_path, [layer_text(large_tile_layer(5003, n, 1500), 0, rounds=1, cu=4) for n in (8, 12)])
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+    assert tables_of(res) == {(8, False)}
+
+
+def mixed_layer(D, n_dense, n_diag, n_multi, n_stripe, frame_tokens, frames):
+    n, L = frame_tokens, frame_tokens * frames
+    table = np.asarray([W.DENSE] * n_dense + [W.DIAG] * n_diag + [W.MULTIDIAG] * n_multi + [W.VSTRIPE] * n_stripe, dtype=np.int32)
+    params = [{}] * n_dense + [{"half_width": n}] * n_diag + [{"half_width": n // 4, "offsets": (-2 * n, -n, 0, n, 2 * n)}] * n_multi \
+        + [{"cols": tuple(range(0, L, L // 2000))}] * n_stripe
+    return W.Workload("mixed", -1, 1, len(table), L, D, n, frames, 0, table, params, 83)
+
+
+@pytest.mark.parametrize("shape,waves", [
+    ((128, 2, 16, 10, 10, 1560, 21), 4),     # a third of the tiles dense
+    ((128, 18, 9, 6, 6, 900, 12), 4),        # four fifths, 505 dense tiles per resident work-group
+    ((128, 18, 9, 6, 6, 1000, 14), 0),       # 830: the layer kernel
+    ((128, 0, 20, 10, 10, 2100, 21), 4),     # none
+    ((128, 0, 20, 10, 10, 2100, 33), 0),     # over 2,500 tiles
+    ((128, 1, 2, 1, 0, 1600, 24), 0),        # 300 long items in 512 slots: 1.3 times the even load
+    ((64, 1, 2, 1, 0, 2000, 33), 0),         # 258 long items in 256 slots
+    ((64, 1, 2, 1, 0, 2000, 32), 8),         # 250
+    ((64, 1, 2, 1, 0, 1600, 24), 4)])        # uneven, but short
+def test_which_layers_run_from_a_table(replay, tmp_path, shape, waves):
+    """Both sides of each line of the rule, with 256 compute units."""
+    res = run(replay, tmp_path, [layer_text(mixed_layer(*shape), 0, rounds=1, tensors=0)])
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+    assert f"layer mixed: table waves {waves}," in res.stdout, res.stdout
 
 
 @pytest.mark.gpu
@@ -51,6 +114,28 @@ def test_cut_items_of_every_kind(D, mode):
     check_layer(wl, q, k, v, out)
     out8, _ = run_fp8(wl, q, k, v)
     check_layer_fp8(wl, q, k, v, out8)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("wl,rows", [(large_tile_layer(20011, 9, 5000), (0, 1, 255, 256, 4999, 5000, 10005, 19967, 19968, 20010)),
+                                     (cut_text_layer(), (0, 127, 128, 255, 256, 257, 3755, 57728, 115455))],
+                         ids=["ragged", "cut-text"])
+def test_eight_wave_table(wl, rows):
+    """Layers of 400 to 2,500 key tiles per resident work-group at D = 64 run on the large query tile: a ragged one with
+    lists appended for it, and one whose text rows are cut into chunks and merged."""
+    gen = torch.Generator(device="cuda:0").manual_seed(wl.seed)
+    q, k, v = (torch.randn(wl.B, wl.H, wl.L, wl.D, generator=gen, device="cuda:0", dtype=torch.bfloat16) for _ in range(3))
+    desc = svd.desc_of(q)
+    ws = torch.empty(svd.svd_plan_workspace_bytes(desc, wl.strategy_table, wl.pattern_params), dtype=torch.uint8, device="cuda:0")
+    plan = svd.svd_plan_create(desc, wl.strategy_table, wl.pattern_params, workspace=ws)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert plan.table()["bf16"] == 8
+    out = torch.full_like(q, float("nan"))
+    svd.svd_attn_forward_planned(plan, q, k, v, out)
+    torch.cuda.synchronize()
+    plan.close()
+    assert torch.isfinite(out).all()
+    check_layer(wl, q, k, v, out, rows=np.asarray(rows))
 
 
 @pytest.mark.gpu
