@@ -329,8 +329,9 @@ svd_status sparse_vdit_attn_forward(const void* q, const void* k, const void* v,
  * (as are the gathered rows of stripe heads and the layer kernel's queue positions):
  * every GPU the library runs on holds its own copy until the process ends.  The
  * call allocates no device memory and creates no streams or events; the groups of
- * the layer run one after the other on hip_stream.  A layer whose split dense
- * heads do not fit the buffer runs them unsplit; a layer whose lists alone do not
+ * the layer run one after the other on hip_stream.  A layer whose table of items does
+ * not fit the buffer with its scratch runs in the form it has without one, a layer whose
+ * split dense heads do not fit runs them unsplit; a layer whose lists alone do not
  * fit is refused with SVD_ERR_STATIC_LIMIT (nothing is enqueued).  The plan of the
  * previous call on the device is reused when table, parameters and descriptor are
  * identical; otherwise the new lists are copied into the buffer on hip_stream and

@@ -1283,12 +1283,21 @@ svd_status sparse_vdit_attn_forward_static(const void* q, const void* k, const v
     if (hipStreamIsCapturing(stream, &capture) != hipSuccess) return SVD_ERR_HIP;
     if (capture != hipStreamCaptureStatusNone) return SVD_ERR_UNSUPPORTED;
     if (c.used && c.last_stream != stream && hipDeviceSynchronize() != hipSuccess) return SVD_ERR_HIP;
-    // the split of the dense heads is the library's choice unless its partial results
-    // do not fit the buffer: then the dense heads run unsplit
+    // The launch form and the split of the dense heads are the library's choice unless their partial results do not fit
+    // the buffer: then without a table of items (whose cut items have some), then with the dense heads unsplit.
     svd_plan_options opt{};
     size_t need = 0;
     if (svd_status st = svd_plan_workspace_bytes(desc, strategy_table, pattern_params, &opt, &need)) return st;
     if (need > scratch_bytes) {
+      int bq = 0, bk = 0;
+      svd::kernel_blocks(desc->D, &bq, &bk);
+      const int form = layer_form(nullptr, *desc, true, device_compute_units(),
+                                  mean_tiles_per_item(*desc, strategy_table, pattern_params, bk, 0));
+      opt.single_launch = form ? form : 2;
+      if (svd_status st = svd_plan_workspace_bytes(desc, strategy_table, pattern_params, &opt, &need)) return st;
+    }
+    if (need > scratch_bytes) {
+      opt.single_launch = 0;
       opt.dense_split = 1;
       if (svd_status st = svd_plan_workspace_bytes(desc, strategy_table, pattern_params, &opt, &need)) return st;
     }

@@ -13,6 +13,7 @@
 #include <cstring>
 #include <map>
 #include <set>
+#include <string>
 #include <unordered_set>
 #include <vector>
 
@@ -37,6 +38,7 @@ int g_cu = 256;
 bool g_tensor_checks = true;
 int g_violations = 0;
 long g_launches = 0, g_nodes = 0, g_seq = 0;
+std::map<std::string, long> g_launches_of;
 int g_captures = 0;                        // captures in progress
 std::map<const char*, size_t> g_allocs;
 // Copies out of page-locked memory (or kernels that read it): the model makes them at once, the device at any time until an event
@@ -100,6 +102,7 @@ void violation(const char* fmt, ...) {
 int violations() { return g_violations; }
 long launches() { return g_launches; }
 long captured_nodes() { return g_nodes; }
+long launches_of(const char* what) { return g_launches_of[what]; }
 void set_compute_units(int n) { g_cu = n; }
 
 namespace {
@@ -170,6 +173,7 @@ void note_launch(hipStream_t s, const char* what) {
   ihipStream_t* st = resolve(s);
   if (!alive(st)) violation("launch of %s on a dead stream", what);
   ++g_launches;
+  ++g_launches_of[what];
   if (st->origin) ++g_nodes;
   work_on(st);
 }

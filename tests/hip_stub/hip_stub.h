@@ -37,6 +37,7 @@ void note_pinned_read(hipStream_t s, const void* src, size_t bytes);
 void violation(const char* fmt, ...);      // prints and counts a broken rule
 int violations();
 long launches();
+long launches_of(const char* what);
 long captured_nodes();
 
 }  // namespace stub
