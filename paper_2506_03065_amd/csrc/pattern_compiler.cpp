@@ -405,7 +405,24 @@ double grid_tiles(const Plan& plan, int32_t block_q, double* dense) {
   return tiles * plan.desc.B;
 }
 
+namespace {
+// Takes back what a table that could not be built has appended to the plan.
+struct TableRollback {
+  Plan* plan;
+  size_t words;
+  std::vector<Group*> listed;   // groups that got lists on the large tile
+  bool keep = false;
+  explicit TableRollback(Plan* p) : plan(p), words(p->ws_image.size()) {}
+  ~TableRollback() {
+    if (keep) return;
+    plan->ws_image.resize(words);
+    for (Group* g : listed) g->ws_list_table_large = 0;
+  }
+};
+}  // namespace
+
 bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_stripes, GridTable* out) {
+  TableRollback rollback(plan);
   const svd_tensor_desc& d = plan->desc;
   const int64_t L = d.L, bk = plan->block_k;
   const int32_t n_qb = static_cast<int32_t>(ceil_div(L, block_q));
@@ -436,6 +453,7 @@ bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_strip
       if (!bands) return false;
       if (bands == &g.bands_small) table = g.ws_list_table_small;
       if (bands == &g.bands_large && !g.ws_list_table_large) {
+        rollback.listed.push_back(&g);
         g.ws_list_table_large = table = append(&img, std::vector<int32_t>(g.bands_large.size() * kListRecordWords, 0));
         emit_band_lists(&img, g.bands_large, table);
       }
@@ -541,6 +559,7 @@ bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_strip
   }
   const size_t deepest = *std::max_element(depth, depth + 8);
   if (deepest * 8 > INT32_MAX / kGridWords) return false;
+  if (deepest * 8 > UINT32_MAX / (2u * block_q)) return false;   // a launch has fewer than 2^32 threads, a work-group 2 * block_q
   img.resize((img.size() + kGridWords - 1) / kGridWords * kGridWords, 0);
   out->table = img.size();
   img.resize(img.size() + deepest * 8 * kGridWords, -1);
@@ -559,6 +578,7 @@ bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_strip
   out->n_blocks = static_cast<int>(deepest * 8);
   out->n_merges = static_cast<int>(merges.size() / kGridWords);
   out->n_slots = static_cast<int>(n_slots);
+  rollback.keep = true;
   return true;
 }
 

@@ -1,6 +1,9 @@
 """The whole layer from a table of items: the table on the host model of the launches (every output row
 stored once, every word inside the workspace, the chunks of cut items complete), and items of every kind
 cut into chunks on the GPU against the oracle."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 import torch
@@ -10,7 +13,7 @@ from paper_2506_03065_amd import workloads as W
 from parity_util import check_layer, run_planned
 from test_gpu_fp8 import check_layer_fp8, run_fp8
 from test_gpu_random_layers import random_layer
-from test_host_launch_model import layer_text, replay, run  # noqa: F401  (replay: the fixture)
+from test_host_launch_model import CSRC, ROOT, STUB, layer_text, replay, run  # noqa: F401  (replay: the fixture)
 
 
 @pytest.mark.parametrize("cu", [8, 256])
@@ -92,6 +95,14 @@ def test_which_layers_run_from_a_table(replay, tmp_path, shape, waves):
     res = run(replay, tmp_path, [layer_text(mixed_layer(*shape), 0, rounds=1, tensors=0)])
     assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
     assert f"layer mixed: table waves {waves}," in res.stdout, res.stdout
+
+
+def test_a_table_that_cannot_be_built_leaves_no_trace(tmp_path):
+    exe = str(tmp_path / "grid_table_fails")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", STUB, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                    os.path.join(CSRC, "pattern_compiler.cpp"), os.path.join(STUB, "grid_table_fails.cpp"), "-o", exe], check=True)
+    res = subprocess.run([exe], capture_output=True, text=True)
+    assert res.returncode == 0, (res.returncode, res.stdout)
 
 
 @pytest.mark.gpu
