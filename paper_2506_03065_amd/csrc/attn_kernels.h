@@ -111,12 +111,12 @@ hipError_t launch_layer(const LayerLaunch& p, int n_compute_units, hipStream_t s
 
 // A layer of short items in one launch (see plan.h for the records of the table).
 struct GridLaunch {
-  AttnLaunch a;          // tensors, shape, strides, scale, ws, gathered, gather_pad
+  AttnLaunch a;          // tensors, shape, strides, scale, ws
   int table, n_blocks;   // word offset of the records in ws; records
   int merge_table, n_merges;
   int head_table, n_heads;   // FP8: word offset and number of the head records of the pre-pass
-  int waves;             // per work-group: the small query tile's (4) or the large one's (8)
-  float* partial;        // device: slots of NW * (D / 32 * 16 + 2) * 64 floats, NW = waves of the small tile
+  int waves;             // per work-group: 4 = the small query tile, 8 = the large one (D = 64 only)
+  float* partial;        // device: slots of grid_slot_floats(D, waves) floats
 };
 // Floats of one slot of partial results.
 inline size_t grid_slot_floats(int D, int waves) { return static_cast<size_t>(waves) * (D / 32 * 16 + 2) * 64; }
@@ -128,7 +128,7 @@ hipError_t launch_grid_merge(const GridLaunch& p, hipStream_t stream);
 size_t partial_floats(int D, int n_items);
 
 void kernel_blocks(int D, int* block_q, int* block_k);
-// Query rows of the small tile (band modes only).
+// Query rows of the small tile.
 int kernel_small_block_q(int D);
 // small_q: the launch uses the small query tile (MODE_BAND, MODE_PBAND and unsplit
 // MODE_DENSE; n_q_blocks and the lists must have been built for it).

@@ -989,6 +989,7 @@ __global__ void __launch_bounds__(kLayerWaves * 64, 2) attn_layer_kernel(const L
 
 // ---- the layer in one launch, work-group = one item of a table ----
 
+// Instantiated for four waves, and at D = 64 for eight (at D = 128 the large tile was never the fastest form).
 // The loops are those of attn_fwd_kernel (same registers, no spill inside them: a work-group takes one branch of the
 // switch to its end).  What bounds short layers is everything around the loops: here one scalar load brings the item,
 // where a group's launch reads head, list record, row pointer and entries one after the other, and one launch
@@ -1189,7 +1190,6 @@ hipError_t launch_grid_merge(const GridLaunch& p, hipStream_t stream) {
   if (p.n_merges < 1) return hipSuccess;
   if (!p.a.ws || !p.partial) return hipErrorInvalidValue;
   if (p.a.D == 128 && p.waves == 4) return launch_merge_shape<128, 4>(p, stream);
-  if (p.a.D == 128 && p.waves == 8) return launch_merge_shape<128, 8>(p, stream);
   if (p.a.D == 64 && p.waves == 4) return launch_merge_shape<64, 4>(p, stream);
   if (p.a.D == 64 && p.waves == 8) return launch_merge_shape<64, 8>(p, stream);
   return hipErrorInvalidValue;
@@ -1199,7 +1199,6 @@ hipError_t launch_grid(const GridLaunch& p, hipStream_t stream) {
   if (p.n_blocks < 1) return hipSuccess;
   if (!p.a.ws || (p.n_merges > 0 && !p.partial)) return hipErrorInvalidValue;
   if (p.a.D == 128 && p.waves == 4) return launch_grid_shape<128, 4, Tile128::BC>(p, stream);
-  if (p.a.D == 128 && p.waves == 8) return launch_grid_shape<128, 8, Tile128::BC>(p, stream);
   if (p.a.D == 64 && p.waves == 4) return launch_grid_shape<64, 4, Tile64::BC>(p, stream);
   if (p.a.D == 64 && p.waves == 8) return launch_grid_shape<64, 8, Tile64::BC>(p, stream);
   return hipErrorInvalidValue;
