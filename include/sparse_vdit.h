@@ -172,10 +172,11 @@ typedef struct svd_plan svd_plan;
  * options).  D must be 64 or 128. */
 svd_status svd_default_blocks(int32_t D, int32_t* block_q, int32_t* block_k);
 
-/* Bytes of device workspace a plan for this layer needs: the compiled lists plus,
- * when the dense heads are split, the scratch of their partial results.  Reads
- * the current device's compute-unit count when dense_split is 0 (no device: no
- * split); touches no device memory. */
+/* Bytes of device workspace a plan for this layer needs: the compiled lists, the
+ * scratch of partial results (split dense heads, split text rows, cut items of a
+ * table), the gathered rows of stripe heads; the scratch of the per-group entry points
+ * is part of it whatever form the forward pass has.  Reads the current device's
+ * compute-unit count (no device: no split, no table); touches no device memory. */
 svd_status svd_plan_workspace_bytes(const svd_tensor_desc* desc, const int32_t* strategy_table,
                                     const svd_head_params* pattern_params,
                                     const svd_plan_options* options, size_t* bytes);

@@ -113,7 +113,7 @@ int layer_form(const svd_plan_options* opt, const svd_tensor_desc& d, bool nativ
   return d.D == 128 ? 1 : 0;
 }
 
-// Key tiles per item of the layer on the 128-row tile, averaged over the heads that compute (what the
+// Key tiles per item of the layer on the layer kernel's tile, averaged over the heads that compute (what the
 // library's choice of the launch form looks at; taken from the table and parameters alone).
 double mean_tiles_per_item(const svd_tensor_desc& d, const int32_t* table, const svd_head_params* pp, int block_k,
                            int text_tokens) {

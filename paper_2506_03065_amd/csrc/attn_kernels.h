@@ -77,21 +77,21 @@ hipError_t launch_gather_kv(const AttnLaunch& p, hipStream_t stream);
 hipError_t launch_copy_lists(const void* src, void* dst, size_t bytes, hipStream_t stream);
 
 // The whole layer in ONE launch (Section 4.2: heads that share a mode are fused;
-// here all groups are): a grid of resident work-groups, two of four waves per
+// here all groups are): a grid of resident work-groups, one of eight waves per
 // compute unit, pulls items off eight work queues, one per XCD, heaviest segment
 // first.  A segment is one group's items in the order of a grouped launch (query
 // tiles of a head consecutive), or the text rows of a sparse group as dense
 // items; every segment has eight queues, queue x holding its x-th eighth, so the
 // query tiles of a head stay on one XCD.  Segment after segment a work-group
 // drains its own XCD's queue, then the other XCDs', and moves on; it leaves after
-// the last segment.  Every item runs on the small query tile (128 rows) and
+// the last segment.  Every item runs on the 256-row query tile and
 // dense heads are not split: the next segment fills the tail that a launch per
 // group pays for.
 constexpr int kMaxSegments = 12;
 struct LayerSegment {
   int kind;          // SEG_*
   int n_items;       // n_q_blocks * n_heads * B - first_item
-  int n_q_blocks;    // query tiles of 128 rows per head in this segment
+  int n_q_blocks;    // query tiles per head in this segment
   int n_heads;
   int heads;         // word offsets into the plan workspace: head ids of the group,
   int list_id;       //   the list of every head,
@@ -105,7 +105,7 @@ struct LayerLaunch {
   int* counters;                     // device: kLayerCounterWords queue positions, zeroed by a fill kernel ahead of the layer kernel
 };
 constexpr int kLayerCounterWords = 8 * kMaxSegments;   // one queue position per (segment, XCD)
-// Query rows per item of the single-launch path (the small query tile).
+// Query rows per item of the single-launch path.
 int layer_block_q(int D);
 hipError_t launch_layer(const LayerLaunch& p, int n_compute_units, hipStream_t stream);
 
