@@ -1223,7 +1223,11 @@ svd_status sparse_vdit_attn_forward(const void* q, const void* k, const void* v,
       delete fresh;
       return st;
     }
-    if (g_oneshot.plan) svd_plan_destroy(g_oneshot.plan);
+    if (g_oneshot.plan) {
+      for (hipStream_t s : g_oneshot.plan->side)
+        if (s) (void)hipStreamSynchronize(s);   // its groups may still be running on them
+      svd_plan_destroy(g_oneshot.plan);
+    }
     g_oneshot.plan = fresh;
     g_oneshot.slot = -1;
     g_oneshot.desc = *desc;

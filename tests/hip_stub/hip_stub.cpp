@@ -23,6 +23,7 @@ struct ihipStream_t {
   std::set<ihipStream_t*> forked;         // origin only: streams that joined its capture
   std::set<ihipStream_t*> unjoined;       // origin only: forked streams with work not yet joined back
   long last_work = 0;                     // sequence number of the last work enqueued
+  long finished = 0;                      // and of the last that the host has waited for
 };
 struct ihipEvent_t {
   unsigned magic = 0xE7E27u;
@@ -36,9 +37,11 @@ struct ihipEvent_t {
 namespace {
 int g_cu = 256;
 bool g_tensor_checks = true;
+bool g_strict_destroy = false;
 int g_violations = 0;
 long g_launches = 0, g_nodes = 0, g_seq = 0;
 std::map<std::string, long> g_launches_of;
+long g_streams = 0;                        // created by the library
 int g_captures = 0;                        // captures in progress
 std::map<const char*, size_t> g_allocs;
 // Copies out of page-locked memory (or kernels that read it): the model makes them at once, the device at any time until an event
@@ -102,6 +105,7 @@ void violation(const char* fmt, ...) {
 int violations() { return g_violations; }
 long launches() { return g_launches; }
 long captured_nodes() { return g_nodes; }
+long streams_created() { return g_streams; }
 long launches_of(const char* what) { return g_launches_of[what]; }
 void set_compute_units(int n) { g_cu = n; }
 
@@ -120,6 +124,7 @@ void note_out_row(const void* row) {
 }
 size_t out_rows_written() { return g_out_rows.size(); }
 void set_tensor_checks(bool on) { g_tensor_checks = on; }
+void set_strict_destroy(bool on) { g_strict_destroy = on; }
 bool tensor_checks() { return g_tensor_checks; }
 
 void* device_alloc(size_t bytes) {
@@ -199,6 +204,7 @@ hipError_t hipDeviceGetAttribute(int* value, hipDeviceAttribute_t attr, int) {
 hipError_t hipGetLastError() { return hipSuccess; }
 
 hipError_t hipStreamCreateWithFlags(hipStream_t* stream, unsigned) {
+  ++g_streams;
   *stream = new ihipStream_t();
   return hipSuccess;
 }
@@ -206,6 +212,7 @@ hipError_t hipStreamDestroy(hipStream_t stream) {
   if (!stream) return hipErrorInvalidResourceHandle;
   if (!alive(stream)) stub::violation("hipStreamDestroy of a dead stream");
   if (stream->origin) stub::violation("hipStreamDestroy of a stream that is capturing");
+  if (g_strict_destroy && stream->last_work > stream->finished) stub::violation("hipStreamDestroy of a stream whose work may be under way");
   copies_made(stream, g_seq);   // what it holds is finished first
   g_waits.erase(stream);
   stream->magic = 0;
@@ -220,6 +227,7 @@ hipError_t hipStreamSynchronize(hipStream_t stream) {
     return hipErrorStreamCaptureUnsupported;
   }
   copies_made(st, g_seq);
+  st->finished = g_seq;
   return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() {

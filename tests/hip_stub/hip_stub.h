@@ -16,8 +16,10 @@ void device_free(void* p);
 // true when [p, p + bytes) lies inside one live device allocation
 bool in_device(const void* p, size_t bytes);
 
+long streams_created();
 hipStream_t create_stream();               // a caller-owned stream
 void destroy_stream(hipStream_t s);
+void set_strict_destroy(bool on);          // a stream may be destroyed only after its work is known to be over
 void begin_capture(hipStream_t s);         // s becomes the origin of a capture
 hipError_t end_capture(hipStream_t s);     // hipErrorStreamCaptureUnjoined when forked work was not joined back
 

@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "hip_stub.h"
@@ -87,6 +88,32 @@ int main(int argc, char** argv) {
     call(i, 0, nullptr, "a call after the capture");
     expect(sparse_vdit_attn_forward(t[0], t[1], t[2], dense, pp, t[3], &d, ws[0], 64, nullptr) == SVD_ERR_WORKSPACE, "a small workspace");
     call(i, 0, nullptr, "a call after a refused one");
+  }
+  {
+    // a plan that forks its groups onto streams of its own is replaced by the next table's only when those are idle
+    stub::set_compute_units(3);
+    stub::set_tensor_checks(false);
+    svd_tensor_desc s{};
+    s.B = 1, s.H = 5, s.L = 9300, s.D = 64;
+    s.stride_l = s.D, s.stride_h = int64_t(s.L) * s.D, s.stride_b = s.stride_h * s.H;
+    svd_head_params sp[5] = {};
+    int32_t table[5] = {};
+    size_t need = 0;
+    for (svd_head_params& p : sp) p.half_width = 60;
+    table[4] = SVD_DIAG;
+    svd_plan_workspace_bytes(&s, table, sp, nullptr, &need);
+    void* w = stub::device_alloc(need);
+    const long before = stub::streams_created();
+    stub::set_strict_destroy(true);
+    for (int i = 0; i < 4; ++i) {
+      table[4] = SVD_DIAG, table[0] = SVD_DENSE;
+      std::swap(table[4], table[i % 2 ? 0 : 4]);
+      const int st = sparse_vdit_attn_forward(t[0], t[1], t[2], table, sp, t[3], &s, w, need, nullptr);
+      expect(st == SVD_OK, "a call whose plan forks", st);
+    }
+    stub::set_strict_destroy(false);
+    expect(stub::streams_created() > before, "the plans have streams of their own");
+    stub::set_compute_units(256);
   }
   {
     // the library's own buffer: where a layer with its table does not fit it, the launches per group keep the split of

@@ -2,6 +2,7 @@
 the same.  On the host model of the runtime, and on the GPU with the workspace overwritten in between."""
 import os
 import subprocess
+import threading
 
 import numpy as np
 import pytest
@@ -60,3 +61,37 @@ def test_workspace_used_in_between(D):
         outs.append(out)
     torch.cuda.synchronize()
     assert all(torch.equal(o.view(torch.int16), want[i % 5]) for i, o in enumerate(outs))
+
+
+@pytest.mark.gpu
+def test_threads_on_streams_of_their_own():
+    """Two threads, each with its stream, workspace and tables, in turn through the one cache: the bits of single calls."""
+    wl = W.small(L=900, D=64, H=5, seed=32)
+    q, k, v = (t.to("cuda:0") for t in W.make_qkv(wl))
+    tables = [np.roll(wl.strategy_table, r).astype(np.int32) for r in range(4)]
+    params = [[wl.pattern_params[(h - r) % 5] for h in range(5)] for r in range(4)]
+    desc = svd.desc_of(q)
+    n = max(svd.svd_plan_workspace_bytes(desc, t, p) for t, p in zip(tables, params))
+    ws = [torch.empty(n, dtype=torch.uint8, device="cuda:0") for _ in range(2)]
+    want = []
+    for t, p in zip(tables, params):
+        out = torch.full_like(q, float("nan"))
+        svd.sparse_vdit_attn_forward(q, k, v, t, p, out, ws[0])
+        torch.cuda.synchronize()
+        want.append(out.view(torch.int16))
+    outs = [[torch.full_like(q, float("nan")) for _ in range(30)] for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+
+    def work(i):
+        for j, out in enumerate(outs[i]):
+            r = 2 * i + (j // 3) % 2
+            svd.sparse_vdit_attn_forward(q, k, v, tables[r], params[r], out, ws[i], stream=streams[i])
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert all(torch.equal(o.view(torch.int16), want[2 * i + (j // 3) % 2]) for j, o in enumerate(outs[i]))
