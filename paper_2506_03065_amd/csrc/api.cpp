@@ -407,8 +407,9 @@ struct OneShot {
 OneShot g_oneshot;
 
 bool copies_over(StagedLists* s) {
-  if (s->pending && hipEventQuery(s->copied) == hipSuccess) s->pending = false;
-  (void)hipGetLastError();   // "not ready" is an answer, not an error of the launch that follows
+  if (!s->pending) return true;
+  if (hipEventQuery(s->copied) == hipSuccess) s->pending = false;
+  else (void)hipGetLastError();   // "not ready" is an answer, not an error of the launch that follows
   return !s->pending;
 }
 
@@ -1213,8 +1214,8 @@ svd_status sparse_vdit_attn_forward(const void* q, const void* k, const void* v,
   // a capture records the launches of a plan whose lists are in the workspace already; the copy is not recorded, because
   // later calls reuse the memory it reads
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  const bool capturing = hipStreamIsCapturing(static_cast<hipStream_t>(hip_stream), &capture) == hipSuccess &&
-                         capture != hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(static_cast<hipStream_t>(hip_stream), &capture) != hipSuccess) (void)hipGetLastError();
+  const bool capturing = capture != hipStreamCaptureStatusNone;
   if (!hit) {
     if (capturing) return SVD_ERR_HIP;
     svd_plan* fresh = nullptr;

@@ -116,6 +116,27 @@ int main(int argc, char** argv) {
     stub::set_compute_units(256);
   }
   {
+    // lists longer than a page-locked area: copied from where they are, and waited for
+    stub::set_tensor_checks(false);
+    svd_tensor_desc s{};
+    s.B = 1, s.H = 6, s.L = 60000, s.D = 64;
+    s.stride_l = s.D, s.stride_h = int64_t(s.L) * s.D, s.stride_b = s.stride_h * s.H;
+    svd_head_params sp[6] = {};
+    int32_t table[6];
+    for (int h = 0; h < 6; ++h) table[h] = SVD_DIAG, sp[h].half_width = 20000 + h;
+    size_t need = 0;
+    svd_plan_workspace_bytes(&s, table, sp, nullptr, &need);
+    expect(need > (size_t(8) << 20), "lists of more than 8 MiB");
+    void* w = stub::device_alloc(need);
+    const long copies = stub::launches_of("copy_lists_kernel");
+    for (int i = 0; i < 2; ++i) {
+      std::memset(w, 0x7f, need);
+      const int st = sparse_vdit_attn_forward(t[0], t[1], t[2], table, sp, t[3], &s, w, need, nullptr);
+      expect(st == SVD_OK, "a call with long lists", st);
+    }
+    expect(stub::launches_of("copy_lists_kernel") == copies, "no page-locked copy of long lists");
+  }
+  {
     // the library's own buffer: where a layer with its table does not fit it, the launches per group keep the split of
     // the dense heads, if that fits (this layer: 346 us with the split, 481 us without)
     stub::set_tensor_checks(false);
