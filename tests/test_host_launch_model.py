@@ -102,7 +102,8 @@ def test_benchmark_layers_index_arithmetic(replay, tmp_path):
 
 
 def test_short_items_keep_the_grouped_launches(replay, tmp_path):
-    """Small layers (few key tiles per item) stay on grouped launches whatever the head size."""
+    """Small layers (few key tiles per item) keep off the layer kernel whatever the head size (left to the library, they
+    run from a table of items; the plan's launch form stays 0)."""
     layers = [layer_text(*random_layer(seed), rounds=1) for seed in range(6)]
     res = run(replay, tmp_path, layers)
     assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
