@@ -13,11 +13,12 @@
 //                        order in which a lane's score accumulators hold them.
 //                        A vertical-stripe head (M_4) is compacted here: its
 //                        arrays hold the listed key columns only.
-//   attn_fwd_fp8_kernel  the loop of the bf16 kernel (transposed scores, lane
-//                        owns a query column, one tile of look-ahead between the
-//                        two products, lazy reference) on the FP8 matrix
-//                        instructions v_mfma_f32_32x32x64_f8f6f4 (both products)
-//                        and v_mfma_f32_16x16x128_f8f6f4 (row sums of P).  Modes:
+//   attn_fwd_fp8_kernel  transposed scores and a lane that owns a query column, as
+//                        in the bf16 kernel, on the FP8 matrix instructions
+//                        v_mfma_f32_32x32x64_f8f6f4 (scores),
+//                        v_mfma_scale_f32_32x32x64_f8f6f4 (P V; its block scale
+//                        carries the reference of the tile's P) and
+//                        v_mfma_f32_16x16x128_f8f6f4 (row sums of P).  Modes:
 //                        DENSE, BAND, GATHER = the dense loop over a compacted
 //                        head, and PBAND = the banded loop of a multi-diagonal
 //                        head in rearranged form (Section 4.1.2): the pre-pass
@@ -26,9 +27,9 @@
 // Operand layout of the 32x32x64 instruction: lane l supplies row (column) l % 32
 // with the 32 contraction indices 32 * (l / 32) .. + 31 in its 32 bytes; the
 // result has the layout of the 32x32 bf16 instructions, so masks, maxima and the
-// epilogue are those of the bf16 kernel.  The reference moves in integer steps:
-// every rescale is an exact power of two and the rounding of P does not depend
-// on the order of the key tiles (outside the subnormal range).
+// epilogue are those of the bf16 kernel.  The reference is an integer: every change
+// of units is an exact power of two and the rounding of P does not depend on the
+// order of the key tiles (outside the subnormal range).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -47,6 +48,7 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x2 __attribute__((ext_vector_type(2)));
 typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
@@ -63,6 +65,13 @@ __device__ __forceinline__ int pack_e4m3(float a, float b, float c, float d) {
   w = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, w, false);
   w = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, w, true);
   return w;
+}
+// The same of a / scale, ...; scale is a power of two.
+__device__ __forceinline__ int pack_e4m3(float a, float b, float c, float d, float scale) {
+  s16x2 w = __builtin_bit_cast(s16x2, a);
+  w = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w, a, b, scale, false);
+  w = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w, c, d, scale, true);
+  return __builtin_bit_cast(int, w);
 }
 __device__ __forceinline__ float sat_e4m3(float x) { return fminf(fmaxf(x, -kE4M3Max), kE4M3Max); }
 
@@ -210,7 +219,6 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
   constexpr int KS = D / 64;         // contraction steps of S^T = K Q^T
   constexpr int DB = D / 32;         // 32-row blocks of O^T
   constexpr int TILE_BYTES = BC * D;
-  constexpr bool DEEP = D == 128 && MODE == MODE_DENSE;   // pipeline shape, see the stages below
   constexpr int LPT = TILE_BYTES / (NW * 1024);   // load instructions per wave, tile and matrix
   static_assert(TILE_BYTES % (NW * 1024) == 0 && LPT >= 1, "tile must split evenly over the waves");
   static_assert(BC % 64 == 0, "key tiles are whole groups of 64");
@@ -256,18 +264,17 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
     }
   }
 
-  // Softmax state.  Scores are kept relative to an INTEGER reference exponent:
-  // the score accumulators start from nm = -reference, so exp2 applies to the
-  // MFMA result as it is.  thr: -inf until the lane has seen its first kept key,
-  // afterwards 8 (the largest relative score the reference allows: P <= 256).
-  constexpr float kHeadroom = 8.0f;
-  f32x16 o[DB], nm;
+  // Softmax state.  top: the integer reference ceil(row max so far) - 8 of the lane's
+  // query, -inf until the lane has seen its first kept key.  Accumulators and row sums
+  // are in units of 2^base; base stays 0 unless a reference leaves +-kReach around it.
+  constexpr float kHeadroom = 8.0f, kReach = 64.0f;
+  f32x16 o[DB];
   f32x4 l4;
-  float thr = kNegInf, mx_raw = kNegInf;
+  float top = kNegInf, base_ref = 0.f, tile_ref = kNegInf;
+  float l = 0.f, l_scale = 1.f;   // row sum; what l4[0], a tile's sum in the units of its P8, counts in it
+  bool based = false;   // some lane of the wave has a base other than 0
 #pragma unroll
   for (int i = 0; i < 4; ++i) l4[i] = 0.f;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) nm[i] = 0.f;
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -330,7 +337,9 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
     constexpr int BUF = decltype(buf_tag)::value;
     const unsigned char* kbase = sK + BUF * TILE_BYTES;
 #pragma unroll
-    for (int kb2 = 0; kb2 < KB2; ++kb2) s[kb2] = nm;
+    for (int kb2 = 0; kb2 < KB2; ++kb2)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[kb2][i] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
@@ -372,6 +381,20 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
         changed = true;
         const int iq = q0 + l32;
         const int jb = jb0 + half * 4;
+        if (rn == 1) {   // one edge of a run, seldom both: each is one comparison with a literal per element
+          const i32x2 run = runs[r0];
+          if (dmin < run.x) {
+            const int lo = run.x - (jb - iq);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[kb2][i] = (i / 4) * 8 + (i % 4) < lo ? kNegInf : s[kb2][i];
+          }
+          if (dmax > run.y || jb0 + 31 >= L) {
+            const int hi = (run.y < L - 1 - iq ? run.y : L - 1 - iq) - (jb - iq);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[kb2][i] = (i / 4) * 8 + (i % 4) > hi ? kNegInf : s[kb2][i];
+          }
+          continue;
+        }
         f32x16 kept;
 #pragma unroll
         for (int i = 0; i < 16; ++i) kept[i] = kNegInf;
@@ -412,46 +435,57 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
         a = fmaxf(fmaxf(a, s[kb2][i]), s[kb2][i + 1]);
         bq = fmaxf(fmaxf(bq, s[kb2][8 + i]), s[kb2][8 + i + 1]);
       }
-    mx_raw = fmaxf(a, bq);
+    tile_ref = __builtin_ceilf(half_max(fmaxf(a, bq))) - kHeadroom;
   };
 
-  // ---- reference update.  When a tile exceeds the reference by more than 8 the
-  // reference moves to ceil(row max) - 8, an integer: the scores already
-  // computed and the accumulator seed shift by it, l and O scale by an exact
-  // power of two.  The branch is wave-uniform and costs 112 vector instructions
-  // at both head sizes (a tile's own work: 64 at D = 128, 128 at D = 64).  Any of
-  // the wave's 32 rows takes it: with N(0, 1) logits in 5 % of the tiles of a list
-  // of 1,182, in 24 to 29 % of 115 to 138, in 61 % of 32 and in 77 to 95 % of 18 to
-  // 8 (simulated); vector instructions per MFMA as counted: 8.8 dense, 13 to 17 in
-  // the band and stripe groups at D = 128, 27 in short D = 64 layers.  `flush` runs
-  // first inside the branch: it adds what is still waiting to be accumulated
-  // under the old reference. ----
-  auto settle_max = [&](f32x16 (&s)[KB2], auto&& flush) {
-    const float mx = half_max(mx_raw);
-    const bool grow = mx > thr;   // false when the lane's tile is fully masked
-    if (__builtin_amdgcn_ballot_w64(grow) != 0) {
-      flush();
-      const float step = __builtin_ceilf(mx) - kHeadroom;
-      const float delta = grow ? step : 0.f;
-      const float alpha = (grow && thr != kNegInf) ? __builtin_amdgcn_exp2f(-step) : 1.0f;
-      thr = grow ? kHeadroom : thr;
-#pragma unroll
-      for (int kb2 = 0; kb2 < KB2; ++kb2)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s[kb2][i] -= delta;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) nm[i] -= delta;
-      l4[0] *= alpha;
+  // ---- reference of a tile's probabilities.  P8 of a tile is taken against the row
+  // maximum so far, and the second product puts it back into the units of the
+  // accumulators: the conversion divides by 2^e and the matrix instruction multiplies
+  // by 2^e (its block scale).  Both run at the rate of the forms without a scale (8.4 and
+  // 65 cycles a wave, measured), so a reference that moves costs nothing: neither the scores
+  // nor the accumulators are touched.  Moving them instead, 112 vector instructions beside
+  // the 64 (D = 128) or 128 (D = 64) of a tile, came with 5 % of the tiles of a list of
+  // 1,182 and with 77 to 95 % of lists of 18 to 8 (any of a wave's 32 rows asks for it).
+  // Both lanes of a query supply the same scale.  (In the 16x16x128 product a lane's scale does
+  // not stay with the lane's own bytes, and its neighbours hold other queries here: the row sums
+  // run unscaled, tile by tile, and one multiply-add per tile applies the scale.) ----
+  auto fold_sum = [&]() {
+    l = fmaf(l4[0], l_scale, l);
+    l4[0] = 0.f;
+  };
+  auto settle = [&](f32x16 (&s)[KB2], int* const prev_scale) -> int {
+    fold_sum();
+    top = fmaxf(top, tile_ref);
+    float e = top;
+    if (based || __builtin_amdgcn_ballot_w64(fabsf(top) > kReach && top != kNegInf) != 0) {
+      // Scores beyond what exp2 and the accumulators hold in units of 1: the lane moves its base to the reference.
+      based = true;
+      const bool far = fabsf(top - base_ref) > kReach && top != kNegInf;
+      const float shift = far ? top - base_ref : 0.f;
+      base_ref += shift;
+      const float alpha = shift > 0.f ? __builtin_amdgcn_exp2f(-shift) : 1.0f;   // shift < 0: the lane's first kept key
+      if (prev_scale) {
+        const int moved = *prev_scale - (int)shift;
+        *prev_scale = moved < 0 ? 0 : (moved > 254 ? 254 : moved);
+      }
+      l *= alpha;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
+#pragma unroll
+      for (int kb2 = 0; kb2 < KB2; ++kb2)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[kb2][i] -= base_ref;
+      e -= base_ref;
     }
+    return (int)fmaxf(e, -kReach) + 127;   // the exponent's bits; nothing kept yet: any (P is 0)
   };
 
   // ---- P = exp2(relative score) as E4M3, in the B-operand layout of the second
   // product: byte 16 blk + i of the lane = element i of block 2 g64 + blk ----
-  auto exponentiate = [&](const f32x16 (&s)[KB2], i32x8 (&pf)[G64]) {
+  auto exponentiate = [&](const f32x16 (&s)[KB2], i32x8 (&pf)[G64], const int scale) {
+    const float sc = __builtin_bit_cast(float, scale << 23);
 #pragma unroll
     for (int g64 = 0; g64 < G64; ++g64)
 #pragma unroll
@@ -461,14 +495,15 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
           const f32x16& sv = s[g64 * 2 + blk];
           pf[g64][blk * 4 + g] =
               pack_e4m3(__builtin_amdgcn_exp2f(sv[4 * g]), __builtin_amdgcn_exp2f(sv[4 * g + 1]),
-                        __builtin_amdgcn_exp2f(sv[4 * g + 2]), __builtin_amdgcn_exp2f(sv[4 * g + 3]));
+                        __builtin_amdgcn_exp2f(sv[4 * g + 2]), __builtin_amdgcn_exp2f(sv[4 * g + 3]), sc);
         }
   };
 
   // ---- O^T += V^T P^T and l += rowsum(P) for the tile held in V buffer BUF ----
-  auto accumulate = [&](auto buf_tag, const i32x8 (&pf)[G64]) {
+  auto accumulate = [&](auto buf_tag, const i32x8 (&pf)[G64], const int scale) {
     constexpr int BUF = decltype(buf_tag)::value;
     const unsigned char* vbase = sV + BUF * TILE_BYTES + v_off;
+    l_scale = __builtin_bit_cast(float, scale << 23);
 #pragma unroll
     for (int g64 = 0; g64 < G64; ++g64) {
 #pragma unroll
@@ -477,214 +512,129 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
         const i32x4 a0 = *reinterpret_cast<const i32x4*>(src);
         const i32x4 a1 = *reinterpret_cast<const i32x4*>(src + 512);
         const i32x8 a = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
-        o[db] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, pf[g64], o[db], 0, 0, 0, 0, 0, 0);
+        o[db] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, pf[g64], o[db], 0, 0, 0, 127, 0, scale);
       }
+      if (g64 == 0)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) l4[i] = 0.f;
       l4 = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(sum_a, pf[g64], l4, 0, 0, 0, 0, 0, 0);
     }
   };
+  // What a stage has computed for later ones is used only there: without these
+  // anchors the compiler moves part of the matrix instructions and exponentials past the
+  // barrier and the branch that follow, away from what hides them.
+  auto keep_here = [&](i32x8 (&pf)[G64]) {
+#pragma unroll
+    for (int g64 = 0; g64 < G64; ++g64) asm volatile("" : "+v"(pf[g64]));
+#pragma unroll
+    for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(o[db]));
+    asm volatile("" : "+v"(l4));
+    asm volatile("" : "+v"(tile_ref));
+  };
 
-  // Two pipeline shapes.  FLAT (two tiles deep, the shape of the bf16 kernel): a
-  // stage turns the scores of tile t into P and accumulates P V of the same tile.
-  // The FP8 product takes the probabilities of 64 keys at once, so its first
-  // instruction waits for the whole tile's exponentials and the matrix pipe of
-  // the wave idles meanwhile (the other wave of the SIMD fills in).  DEEP (three
-  // tiles deep): P of tile t is consumed one stage later, nothing in a stage
-  // waits for anything else in it; it costs one more stage per list and eight
-  // more registers per 64 keys of tile, and pays only for long dense lists at
-  // D = 128.
+  // ---- the loop, three tiles deep: a stage computes the scores of tile t + 1, the
+  // probabilities of tile t and O += P V of tile t - 1, so that nothing in it waits for
+  // anything else in it (the FP8 product takes the probabilities of 64 keys at once: in
+  // the stage that produces them it would wait for all of them).  On entry LDS holds
+  // K(t+1) and V(t-1); K(t+2) and V(t) are requested.  One barrier a stage: two stages to a
+  // barrier on rings of four slots measured 3 to 5 % slower at both head sizes.
+  // What bounds it: long lists run at the power limit (40 heads of 75,600 tokens: the
+  // same instructions on zeros take 6.1 ms, on normal inputs 7.4); there a wave's tile at D = 128 takes
+  // 990 cycles, 486 of them on the vector pipe and 544 on the matrix pipe.  Short lists are
+  // bound by the vector pipe and what surrounds the loop.  Against a loop two tiles deep whose
+  // reference moved scores and accumulators: 48 heads x 17,550, D = 64: 457 -> 400 us;
+  // 40 heads x 75,600, D = 128: 7.64 -> 7.11 ms; 24 heads x 8,536, D = 128: 230 -> 199 us. ----
   f32x16 s_a[KB2], s_b[KB2];
-  if (!DEEP) {
-    if (n_tiles > 0) {
-      load_tile(Int<1>{}, 0, 0);
-      load_tile(Int<0>{}, 0, 0);
-      if (n_tiles > 1) load_tile(Int<1>{}, 1, 1);
-    }
-    __syncthreads();
-    if (n_tiles > 0) {
-      scores(Int<0>{}, s_a);
-      tile_max(s_a);
-    }
-    __syncthreads();   // K(0) has been read by every wave before the first stage requests K(2) into its buffer
-
-    // One pipeline stage (see the bf16 kernel): on entry s_cur holds the raw scores
-    // of tile t; LDS holds K(t+1) and V(t); K(t+2) and V(t+1) are requested here.
-    // INNER: t + 2 is not the last tile of the list, so outside band lists nothing
-    // of tile t can be masked.
-    auto flat_stage = [&](auto par_tag, auto next_tag, auto inner_tag, const int t, f32x16 (&s_cur)[KB2],
-                     f32x16 (&s_next)[KB2]) {
-      constexpr int PAR = decltype(par_tag)::value;
-      constexpr bool has1 = decltype(next_tag)::value != 0;
-      constexpr bool INNER = decltype(inner_tag)::value != 0;
-      const bool has2 = INNER || t + 2 < n_tiles;
-      if (has2) load_tile(Int<1>{}, PAR, t + 2);
-      if (has1) load_tile(Int<0>{}, PAR ^ 1, t + 1);
-      bool masked;
-      if (kBand) masked = !(entries[t].y & 1);
-      else if (INNER) masked = false;
-      else masked = (t + t_base + 1) * BC > n_keys;
-      if (masked && apply_mask(s_cur, t)) tile_max(s_cur);
-      settle_max(s_cur, []() {});
-      i32x8 pf[G64];
-      if (has1) scores(Int<PAR ^ 1>{}, s_next);
-      exponentiate(s_cur, pf);
-      if (has1) tile_max(s_next);
-      accumulate(Int<PAR>{}, pf);
-      if (has1) {
-        // Issue order: one MFMA, the LDS reads that feed the MFMAs two steps later,
-        // then a share of the vector work (0x008 MFMA, 0x100 DS read, 0x002 VALU, 0x400 TRANS).
-        constexpr int N_QK = KS * KB2, N_PV = G64 * DB, N_SUM = G64;
-        constexpr int N_KRD = N_QK * 2, N_VRD = N_PV * 2;
-        // per score element: one exp2, half a conversion, half a max3
-        constexpr int VALU_PER = (KB2 * 16 * 2 + N_QK + N_PV + N_SUM - 1) / (N_QK + N_PV + N_SUM);
-        constexpr int AHEAD = 4;   // reads issued ahead of the MFMA that needs them (two MFMAs' worth)
-        __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
+  i32x8 pf_a[G64], pf_b[G64];
+  int pf_scale = 127;   // of the probabilities still to be accumulated
+  // FIRST: t = 0, nothing to accumulate yet.  NEXT: a tile t + 1 exists, so outside band lists nothing of tile t
+  // can be masked.
+  auto stage = [&](auto par_tag, auto first_tag, auto next_tag, const int t, f32x16 (&s_cur)[KB2], f32x16 (&s_next)[KB2],
+                   i32x8 (&pf_prev)[G64], i32x8 (&pf_cur)[G64]) {
+    constexpr int PAR = decltype(par_tag)::value;   // t & 1
+    constexpr bool FIRST = decltype(first_tag)::value != 0, NEXT = decltype(next_tag)::value != 0;
+    if (NEXT && t + 2 < n_tiles) load_tile(Int<1>{}, PAR, t + 2);   // K(t+2) takes the place of K(t), read in the last stage
+    load_tile(Int<0>{}, PAR, t);                                    // V(t) takes the place of V(t-2)
+    bool masked;
+    if (kBand) masked = !(entries[t].y & 1);
+    else masked = !NEXT && (t + t_base + 1) * BC > n_keys;
+    if (masked && apply_mask(s_cur, t)) tile_max(s_cur);
+    const int scale = settle(s_cur, &pf_scale);
+    if (NEXT) scores(Int<PAR ^ 1>{}, s_next);
+    if (!FIRST) accumulate(Int<PAR ^ 1>{}, pf_prev, pf_scale);
+    exponentiate(s_cur, pf_cur, scale);
+    pf_scale = scale;
+    if (NEXT) tile_max(s_next);
+    if (NEXT && !FIRST) {
+      // Issue order: the first LDS reads and, under them, a few exponentials; then one
+      // MFMA, the LDS reads that feed the MFMAs two steps later, and a share of the
+      // vector work (0x008 MFMA, 0x100 DS read, 0x002 VALU, 0x400 TRANS).
+      constexpr int N_QK = KS * KB2, N_PV = G64 * DB, N_SUM = G64;
+      constexpr int N_RD = (N_QK + N_PV) * 2;
+      // per score element: one exp2, half a conversion, half a max3
+      constexpr int VALU_PER = (KB2 * 16 * 2 + N_QK + N_PV + N_SUM - 1) / (N_QK + N_PV + N_SUM);
+      constexpr int AHEAD = 4;   // reads issued ahead of the MFMA that needs them (two MFMAs' worth)
+      __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
+      __builtin_amdgcn_sched_group_barrier(0x402, 8, 0);
 #pragma unroll
-        for (int i = 0; i < N_QK; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          if (2 * i + AHEAD < N_KRD + N_VRD) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-          __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER, 0);
-        }
-#pragma unroll
-        for (int g = 0; g < G64; ++g) {
-#pragma unroll
-          for (int j = 0; j < DB; ++j) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (2 * (N_QK + g * DB + j) + AHEAD < N_KRD + N_VRD) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER, 0);
-          }
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER, 0);
-        }
+      for (int i = 0; i < N_QK; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (2 * i + AHEAD < N_RD) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER, 0);
       }
-      if (has1) asm volatile("" : "+v"(mx_raw));   // keeps the maximum chain of the next tile inside this block
-      __syncthreads();
-    };
-
-    int t = 0;
-    for (; t + 5 <= n_tiles; t += 2) {
-      flat_stage(Int<0>{}, Int<1>{}, Int<1>{}, t, s_a, s_b);
-      flat_stage(Int<1>{}, Int<1>{}, Int<1>{}, t + 1, s_b, s_a);
+#pragma unroll
+      for (int g = 0; g < G64; ++g) {
+#pragma unroll
+        for (int j = 0; j < DB; ++j) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          if (2 * (N_QK + g * DB + j) + AHEAD < N_RD) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER, 0);
+      }
     }
+    keep_here(pf_cur);
+    __syncthreads();   // what was requested has landed, what was read may be overwritten
+  };
+
+  if (n_tiles > 0) {
+    load_tile(Int<1>{}, 0, 0);
+    if (n_tiles > 1) load_tile(Int<1>{}, 1, 1);
+  }
+  __syncthreads();
+  if (n_tiles > 0) {
+    scores(Int<0>{}, s_a);
+    tile_max(s_a);
+  }
+  __syncthreads();   // K(0) has been read by every wave before the first stage requests K(2) into its buffer
+  // Tile 0 alone, then two stages per trip (odd tile first) so that buffer indices
+  // and register sets stay static; after the last stage the probabilities of the
+  // last tile are still to be accumulated.
+  constexpr Int<0> even{}, no{};
+  constexpr Int<1> odd{}, yes{};
+  if (n_tiles > 1) {
+    stage(even, yes, yes, 0, s_a, s_b, pf_b, pf_a);
+    int t = 1;
     for (; t + 2 < n_tiles; t += 2) {
-      flat_stage(Int<0>{}, Int<1>{}, Int<0>{}, t, s_a, s_b);
-      flat_stage(Int<1>{}, Int<1>{}, Int<0>{}, t + 1, s_b, s_a);
+      stage(odd, no, yes, t, s_b, s_a, pf_a, pf_b);
+      stage(even, no, yes, t + 1, s_a, s_b, pf_b, pf_a);
     }
     if (t + 1 < n_tiles) {
-      flat_stage(Int<0>{}, Int<1>{}, Int<0>{}, t, s_a, s_b);
-      flat_stage(Int<1>{}, Int<0>{}, Int<0>{}, t + 1, s_b, s_a);
-    } else if (t < n_tiles) {
-      flat_stage(Int<0>{}, Int<0>{}, Int<0>{}, t, s_a, s_b);
+      stage(odd, no, yes, t, s_b, s_a, pf_a, pf_b);
+      stage(even, no, no, t + 1, s_a, s_b, pf_b, pf_a);
+      fold_sum();
+      accumulate(even, pf_a, pf_scale);
+    } else {
+      stage(odd, no, no, t, s_b, s_a, pf_a, pf_b);
+      fold_sum();
+      accumulate(odd, pf_b, pf_scale);
     }
-  } else {
-    i32x8 pf_a[G64], pf_b[G64];
-    if (n_tiles > 0) {
-      load_tile(Int<1>{}, 0, 0);
-      if (n_tiles > 1) load_tile(Int<1>{}, 1, 1);
-    }
-    __syncthreads();
-    if (n_tiles > 0) {
-      scores(Int<0>{}, s_a);
-      tile_max(s_a);
-    }
-    __syncthreads();   // K(0) has been read by every wave before the first stage requests K(2) into its buffer
-
-    // One pipeline stage, three tiles deep.  On entry s_cur holds the raw scores of
-    // tile t and pf_prev the probabilities of tile t - 1; LDS holds K(t+1) and
-    // V(t-1); K(t+2) and V(t) are requested here.  The block then contains the
-    // scores of tile t + 1 and O += P V of tile t - 1 on the matrix pipe, and the
-    // exponentials of tile t plus the maximum of tile t + 1 on the vector pipe:
-    // nothing in it waits for anything else in it.  (The FP8 product takes the
-    // probabilities of 64 keys at once, so P of a tile cannot be consumed in the
-    // stage that produces it without stalling the matrix pipe.)
-    // FIRST: t = 0, nothing to accumulate yet.  NEXT: a tile t + 1 exists.
-    // INNER: t + 2 is not the last tile of the list, so outside band lists nothing
-    // of tile t can be masked.
-    auto deep_stage = [&](auto par_tag, auto first_tag, auto next_tag, auto inner_tag, const int t, f32x16 (&s_cur)[KB2],
-                     f32x16 (&s_next)[KB2], i32x8 (&pf_prev)[G64], i32x8 (&pf_cur)[G64]) {
-      constexpr int PAR = decltype(par_tag)::value;     // t & 1
-      constexpr bool FIRST = decltype(first_tag)::value != 0;
-      constexpr bool has1 = decltype(next_tag)::value != 0;
-      constexpr bool INNER = decltype(inner_tag)::value != 0;
-      const bool has2 = INNER || t + 2 < n_tiles;
-      if (has2) load_tile(Int<1>{}, PAR, t + 2);   // K(t+2) takes the place of K(t), read in the last stage
-      load_tile(Int<0>{}, PAR, t);                 // V(t) takes the place of V(t-2)
-      bool masked;
-      if (kBand) masked = !(entries[t].y & 1);
-      else if (INNER) masked = false;
-      else masked = (t + t_base + 1) * BC > n_keys;
-      if (masked && apply_mask(s_cur, t)) tile_max(s_cur);
-      settle_max(s_cur, [&]() {
-        if (!FIRST) {
-          accumulate(Int<PAR ^ 1>{}, pf_prev);
-#pragma unroll
-          for (int g64 = 0; g64 < G64; ++g64)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) pf_prev[g64][i] = 0;   // the block below adds it once more: zeros now
-        }
-      });
-      if (has1) scores(Int<PAR ^ 1>{}, s_next);
-      if (!FIRST) accumulate(Int<PAR ^ 1>{}, pf_prev);
-      exponentiate(s_cur, pf_cur);
-      if (has1) tile_max(s_next);
-      if (has1 && !FIRST) {
-        // Issue order: one MFMA, the LDS reads that feed the MFMAs two steps later,
-        // then a share of the vector work (0x008 MFMA, 0x100 DS read, 0x002 VALU, 0x400 TRANS).
-        constexpr int N_QK = KS * KB2, N_PV = G64 * DB, N_SUM = G64;
-        constexpr int N_RD = (N_QK + N_PV) * 2;
-        // per score element: one exp2, half a conversion, half a max3
-        constexpr int VALU_PER = (KB2 * 16 * 2 + N_QK + N_PV + N_SUM - 1) / (N_QK + N_PV + N_SUM);
-        constexpr int AHEAD = 4;   // reads issued ahead of the MFMA that needs them (two MFMAs' worth)
-        __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
-#pragma unroll
-        for (int i = 0; i < N_QK; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          if (2 * i + AHEAD < N_RD) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-          __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER, 0);
-        }
-#pragma unroll
-        for (int g = 0; g < G64; ++g) {
-#pragma unroll
-          for (int j = 0; j < DB; ++j) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (2 * (N_QK + g * DB + j) + AHEAD < N_RD) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER, 0);
-          }
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER, 0);
-        }
-      }
-      if (has1) asm volatile("" : "+v"(mx_raw));   // keeps the maximum chain of the next tile inside this block
-      // the loads issued at the top of the stage must have landed before anyone reads them
-      __syncthreads();
-    };
-
-    // Tile 0 alone, then two stages per trip (odd tile first) so that buffer indices
-    // and register sets stay static; after the last stage the probabilities of the
-    // last tile are still to be accumulated.
-    if (n_tiles > 1) {
-      deep_stage(Int<0>{}, Int<1>{}, Int<1>{}, Int<0>{}, 0, s_a, s_b, pf_b, pf_a);
-      int t = 1;
-      for (; t + 5 <= n_tiles; t += 2) {
-        deep_stage(Int<1>{}, Int<0>{}, Int<1>{}, Int<1>{}, t, s_b, s_a, pf_a, pf_b);
-        deep_stage(Int<0>{}, Int<0>{}, Int<1>{}, Int<1>{}, t + 1, s_a, s_b, pf_b, pf_a);
-      }
-      for (; t + 2 < n_tiles; t += 2) {
-        deep_stage(Int<1>{}, Int<0>{}, Int<1>{}, Int<0>{}, t, s_b, s_a, pf_a, pf_b);
-        deep_stage(Int<0>{}, Int<0>{}, Int<1>{}, Int<0>{}, t + 1, s_a, s_b, pf_b, pf_a);
-      }
-      if (t + 1 < n_tiles) {
-        deep_stage(Int<1>{}, Int<0>{}, Int<1>{}, Int<0>{}, t, s_b, s_a, pf_a, pf_b);
-        deep_stage(Int<0>{}, Int<0>{}, Int<0>{}, Int<0>{}, t + 1, s_a, s_b, pf_b, pf_a);
-        accumulate(Int<0>{}, pf_a);
-      } else {
-        deep_stage(Int<1>{}, Int<0>{}, Int<0>{}, Int<0>{}, t, s_b, s_a, pf_a, pf_b);
-        accumulate(Int<1>{}, pf_b);
-      }
-    } else if (n_tiles == 1) {
-      deep_stage(Int<0>{}, Int<1>{}, Int<0>{}, Int<0>{}, 0, s_a, s_b, pf_b, pf_a);
-      accumulate(Int<0>{}, pf_a);
-    }
+  } else if (n_tiles == 1) {
+    stage(even, yes, no, 0, s_a, s_b, pf_b, pf_a);
+    accumulate(even, pf_a, pf_scale);
   }
+  fold_sum();
 
   // ---- split launch: leave the chunk's state for the merge kernel (layout of the bf16 kernel) ----
   if (MODE != MODE_PBAND && it.partial) {
@@ -694,13 +644,13 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int i = 0; i < 16; ++i) dst[(db * 16 + i) * 64] = o[db][i];
-    dst[(DB * 16) * 64] = thr == kNegInf ? kNegInf : -nm[0];   // none: the row has no finite score in this chunk
-    dst[(DB * 16 + 1) * 64] = l4[0];
+    dst[(DB * 16) * 64] = top == kNegInf ? kNegInf : base_ref;   // none: the row has no finite score in this chunk
+    dst[(DB * 16 + 1) * 64] = l;
     return;
   }
 
   // ---- epilogue: O = O^T / l, bf16, lane owns query l32: 4 consecutive d per store ----
-  const float inv = 1.0f / l4[0];
+  const float inv = 1.0f / l;
   const int row = q0 + l32;
   if (row < L) {
     __bf16* dst = O + (int64_t)(MODE == MODE_PBAND ? row_map[row] : row) * p.stride_l;

@@ -201,6 +201,25 @@ def test_peaked_scores_move_the_reference(D, profile):
     check_layer_fp8(wl, q, k, v, out, slack_share=None)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("split", [0, 3])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_scores_beyond_one_base(D, split, sign):
+    """Scores that pass +-64 in units of log 2 (the reach of the accumulators' unit) several times along the keys, from
+    0 to 190 or to -190: lanes take a new unit in the middle of a list, chunks of a split list end with different ones.
+    Bars as for the other peaked profiles."""
+    L, H = 1500, 5
+    wl = W.small(L=L, D=D, H=H, seed=43)
+    q, k, v = W.make_qkv(wl)
+    gain = 190.0 / (2.0 * 1.4426950408889634 * D ** 0.5) * torch.arange(L, dtype=torch.float32) / L
+    u = torch.nn.functional.normalize(torch.ones(D), dim=0) * (D ** 0.5)
+    q = (0.3 * q.float() + 2.0 * u).to(torch.bfloat16)
+    k = (0.3 * k.float() + sign * gain[None, None, :, None] * u).to(torch.bfloat16)
+    q, k, v = _cuda([q, k, v])
+    out, _ = run_fp8(wl, q, k, v, dense_split=split)
+    check_layer_fp8(wl, q, k, v, out, slack_share=None)
+
+
 @pytest.mark.parametrize("L,D,split", [(1000, 64, 3), (1000, 128, 5), (130, 64, 8)])
 def test_dense_key_range_split(L, D, split):
     wl = W.small(L=L, D=D, H=5, seed=51, B=2)
