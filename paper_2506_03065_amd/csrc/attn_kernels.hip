@@ -248,8 +248,11 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   // The XOR swizzle is applied on the global side: the lane that fills chunk
   // slot c' of row r fetches chunk c' ^ swz(r) of that key row, so K and V use
   // different per-lane offsets.  A tile is addressed as a uniform base (scalar
-  // registers) plus those 32-bit offsets; only a ragged last tile recomputes
-  // them with the row clamped to L - 1 (those rows are masked later). ----
+  // register) plus those 32-bit offsets.  Rows past the head's last one lie past the range of
+  // its buffer, the uniform base counted in: the hardware delivers zeros (and the scores are
+  // masked), so a list's last tiles take the code of the others.  A test for a ragged tile, with
+  // rows clamped to L - 1, around every load of the last four stages of a list: 12 heads x 1,998 x 2, D = 128: 55.7 us
+  // against 53.1 without; 24 heads x 2,352, D = 128: 86.0 / 82.3; 48 x 17,550, D = 64: 530 / 522. ----
   constexpr int LPT = TILE_BYTES / (NW * 1024);   // load instructions per wave, tile and matrix
   static_assert(TILE_BYTES % (NW * 1024) == 0, "tile must split evenly over the waves");
   typedef __attribute__((address_space(3))) void* lds_ptr;
@@ -271,7 +274,6 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
                                         : (unsigned)(L - 1) * stride_bytes + (unsigned)ROW_BYTES;
   const __amdgpu_buffer_rsrc_t rsrc_k = __builtin_amdgcn_make_buffer_rsrc((void*)K, 0, (int)head_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsrc_v = __builtin_amdgcn_make_buffer_rsrc((void*)V, 0, (int)head_bytes, 0x00020000);
-  // INNER: the tile is known to lie inside [0, L) (anything but the last tile of a list)
   // Key rows through an index list.  An index read in the loop from memory would hold up
   // the tile load that needs it by a whole trip (and wait, in order, for every load in
   // flight); so the indices of a tile travel to LDS one stage ahead of its K.  -1 =
@@ -289,11 +291,9 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
                                                lane * 4 + wave * 256, index_base(t) * 4, 0, 0);
   };
   // FIRST: the prologue's loads, whose indices are read from memory
-  auto load_tile = [&](auto is_k_tag, auto inner_tag, const int buf, const int t, auto first_tag) {
+  auto load_tile = [&](auto is_k_tag, const int buf, const int t, auto first_tag) {
     constexpr bool IS_K = decltype(is_k_tag)::value != 0;
-    constexpr bool INNER = decltype(inner_tag)::value != 0;
     constexpr bool FIRST = decltype(first_tag)::value != 0;
-    const char* src_b = reinterpret_cast<const char*>(IS_K ? K : V);
     const __amdgpu_buffer_rsrc_t rsrc = IS_K ? rsrc_k : rsrc_v;
     unsigned char* dst = (IS_K ? sK : sV) + buf * TILE_BYTES + wave * (LPT * 1024);
     if (kIndirect) {
@@ -310,25 +310,10 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
       }
     } else {
       const int row0 = (kBand ? entries[t].x : t + t_base) * BC;
-      const char* base_b = src_b + (unsigned)row0 * stride_bytes;
-      if (INNER || kGathered || row0 + BC <= L) {   // gathered arrays are padded to whole tiles
 #pragma unroll
-        for (int u = 0; u < LPT; ++u)
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr)(dst + u * 1024), 16, (int)(IS_K ? g_k[u] : g_v[u]),
-                                                   (int)((unsigned)row0 * stride_bytes), 0, 0);
-      } else {
-#pragma unroll
-        for (int u = 0; u < LPT; ++u) {
-          const int byte = (wave * LPT + u) * 1024 + lane * 16;
-          int r = byte / ROW_BYTES;
-          const int slot = (byte % ROW_BYTES) >> 4;
-          const unsigned c = (unsigned)(slot ^ (IS_K ? swz_k<D>(r) : swz_v<D>(r))) * 16u;
-          r = r < L - 1 - row0 ? r : L - 1 - row0;
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr)(dst + u * 1024), 16,
-                                                   (int)((unsigned)r * stride_bytes + c),
-                                                   (int)((unsigned)row0 * stride_bytes), 0, 0);
-        }
-      }
+      for (int u = 0; u < LPT; ++u)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr)(dst + u * 1024), 16, (int)(IS_K ? g_k[u] : g_v[u]),
+                                                 (int)((unsigned)row0 * stride_bytes), 0, 0);
     }
   };
 
@@ -554,9 +539,9 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   if (n_tiles > 0) {
     if (kIndirect && n_tiles > 1) load_index(1);
     if (kIndirect && n_tiles > 2) load_index(2);
-    load_tile(Int<1>{}, Int<0>{}, 0, 0, Int<1>{});
-    load_tile(Int<0>{}, Int<0>{}, 0, 0, Int<1>{});
-    if (n_tiles > 1) load_tile(Int<1>{}, Int<0>{}, 1, 1, Int<1>{});
+    load_tile(Int<1>{}, 0, 0, Int<1>{});
+    load_tile(Int<0>{}, 0, 0, Int<1>{});
+    if (n_tiles > 1) load_tile(Int<1>{}, 1, 1, Int<1>{});
   }
   __syncthreads();
   if (n_tiles > 0) {
@@ -575,23 +560,19 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   // exponentials sit in one basic block: the matrix pipe computes the scores of
   // tile t + 1 and then O += P V of tile t while the vector pipe turns the
   // scores of tile t into P.
-  // INNER: t + 2 is not the last tile of the list.  Lists are ascending, so only
-  // their last tile can reach past L (or hold padding of a column list): an INNER
-  // stage loads without the ragged-tile test and, outside band lists, never masks.
-  auto stage = [&](auto par_tag, auto next_tag, auto inner_tag, const int t, f32x16 (&s_cur)[KB2][QB],
-                   f32x16 (&s_next)[KB2][QB]) {
+  // Lists are ascending, so only their last tile can reach past L (or hold padding of a column list).
+  auto stage = [&](auto par_tag, auto next_tag, auto inner_tag, const int t, f32x16 (&s_cur)[KB2][QB], f32x16 (&s_next)[KB2][QB]) {
     constexpr int PAR = decltype(par_tag)::value;     // t & 1
     constexpr bool has1 = decltype(next_tag)::value != 0;
-    constexpr bool INNER = decltype(inner_tag)::value != 0;
-    const bool has2 = INNER || t + 2 < n_tiles;
+    constexpr bool INNER = decltype(inner_tag)::value != 0;   // t + 2 exists
     if (kIndirect && t + 3 < n_tiles) load_index(t + 3);
-    if (has2) load_tile(Int<1>{}, inner_tag, PAR, t + 2, Int<0>{});       // K(t+2) takes the place of K(t), read in the last stage
-    if (has1) load_tile(Int<0>{}, inner_tag, PAR ^ 1, t + 1, Int<0>{});   // V(t+1) takes the place of V(t-1)
+    if (INNER || (has1 && t + 2 < n_tiles)) load_tile(Int<1>{}, PAR, t + 2, Int<0>{});       // K(t+2) takes the place of K(t), read in the last stage
+    if (has1) load_tile(Int<0>{}, PAR ^ 1, t + 1, Int<0>{});   // V(t+1) takes the place of V(t-1)
     // partly kept tile?  band lists flag it per entry; the dense and gather loops
     // can only meet one at the very end (keys past L, padding of the column list)
     bool masked;
     if (kBand) masked = !(entries[t].y & 1);
-    else if (INNER) masked = false;
+    else if (has1) masked = false;
     else if (MODE == MODE_DENSE) masked = (t + t_base + 1) * BC > L;
     else masked = (t + 1) * BC > n_cols;
     if (masked && apply_mask(s_cur, t)) tile_max(s_cur);   // the maximum taken before masking may belong to a dropped key
@@ -644,16 +625,17 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
     __syncthreads();
   };
 
-  // Two stages per trip keep buffer indices and the score registers static.
-  // The bulk of a list runs through INNER stages (t + 3 is at most the last tile
-  // but one for both stages of the trip); the generic stages finish it.
+  // Two stages per trip keep buffer indices and the score registers static.  One loop, whose second stage asks whether
+  // K(t+3) exists; at D = 128 the bulk of a list runs through a copy that knows it (long lists
+  // are 0.5 % faster for it; at D = 64 it brings nothing).
+  constexpr bool kLong = D == 128;
   int t = 0;
-  for (; t + 5 <= n_tiles; t += 2) {
+  for (; kLong && t + 3 < n_tiles; t += 2) {
     stage(Int<0>{}, Int<1>{}, Int<1>{}, t, s_a, s_b);
     stage(Int<1>{}, Int<1>{}, Int<1>{}, t + 1, s_b, s_a);
   }
   for (; t + 2 < n_tiles; t += 2) {
-    stage(Int<0>{}, Int<1>{}, Int<0>{}, t, s_a, s_b);
+    stage(Int<0>{}, Int<1>{}, Int<1>{}, t, s_a, s_b);
     stage(Int<1>{}, Int<1>{}, Int<0>{}, t + 1, s_b, s_a);
   }
   if (t + 1 < n_tiles) {
