@@ -267,16 +267,19 @@ int grid_waves(const Plan& p, const svd_plan_options* opt, int form, int n_cu) {
 
 // The same for the FP8 forward pass, always on the small query tile.  It gains more, because its pre-pass is one launch
 // too (us per layer, before / now: 37 heads x 1,104, D = 128: 140 / 44; 24 x 8,536 with text borders, D = 128: 437 /
-// 248; 48 x 17,550, D = 64: 556 / 450; 48 x 86,400, D = 64, 3,620 tiles per slot: 5,372 / 5,160).  Only dense items are
-// faster on the large tile of a launch per group (by 2 to 10 %, from one card to the next), and in a long layer the
-// partly empty rounds of the groups weigh little: 40 x 75,600, D = 128, 39 % of the tiles dense, 6,880 per slot: 7,800 /
-// 7,230 to 8,040; D = 64, 85 % dense, 5,000 per slot: 6,244 / 6,348.
+// 248; 48 x 17,550, D = 64: 556 / 450).  In long layers the partly empty rounds of the groups weigh little, but the items
+// of the table still come out more even; only layers of little else than dense heads, which are faster on the large
+// tile of a launch per group, keep that form.  Groups / table, by the dense share of the tiles, two cards:
+//   D = 128, 75,600 tokens   0.21: 3,955 / 3,810; 0.39 (40 heads): 7,170 to 7,270 / 6,900 to 7,030; 0.63: 6,429 / 6,282;
+//                            0.81: 13,189 / 12,484 to 12,610; 0.87: 17,275 / 17,451; 0.91: 24,580 / 24,920
+//   D = 128, 115,456 tokens  0.39: 7,854 to 7,982 / 7,600 to 7,694
+//   D = 64, 86,400 tokens    0.65: 6,994 / 6,829; 0.79: 11,368 / 11,017; 0.85: 15,284 / 15,223 to 15,300
 bool grid_fp8(const Plan& p, const svd_plan_options* opt, int n_cu) {
   if (n_cu < 1) return false;
   if (opt && (opt->block_q || opt->block_k || opt->dense_split || opt->single_launch)) return false;
   double dense = 0.0;
   const double tiles = svd::grid_tiles(p, svd::kernel_small_block_q(p.desc.D), &dense);
-  return tiles / (2.0 * n_cu) < 3000.0 || (p.desc.D == 64 && dense < 0.6 * tiles);
+  return tiles / (2.0 * n_cu) < 3000.0 || dense < 0.84 * tiles;
 }
 
 // The tables a plan gets.  A compute unit runs eight of the kernels' waves at a time.
