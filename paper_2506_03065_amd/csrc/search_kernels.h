@@ -22,6 +22,10 @@ size_t mse_scratch_floats(const TensorView& t);
 // mse[h] = mean over b, l, d of (a - ref)^2; two passes, fixed summation order.
 hipError_t launch_head_mse(const __bf16* a, const __bf16* ref, const TensorView& t, float* mse, float* scratch,
                            hipStream_t stream);
+// The same of four tensors against one, in one launch of each pass: mse[i * H + h] of a[i] (nullptr: a tensor of zeros).
+// scratch: 4 * mse_scratch_floats(t).  Same bits as four launches.
+hipError_t launch_head_mse4(const __bf16* const a[4], const __bf16* ref, const TensorView& t, float* mse, float* scratch,
+                            hipStream_t stream);
 
 constexpr int kMaxSelectHeads = 1024;
 // out[:, h] = src[mode_of_head[h]][:, h]; the sources share the layout `src_view`.

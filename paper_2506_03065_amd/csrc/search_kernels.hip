@@ -16,9 +16,17 @@ constexpr int kMseChunkBytes = 1 << 18;   // of one tensor, per work-group
 __device__ __forceinline__ float bf16_lo(unsigned w) { return __builtin_bit_cast(float, w << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
 
+template <int N>
+struct MseSources {
+  const __bf16* a[N];   // nullptr: zeros
+};
+
 // Pass 1: work-group (chunk, b * H + h) sums (a - ref)^2 over its share of the
-// head's L * D elements, 16 bytes per thread and step.
-__global__ void __launch_bounds__(kMseThreads) head_mse_partial_kernel(const __bf16* __restrict__ a,
+// head's L * D elements, 16 bytes per thread, tensor and step.  N = 4: the modes of the
+// search step against the dense output, which is read once for all of them, the zeros of skipped heads not at all
+// (with the lists copied ahead, 24 heads x 11,880, D = 64: the step 1,665 -> 1,638 us).
+template <int N>
+__global__ void __launch_bounds__(kMseThreads) head_mse_partial_kernel(const MseSources<N> src,
                                                                        const __bf16* __restrict__ ref,
                                                                        const TensorView t, const int n_chunks,
                                                                        float* __restrict__ partial) {
@@ -29,57 +37,82 @@ __global__ void __launch_bounds__(kMseThreads) head_mse_partial_kernel(const __b
   const int64_t per = (total + n_chunks - 1) / n_chunks;
   const int64_t g0 = (int64_t)blockIdx.x * per;
   const int64_t g1 = g0 + per < total ? g0 + per : total;
-  float acc = 0.f;
-  auto piece = [&](const int64_t g, u32x4* x, u32x4* y) {
+  float acc[N];
+#pragma unroll
+  for (int m = 0; m < N; ++m) acc[m] = 0.f;
+  struct Piece {
+    u32x4 x[N], y;
+  };
+  auto piece = [&](const int64_t g) {
+    Piece p;
     const int64_t off = base + (g / cpr) * t.stride_l + (g % cpr) * 8;
-    *x = *reinterpret_cast<const u32x4*>(a + off);
-    *y = *reinterpret_cast<const u32x4*>(ref + off);
-  };
-  auto add = [&](const u32x4& x, const u32x4& y) {
+    p.y = *reinterpret_cast<const u32x4*>(ref + off);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float d0 = bf16_lo(x[i]) - bf16_lo(y[i]), d1 = bf16_hi(x[i]) - bf16_hi(y[i]);
-      acc = __builtin_fmaf(d0, d0, acc);
-      acc = __builtin_fmaf(d1, d1, acc);
+    for (int m = 0; m < N; ++m) {
+      p.x[m] = u32x4{0u, 0u, 0u, 0u};
+      if (src.a[m]) p.x[m] = *reinterpret_cast<const u32x4*>(src.a[m] + off);
     }
+    return p;
   };
+  auto add = [&](const Piece& p) {
+#pragma unroll
+    for (int m = 0; m < N; ++m)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float d0 = bf16_lo(p.x[m][i]) - bf16_lo(p.y[i]), d1 = bf16_hi(p.x[m][i]) - bf16_hi(p.y[i]);
+        acc[m] = __builtin_fmaf(d0, d0, acc[m]);
+        acc[m] = __builtin_fmaf(d1, d1, acc[m]);
+      }
+  };
+  constexpr int U = N == 1 ? 4 : 2;   // eight to ten loads in flight per thread
   int64_t g = g0 + threadIdx.x;
-  for (; g + 3 * kMseThreads < g1; g += 4 * kMseThreads) {   // eight loads in flight per thread
-    u32x4 x[4], y[4];
+  for (; g + (U - 1) * kMseThreads < g1; g += U * kMseThreads) {
+    Piece p[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) piece(g + u * kMseThreads, &x[u], &y[u]);
+    for (int u = 0; u < U; ++u) p[u] = piece(g + u * kMseThreads);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) add(x[u], y[u]);
+    for (int u = 0; u < U; ++u) add(p[u]);
   }
-  for (; g < g1; g += kMseThreads) {
-    u32x4 x, y;
-    piece(g, &x, &y);
-    add(x, y);
-  }
+  for (; g < g1; g += kMseThreads) add(piece(g));
   // wave reduction, then the four waves through LDS, always in the same order
+  __shared__ float wave_sum[N][kMseThreads / 64];
 #pragma unroll
-  for (int s = 32; s > 0; s >>= 1) acc += __shfl_down(acc, s, 64);
-  __shared__ float wave_sum[kMseThreads / 64];
-  if ((threadIdx.x & 63) == 0) wave_sum[threadIdx.x >> 6] = acc;
+  for (int m = 0; m < N; ++m) {
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) acc[m] += __shfl_down(acc[m], s, 64);
+    if ((threadIdx.x & 63) == 0) wave_sum[m][threadIdx.x >> 6] = acc[m];
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < N) {
     float s = 0.f;
 #pragma unroll
-    for (int w = 0; w < kMseThreads / 64; ++w) s += wave_sum[w];
-    partial[(int64_t)bh * n_chunks + blockIdx.x] = s;
+    for (int w = 0; w < kMseThreads / 64; ++w) s += wave_sum[threadIdx.x][w];
+    partial[((int64_t)threadIdx.x * gridDim.y + bh) * n_chunks + blockIdx.x] = s;
   }
 }
 
-// Pass 2: one thread per head adds the partial sums of all batch entries and
+// Pass 2: one thread per (tensor, head) adds the partial sums of all batch entries and
 // chunks in double, in index order.
 __global__ void head_mse_final_kernel(const float* __restrict__ partial, const TensorView t, const int n_chunks,
-                                      float* __restrict__ mse) {
-  const int h = blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= t.H) return;
+                                      const int n_tensors, float* __restrict__ mse) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= t.H * n_tensors) return;
+  const int h = i % t.H, m = i / t.H;
   double s = 0.0;
   for (int b = 0; b < t.B; ++b)
-    for (int c = 0; c < n_chunks; ++c) s += (double)partial[((int64_t)b * t.H + h) * n_chunks + c];
-  mse[h] = (float)(s / ((double)t.B * t.L * t.D));
+    for (int c = 0; c < n_chunks; ++c) s += (double)partial[(((int64_t)m * t.B + b) * t.H + h) * n_chunks + c];
+  mse[i] = (float)(s / ((double)t.B * t.L * t.D));
+}
+
+template <int N>
+hipError_t launch_mse(const MseSources<N>& src, const __bf16* ref, const TensorView& t, float* mse, float* scratch,
+                      hipStream_t stream) {
+  const int n_chunks = mse_chunks(t);
+  hipLaunchKernelGGL(head_mse_partial_kernel<N>, dim3(n_chunks, t.B * t.H), dim3(kMseThreads), 0, stream, src, ref, t,
+                     n_chunks, scratch);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  hipLaunchKernelGGL(head_mse_final_kernel, dim3((t.H * N + 63) / 64), dim3(64), 0, stream, scratch, t, n_chunks, N, mse);
+  return hipGetLastError();
 }
 
 struct SelectArgs {
@@ -114,12 +147,12 @@ size_t mse_scratch_floats(const TensorView& t) { return (size_t)t.B * t.H * mse_
 
 hipError_t launch_head_mse(const __bf16* a, const __bf16* ref, const TensorView& t, float* mse, float* scratch,
                            hipStream_t stream) {
-  const int n_chunks = mse_chunks(t);
-  hipLaunchKernelGGL(head_mse_partial_kernel, dim3(n_chunks, t.B * t.H), dim3(kMseThreads), 0, stream, a, ref, t,
-                     n_chunks, scratch);
-  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  hipLaunchKernelGGL(head_mse_final_kernel, dim3((t.H + 63) / 64), dim3(64), 0, stream, scratch, t, n_chunks, mse);
-  return hipGetLastError();
+  return launch_mse<1>(MseSources<1>{{a}}, ref, t, mse, scratch, stream);
+}
+
+hipError_t launch_head_mse4(const __bf16* const a[4], const __bf16* ref, const TensorView& t, float* mse, float* scratch,
+                            hipStream_t stream) {
+  return launch_mse<4>(MseSources<4>{{a[0], a[1], a[2], a[3]}}, ref, t, mse, scratch, stream);
 }
 
 hipError_t launch_select_heads(const __bf16* const src[5], const TensorView& src_view, const int32_t* mode_of_head,

@@ -416,6 +416,14 @@ int mse_chunks(const TensorView& t) {
 }
 size_t mse_scratch_floats(const TensorView& t) { return (size_t)t.B * t.H * mse_chunks(t); }
 
+hipError_t launch_head_mse4(const __bf16* const*, const __bf16*, const TensorView& t, float* mse, float* scratch, hipStream_t stream) {
+  stub::note_launch(stream, "head_mse_partial_kernel");
+  touch_write(scratch, 4 * mse_scratch_floats(t) * sizeof(float), "mse partial sums", 0x66);
+  stub::note_launch(stream, "head_mse_final_kernel");
+  touch_write(mse, (size_t)4 * t.H * sizeof(float), "mse", 0x00);
+  return hipSuccess;
+}
+
 hipError_t launch_head_mse(const __bf16*, const __bf16*, const TensorView& t, float* mse, float* scratch, hipStream_t stream) {
   stub::note_launch(stream, "head_mse_partial_kernel");
   touch_write(scratch, mse_scratch_floats(t) * sizeof(float), "mse partial sums", 0x66);
