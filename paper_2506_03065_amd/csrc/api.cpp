@@ -270,7 +270,7 @@ int grid_waves(const Plan& p, const svd_plan_options* opt, int form, int n_cu) {
 // 248; 48 x 17,550, D = 64: 556 / 450).  In long layers the partly empty rounds of the groups weigh little, but the items
 // of the table still come out more even; only layers of little else than dense heads, which are faster on the large
 // tile of a launch per group, keep that form.  Groups / table, by the dense share of the tiles, two cards:
-//   D = 128, 75,600 tokens   0.21: 3,955 / 3,810; 0.39 (40 heads): 7,170 to 7,270 / 6,900 to 7,030; 0.63: 6,429 / 6,282;
+//   D = 128, 75,600 tokens   0.35: 3,955 / 3,810; 0.39 (40 heads): 7,170 to 7,270 / 6,900 to 7,030; 0.62: 6,429 / 6,282;
 //                            0.81: 13,189 / 12,484 to 12,610; 0.87: 17,275 / 17,451; 0.91: 24,580 / 24,920
 //   D = 128, 115,456 tokens  0.39: 7,854 to 7,982 / 7,600 to 7,694
 //   D = 64, 86,400 tokens    0.65: 6,994 / 6,829; 0.79: 11,368 / 11,017; 0.85: 15,284 / 15,223 to 15,300

@@ -25,8 +25,8 @@
 //                        writes K8 and V8 in the rearranged order, Q rows and O
 //                        rows go through the list's row map.
 // Operand layout of the 32x32x64 instruction: lane l supplies row (column) l % 32
-// with the 32 contraction indices 32 * (l / 32) .. + 31 in its 32 bytes; the
-// result has the layout of the 32x32 bf16 instructions, so masks, maxima and the
+// with 32 of the 64 contraction indices in its 32 bytes, the same ones in both
+// operands (all that the layouts here rely on); the result has the layout of the 32x32 bf16 instructions, so masks, maxima and the
 // epilogue are those of the bf16 kernel.  The reference is an integer: every change
 // of units is an exact power of two and the rounding of P does not depend on the
 // order of the key tiles (outside the subnormal range).
