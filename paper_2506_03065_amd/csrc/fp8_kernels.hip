@@ -640,12 +640,15 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
   if (MODE != MODE_PBAND && it.partial) {
     typedef float __attribute__((address_space(1)))* global_float_ptr;   // global stores, not FLAT ones
     global_float_ptr dst = (global_float_ptr)(uintptr_t)(it.partial + (size_t)wave * ((DB * 16 + 2) * 64) + lane);
+    // in units of the row's own reference, an exact power of two away: the units of two chunks that count alike can lie
+    // 2^128 apart, and a weight of that size is zero in fp32
+    const float to_top = top == kNegInf ? 1.0f : __builtin_amdgcn_exp2f(base_ref - top);
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) dst[(db * 16 + i) * 64] = o[db][i];
-    dst[(DB * 16) * 64] = top == kNegInf ? kNegInf : base_ref;   // none: the row has no finite score in this chunk
-    dst[(DB * 16 + 1) * 64] = l;
+      for (int i = 0; i < 16; ++i) dst[(db * 16 + i) * 64] = o[db][i] * to_top;
+    dst[(DB * 16) * 64] = top;   // -inf: the row has no finite score in this chunk
+    dst[(DB * 16 + 1) * 64] = l * to_top;
     return;
   }
 

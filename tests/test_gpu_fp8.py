@@ -220,6 +220,32 @@ def test_scores_beyond_one_base(D, split, sign):
     check_layer_fp8(wl, q, k, v, out, slack_share=None)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("split", [2, 3, 0])
+@pytest.mark.parametrize("first,rest", [(15, 7), (14, 15), (8, 7), (-7, -15)])
+def test_chunks_in_different_units(D, split, first, rest):
+    """Chunks of one row that end in different units and still count alike, by launches per group with the key range cut
+    and (split 0) by the table's chunks of two key tiles: 8 * `rest` binary orders below zero is the largest logit of
+    every chunk, 8 * `first` that of its first tile from the second chunk on.  (15, 7): those chunks take a unit of
+    2^-128 and end 64 orders above it, beside a first chunk in units of 1; a weight of 2^-128 is zero in fp32.  All
+    operands are exact in E4M3 (Q8 = -8 / D, K8 = the integers named here), half the rows have half the logits."""
+    bk = svd.svd_default_blocks(D)[1]
+    n_tiles = 16
+    L = n_tiles * bk - 11
+    starts = range(2, n_tiles, 2) if split == 0 else [n_tiles * c // split for c in range(1, split)]
+    level = torch.full((n_tiles,), float(rest))
+    level[list(starts)] = float(first)
+    wl = W.Workload("units", -1, 1, 1, L, D, 386, 5, 0, np.asarray([W.DENSE], dtype=np.int32), [{}], 83)
+    _, _, v = W.make_qkv(wl)
+    half = 0.5 + 0.5 * (torch.arange(L) % 2)
+    q = (-8.0 / D * D ** 0.5 / (4 * np.log2(np.e)) * half)[None, None, :, None].expand(1, 1, L, D).to(torch.bfloat16).contiguous()
+    k = (4.0 * level.repeat_interleave(bk)[:L])[None, None, :, None].expand(1, 1, L, D).to(torch.bfloat16).contiguous()
+    assert (F8.quantise_q(f64(q[0, 0, 1::2])) == -8.0 / D).all() and (F8.quantise_k(f64(k[0, 0]))[:, 0] == f64(k[0, 0, :, 0]) / 4).all()
+    q, k, v = _cuda([q, k, v])
+    out, _ = run_fp8(wl, q, k, v, dense_split=split)
+    check_layer_fp8(wl, q, k, v, out)
+
+
 @pytest.mark.parametrize("L,D,split", [(1000, 64, 3), (1000, 128, 5), (130, 64, 8)])
 def test_dense_key_range_split(L, D, split):
     wl = W.small(L=L, D=D, H=5, seed=51, B=2)
