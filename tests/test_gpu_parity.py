@@ -204,6 +204,56 @@ def test_band_edges_in_every_place_of_a_block(L, D, w):
     check_layer(wl, q, k, v, run_planned(wl, q, k, v))
 
 
+@pytest.mark.parametrize("layout", ["bhld", "blhd"])
+@pytest.mark.parametrize("L,D", [(1, 64), (77, 128), (449, 64), (449, 128), (1000, 64), (1001, 128), (1930, 64)])
+@pytest.mark.parametrize("options", [{}, {"single_launch": 2}, {"single_launch": 2, "dense_split": 3}, {"single_launch": 1}],
+                         ids=["table", "groups", "split", "layer"])
+def test_rows_behind_the_last_one_are_not_read(layout, L, D, options):
+    """Q, K, V and O as views of larger storage in which every row behind a head's last one holds NaN: a key row past the
+    end is no row of the tensor for the loads of a ragged last tile either (a masked probability of 0 times NaN is NaN)."""
+    wl = W.small(L=L, D=D, H=5, seed=57, B=2)
+    pad = 192
+    views = []
+    for t in W.make_qkv(wl) + [torch.full((wl.B, wl.H, L, D), float("nan"), dtype=torch.bfloat16)]:
+        store = torch.full((wl.B, wl.H, L + pad, D) if layout == "bhld" else (wl.B, L + pad, wl.H, D), float("nan"),
+                           dtype=torch.bfloat16, device=DEV)
+        view = store[:, :, :L] if layout == "bhld" else store[:, :L].permute(0, 2, 1, 3)
+        view.copy_(t)
+        views.append((store, view))
+    (_, q), (_, k), (_, v), (out_store, out) = views
+    desc = svd.desc_of(q)
+    ws = torch.empty(svd.svd_plan_workspace_bytes(desc, wl.strategy_table, wl.pattern_params, **options), dtype=torch.uint8, device=DEV)
+    plan = svd.svd_plan_create(desc, wl.strategy_table, wl.pattern_params, workspace=ws, **options)
+    svd.svd_attn_forward_planned(plan, q, k, v, out)
+    torch.cuda.synchronize()
+    plan.close()
+    check_layer(wl, q, k, v, out)
+    behind = out_store[:, :, L:] if layout == "bhld" else out_store[:, L:]
+    assert torch.isnan(behind).all(), "a row behind the last one was written"
+
+
+@pytest.mark.parametrize("D,options", [(64, {}), (128, {}), (128, {"single_launch": 1})])
+def test_rows_behind_the_last_one_past_32_bits(D, options):
+    """The largest row stride: the last row starts below byte 2^32 of its head, the rows that fill its key tile lie past
+    it.  All storage between and behind the rows (mapped, and as far as those rows reach) holds NaN."""
+    L, rows_of_tiles, H = 1985, 2048, 3
+    stride = (2 ** 32 - 1) // L // 16 * 8
+    assert L * stride * 2 < 2 ** 32 < (rows_of_tiles - 1) * stride * 2
+    wl = W.small(L=L, D=D, H=H, seed=58)   # dense, diagonal, multi-diagonal
+    store = torch.full((rows_of_tiles * stride + 16 * 128,), float("nan"), dtype=torch.bfloat16, device=DEV)
+    q, k, v, out = (torch.as_strided(store, (1, H, L, D), (H * 128, 128, stride, 1), i * H * 128) for i in range(4))
+    for view, t in zip((q, k, v), W.make_qkv(wl)):
+        view.copy_(t)
+    desc = svd.desc_of(q)
+    ws = torch.empty(svd.svd_plan_workspace_bytes(desc, wl.strategy_table, wl.pattern_params, **options), dtype=torch.uint8, device=DEV)
+    plan = svd.svd_plan_create(desc, wl.strategy_table, wl.pattern_params, workspace=ws, **options)
+    svd.svd_attn_forward_planned(plan, q, k, v, out)
+    torch.cuda.synchronize()
+    plan.close()
+    check_layer(wl, q, k, v, out, rows=np.asarray([0, 1, 127, 128, 993, 1856, 1919, 1920, 1983, 1984]))
+    del store
+
+
 @pytest.mark.parametrize("L,D,split", [(1000, 64, 2), (1000, 64, 3), (1000, 128, 5), (777, 128, 8), (130, 64, 8),
                                        (60, 128, 4)])
 def test_dense_key_range_split(L, D, split):
