@@ -633,7 +633,7 @@ static void build_layer_segments(svd_plan* sp) {
 }
 
 // First half of a plan's creation, on the host: the compiled lists, the launch form and the workspace it needs.  device =
-// false: a plan for inspection only.  fp8 = false: a plan that no FP8 pass can reach (the one-shot call's, the search step's),
+// false: a plan for inspection only.  fp8 = false: a plan that no FP8 pass can reach (the one-shot calls', the search step's),
 // without a table for it (24 heads x 115,456: 3.2 ms with, 1.8 ms without).
 static svd_status compile_for(svd_plan** plan, const svd_tensor_desc* desc, const int32_t* strategy_table,
                               const svd_head_params* pattern_params, const svd_plan_options* options, bool device, bool fp8 = true) {
@@ -1295,26 +1295,22 @@ svd_status sparse_vdit_attn_forward_static(const void* q, const void* k, const v
     // The launch form and the split of the dense heads are the library's choice unless their partial results do not fit
     // the buffer: then without a table of items (whose cut items have some), then with the dense heads unsplit.
     svd_plan_options opt{};
-    size_t need = 0;
-    if (svd_status st = svd_plan_workspace_bytes(desc, strategy_table, pattern_params, &opt, &need)) return st;
-    if (need > scratch_bytes) {
-      int bq = 0, bk = 0;
-      svd::kernel_blocks(desc->D, &bq, &bk);
-      const int form = layer_form(nullptr, *desc, true, device_compute_units(),
-                                  mean_tiles_per_item(*desc, strategy_table, pattern_params, bk, 0));
-      opt.single_launch = form ? form : 2;
-      if (svd_status st = svd_plan_workspace_bytes(desc, strategy_table, pattern_params, &opt, &need)) return st;
-    }
-    if (need > scratch_bytes) {
-      opt.single_launch = 0;
-      opt.dense_split = 1;
-      if (svd_status st = svd_plan_workspace_bytes(desc, strategy_table, pattern_params, &opt, &need)) return st;
-    }
-    if (need > scratch_bytes) return SVD_ERR_STATIC_LIMIT;
     svd_plan* fresh = nullptr;
-    if (svd_status st = create_plan(&fresh, desc, strategy_table, pattern_params, &opt, scratch, scratch_bytes,
-                                    hip_stream, false))
+    for (int attempt = 0; attempt < 3; ++attempt) {
+      if (attempt == 1) opt.single_launch = fresh->form ? fresh->form : 2;
+      if (attempt == 2) opt.single_launch = 0, opt.dense_split = 1;
+      delete fresh;
+      if (svd_status st = compile_for(&fresh, desc, strategy_table, pattern_params, &opt, true, false)) return st;
+      if (fresh->workspace_bytes <= scratch_bytes) break;
+    }
+    if (fresh->workspace_bytes > scratch_bytes) {
+      delete fresh;
+      return SVD_ERR_STATIC_LIMIT;
+    }
+    if (svd_status st = attach_workspace(fresh, &opt, scratch, scratch_bytes, hip_stream, false)) {
+      delete fresh;
       return st;
+    }
     if (c.plan) svd_plan_destroy(c.plan);
     c.plan = fresh;
     c.desc = *desc;

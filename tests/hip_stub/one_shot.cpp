@@ -158,6 +158,31 @@ int main(int argc, char** argv) {
     expect(st == SVD_OK, "static one-shot call", st);
     expect(stub::launches_of("combine_partials_kernel") > merges && stub::launches_of("attn_grid_kernel") == tables, "the dense head runs split");
   }
+  {
+    // nothing of an FP8 pass, which these calls do not have, counts against that buffer: a layer that fits it with its own
+    // table and would not fit it with a second one for FP8 keeps its table
+    stub::set_tensor_checks(false);
+    constexpr int N = 27;
+    svd_tensor_desc s{};
+    s.B = 1, s.H = N, s.L = 40000, s.D = 64;
+    s.stride_l = s.D, s.stride_h = int64_t(s.L) * s.D, s.stride_b = s.stride_h * s.H;
+    int32_t table[N];
+    std::vector<int32_t> many(s.L);
+    for (int c = 0; c < s.L; ++c) many[c] = c;
+    svd_head_params sp[N] = {};
+    for (int h = 0; h < N; ++h) table[h] = h < 7 ? SVD_VSTRIPE : SVD_DIAG, sp[h].half_width = 60, sp[h].cols = many.data();
+    size_t need = 0;
+    for (int n = 128 * 280; need <= SVD_STATIC_SCRATCH_BYTES && n <= s.L; n += 128) {   // the shortest lists that are too long with both
+      for (int h = 0; h < 7; ++h) sp[h].n_cols = n;
+      expect(svd_plan_workspace_bytes(&s, table, sp, nullptr, &need) == SVD_OK, "svd_plan_workspace_bytes");
+    }
+    expect(need > SVD_STATIC_SCRATCH_BYTES, "a layer that does not fit with both tables");
+    const long tables = stub::launches_of("attn_grid_kernel");
+    stub::new_forward();
+    const int st = sparse_vdit_attn_forward_static(t[0], t[1], t[2], table, sp, t[3], &s, nullptr);
+    expect(st == SVD_OK, "static one-shot call near the buffer's limit", st);
+    expect(stub::launches_of("attn_grid_kernel") > tables, "the layer runs from its table");
+  }
   std::printf("%d violations, %d failures\n", stub::violations(), g_failures);
   return stub::violations() || g_failures ? 1 : 0;
 }
