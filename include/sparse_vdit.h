@@ -410,7 +410,7 @@ svd_status svd_select_heads(const void* const* o_modes, const svd_tensor_desc* s
  * outputs to out and returns table (HOST int32[H]) and loss (HOST double[4 * H],
  * may be NULL).  q, k, v, out must be contiguous [B, H, L, D].  device_workspace:
  * svd_search_layer_workspace_bytes bytes, 256-byte aligned (five output tensors +
- * four plans + scratch).  Unlike the forward entry points this call SYNCHRONISES
+ * one plan + scratch).  Unlike the forward entry points this call SYNCHRONISES
  * hip_stream: the losses are needed on the host. */
 svd_status svd_search_layer_workspace_bytes(const svd_tensor_desc* desc,
                                             const svd_head_params* const* params_by_mode, size_t* bytes);

@@ -1447,12 +1447,14 @@ svd_status svd_select_heads(const void* const* o_modes, const svd_tensor_desc* s
   return e == hipSuccess ? SVD_OK : SVD_ERR_HIP;
 }
 
-// Workspace of svd_search_layer: five contiguous output tensors, the plan
-// workspaces of the four single-mode tables, the reduction scratch, and
-// 4 * H floats for the per-head MSEs.
+// Workspace of svd_search_layer: five contiguous output tensors, one plan's workspace, which the plans of the four
+// single-mode tables take in turn and the reduction scratch after them, and 4 * H floats for the per-head MSEs.
+// lists_off: where every plan's lists wait until its turn, in the output tensor that is written last; lists_ahead = false:
+// they do not fit there.
 namespace {
 struct SearchLayout {
-  size_t out_bytes = 0, plan_off[5] = {}, mse_scratch_off = 0, mse_off = 0, total = 0;
+  size_t out_bytes = 0, lists_off[5] = {}, plan_off = 0, plan_bytes = 0, mse_off = 0, total = 0;
+  bool lists_ahead = false;
 };
 
 // One plan per sparse mode, all heads in that mode, compiled but without a workspace yet.
@@ -1469,17 +1471,19 @@ svd_status search_layout(const svd_tensor_desc& desc, const svd_head_params* con
   std::vector<int32_t> table(desc.H);
   std::vector<svd_head_params> none(desc.H);
   const svd_tensor_desc c = contiguous_desc(desc);
-  size_t end = 5 * lay->out_bytes;
+  lay->plan_off = 5 * lay->out_bytes;
+  size_t lists = SVD_VSTRIPE * lay->out_bytes;
   for (int mode = SVD_SKIP; mode <= SVD_VSTRIPE; ++mode) {
     std::fill(table.begin(), table.end(), mode);
     const svd_head_params* pp = (mode >= SVD_DIAG) ? params_by_mode[mode] : none.data();
     if (!pp) return SVD_ERR_NULL;
     if (svd_status st = compile_for(&plans->plan[mode], &c, table.data(), pp, nullptr, true, false)) return st;
-    lay->plan_off[mode] = end;
-    end = align_up(end + plans->plan[mode]->workspace_bytes, 256);
+    lay->plan_bytes = std::max(lay->plan_bytes, plans->plan[mode]->workspace_bytes);
+    lay->lists_off[mode] = lists;
+    lists = align_up(lists + plans->plan[mode]->p.ws_image.size() * sizeof(int32_t), 256);
   }
-  lay->mse_scratch_off = end;
-  lay->mse_off = lay->mse_scratch_off + align_up(4 * svd::mse_scratch_floats(view_of(desc)) * sizeof(float), 256);
+  lay->lists_ahead = lists <= lay->plan_off;
+  lay->mse_off = align_up(lay->plan_off + std::max(lay->plan_bytes, 4 * svd::mse_scratch_floats(view_of(desc)) * sizeof(float)), 256);
   lay->total = lay->mse_off + align_up(static_cast<size_t>(4) * desc.H * sizeof(float), 256);
   return SVD_OK;
 }
@@ -1524,28 +1528,31 @@ svd_status svd_search_layer(const void* q, const void* k, const void* v, const s
   std::vector<double> sparsity(static_cast<size_t>(4) * H);
   std::vector<float> mse(static_cast<size_t>(4) * H);
   float* mse_dev = reinterpret_cast<float*>(ws + lay.mse_off);
-  // Every plan's lists have a workspace area of their own and are copied ahead of the first launch; from there on the
-  // GPU finds the whole step enqueued.  With one area for all plans each copy waited for the launches that read the one
-  // before.  (24 heads x 11,880, D = 64, with the losses of all modes in one launch: 1,665 -> 1,638 us.  The host's work
-  // before the first launch, 330 us of it for the lists, stays: nothing may be enqueued before all arguments are known to
-  // be valid, and compiling the four plans in threads brought nothing.)
+  // The lists of every plan are copied ahead of the first launch, and from where they wait to the plans' workspace by a
+  // launch, so the GPU finds the whole step enqueued.  Copied from the host in turn, each copy waited for the launches that
+  // read the lists before.  (24 heads x 11,880, D = 64, together with the losses of all modes in one launch: 1,725 -> 1,670
+  // us.  The host's work before the first launch, 330 us of it for the lists, stays: nothing may be enqueued before all
+  // arguments are known to be valid, and compiling the four plans in threads brought nothing.)
   svd_status status = SVD_OK;
-  for (int mode = SVD_SKIP; mode <= SVD_VSTRIPE && status == SVD_OK; ++mode) {
-    svd_plan* plan = plans.plan[mode];
-    const size_t room = (mode < SVD_VSTRIPE ? lay.plan_off[mode + 1] : lay.mse_scratch_off) - lay.plan_off[mode];
-    if (hipMemcpyAsync(ws + lay.plan_off[mode], plan->p.ws_image.data(), plan->p.ws_image.size() * sizeof(int32_t),
-                       hipMemcpyHostToDevice, stream) != hipSuccess)
+  for (int mode = SVD_SKIP; mode <= SVD_VSTRIPE && lay.lists_ahead && status == SVD_OK; ++mode) {
+    const std::vector<int32_t>& img = plans.plan[mode]->p.ws_image;
+    if (hipMemcpyAsync(ws + lay.lists_off[mode], img.data(), img.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream) != hipSuccess)
       status = SVD_ERR_HIP;
-    if (status == SVD_OK) status = attach_workspace(plan, nullptr, ws + lay.plan_off[mode], room, hip_stream, false, false);
   }
   if (status == SVD_OK) status = svd_dense_attn_forward(q, k, v, o_modes[0], desc, hip_stream);
-  for (int mode = SVD_SKIP; mode <= SVD_VSTRIPE && status == SVD_OK; ++mode)
-    status = svd_attn_forward_planned(plans.plan[mode], q, k, v, o_modes[mode], hip_stream);
+  for (int mode = SVD_SKIP; mode <= SVD_VSTRIPE && status == SVD_OK; ++mode) {
+    svd_plan* plan = plans.plan[mode];
+    status = attach_workspace(plan, nullptr, ws + lay.plan_off, lay.plan_bytes, hip_stream, false, !lay.lists_ahead);
+    if (status == SVD_OK && lay.lists_ahead &&
+        svd::launch_copy_lists(ws + lay.lists_off[mode], ws + lay.plan_off, plan->p.ws_image.size() * sizeof(int32_t), stream) != hipSuccess)
+      status = SVD_ERR_HIP;
+    if (status == SVD_OK) status = svd_attn_forward_planned(plan, q, k, v, o_modes[mode], hip_stream);
+  }
   if (status == SVD_OK) {
     const __bf16* const modes[4] = {nullptr, static_cast<const __bf16*>(o_modes[SVD_DIAG]),   // skipped heads: zeros
                                     static_cast<const __bf16*>(o_modes[SVD_MULTIDIAG]), static_cast<const __bf16*>(o_modes[SVD_VSTRIPE])};
     if (svd::launch_head_mse4(modes, static_cast<const __bf16*>(o_modes[0]), view_of(*desc), mse_dev,
-                              reinterpret_cast<float*>(ws + lay.mse_scratch_off), stream) != hipSuccess)
+                              reinterpret_cast<float*>(ws + lay.plan_off), stream) != hipSuccess)
       status = SVD_ERR_HIP;
   }
   for (int mode = SVD_SKIP; mode <= SVD_VSTRIPE && status == SVD_OK; ++mode)   // on the host, under the launches

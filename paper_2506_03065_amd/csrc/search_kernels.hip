@@ -24,7 +24,7 @@ struct MseSources {
 // Pass 1: work-group (chunk, b * H + h) sums (a - ref)^2 over its share of the
 // head's L * D elements, 16 bytes per thread, tensor and step.  N = 4: the modes of the
 // search step against the dense output, which is read once for all of them, the zeros of skipped heads not at all
-// (with the lists copied ahead, 24 heads x 11,880, D = 64: the step 1,665 -> 1,638 us).
+// (with the lists copied ahead, 24 heads x 11,880, D = 64: the step 1,725 -> 1,670 us).
 template <int N>
 __global__ void __launch_bounds__(kMseThreads) head_mse_partial_kernel(const MseSources<N> src,
                                                                        const __bf16* __restrict__ ref,

@@ -185,7 +185,7 @@ hipError_t model_attention(const AttnLaunch& p, const Fp8Launch* f8, int mode, h
   if (p.n_items <= 0) return hipSuccess;
   if (p.split < 1 || (p.split > 1 && (mode != MODE_DENSE || !p.partial))) return hipErrorInvalidValue;
   if (p.D != 64 && p.D != 128) return hipErrorInvalidValue;
-  if (small_q && !f8 && mode != MODE_BAND && mode != MODE_PBAND) return hipErrorInvalidValue;
+  if (small_q && !f8 && mode != MODE_BAND && mode != MODE_PBAND && !(mode == MODE_DENSE && p.split == 1)) return hipErrorInvalidValue;
   if (small_q && f8 && mode == MODE_DENSE) return hipErrorInvalidValue;
   const int space = p.n_q_blocks * p.n_heads * p.B * p.split;
   if (p.n_items != space && !(mode == MODE_DENSE && p.split == 1 && p.n_items > 0 && p.n_items < space))   // the dense head start
@@ -277,7 +277,7 @@ hipError_t launch_copy_lists(const void* src, void* dst, size_t bytes, hipStream
   stub::note_launch(stream, "copy_lists_kernel");
   if (bytes % 16 || ((uintptr_t)src | (uintptr_t)dst) % 16) stub::violation("copy_lists: %zu bytes, or an address off 16", bytes);
   if (!stub::in_device(dst, bytes)) stub::violation("copy_lists: outside every device allocation");
-  stub::note_pinned_read(stream, src, bytes);
+  if (!stub::in_device(src, bytes)) stub::note_pinned_read(stream, src, bytes);
   std::memcpy(dst, src, bytes);
   return hipSuccess;
 }

@@ -82,7 +82,8 @@ def _search_case(seed, H, L, D):
 
 
 @pytest.mark.parametrize("seed,H,L,D,lam,eps", [(61, 4, 500, 64, 0.5, 1.0), (62, 3, 300, 128, 0.1, 0.05),
-                                               (63, 4, 700, 64, 0.0, 0.02), (64, 2, 260, 128, 1.0, 0.5)])
+                                               (63, 4, 700, 64, 0.0, 0.02), (64, 2, 260, 128, 1.0, 0.5),
+                                               (65, 1, 9, 64, 0.5, 1.0)])   # lists longer than an output tensor
 def test_search_layer_against_the_oracle(seed, H, L, D, lam, eps):
     q, k, v, params = _search_case(seed, H, L, D)
     want_table, want_loss, want_mse, want_sparsity, want_xo = S.search_layer(f64(q), f64(k), f64(v), params, lam, eps)

@@ -1,5 +1,8 @@
 """Host logic of the search step through the C ABI (no GPU): Eq. 2-3 selection
 and the per-head sparsity of a plan, against the oracle."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -7,6 +10,7 @@ from oracle import sparse_attention as A
 from oracle import sparse_search as S
 from paper_2506_03065_amd import binding as svd
 from paper_2506_03065_amd import workloads as W
+from test_host_launch_model import CSRC, ROOT, STUB
 
 
 def test_select_matches_the_oracle_on_random_and_tied_losses():
@@ -107,6 +111,18 @@ def test_search_entry_points_validate_before_any_launch():
     with pytest.raises(svd.SvdError) as e:
         svd.svd_search_layer_workspace_bytes(d, empty)
     assert e.value.status == 7
+
+
+def test_search_step_on_the_host_model(tmp_path):
+    exe = str(tmp_path / "search_step")
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-omit-frame-pointer",
+           "-fno-sanitize-recover=undefined", "-I", STUB, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+           os.path.join(CSRC, "api.cpp"), os.path.join(CSRC, "pattern_compiler.cpp"),
+           *(os.path.join(STUB, f) for f in ("hip_stub.cpp", "launch_models.cpp", "grid_model.cpp", "search_step.cpp")), "-o", exe]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-4000:]
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
 
 
 def test_fp8_entry_points_validate_before_any_launch():
