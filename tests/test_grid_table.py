@@ -105,6 +105,14 @@ def test_a_table_that_cannot_be_built_leaves_no_trace(tmp_path):
     assert res.returncode == 0, (res.returncode, res.stdout)
 
 
+def test_a_long_plan_is_compiled_in_memory_reserved_once(tmp_path):
+    exe = str(tmp_path / "plan_memory")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", STUB, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                    os.path.join(CSRC, "pattern_compiler.cpp"), os.path.join(STUB, "plan_memory.cpp"), "-o", exe], check=True)
+    res = subprocess.run([exe], capture_output=True, text=True)
+    assert res.returncode == 0, (res.returncode, res.stdout)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("mode", [W.DENSE, W.DIAG, W.MULTIDIAG, W.VSTRIPE])
