@@ -155,7 +155,8 @@ typedef struct {
  * (head, query tile, key range) its record in the workspace names, long items cut
  * into chunks that a second launch merges; most layers run that way, the long
  * D = 128 ones through the layer kernel, the longest D = 64 ones group by group.
- * svd_attn_forward_fp8 may run from a table of its own, with one pre-pass for all
+ * svd_attn_forward_fp8 may run from a table of its own (a long layer's plan that is given
+ * a workspace too small for that table alone does without), with one pre-pass for all
  * heads, whatever the form of the bf16 pass (svd_plan_table tells which pass does;
  * svd_plan_single_launch keeps reporting the form named above); where it does not, it
  * runs group by group.  The split of the dense heads is chosen in any case and its

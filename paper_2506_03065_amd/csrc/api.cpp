@@ -65,6 +65,7 @@ struct svd_plan {
   svd::GridTable grid_table{};
   bool grid8 = false;              // the FP8 forward pass runs from a table too, on the small query tile
   svd::GridTable grid8_table{};
+  bool grid8_optional = false;     // a workspace without room for that table is taken all the same (long layers)
   size_t grid_partial_offset = 0;
   ~svd_plan() {
     for (int i = 0; i < kSideStreams; ++i) {
@@ -274,18 +275,21 @@ int grid_waves(const Plan& p, const svd_plan_options* opt, int form, int n_cu) {
 //                            0.81: 13,189 / 12,484 to 12,610; 0.87: 17,275 / 17,451; 0.91: 24,580 / 24,920
 //   D = 128, 115,456 tokens  0.39: 7,854 to 7,982 / 7,600 to 7,694
 //   D = 64, 86,400 tokens    0.65: 6,994 / 6,829; 0.79: 11,368 / 11,017; 0.85: 15,284 / 15,223 to 15,300
-bool grid_fp8(const Plan& p, const svd_plan_options* opt, int n_cu) {
+// optional: a long layer, which only gains those 2 to 5 % from the table.
+bool grid_fp8(const Plan& p, const svd_plan_options* opt, int n_cu, bool* optional) {
+  *optional = false;
   if (n_cu < 1) return false;
   if (opt && (opt->block_q || opt->block_k || opt->dense_split || opt->single_launch)) return false;
   double dense = 0.0;
   const double tiles = svd::grid_tiles(p, svd::kernel_small_block_q(p.desc.D), &dense);
-  return tiles / (2.0 * n_cu) < 3000.0 || dense < 0.84 * tiles;
+  *optional = tiles / (2.0 * n_cu) >= 3000.0;
+  return !*optional || dense < 0.84 * tiles;
 }
 
 // The tables a plan gets.  A compute unit runs eight of the kernels' waves at a time.
 struct GridTables {
   int waves = 0;                    // of the bf16 forward pass
-  bool bf16 = false, fp8 = false;
+  bool bf16 = false, fp8 = false, fp8_optional = false;
   svd::GridTable table, table8;
   size_t partial_bytes = 0;         // partial results of cut items (the two passes do not overlap)
 };
@@ -293,7 +297,7 @@ GridTables add_grid_tables(Plan* p, const svd_plan_options* opt, int form, int n
   GridTables g;
   g.waves = grid_waves(*p, opt, form, n_cu);
   if (g.waves) g.bf16 = svd::build_grid_table(p, g.waves * 32, 8 / g.waves * n_cu, true, &g.table);
-  if (fp8 && grid_fp8(*p, opt, n_cu)) {
+  if (fp8 && grid_fp8(*p, opt, n_cu, &g.fp8_optional)) {
     bool stripes = false;
     for (const svd::Group& gr : p->groups) stripes = stripes || gr.mode == SVD_VSTRIPE;
     if (g.bf16 && g.waves == 4 && !(stripes && p->text_tokens > 0)) {
@@ -670,6 +674,7 @@ static svd_status compile_for(svd_plan** plan, const svd_tensor_desc* desc, cons
       sp->grid_table = grid.table;
       sp->grid8 = grid.fp8;
       sp->grid8_table = grid.table8;
+      sp->grid8_optional = grid.fp8 && grid.fp8_optional;
       sp->workspace_bytes = workspace_need(sp->p, sp->dense_split, native ? n_cu : 0, &sp->partial_offset, &sp->text_split,
                                            &sp->text_partial_offset, sp->form != 0, &sp->counters_offset, &sp->gather_offset,
                                            grid.partial_bytes, &sp->grid_partial_offset);
@@ -740,6 +745,10 @@ static svd_status create_plan(svd_plan** plan, const svd_tensor_desc* desc,
                               size_t workspace_bytes, void* hip_stream, bool with_side_streams) {
   if (svd_status st = compile_for(plan, desc, strategy_table, pattern_params, options, device_workspace != nullptr)) return st;
   if (!device_workspace) return SVD_OK;
+  if ((*plan)->grid8_optional && workspace_bytes < (*plan)->workspace_bytes) {   // without the FP8 table, if that fits
+    delete *plan;
+    if (svd_status st = compile_for(plan, desc, strategy_table, pattern_params, options, true, false)) return st;
+  }
   const svd_status st = attach_workspace(*plan, options, device_workspace, workspace_bytes, hip_stream, with_side_streams);
   if (st != SVD_OK) {
     delete *plan;

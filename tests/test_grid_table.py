@@ -105,6 +105,18 @@ def test_a_table_that_cannot_be_built_leaves_no_trace(tmp_path):
     assert res.returncode == 0, (res.returncode, res.stdout)
 
 
+def test_a_workspace_without_room_for_an_optional_table(tmp_path):
+    exe = str(tmp_path / "small_workspace")
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-omit-frame-pointer",
+           "-fno-sanitize-recover=undefined", "-I", STUB, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+           os.path.join(CSRC, "api.cpp"), os.path.join(CSRC, "pattern_compiler.cpp"),
+           *(os.path.join(STUB, f) for f in ("hip_stub.cpp", "launch_models.cpp", "grid_model.cpp", "small_workspace.cpp")), "-o", exe]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-4000:]
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+
+
 def test_a_long_plan_is_compiled_in_memory_reserved_once(tmp_path):
     exe = str(tmp_path / "plan_memory")
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", STUB, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
