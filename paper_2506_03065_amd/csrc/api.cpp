@@ -469,15 +469,19 @@ int stage_lists(OneShot* c, const std::vector<int32_t>& img) {
   return n;
 }
 
+// The plan's lists to device memory, from where they are (pageable memory) and in stream order.
+bool copy_lists(const Plan& p, void* to, hipStream_t stream, bool wait) {
+  return hipMemcpyAsync(to, p.ws_image.data(), p.ws_image.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream) == hipSuccess &&
+         (!wait || hipStreamSynchronize(stream) == hipSuccess);
+}
+
 // Copies the plan's lists to its workspace, ahead of the launches that `stream` gets next.
 svd_status upload_lists(OneShot* c, hipStream_t stream) {
   const std::vector<int32_t>& img = c->plan->p.ws_image;
   const size_t bytes = img.size() * sizeof(int32_t);
   void* to = c->plan->p.device_workspace;
   if (c->slot < 0) c->slot = stage_lists(c, img);
-  if (c->slot < 0)
-    return hipMemcpyAsync(to, img.data(), bytes, hipMemcpyHostToDevice, stream) == hipSuccess &&
-                   hipStreamSynchronize(stream) == hipSuccess ? SVD_OK : SVD_ERR_HIP;
+  if (c->slot < 0) return copy_lists(c->plan->p, to, stream, true) ? SVD_OK : SVD_ERR_HIP;
   StagedLists& s = c->slots[c->slot];
   // on another stream than the last time: one event covers both copies only if they are in order
   if (s.pending && s.stream != stream && hipStreamWaitEvent(stream, s.copied, 0) != hipSuccess) return SVD_ERR_HIP;
@@ -696,10 +700,7 @@ static svd_status attach_workspace(svd_plan* sp, const svd_plan_options* options
                                    size_t workspace_bytes, void* hip_stream, bool with_side_streams, bool copy = true) {
   if (workspace_bytes < sp->workspace_bytes || !aligned16(device_workspace)) return SVD_ERR_WORKSPACE;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (copy && (hipMemcpyAsync(device_workspace, sp->p.ws_image.data(), sp->p.ws_image.size() * sizeof(int32_t),
-                              hipMemcpyHostToDevice, stream) != hipSuccess ||
-               hipStreamSynchronize(stream) != hipSuccess))
-    return SVD_ERR_HIP;
+  if (copy && !copy_lists(sp->p, device_workspace, stream, true)) return SVD_ERR_HIP;
   const svd_tensor_desc& desc = sp->p.desc;
   const bool single = sp->form != 0;
   sp->p.device_workspace = device_workspace;
@@ -1543,11 +1544,8 @@ svd_status svd_search_layer(const void* q, const void* k, const void* v, const s
   // us.  The host's work before the first launch, 330 us of it for the lists, stays: nothing may be enqueued before all
   // arguments are known to be valid, and compiling the four plans in threads brought nothing.)
   svd_status status = SVD_OK;
-  for (int mode = SVD_SKIP; mode <= SVD_VSTRIPE && lay.lists_ahead && status == SVD_OK; ++mode) {
-    const std::vector<int32_t>& img = plans.plan[mode]->p.ws_image;
-    if (hipMemcpyAsync(ws + lay.lists_off[mode], img.data(), img.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream) != hipSuccess)
-      status = SVD_ERR_HIP;
-  }
+  for (int mode = SVD_SKIP; mode <= SVD_VSTRIPE && lay.lists_ahead && status == SVD_OK; ++mode)
+    if (!copy_lists(plans.plan[mode]->p, ws + lay.lists_off[mode], stream, false)) status = SVD_ERR_HIP;
   if (status == SVD_OK) status = svd_dense_attn_forward(q, k, v, o_modes[0], desc, hip_stream);
   for (int mode = SVD_SKIP; mode <= SVD_VSTRIPE && status == SVD_OK; ++mode) {
     svd_plan* plan = plans.plan[mode];

@@ -256,7 +256,6 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   constexpr int LPT = TILE_BYTES / (NW * 1024);   // load instructions per wave, tile and matrix
   static_assert(TILE_BYTES % (NW * 1024) == 0, "tile must split evenly over the waves");
   typedef __attribute__((address_space(3))) void* lds_ptr;
-  typedef __attribute__((address_space(1))) const void* glb_ptr;
   const unsigned stride_bytes = kGathered ? (unsigned)ROW_BYTES : (unsigned)p.stride_l * 2u;   // of a key row
   unsigned g_k[LPT], g_v[LPT];   // byte offset inside the tile; kIndirect: chunk offset inside the row
   unsigned g_r[LPT];             // kIndirect: 4 * row of the slab's lane inside the tile

@@ -453,7 +453,8 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
     l = fmaf(l4[0], l_scale, l);
     l4[0] = 0.f;
   };
-  auto settle = [&](f32x16 (&s)[KB2], int* const prev_scale) -> int {
+  int pf_scale = 127;   // of the probabilities still to be accumulated
+  auto settle = [&](f32x16 (&s)[KB2]) -> int {
     fold_sum();
     top = fmaxf(top, tile_ref);
     float e = top;
@@ -464,10 +465,8 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
       const float shift = far ? top - base_ref : 0.f;
       base_ref += shift;
       const float alpha = shift > 0.f ? __builtin_amdgcn_exp2f(-shift) : 1.0f;   // shift < 0: the lane's first kept key
-      if (prev_scale) {
-        const int moved = *prev_scale - (int)shift;
-        *prev_scale = moved < 0 ? 0 : (moved > 254 ? 254 : moved);
-      }
+      const int moved = pf_scale - (int)shift;
+      pf_scale = moved < 0 ? 0 : (moved > 254 ? 254 : moved);
       l *= alpha;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
@@ -546,7 +545,6 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
   // 40 heads x 75,600, D = 128: 7.64 -> 7.11 ms; 24 heads x 8,536, D = 128: 230 -> 199 us. ----
   f32x16 s_a[KB2], s_b[KB2];
   i32x8 pf_a[G64], pf_b[G64];
-  int pf_scale = 127;   // of the probabilities still to be accumulated
   // FIRST: t = 0, nothing to accumulate yet.  NEXT: a tile t + 1 exists, so outside band lists nothing of tile t
   // can be masked.
   auto stage = [&](auto par_tag, auto first_tag, auto next_tag, const int t, f32x16 (&s_cur)[KB2], f32x16 (&s_next)[KB2],
@@ -559,7 +557,7 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
     if (kBand) masked = !(entries[t].y & 1);
     else masked = !NEXT && (t + t_base + 1) * BC > n_keys;
     if (masked && apply_mask(s_cur, t)) tile_max(s_cur);
-    const int scale = settle(s_cur, &pf_scale);
+    const int scale = settle(s_cur);
     if (NEXT) scores(Int<PAR ^ 1>{}, s_next);
     if (!FIRST) accumulate(Int<PAR ^ 1>{}, pf_prev, pf_scale);
     exponentiate(s_cur, pf_cur, scale);
