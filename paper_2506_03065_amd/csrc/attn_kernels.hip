@@ -242,7 +242,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
     for (int i = 0; i < 8; ++i) sum_a[i] = v;
   }
 
-  // ---- tile loader: direct global -> LDS loads (global_load_lds_dwordx4: 16 bytes
+  // ---- tile loader: direct global -> LDS loads (buffer_load_dwordx4 with the LDS bit: 16 bytes
   // per lane, a wave instruction fills 1 KB of LDS linearly from a uniform base,
   // no staging registers).  Wave w fills the slabs w*LPT .. w*LPT+LPT-1 of a tile.
   // The XOR swizzle is applied on the global side: the lane that fills chunk
@@ -251,8 +251,9 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   // register) plus those 32-bit offsets.  Rows past the head's last one lie past the range of
   // its buffer, the uniform base counted in: the hardware delivers zeros (and the scores are
   // masked), so a list's last tiles take the code of the others.  A test for a ragged tile, with
-  // rows clamped to L - 1, around every load of the last four stages of a list: 12 heads x 1,998 x 2, D = 128: 55.7 us
-  // against 53.1 without; 24 heads x 2,352, D = 128: 86.0 / 82.3; 48 x 17,550, D = 64: 530 / 522. ----
+  // rows clamped to L - 1, around every load of the last four stages of a list, one plan run again and again: 12 heads x
+  // 1,998 x 2, D = 128: 55.7 us against 53.1 without; 24 heads x 2,352, D = 128: 86.0 / 82.3; 48 x 17,550, D = 64:
+  // 530 / 522. ----
   constexpr int LPT = TILE_BYTES / (NW * 1024);   // load instructions per wave, tile and matrix
   static_assert(TILE_BYTES % (NW * 1024) == 0, "tile must split evenly over the waves");
   typedef __attribute__((address_space(3))) void* lds_ptr;
@@ -554,7 +555,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
 
   // One pipeline stage.  On entry s_cur holds the raw scores of tile t; LDS holds
   // K(t+1) in K buffer (t+1)&1 and V(t) in V buffer t&1, while K(t+2) and V(t+1)
-  // travel global -> registers -> LDS.  NEXT: 1 = a tile t + 1 is known
+  // travel global -> LDS.  NEXT: 1 = a tile t + 1 is known
   // to exist, 0 = tile t is the last one.  With NEXT the two products and the
   // exponentials sit in one basic block: the matrix pipe computes the scores of
   // tile t + 1 and then O += P V of tile t while the vector pipe turns the

@@ -163,9 +163,9 @@ void model_item(const AttnLaunch& p, const Fp8Launch* f8, int mode, bool small_q
       int row = tile * BC + r;
       if (mode == MODE_GATHER || mode == MODE_PBAND) {
         row = read_word(map + row, "column list / row map");
-        row = row < 0 ? 0 : row;
-      } else {
-        row = row < L ? row : L - 1;
+        if (row < 0) continue;   // padding: past the buffer's range, zeros
+      } else if (row >= L) {
+        continue;                // a ragged last tile: past the head's last row, zeros
       }
       if (row >= L) {
         stub::violation("key row %d outside [0, %d)", row, L);

@@ -9,6 +9,7 @@ from oracle import sparse_attention as O
 from paper_2506_03065_amd import binding as svd
 from paper_2506_03065_amd import workloads as W
 from parity_util import MAX_ABS, MAX_OVER_RMS, MEAN_ABS, REL_L2, assert_close, f64
+from test_gpu_parity import band_edges_layer
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -218,6 +219,24 @@ def test_scores_beyond_one_base(D, split, sign):
     q, k, v = _cuda([q, k, v])
     out, _ = run_fp8(wl, q, k, v, dense_split=split)
     check_layer_fp8(wl, q, k, v, out, slack_share=None)
+
+
+@pytest.mark.parametrize("L,D", [(449, 64), (449, 128), (640, 128)])
+@pytest.mark.parametrize("w", [0, 1, 15, 16, 31, 32, 33, 64, 100, 127, 128, 130])
+def test_band_edges_in_every_place_of_a_block(L, D, w):
+    """The masks of the bands that the bf16 test of this name walks, in the FP8 loop's own copy.  Queries of zero: every
+    kept key has the same P, and a row is the mean of its keys' V8, whatever the rounding of scores.  bf16, 8 significant
+    bits, rounds a result by up to 2^-8 of itself, and the matrix instruction, which keeps 2^-12 of the largest
+    product in a sum of 64, moves a mean by max |V8| * 2^-12 / 64 < 2^-15.  One key too many or too few moves some element
+    of a row by 14 times the bar or more (from the masks and values, on the CPU)."""
+    wl = band_edges_layer(L, D, w)
+    _, k, v = _cuda(W.make_qkv(wl))
+    out, _ = run_fp8(wl, torch.zeros_like(k), k, v)
+    for h in range(wl.H):
+        mask = O.allowed_mask(int(wl.strategy_table[h]), wl.pattern_params[h], L, np.arange(L)).astype(np.float64)
+        want = mask @ F8.quantise_v(f64(v[0, h])) / mask.sum(axis=1, keepdims=True)
+        got = f64(out[0, h])
+        assert (np.abs(got - want) <= 2.0 ** -8 * np.abs(want) + 2.0 ** -14).all(), (h, np.abs(got - want).max())
 
 
 @pytest.mark.parametrize("D", [64, 128])

@@ -188,18 +188,23 @@ def test_peaked_scores_move_the_softmax_reference(D, profile):
     check_layer(wl, q, k, v, out)
 
 
-@pytest.mark.parametrize("L,D", [(449, 64), (449, 128), (640, 128)])
-@pytest.mark.parametrize("w", [0, 1, 15, 16, 31, 32, 33, 64, 100, 127, 128, 130])
-def test_band_edges_in_every_place_of_a_block(L, D, w):
-    """Bands whose edges cross the 32 x 32 blocks of a tile one at a time, both in one block (2 w + 1 < 32), on a
-    block's border, and together with the end of the sequence: one diagonal head, one with several bands, and the
-    same band shifted off the diagonal so that only its lower or only its upper edge lies inside the sequence."""
+def band_edges_layer(L, D, w):
     far = L - 1 - w // 2
     params = [{"half_width": w}, {"half_width": w, "offsets": (-3 * w - 40, 0, 3 * w + 40)},
               {"half_width": max(w, far // 2), "offsets": (far // 2, 0)}, {"half_width": max(w, far // 2), "offsets": (0, -far // 2)}]
     wl = W.small(L=L, D=D, H=4, seed=53)
     wl.strategy_table = np.asarray([W.DIAG, W.MULTIDIAG, W.MULTIDIAG, W.MULTIDIAG], dtype=np.int32)
     wl.pattern_params = [dict(p, offsets=p.get("offsets", ()), cols=()) for p in params]
+    return wl
+
+
+@pytest.mark.parametrize("L,D", [(449, 64), (449, 128), (640, 128)])
+@pytest.mark.parametrize("w", [0, 1, 15, 16, 31, 32, 33, 64, 100, 127, 128, 130])
+def test_band_edges_in_every_place_of_a_block(L, D, w):
+    """Bands whose edges cross the 32 x 32 blocks of a tile one at a time, both in one block (2 w + 1 < 32), on a
+    block's border, and together with the end of the sequence: one diagonal head, one with several bands, and the
+    same band shifted off the diagonal so that only its lower or only its upper edge lies inside the sequence."""
+    wl = band_edges_layer(L, D, w)
     q, k, v = _cuda(W.make_qkv(wl))
     check_layer(wl, q, k, v, run_planned(wl, q, k, v))
 
