@@ -1,7 +1,7 @@
 // gfx950 (MI355X, CDNA4) kernels of the FP8 variant of the sparse attention
 // forward (Appendix B: the sparse kernels of Section 4.2 with FP8 quantisation).
 //
-// The paper names neither format nor recipe; this build quantises Q, K, V and P
+// The paper names neither format nor recipe; this library quantises Q, K, V and P
 // to OCP E4M3 with fixed power-of-two scales:
 //   Q8 = e4m3(q * 4 log2(e) / sqrt(D)),  K8 = e4m3(k / 4),  V8 = e4m3(v),
 //   P8 = e4m3(2^(Q8.K8 - m)) with the integer reference m = ceil(row max) - 8,
@@ -26,8 +26,9 @@
 //                        rows go through the list's row map.
 // Operand layout of the 32x32x64 instruction: lane l supplies row (column) l % 32
 // with 32 of the 64 contraction indices in its 32 bytes, the same ones in both
-// operands (all that the layouts here rely on); the result has the layout of the 32x32 bf16 instructions, so masks, maxima and the
-// epilogue are those of the bf16 kernel.  The reference is an integer: every change
+// operands (all that the layouts here rely on); the result has the layout of the
+// 32x32 bf16 instructions, so masks, maxima and the epilogue are those of the bf16
+// kernel.  The reference is an integer: every change
 // of units is an exact power of two and the rounding of P does not depend on the
 // order of the key tiles (outside the subnormal range).
 #include <hip/hip_runtime.h>
@@ -537,12 +538,12 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
   // the stage that produces them it would wait for all of them).  On entry LDS holds
   // K(t+1) and V(t-1); K(t+2) and V(t) are requested.  One barrier a stage: two stages to a
   // barrier on rings of four slots measured 3 to 5 % slower at both head sizes.
-  // What bounds it: long lists run at the power limit (40 heads of 75,600 tokens: the
-  // same instructions on zeros take 6.1 ms, on normal inputs 7.4); there a wave's tile at D = 128 takes
-  // 990 cycles, 486 of them on the vector pipe and 544 on the matrix pipe.  Short lists are
+  // What bounds it: long lists run at the power limit (40 heads of 75,600 tokens, from the table: 7.0
+  // ms on normal inputs, 5.6 on zeros, the same instructions with no bits that toggle); a wave's tile
+  // at D = 128 asks for 486 cycles of the vector pipe and 544 of the matrix pipe.  Short lists are
   // bound by the vector pipe and what surrounds the loop.  Against a loop two tiles deep whose
-  // reference moved scores and accumulators: 48 heads x 17,550, D = 64: 457 -> 400 us;
-  // 40 heads x 75,600, D = 128: 7.64 -> 7.11 ms; 24 heads x 8,536, D = 128: 230 -> 199 us. ----
+  // reference moved scores and accumulators: 48 heads x 17,550, D = 64: 457 -> 400 us; 24 heads x
+  // 8,536, D = 128: 230 -> 199 us; 40 heads x 75,600, D = 128, a launch per group: 7.64 -> 7.11 ms. ----
   f32x16 s_a[KB2], s_b[KB2];
   i32x8 pf_a[G64], pf_b[G64];
   // FIRST: t = 0, nothing to accumulate yet.  NEXT: a tile t + 1 exists, so outside band lists nothing of tile t

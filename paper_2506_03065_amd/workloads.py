@@ -7,7 +7,7 @@ callers of the HIP library use.
 
 Shapes follow Section 5.1 (tokens per frame, frame counts, text prefix) and the
 frame-major token order of Section 4.1.1; the widths, column counts and the mix
-of modes per layer are this build's stand-ins for the constants the paper only
+of modes per layer are this module's stand-ins for the constants the paper only
 shows in a figure.  The tensors stand in for the post-RoPE/Norm Q, K, V of
 CogVideoX1.5, HunyuanVideo and Wan2.1 on VBench / Penguin prompts, which are
 not available here.

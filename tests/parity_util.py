@@ -10,7 +10,7 @@ from paper_2506_03065_amd import binding as svd
 # oracle.  With N(0,1) inputs the outputs of long heads are small, so two
 # scale-free gates are added per head: relative L2 error <= 1e-2 and
 # max abs error <= 8e-2 * rms(reference) + 1e-3.  Where the 8e-2 comes from:
-# the precision this build specifies (bf16 pre-scaled Q, bf16 P, bf16 output,
+# the precision this library specifies (bf16 pre-scaled Q, bf16 P, bf16 output,
 # everything else exact), carried out on the CPU, already deviates from the
 # exact definition by up to 6.6 % of a head's rms on a single element of a
 # narrow-band head (tests/test_tolerance_derivation.py, which also holds the

@@ -1,6 +1,6 @@
 """Where the per-head relative gate of the bf16 parity tests comes from (parity_util.MAX_OVER_RMS).
 
-The precision reading of this build (the paper states none): bf16 inputs, Q multiplied by log2(e)/sqrt(D) and
+The precision reading of this library (the paper states none): bf16 inputs, Q multiplied by log2(e)/sqrt(D) and
 rounded back to bf16, scores and softmax in fp32, P rounded to bf16 before PV, fp32 accumulation, bf16 output.
 This test carries that arithmetic out on the CPU (numpy float64 between the roundings, no blocking, exact row
 maximum) for the narrow-band heads that gave the largest deviations in a sweep of random layers, and compares it
