@@ -1541,7 +1541,7 @@ svd_status svd_search_layer(const void* q, const void* k, const void* v, const s
   // The lists of every plan are copied ahead of the first launch, and from where they wait to the plans' workspace by a
   // launch, so the GPU finds the whole step enqueued.  Copied from the host in turn, each copy waited for the launches that
   // read the lists before.  (24 heads x 11,880, D = 64, together with the losses of all modes in one launch: 1,725 -> 1,670
-  // us.  The host's work before the first launch, 330 us of it for the lists, stays: nothing may be enqueued before all
+  // us.  The host's work before the first launch, 90 us of it for the lists, stays: nothing may be enqueued before all
   // arguments are known to be valid, and compiling the four plans in threads brought nothing.)
   svd_status status = SVD_OK;
   for (int mode = SVD_SKIP; mode <= SVD_VSTRIPE && lay.lists_ahead && status == SVD_OK; ++mode)
