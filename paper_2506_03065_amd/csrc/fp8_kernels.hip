@@ -268,7 +268,9 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
   // Softmax state.  top: the integer reference ceil(row max so far) - 8 of the lane's
   // query, -inf until the lane has seen its first kept key.  Accumulators and row sums
   // are in units of 2^base; base stays 0 unless a reference leaves +-kReach around it.
-  constexpr float kHeadroom = 8.0f, kReach = 64.0f;
+  // kReach: 2^(reach + 8) a probability, 2^9 a value, 2^24 keys stay below 2^127, and the smallest product
+  // that counts, 2^(-reach - 18), above 2^-126.
+  constexpr float kHeadroom = 8.0f, kReach = 80.0f;
   f32x16 o[DB];
   f32x4 l4;
   float top = kNegInf, base_ref = 0.f, tile_ref = kNegInf;
@@ -459,10 +461,10 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
     fold_sum();
     top = fmaxf(top, tile_ref);
     float e = top;
-    if (based || __builtin_amdgcn_ballot_w64(fabsf(top) > kReach && top != kNegInf) != 0) {
-      // Scores beyond what exp2 and the accumulators hold in units of 1: the lane moves its base to the reference.
+    const bool far = fabsf(top - base_ref) > kReach && top != kNegInf;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(far) != 0, 0)) {
+      // Scores beyond what exp2 and the accumulators hold in units of 2^base: the lane moves its base to the reference.
       based = true;
-      const bool far = fabsf(top - base_ref) > kReach && top != kNegInf;
       const float shift = far ? top - base_ref : 0.f;
       base_ref += shift;
       const float alpha = shift > 0.f ? __builtin_amdgcn_exp2f(-shift) : 1.0f;   // shift < 0: the lane's first kept key
@@ -473,6 +475,12 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
       for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
+    }
+    if (__builtin_expect(based, 0)) {
+      // A base that has moved once stays for most tiles, and those pay for this alone.  (40 heads x 75,600, D = 128, logits
+      // of up to 140 binary orders: 8.2 ms where they paid for the accumulators too, 7.35 so; of up to 9: 7.1 / 7.1.  A
+      // reference in the seed of the scores, 16 registers that all other inputs would pay for, spares them this too where
+      // a head's logits share one large offset: all at -150: 7.1 ms so, 6.7 with a seed.)
 #pragma unroll
       for (int kb2 = 0; kb2 < KB2; ++kb2)
 #pragma unroll

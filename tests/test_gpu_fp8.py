@@ -206,8 +206,8 @@ def test_peaked_scores_move_the_reference(D, profile):
 @pytest.mark.parametrize("split", [0, 3])
 @pytest.mark.parametrize("sign", [1.0, -1.0])
 def test_scores_beyond_one_base(D, split, sign):
-    """Scores that pass +-64 in units of log 2 (the reach of the accumulators' unit) several times along the keys, from
-    0 to 190 or to -190: lanes take a new unit in the middle of a list, chunks of a split list end with different ones.
+    """Scores that pass +-80 in units of log 2 (the reach of the accumulators' unit) along the keys, from 0 to 190 or to
+    -190: lanes take a new unit in the middle of a list, chunks of a split list end with different ones.
     Bars as for the other peaked profiles."""
     L, H = 1500, 5
     wl = W.small(L=L, D=D, H=H, seed=43)
