@@ -244,10 +244,11 @@ def test_band_edges_in_every_place_of_a_block(L, D, w):
 @pytest.mark.parametrize("first,rest", [(15, 7), (14, 15), (8, 7), (-7, -15)])
 def test_chunks_in_different_units(D, split, first, rest):
     """Chunks of one row that end in different units and still count alike, by launches per group with the key range cut
-    and (split 0) by the table's chunks of two key tiles: 8 * `rest` binary orders below zero is the largest logit of
-    every chunk, 8 * `first` that of its first tile from the second chunk on.  (15, 7): those chunks take a unit of
-    2^-128 and end 64 orders above it, beside a first chunk in units of 1; a weight of 2^-128 is zero in fp32.  All
-    operands are exact in E4M3 (Q8 = -8 / D, K8 = the integers named here), half the rows have half the logits."""
+    and (split 0) by the table's chunks of two key tiles.  8 * `first` binary orders below zero is the logit of the first
+    key tile of every chunk but the first, 8 * `rest` that of all other tiles.  (15, 7): those chunks take a unit of 2^-128
+    and end 64 orders above it, beside a first chunk in units of 1; a weight of 2^-128 is zero in fp32.  (14, 15) and
+    (-7, -15): units other than 1 on both sides, taken at once or in the second tile; (8, 7): none.  All operands are exact
+    in E4M3 (Q8 = -8 / D, K8 = the integers named here), half the rows have half the logits."""
     bk = svd.svd_default_blocks(D)[1]
     n_tiles = 16
     L = n_tiles * bk - 11
