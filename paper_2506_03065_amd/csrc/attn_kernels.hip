@@ -352,13 +352,15 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   };
 
   // ---- masks: element (kb2, i) of a lane is key kb2*32 + (i/4)*8 + half*4 + i%4 ----
-  // Returns false when nothing was changed (the wave's part of the tile is kept
-  // as a whole).  Band tiles: a wave first classifies each of its 32 x 32 blocks
-  // against the run with wave-uniform arithmetic; only blocks that a band edge
-  // (or the end of the sequence) actually crosses are masked element by element, one
-  // comparison with a literal per element and edge (both ends of the run in one test: a
-  // subtraction more per element and a copy of the block; 48 heads x 86,400, D = 64: 7.26 ->
-  // 7.21 ms; 12 heads x 1,998 x 2, D = 128: 57.6 -> 55.7 us).
+  // Returns false when nothing was changed (the wave's part of the tile is kept as a whole).
+  // Band tiles: the elements of a lane ascend with their keys, so a run of kept diagonals keeps a
+  // range of them: one bit per element in a word or two per lane, then a sign-extended bit and a
+  // bitwise select per element, in place, whatever the number of runs and edges.  (A classification
+  // of every 32 x 32 block, with a comparison and a conditional move per element in the blocks that
+  // an edge crosses, issues no more vector instructions, but its branches cost copies of the
+  // scores where they meet: 1,500 cycles a masked tile at D = 128 where a whole tile takes 2,200, and
+  // 30 KB of code per mode.  Band heads of 81 diagonals around five offsets, 24 heads x 1,998, D = 128:
+  // 50.8 -> 47.6 us; a layer of 12 heads x 1,998 x 2: 46.7 -> 40.0; 4 x 1,024, D = 64: 13.2 -> 11.9.)
   auto apply_mask = [&](f32x16 (&s)[KB2][QB], const int t) -> bool {
     bool changed = false;
     if (kBand) {
@@ -366,59 +368,47 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
       const int kv0 = ent.x * BC;
       const int r0 = (ent.y >> 1) & 0x7fff, rn = ent.y >> 16;
       const int qw0 = __builtin_amdgcn_readfirstlane(q0);
+      const i32x2 first = runs[r0];
 #pragma unroll
-      for (int kb2 = 0; kb2 < KB2; ++kb2) {
+      for (int qb = 0; qb < QB; ++qb) {
+        const int dmin = kv0 - (qw0 + qb * 32) - 31, dmax = kv0 + BC - 1 - (qw0 + qb * 32);   // diagonals the wave's part touches
+        if (dmin >= first.x && dmax <= first.y && kv0 + BC <= L) continue;   // kept as a whole
+        changed = true;
+        constexpr int WORDS = KB2 / 2;
+        unsigned kept[WORDS];
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-          const int jb0 = kv0 + kb2 * 32;                      // first key of the block
-          const int dmin = jb0 - (qw0 + qb * 32) - 31, dmax = dmin + 62;   // diagonals the block touches
-          if (rn == 1) {
-            const i32x2 run = runs[r0];
-            if (dmin >= run.x && dmax <= run.y && jb0 + 31 < L) continue;   // kept as a whole
-            changed = true;
-            if (dmax < run.x || dmin > run.y || jb0 >= L) {                    // dropped as a whole
+        for (int w = 0; w < WORDS; ++w) kept[w] = 0u;
+        const int iq = q0 + qb * 32 + l32;
+        const int rel = kv0 + half * 4 - iq;   // diagonal of the lane's element 0
+        i32x2 run = first;
+        for (int r = r0;;) {
+          // elements whose keys lie below x: (x / 8) * 4 + min(x % 8, 4)
+          int lo = run.x - rel, hi = (run.y < L - 1 - iq ? run.y : L - 1 - iq) - rel + 1;
+          lo = lo < 0 ? 0 : (lo > BC ? BC : lo);
+          hi = hi < 0 ? 0 : (hi > BC ? BC : hi);
+          lo = (lo >> 3) * 4 + ((lo & 7) < 4 ? (lo & 7) : 4);
+          hi = (hi >> 3) * 4 + ((hi & 7) < 4 ? (hi & 7) : 4);
 #pragma unroll
-              for (int i = 0; i < 16; ++i) s[kb2][qb][i] = kNegInf;
-              continue;
+          for (int w = 0; w < WORDS; ++w) {
+            int nl = lo - 32 * w, nh = hi - 32 * w;
+            if (WORDS > 1) {
+              nl = nl < 0 ? 0 : (nl > 32 ? 32 : nl);
+              nh = nh < 0 ? 0 : (nh > 32 ? 32 : nh);
             }
+            kept[w] |= (unsigned)((1ull << nh) - 1) & ~(unsigned)((1ull << nl) - 1);
           }
-          changed = true;
-          const int iq = q0 + qb * 32 + l32;
-          const int jb = jb0 + half * 4;   // key of element 0
-          if (rn == 1) {   // one edge of a run, seldom both: each is one comparison with a literal per element
-            const i32x2 run = runs[r0];
-            if (dmin < run.x) {
-              const int lo = run.x - (jb - iq);
-#pragma unroll
-              for (int i = 0; i < 16; ++i) s[kb2][qb][i] = (i / 4) * 8 + (i % 4) < lo ? kNegInf : s[kb2][qb][i];
-            }
-            if (dmax > run.y || jb0 + 31 >= L) {
-              const int hi = (run.y < L - 1 - iq ? run.y : L - 1 - iq) - (jb - iq);
-#pragma unroll
-              for (int i = 0; i < 16; ++i) s[kb2][qb][i] = (i / 4) * 8 + (i % 4) > hi ? kNegInf : s[kb2][qb][i];
-            }
-            continue;
-          }
-          f32x16 kept;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) kept[i] = kNegInf;
-          for (int r = r0; r < r0 + rn; ++r) {
-            const i32x2 run = runs[r];
-            // kept iff run.x <= j - iq <= run.y and j < L
-            int hi = run.y;
-            hi = hi < L - 1 - iq ? hi : L - 1 - iq;
-            const int t0 = jb - iq - run.x;
-            const unsigned span = (unsigned)(hi - run.x);    // wraps when nothing is kept: tested below
-            if (hi >= run.x) {
-#pragma unroll
-              for (int i = 0; i < 16; ++i) {
-                const unsigned d = (unsigned)(t0 + (i / 4) * 8 + (i % 4));
-                kept[i] = d <= span ? s[kb2][qb][i] : kept[i];
-              }
-            }
-          }
-          s[kb2][qb] = kept;
+          if (++r >= r0 + rn) break;
+          run = runs[r];
         }
+#pragma unroll
+        for (int kb2 = 0; kb2 < KB2; ++kb2)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int m = __builtin_amdgcn_sbfe((int)kept[kb2 / 2], (kb2 % 2) * 16 + i, 1);
+            const float score = s[kb2][qb][i];   // a scalar first: bit_cast of a vector element misreads element 0
+            const int x = __builtin_bit_cast(int, score);
+            s[kb2][qb][i] = __builtin_bit_cast(float, (x & m) | (__builtin_bit_cast(int, kNegInf) & ~m));
+          }
       }
     } else {
       // dense: keys past L in the last tile; gather: padding of the column list

@@ -356,77 +356,62 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
   };
 
   // ---- masks: element (kb2, i) of a lane is key kb2*32 + (i/4)*8 + half*4 + i%4 ----
-  // Returns false when nothing was changed.  Band tiles: a wave first classifies
-  // each of its 32 x 32 blocks against the run with wave-uniform arithmetic; only
-  // blocks that a band edge (or the end of the sequence) crosses are masked
-  // element by element.
+  // Returns false when nothing was changed.  Band tiles: a bit per element for the range of
+  // elements that each run of kept diagonals keeps, as in the bf16 kernel (against a classification of
+  // every 32 x 32 block with a comparison per element, 48 heads x 17,550, D = 64: 397 -> 383 us; 12 heads x 5,805 behind a
+  // text prefix, D = 128: 84 -> 70.5; 40 heads x 75,600, D = 128: 7.14 -> 6.86 ms).
   auto apply_mask = [&](f32x16 (&s)[KB2], const int t) -> bool {
-    bool changed = false;
     if (kBand) {
       const i32x2 ent = entries[t];
       const int kv0 = ent.x * BC;
       const int r0 = (ent.y >> 1) & 0x7fff, rn = ent.y >> 16;
       const int qw0 = __builtin_amdgcn_readfirstlane(q0);
+      i32x2 run = runs[r0];
+      const int dmin = kv0 - qw0 - 31, dmax = kv0 + BC - 1 - qw0;   // diagonals the wave's part touches
+      if (dmin >= run.x && dmax <= run.y && kv0 + BC <= L) return false;   // kept as a whole
+      constexpr int WORDS = KB2 / 2;
+      unsigned kept[WORDS];
 #pragma unroll
-      for (int kb2 = 0; kb2 < KB2; ++kb2) {
-        const int jb0 = kv0 + kb2 * 32;
-        const int dmin = jb0 - qw0 - 31, dmax = dmin + 62;
-        if (rn == 1) {
-          const i32x2 run = runs[r0];
-          if (dmin >= run.x && dmax <= run.y && jb0 + 31 < L) continue;
-          changed = true;
-          if (dmax < run.x || dmin > run.y || jb0 >= L) {
+      for (int w = 0; w < WORDS; ++w) kept[w] = 0u;
+      const int iq = q0 + l32;
+      const int rel = kv0 + half * 4 - iq;   // diagonal of the lane's element 0
+      for (int r = r0;;) {
+        // elements whose keys lie below x: (x / 8) * 4 + min(x % 8, 4)
+        int lo = run.x - rel, hi = (run.y < L - 1 - iq ? run.y : L - 1 - iq) - rel + 1;
+        lo = lo < 0 ? 0 : (lo > BC ? BC : lo);
+        hi = hi < 0 ? 0 : (hi > BC ? BC : hi);
+        lo = (lo >> 3) * 4 + ((lo & 7) < 4 ? (lo & 7) : 4);
+        hi = (hi >> 3) * 4 + ((hi & 7) < 4 ? (hi & 7) : 4);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[kb2][i] = kNegInf;
-            continue;
+        for (int w = 0; w < WORDS; ++w) {
+          int nl = lo - 32 * w, nh = hi - 32 * w;
+          if (WORDS > 1) {
+            nl = nl < 0 ? 0 : (nl > 32 ? 32 : nl);
+            nh = nh < 0 ? 0 : (nh > 32 ? 32 : nh);
           }
+          kept[w] |= (unsigned)((1ull << nh) - 1) & ~(unsigned)((1ull << nl) - 1);
         }
-        changed = true;
-        const int iq = q0 + l32;
-        const int jb = jb0 + half * 4;
-        if (rn == 1) {   // one edge of a run, seldom both: each is one comparison with a literal per element
-          const i32x2 run = runs[r0];
-          if (dmin < run.x) {
-            const int lo = run.x - (jb - iq);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) s[kb2][i] = (i / 4) * 8 + (i % 4) < lo ? kNegInf : s[kb2][i];
-          }
-          if (dmax > run.y || jb0 + 31 >= L) {
-            const int hi = (run.y < L - 1 - iq ? run.y : L - 1 - iq) - (jb - iq);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) s[kb2][i] = (i / 4) * 8 + (i % 4) > hi ? kNegInf : s[kb2][i];
-          }
-          continue;
-        }
-        f32x16 kept;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) kept[i] = kNegInf;
-        for (int r = r0; r < r0 + rn; ++r) {
-          const i32x2 run = runs[r];
-          int hi = run.y;
-          hi = hi < L - 1 - iq ? hi : L - 1 - iq;
-          const int t0 = jb - iq - run.x;
-          const unsigned span = (unsigned)(hi - run.x);
-          if (hi >= run.x) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-              const unsigned d = (unsigned)(t0 + (i / 4) * 8 + (i % 4));
-              kept[i] = d <= span ? s[kb2][i] : kept[i];
-            }
-          }
-        }
-        s[kb2] = kept;
+        if (++r >= r0 + rn) break;
+        run = runs[r];
       }
+#pragma unroll
+      for (int kb2 = 0; kb2 < KB2; ++kb2)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int m = __builtin_amdgcn_sbfe((int)kept[kb2 / 2], (kb2 % 2) * 16 + i, 1);
+          const float score = s[kb2][i];   // a scalar first: bit_cast of a vector element misreads element 0
+          const int x = __builtin_bit_cast(int, score);
+          s[kb2][i] = __builtin_bit_cast(float, (x & m) | (__builtin_bit_cast(int, kNegInf) & ~m));
+        }
     } else {
       const int limit = n_keys - (t + t_base) * BC - half * 4;
-      changed = true;
 #pragma unroll
       for (int kb2 = 0; kb2 < KB2; ++kb2)
 #pragma unroll
         for (int i = 0; i < 16; ++i)
           s[kb2][i] = kb2 * 32 + (i / 4) * 8 + (i % 4) < limit ? s[kb2][i] : kNegInf;
     }
-    return changed;
+    return true;
   };
 
   auto tile_max = [&](const f32x16 (&s)[KB2]) {
