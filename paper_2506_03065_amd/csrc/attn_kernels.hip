@@ -136,16 +136,27 @@ struct Item {
   float* partial;           // split item: where its unnormalised result goes, else nullptr
 };
 
-// Bytes of LDS a work-group needs: two K and two V tiles, and a ring of the key rows of four
-// tiles for the modes that reach them through an index list.
-constexpr int body_lds(int D, int BC) { return 4 * BC * D * 2 + 4 * BC * 4; }
+// LDS of a work-group: two K and two V tiles, and a ring of the key rows of four tiles for the
+// modes that reach them through an index list.  Five objects and not one, so that the compiler
+// can tell a transposing read of one V tile from the tile loads into the other buffers: out of
+// one array every stage waited, before the first of its V reads, after a third of its MFMAs, for the
+// loads that it had requested itself.  (42 heads x 32,760, D = 128: 2,596 -> 2,551 us; 40 heads x
+// 75,600, 18 of them dense, layer kernel: 43.56 -> 42.90 ms; short layers the same.)
+enum { LDS_K0, LDS_K1, LDS_V0, LDS_V1, LDS_INDEX };
+template <int D, int BC, int PART>
+__device__ __forceinline__ unsigned char* lds_part() {
+  __shared__ __attribute__((aligned(16))) unsigned char part[PART == LDS_INDEX ? 4 * BC * 4 : BC * D * 2];
+  return part;
+}
 
-// Everything a work-group does between picking the item and storing its rows.  smem:
-// body_lds(D, BC) bytes of LDS, 16-byte aligned.  Every wave of the work-group calls it
+// Everything a work-group does between picking the item and storing its rows.  K, V: first rows
+// of the item's head (or of its gathered arrays).  Every wave of the work-group calls it
 // with the same item; a return leaves no wave behind at a barrier (all returns are
 // work-group uniform).
 template <int D, int NW, int QB, int BC, int OCC, int MODE>
-__device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, unsigned char* const smem) {
+__device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, const __bf16* const K, const __bf16* const V,
+                                          unsigned char* const k0, unsigned char* const k1, unsigned char* const v0,
+                                          unsigned char* const v1, unsigned char* const sI) {
   constexpr bool kBand = MODE == MODE_BAND || MODE == MODE_PBAND;        // walks a CSR list of key tiles
   constexpr bool kIndirect = MODE == MODE_PBAND || MODE == MODE_COLS;   // key rows come through an index list
   constexpr bool kGathered = MODE == MODE_GATHER;  // K and V are the group's gathered rows: a short dense head
@@ -160,9 +171,8 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   constexpr int TILE_BYTES = BC * D * 2;
   constexpr int ROW_BYTES = D * 2;
 
-  unsigned char* const sK = smem;                    // [2][BC][D] bf16, swizzled
-  unsigned char* const sV = smem + 2 * TILE_BYTES;   // [2][BC][D] bf16, swizzled
-  unsigned char* const sI = smem + 4 * TILE_BYTES;   // [4][BC] key rows, slot = tile & 3 (kIndirect)
+  unsigned char* const sK[2] = {k0, k1};   // each [BC][D] bf16, swizzled
+  unsigned char* const sV[2] = {v0, v1};   // sI: [4][BC] key rows, slot = tile & 3 (kIndirect)
 
   const int qblk = it.qblk, head = it.head, b = it.b;
   const int n_tiles = it.n_tiles, t_base = it.t_base, n_cols = it.n_cols;
@@ -177,8 +187,6 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
 
   const int64_t base = (int64_t)b * p.stride_b + (int64_t)head * p.stride_h;
   const __bf16* __restrict__ Q = p.q + base;
-  const __bf16* __restrict__ K = kGathered ? it.gathered : p.k + base;
-  const __bf16* __restrict__ V = kGathered ? K + (size_t)p.gather_pad * D : p.v + base;
   __bf16* __restrict__ O = p.out + base;
   const int L = p.L;
 
@@ -295,7 +303,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
     constexpr bool IS_K = decltype(is_k_tag)::value != 0;
     constexpr bool FIRST = decltype(first_tag)::value != 0;
     const __amdgpu_buffer_rsrc_t rsrc = IS_K ? rsrc_k : rsrc_v;
-    unsigned char* dst = (IS_K ? sK : sV) + buf * TILE_BYTES + wave * (LPT * 1024);
+    unsigned char* dst = (IS_K ? sK : sV)[buf] + wave * (LPT * 1024);
     if (kIndirect) {
       int c[LPT];
 #pragma unroll
@@ -334,7 +342,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   // ---- S^T = K Q^T for the tile held in K buffer BUF ----
   auto scores = [&](auto buf_tag, f32x16 (&s)[KB2][QB]) {
     constexpr int BUF = decltype(buf_tag)::value;
-    const unsigned char* kbase = sK + BUF * TILE_BYTES;
+    const unsigned char* kbase = sK[BUF];
 #pragma unroll
     for (int kb2 = 0; kb2 < KB2; ++kb2)
 #pragma unroll
@@ -499,7 +507,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   // ---- O^T += V^T P^T and l += rowsum(P) for the tile held in V buffer BUF ----
   auto accumulate = [&](auto buf_tag, const bf16x8 (&pf)[KB2][2][QB]) {
     constexpr int BUF = decltype(buf_tag)::value;
-    const unsigned char* vbase = sV + BUF * TILE_BYTES;
+    const unsigned char* vbase = sV[BUF];
 #pragma unroll
     for (int kb2 = 0; kb2 < KB2; ++kb2) {
 #pragma unroll
@@ -556,8 +564,15 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
     constexpr bool has1 = decltype(next_tag)::value != 0;
     constexpr bool INNER = decltype(inner_tag)::value != 0;   // t + 2 exists
     if (kIndirect && t + 3 < n_tiles) load_index(t + 3);
-    if (INNER || (has1 && t + 2 < n_tiles)) load_tile(Int<1>{}, PAR, t + 2, Int<0>{});       // K(t+2) takes the place of K(t), read in the last stage
-    if (has1) load_tile(Int<0>{}, PAR ^ 1, t + 1, Int<0>{});   // V(t+1) takes the place of V(t-1)
+    // The requests cost a wave 470 cycles of issue in a row; four waves spread them over the first MFMAs of the stage
+    // (24 heads x 1,998, five bands of 81, D = 128: 47.5 -> 46.2 us; 8 heads x 75,600, one band: 561 -> 557).  With eight waves,
+    // half as many requests each, the order that the compiler then finds for the rest loses 10 %.
+    constexpr bool kLoadsInside = INNER && !kIndirect && NW == 4;
+    auto request = [&]() {
+      if (INNER || (has1 && t + 2 < n_tiles)) load_tile(Int<1>{}, PAR, t + 2, Int<0>{});       // K(t+2) takes the place of K(t), read in the last stage
+      if (has1) load_tile(Int<0>{}, PAR ^ 1, t + 1, Int<0>{});   // V(t+1) takes the place of V(t-1)
+    };
+    if (!kLoadsInside) request();
     // partly kept tile?  band lists flag it per entry; the dense and gather loops
     // can only meet one at the very end (keys past L, padding of the column list)
     bool masked;
@@ -567,6 +582,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
     else masked = (t + 1) * BC > n_cols;
     if (masked && apply_mask(s_cur, t)) tile_max(s_cur);   // the maximum taken before masking may belong to a dropped key
     settle_max(s_cur);
+    if (kLoadsInside) request();
     bf16x8 pf[KB2][2][QB];
     if (has1) scores(Int<PAR ^ 1>{}, s_next);
     exponentiate(s_cur, pf);
@@ -585,6 +601,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
 #pragma unroll
       for (int i = 0; i < N_QK; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (kLoadsInside && i < 2 * LPT) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         if (i * N_KRD / N_QK + K_AHEAD < N_KRD) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         else if (i >= N_QK - V_AHEAD / 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER, 0);
@@ -675,11 +692,34 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, u
   }
 }
 
+// The same for a function that is not inlined into its kernel, where the compiler does not tell the
+// LDS objects apart by themselves: parameters that do not alias say it.
+template <int D, int NW, int QB, int BC, int OCC, int MODE>
+__device__ __forceinline__ void attn_body_callee(const AttnLaunch& p, const Item& it, const __bf16* __restrict__ const K,
+                                                 const __bf16* __restrict__ const V, unsigned char* __restrict__ const k0,
+                                                 unsigned char* __restrict__ const k1, unsigned char* __restrict__ const v0,
+                                                 unsigned char* __restrict__ const v1, unsigned char* __restrict__ const sI) {
+  attn_body<D, NW, QB, BC, OCC, MODE>(p, it, K, V, k0, k1, v0, v1, sI);
+}
+
+template <int D, int NW, int QB, int BC, int OCC, int MODE, bool CALLEE = false>
+__device__ __forceinline__ void attn_run(const AttnLaunch& p, const Item& it) {
+  const int64_t base = (int64_t)it.b * p.stride_b + (int64_t)it.head * p.stride_h;
+  const __bf16* const K = MODE == MODE_GATHER ? it.gathered : p.k + base;
+  const __bf16* const V = MODE == MODE_GATHER ? K + (size_t)p.gather_pad * D : p.v + base;
+  unsigned char* const k0 = lds_part<D, BC, LDS_K0>();
+  unsigned char* const k1 = lds_part<D, BC, LDS_K1>();
+  unsigned char* const v0 = lds_part<D, BC, LDS_V0>();
+  unsigned char* const v1 = lds_part<D, BC, LDS_V1>();
+  unsigned char* const sI = lds_part<D, BC, LDS_INDEX>();
+  if (CALLEE) attn_body_callee<D, NW, QB, BC, OCC, MODE>(p, it, K, V, k0, k1, v0, v1, sI);
+  else attn_body<D, NW, QB, BC, OCC, MODE>(p, it, K, V, k0, k1, v0, v1, sI);
+}
 
 // The item `item` of a launch over one group of heads (or of a segment of the layer
 // kernel): its place in the (batch entry, head, chunk, query tile) order and its list.
-template <int D, int NW, int QB, int BC, int OCC, int MODE>
-__device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item, unsigned char* const smem) {
+template <int D, int NW, int QB, int BC, int OCC, int MODE, bool CALLEE = false>
+__device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item) {
   constexpr bool kBand = MODE == MODE_BAND || MODE == MODE_PBAND;
   constexpr int DB = D / 32;
   Item it{};
@@ -724,19 +764,18 @@ __device__ __forceinline__ void attn_item(const AttnLaunch& p, const int item, u
   it.n_tiles = uni(n_tiles);
   it.n_cols = uni(n_cols);
   it.t_base = uni(t_base);
-  attn_body<D, NW, QB, BC, OCC, MODE>(p, it, smem);
+  attn_run<D, NW, QB, BC, OCC, MODE, CALLEE>(p, it);
 }
 
 
 // One launch per group: work-group = one item.
 template <int D, int NW, int QB, int BC, int OCC, int MODE>
 __global__ void __launch_bounds__(NW * 64, OCC) attn_fwd_kernel(const AttnLaunch p) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[body_lds(D, BC)];
   // which tile of which head (XCD-aware: consecutive items share an XCD)
   const int per_xcd = (p.n_items + 7) >> 3;
   const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (item >= p.n_items) return;
-  attn_item<D, NW, QB, BC, OCC, MODE>(p, item, smem);
+  attn_item<D, NW, QB, BC, OCC, MODE>(p, item);
 }
 
 
@@ -887,8 +926,7 @@ __device__ __forceinline__ void zero_item(const AttnLaunch& p, const int item) {
 constexpr int kZeroKind = 100;
 template <int D, int BC, int KIND>
 __device__ __attribute__((noinline)) void layer_segment(const AttnLaunch av, const int first_item_v, const int n_rest_v,
-                                                        int* const counters_v, const int home_v, const unsigned smem_v,
-                                                        const unsigned pick_v) {
+                                                        int* const counters_v, const int home_v, const unsigned pick_v) {
   AttnLaunch a;
   a.q = uni(av.q);
   a.k = uni(av.k);
@@ -916,9 +954,7 @@ __device__ __attribute__((noinline)) void layer_segment(const AttnLaunch av, con
   a.skip_q_blocks = uni(av.skip_q_blocks);
   const int first_item = uni(first_item_v), n_rest = uni(n_rest_v), home = uni(home_v);
   int* const counters = uni(counters_v);   // this segment's eight queue positions
-  typedef __attribute__((address_space(3))) unsigned char* lds_bytes;
   typedef __attribute__((address_space(3))) int* lds_int;
-  unsigned char* const smem = (unsigned char*)(lds_bytes)(uintptr_t)uni((int)smem_v);
   lds_int const pick = (lds_int)(uintptr_t)uni((int)pick_v);
   const int per = (n_rest + 7) >> 3;
   // Every queue position only grows, so every loop below ends, and all waves of the
@@ -939,7 +975,7 @@ __device__ __attribute__((noinline)) void layer_segment(const AttnLaunch av, con
       }
       const int item = first_item + x * per + pos;
       if (KIND == kZeroKind) zero_item<D>(a, item);
-      else attn_item<D, kLayerWaves, 1, BC, 2, (KIND == kZeroKind ? MODE_DENSE : KIND)>(a, item, smem);
+      else attn_item<D, kLayerWaves, 1, BC, 2, (KIND == kZeroKind ? MODE_DENSE : KIND), true>(a, item);
       __syncthreads();
     }
   }
@@ -947,11 +983,8 @@ __device__ __attribute__((noinline)) void layer_segment(const AttnLaunch av, con
 
 template <int D, int BC>
 __global__ void __launch_bounds__(kLayerWaves * 64, 2) attn_layer_kernel(const LayerLaunch lp) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[body_lds(D, BC)];
   __shared__ int pick;
-  typedef __attribute__((address_space(3))) unsigned char* lds_bytes;
   typedef __attribute__((address_space(3))) int* lds_int;
-  const unsigned smem_addr = (unsigned)(uintptr_t)(lds_bytes)smem;
   const unsigned pick_addr = (unsigned)(uintptr_t)(lds_int)&pick;
   const int home = blockIdx.x & 7;   // work-groups are dealt to the XCDs in turn
   // Segment after segment, heaviest first; inside a segment a work-group first drains
@@ -967,11 +1000,11 @@ __global__ void __launch_bounds__(kLayerWaves * 64, 2) attn_layer_kernel(const L
     a.list_table = sg.list_table;
     int* const counters = lp.counters + s * 8;
     switch (sg.kind) {
-      case SEG_DENSE: layer_segment<D, BC, MODE_DENSE>(a, sg.first_item, sg.n_items, counters, home, smem_addr, pick_addr); break;
-      case SEG_BAND: layer_segment<D, BC, MODE_BAND>(a, sg.first_item, sg.n_items, counters, home, smem_addr, pick_addr); break;
-      case SEG_GATHER: layer_segment<D, BC, MODE_GATHER>(a, sg.first_item, sg.n_items, counters, home, smem_addr, pick_addr); break;
-      case SEG_PBAND: layer_segment<D, BC, MODE_PBAND>(a, sg.first_item, sg.n_items, counters, home, smem_addr, pick_addr); break;
-      default: layer_segment<D, BC, kZeroKind>(a, sg.first_item, sg.n_items, counters, home, smem_addr, pick_addr); break;
+      case SEG_DENSE: layer_segment<D, BC, MODE_DENSE>(a, sg.first_item, sg.n_items, counters, home, pick_addr); break;
+      case SEG_BAND: layer_segment<D, BC, MODE_BAND>(a, sg.first_item, sg.n_items, counters, home, pick_addr); break;
+      case SEG_GATHER: layer_segment<D, BC, MODE_GATHER>(a, sg.first_item, sg.n_items, counters, home, pick_addr); break;
+      case SEG_PBAND: layer_segment<D, BC, MODE_PBAND>(a, sg.first_item, sg.n_items, counters, home, pick_addr); break;
+      default: layer_segment<D, BC, kZeroKind>(a, sg.first_item, sg.n_items, counters, home, pick_addr); break;
     }
   }
 }
@@ -988,7 +1021,6 @@ typedef const int __attribute__((address_space(4)))* const_int_ptr;
 
 template <int D, int NW, int BC>
 __global__ void __launch_bounds__(NW * 64, 2) attn_grid_kernel(const GridLaunch g) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[body_lds(D, BC)];
   const const_int_ptr r = (const_int_ptr)(uintptr_t)(g.a.ws + g.table) + (size_t)blockIdx.x * kGridWords;
   if (r[0] < 0) return;
   const int kind = r[0] & 255, t0 = r[0] >> 8;
@@ -1010,10 +1042,10 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_grid_kernel(const GridLaunch 
   if (kind == SEG_PBAND) it.index = g.a.ws + last;
   else if (last >= 0) it.partial = g.partial + (size_t)last * NW * ((D / 32 * 16 + 2) * 64);
   switch (kind) {
-    case SEG_DENSE: attn_body<D, NW, 1, BC, 2, MODE_DENSE>(g.a, it, smem); break;
-    case SEG_BAND: attn_body<D, NW, 1, BC, 2, MODE_BAND>(g.a, it, smem); break;
-    case SEG_GATHER: attn_body<D, NW, 1, BC, 2, MODE_COLS>(g.a, it, smem); break;
-    case SEG_PBAND: attn_body<D, NW, 1, BC, 2, MODE_PBAND>(g.a, it, smem); break;
+    case SEG_DENSE: attn_run<D, NW, 1, BC, 2, MODE_DENSE>(g.a, it); break;
+    case SEG_BAND: attn_run<D, NW, 1, BC, 2, MODE_BAND>(g.a, it); break;
+    case SEG_GATHER: attn_run<D, NW, 1, BC, 2, MODE_COLS>(g.a, it); break;
+    case SEG_PBAND: attn_run<D, NW, 1, BC, 2, MODE_PBAND>(g.a, it); break;
     default: {   // zero fill of kGridZeroRows rows of a skipped head
       __bf16* O = g.a.out + (int64_t)it.b * g.a.stride_b + (int64_t)it.head * g.a.stride_h;
       constexpr int CH = D / 8;
