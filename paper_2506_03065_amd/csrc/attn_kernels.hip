@@ -674,15 +674,25 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
     return;
   }
 
-  // ---- epilogue: O = O^T / l, bf16, lane owns query l32: 4 consecutive d per store ----
+  // ---- epilogue: O = O^T / l, bf16.  A lane owns query l32 and holds 4 consecutive d at a time: stored from there, an
+  // instruction writes 16 bytes to each of 32 rows, 5,000 cycles at the end of an item.  Through LDS (the tiles are done
+  // with: every stage ends with a barrier), 64 d of the wave's rows at a time, it writes 128 bytes to each of eight.
+  // 24 heads x 1,998, D = 128, dense: 57.8 -> 55.9 us, 200 columns: 16.6 -> 15.4; 36 heads x 7,560: 155 -> 149; 42 heads x
+  // 32,760: 2,536 -> 2,499. ----
+  unsigned char* const stage_out = (wave * 4096 < TILE_BYTES ? k0 + wave * 4096 : k1 + (wave * 4096 - TILE_BYTES));
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const float inv = 1.0f / l4[qb][0];   // every lane holds the complete sum of its query
-    const int row = q0 + qb * 32 + l32;
-    if (row < L) {
-      __bf16* dst = O + (int64_t)(MODE == MODE_PBAND ? cols[row] : row) * p.stride_l;
+    int to[4];   // rows that the lane stores to
 #pragma unroll
-      for (int db = 0; db < DB; ++db) {
+    for (int j = 0; j < 4; ++j) {
+      to[j] = q0 + qb * 32 + j * 8 + (lane >> 3);
+      if (MODE == MODE_PBAND && to[j] < L) to[j] = cols[to[j]];
+    }
+#pragma unroll
+    for (int d0 = 0; d0 < DB; d0 += 2) {
+#pragma unroll
+      for (int db = d0; db < d0 + 2; ++db) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x2 a01 = {o[db][qb][g * 4 + 0] * inv, o[db][qb][g * 4 + 1] * inv};
@@ -690,8 +700,14 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
           const bf16x2 b01 = __builtin_convertvector(a01, bf16x2);
           const bf16x2 b23 = __builtin_convertvector(a23, bf16x2);
           const bf16x4 out4 = {b01[0], b01[1], b23[0], b23[1]};
-          *reinterpret_cast<bf16x4*>(dst + db * 32 + g * 8 + half * 4) = out4;
+          *reinterpret_cast<bf16x4*>(stage_out + l32 * 128 + ((((db - d0) * 4 + g) ^ (l32 & 7)) << 4) + half * 8) = out4;
         }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int r = j * 8 + (lane >> 3);
+        const u32x4 piece = *reinterpret_cast<const u32x4*>(stage_out + r * 128 + (((lane & 7) ^ (r & 7)) << 4));
+        if (q0 + qb * 32 + r < L) *reinterpret_cast<u32x4*>(O + (int64_t)to[j] * p.stride_l + d0 * 32 + (lane & 7) * 8) = piece;
       }
     }
   }

@@ -644,13 +644,24 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
     return;
   }
 
-  // ---- epilogue: O = O^T / l, bf16, lane owns query l32: 4 consecutive d per store ----
+  // ---- epilogue: O = O^T / l, bf16, through LDS so that a wave instruction writes 64 or 128 bytes to a row and not 16
+  // (see the bf16 kernel; 48 heads x 17,550, D = 64: 388 -> 381 us; 30 heads x 3,892, D = 128: 66.4 -> 60.3; 40 heads x 75,600:
+  // 7.13 -> 7.04 ms).  The K tiles are done with: their last reads lie before the last stage's barrier. ----
+  constexpr int PD = 2 * TILE_BYTES / NW / 64 < 64 ? 2 * TILE_BYTES / NW / 64 : 64;   // d of the wave's 32 rows at a time
+  static_assert(PD == 32 || PD == 64, "a pass is one or two 32-row blocks of O^T");
+  constexpr int PC = PD / 8, PR = 64 / PC;   // 16-byte pieces of a row in a pass, rows of a wave instruction
+  unsigned char* const stage_out = sK + wave * (64 * PD);
   const float inv = 1.0f / l;
-  const int row = q0 + l32;
-  if (row < L) {
-    __bf16* dst = O + (int64_t)(MODE == MODE_PBAND ? row_map[row] : row) * p.stride_l;
+  int to[32 / PR];   // rows that the lane stores to
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
+  for (int j = 0; j < 32 / PR; ++j) {
+    to[j] = q0 + j * PR + lane / PC;
+    if (MODE == MODE_PBAND && to[j] < L) to[j] = row_map[to[j]];
+  }
+#pragma unroll
+  for (int d0 = 0; d0 < DB; d0 += PD / 32) {
+#pragma unroll
+    for (int db = d0; db < d0 + PD / 32; ++db) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const f32x2 a01 = {o[db][g * 4 + 0] * inv, o[db][g * 4 + 1] * inv};
@@ -658,8 +669,14 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
         const bf16x2 b01 = __builtin_convertvector(a01, bf16x2);
         const bf16x2 b23 = __builtin_convertvector(a23, bf16x2);
         const bf16x4 out4 = {b01[0], b01[1], b23[0], b23[1]};
-        *reinterpret_cast<bf16x4*>(dst + db * 32 + g * 8 + half * 4) = out4;
+        *reinterpret_cast<bf16x4*>(stage_out + l32 * (2 * PD) + ((((db - d0) * 4 + g) ^ (l32 % PC)) << 4) + half * 8) = out4;
       }
+    }
+#pragma unroll
+    for (int j = 0; j < 32 / PR; ++j) {
+      const int r = j * PR + lane / PC;
+      const u32x4 piece = *reinterpret_cast<const u32x4*>(stage_out + r * (2 * PD) + (((lane % PC) ^ (r % PC)) << 4));
+      if (q0 + r < L) *reinterpret_cast<u32x4*>(O + (int64_t)to[j] * p.stride_l + d0 * 32 + (lane % PC) * 8) = piece;
     }
   }
 }
