@@ -528,7 +528,22 @@ bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_strip
   // have finished: it is cut into chunks.  Not below 1.6 times the share: a chunk's partial results
   // (64 KB) and the merge pass (5 us) cost more than the shorter tail gives (24 heads x 2,352 tokens,
   // D = 128: 83 us at 0.5, 52 at 1.2, 45 at 1.6, 58 uncut).
-  const double longest = std::max(2.0, 1.6 * total / slots);
+  // Long lists carry more chunks, and where the long items are most of the layer, nothing else is left to fill the slots
+  // beside them: items above the share are then halved.  us, uncut / halved, by what the long items are of the layer:
+  // 0.75 (2 dense heads x 20,000, D = 64): 271 / 251, FP8 193 / 177; 0.77 (1 x 34,012, FP8, D = 128): 472 / 409; 0.78
+  // (2 x 20,000, D = 128): 484 / 441, FP8 284 / 262; but 0.67 (1 x 30,000, D = 128): 646 / 648, FP8 320 / 340; 0.37 to 0.48: 3 to
+  // 5 % slower; below 100 tiles a slot 2 to 10 % slower.  (At most 1.5 chunks a slot: 50 MB of partial results.)
+  const double share = total / slots;
+  double long_cost = 0.0;
+  int64_t halves = 0;
+  for (const Segment& s : segs)
+    for (const Rec& r : s.recs)
+      if (s.longest > share && r.w[0] != SEG_PBAND && r.cost() > share) {
+        long_cost += r.cost();
+        halves += 2;
+      }
+  const bool halve = share > 100.0 && long_cost > 0.72 * total && 2 * halves <= 3 * slots;
+  const double longest = std::max(2.0, (halve ? 0.8 : 1.6) * share);
   std::vector<int32_t> merges;
   int64_t n_slots = 0;
   for (Segment& s : segs) {

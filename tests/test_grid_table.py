@@ -97,6 +97,19 @@ def test_which_layers_run_from_a_table(replay, tmp_path, shape, waves):
     assert f"layer mixed: table waves {waves}," in res.stdout, res.stdout
 
 
+@pytest.mark.parametrize("shape,cut", [
+    ((64, 2, 3, 1, 1, 1000, 20), True),      # long items three quarters of the layer, a quarter above the share: halved
+    ((64, 1, 8, 4, 4, 1000, 20), False),     # two fifths: whole
+    ((64, 2, 3, 1, 1, 600, 20), False),      # under 100 tiles a slot: whole up to twice the share
+    ((128, 2, 3, 1, 1, 1000, 20), True)])
+def test_which_long_items_are_halved(replay, tmp_path, shape, cut):
+    """Both sides of the rule that cuts items above an even share, with 256 compute units."""
+    res = run(replay, tmp_path, [layer_text(mixed_layer(*shape), 0, rounds=1, tensors=0)])
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+    first = next(line.split() for line in res.stdout.splitlines() if line.startswith("grid:"))   # (the last one is of a rotated table)
+    assert (int(first[2]), int(first[6]) > 0) == (4, cut), res.stdout
+
+
 def test_a_table_that_cannot_be_built_leaves_no_trace(tmp_path):
     exe = str(tmp_path / "grid_table_fails")
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", STUB, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
