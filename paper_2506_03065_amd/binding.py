@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 
 import numpy as np
 
@@ -126,6 +127,8 @@ def _check(status, where):
 
 
 def _i32(a):
+    if type(a) is np.ndarray and a.dtype == np.int32 and a.flags.c_contiguous and a.ndim:
+        return a
     return np.ascontiguousarray(np.asarray(a, dtype=np.int32))
 
 
@@ -148,28 +151,57 @@ def desc_of(t) -> TensorDesc:
     return TensorDesc(B, H, L, D, t.stride(0), t.stride(1), t.stride(2))
 
 
+# svd_head_params as the C compiler lays it out
+_HEAD_RECORD = "iiPiPiii0P"
+assert struct.calcsize("@" + _HEAD_RECORD) == C.sizeof(HeadParams)
+
+
+def _wrap32(x):
+    return ((int(x) + (1 << 31)) & 0xffffffff) - (1 << 31)
+
+
 class _Marshalled:
-    """Host arrays behind an svd_head_params[H]; keeps them alive."""
+    """Host arrays behind an svd_head_params[H]; keeps them alive.  All lists of a layer in one array and all records in one
+    conversion: attribute by attribute of a ctypes array, with a typed pointer per list, a call took longer here than for the
+    compilation of its plan."""
 
     def __init__(self, strategy_table, pattern_params):
         self.table = _i32(strategy_table)
         H = self.table.size
         if len(pattern_params) != H:
             raise ValueError("pattern_params must have one entry per head")
-        self.keep = []
-        self.params = (HeadParams * H)()
-        for h, p in enumerate(pattern_params):
-            p = p or {}
-            offs = _i32(p.get("offsets", ()))
-            cols = _i32(p.get("cols", ()))
-            self.keep += [offs, cols]
-            self.params[h].half_width = int(p.get("half_width", 0))
-            self.params[h].n_offsets = offs.size
-            self.params[h].offsets = _ptr(offs) if offs.size else None
-            self.params[h].n_cols = cols.size
-            self.params[h].cols = _ptr(cols) if cols.size else None
+        # Heads often share a list, or the whole dict: by object, each held until the end.
+        pattern_params = list(pattern_params)
+        heads = {id(p): p for p in pattern_params}
+        lists, parts, total, given = {id(None): (0, 0, None)}, [], 0, {}
+        for key, p in heads.items():
+            if p:
+                pair = given[key] = (p.get("offsets"), p.get("cols"))
+                for x in pair:
+                    if id(x) not in lists:
+                        arr = _i32(x)
+                        lists[id(x)] = (arr.size, total, x)   # its length, where it starts
+                        parts.append(arr if arr.ndim == 1 else arr.reshape(-1))
+                        total += arr.size
+        self.lists = np.concatenate(parts) if total else None
+        base = self.lists.ctypes.data if total else 0
+        records = {}
+        for key, p in heads.items():
+            if not p:
+                records[key] = (0, 0, 0, 0, 0, 0, 0, 0)
+                continue
+            offsets, cols = given[key]
+            n_offsets, offsets, _ = lists[id(offsets)]
+            n_cols, cols, _ = lists[id(cols)]
             first, n, f = p.get("rearranged") or (0, 0, 0)
-            self.params[h].rearr_first, self.params[h].rearr_frame_tokens, self.params[h].rearr_frames = int(first), int(n), int(f)
+            records[key] = (int(p.get("half_width", 0)), n_offsets, base + 4 * offsets if n_offsets else 0,
+                            n_cols, base + 4 * cols if n_cols else 0, int(first), int(n), int(f))
+        words = [w for p in pattern_params for w in records[id(p)]]
+        try:
+            packed = struct.pack("@" + _HEAD_RECORD * H, *words)
+        except struct.error:   # integers beyond 32 bits wrap, as a C conversion does
+            packed = struct.pack("@" + _HEAD_RECORD * H, *(w if i % 8 in (2, 4) else _wrap32(w) for i, w in enumerate(words)))
+        self.params = (HeadParams * H).from_buffer_copy(packed)
 
 
 def _text_tokens(strategy_table, pattern_params, text_tokens):
@@ -335,6 +367,8 @@ def svd_plan_create(desc, strategy_table, pattern_params, block_q=0, block_k=0, 
 def _stream_ptr(stream):
     if stream is None:
         import torch
+        if torch.cuda.is_initialized():   # the stream's handle without a stream object: 0.7 us in place of 3.5
+            return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
         if torch.cuda.is_available():
             return C.c_void_p(torch.cuda.current_stream().cuda_stream)
         return None

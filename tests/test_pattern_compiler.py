@@ -432,3 +432,23 @@ def test_wide_bands_run_on_the_large_tile_and_keep_small_tile_lists_for_the_fp8_
         assert plan.work_fp8(gi)["computed_flops"] < plan.work(gi)["computed_flops"] <= plan.work_fp8(gi)["computed_flops"] / 0.92
     assert plan.work_fp8()["computed_tiles"] == sum(plan.work_fp8(gi)["computed_tiles"] for gi in range(len(groups)))
     plan.close()
+
+
+def test_marshalled_parameters_word_for_word():
+    """The svd_head_params array of dicts of every kind: shared dicts and lists, none at all, read-only, strided, converted
+    and two-dimensional lists, integers past 32 bits (which wrap)."""
+    fixed = np.arange(5, dtype=np.int32)
+    fixed.flags.writeable = False
+    shared = {"half_width": 7, "offsets": [-3, 0, 3]}
+    params = [None, {}, shared, shared, {"cols": fixed}, {"cols": np.arange(20)[::2]}, {"offsets": (), "cols": ()},
+              {"half_width": np.int64(5), "offsets": np.array([[1, 2], [3, 4]])}, {"half_width": 2 ** 31 + 5},
+              {"half_width": -2 ** 40 - 1, "rearranged": (1, 2, 3)}, {"half_width": 2.7, "cols": np.array([1.0, 2.0])}]
+    want = [(0, [], [], (0, 0, 0))] * 2 + [(7, [-3, 0, 3], [], (0, 0, 0))] * 2 + [
+        (0, [], list(range(5)), (0, 0, 0)), (0, [], list(range(0, 20, 2)), (0, 0, 0)), (0, [], [], (0, 0, 0)),
+        (5, [1, 2, 3, 4], [], (0, 0, 0)), (5 - 2 ** 31, [], [], (0, 0, 0)), (-1, [], [], (1, 2, 3)), (2, [], [1, 2], (0, 0, 0))]
+    m = svd._Marshalled([2] * len(params), params)
+    got = [(p.half_width, [p.offsets[i] for i in range(p.n_offsets)], [p.cols[i] for i in range(p.n_cols)],
+            (p.rearr_first, p.rearr_frame_tokens, p.rearr_frames)) for p in m.params]
+    assert got == want and not any(bool(p.offsets) != (p.n_offsets > 0) or bool(p.cols) != (p.n_cols > 0) for p in m.params)
+    with pytest.raises(ValueError):
+        svd._Marshalled([1, 2], [{}])
