@@ -572,12 +572,22 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
     // (24 heads x 1,998, five bands of 81, D = 128: 47.5 -> 46.2 us; 8 heads x 75,600, one band: 561 -> 557).  With eight waves,
     // half as many requests each, the order that the compiler then finds for the rest loses 10 %.
     constexpr bool kLoadsInside = INNER && !kIndirect && NW == 4;
+    // Rows through a row map: those of K(t+2) wait for the index ring, at the top; those of V(t+1) are known (window of 8
+    // heads x 75,600, D = 128: 577 -> 560 us; both inside: 637; the same for column lists: 24 heads x 1,998, 200 columns: 15.1 -> 16.7).
+    constexpr bool kRowsInside = INNER && MODE == MODE_PBAND && NW == 4;
     auto request = [&]() {
       if (kIndirect && has1) load_tile(Int<0>{}, PAR ^ 1, t + 1, Int<0>{});   // the rows of K(t+1), requested last
       if (INNER || (has1 && t + 2 < n_tiles)) load_tile(Int<1>{}, PAR, t + 2, Int<0>{});       // K(t+2) takes the place of K(t), read in the last stage
       if (!kIndirect && has1) load_tile(Int<0>{}, PAR ^ 1, t + 1, Int<0>{});   // V(t+1) takes the place of V(t-1)
     };
-    if (!kLoadsInside) request();
+    unsigned v_rows[LPT];
+    if (kRowsInside) {
+#pragma unroll
+      for (int u = 0; u < LPT; ++u) v_rows[u] = row_at[u];
+      load_tile(Int<1>{}, PAR, t + 2, Int<0>{});
+    } else if (!kLoadsInside) {
+      request();
+    }
     // partly kept tile?  band lists flag it per entry; the dense and gather loops
     // can only meet one at the very end (keys past L, padding of the column list)
     bool masked;
@@ -588,6 +598,12 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
     if (masked && apply_mask(s_cur, t)) tile_max(s_cur);   // the maximum taken before masking may belong to a dropped key
     settle_max(s_cur);
     if (kLoadsInside) request();
+    if (kRowsInside) {
+#pragma unroll
+      for (int u = 0; u < LPT; ++u)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_v, (lds_ptr)(sV[PAR ^ 1] + wave * (LPT * 1024) + u * 1024), 16,
+                                                 (int)(v_rows[u] + g_v[u]), 0, 0, 0);
+    }
     bf16x8 pf[KB2][2][QB];
     if (has1) scores(Int<PAR ^ 1>{}, s_next);
     exponentiate(s_cur, pf);
@@ -606,7 +622,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
 #pragma unroll
       for (int i = 0; i < N_QK; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (kLoadsInside && i < 2 * LPT) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        if (i < (kLoadsInside ? 2 * LPT : kRowsInside ? LPT : 0)) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         if (i * N_KRD / N_QK + K_AHEAD < N_KRD) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         else if (i >= N_QK - V_AHEAD / 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         __builtin_amdgcn_sched_group_barrier(0x402, VALU_PER, 0);
