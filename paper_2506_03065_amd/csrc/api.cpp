@@ -262,7 +262,9 @@ int grid_waves(const Plan& p, const svd_plan_options* opt, int form, int n_cu) {
   const int waves = p.desc.D == 64 && per_slot > 400.0 && 2.0 * svd::grid_tiles(p, p.block_q) < 1.03 * small ? 8 : 4;
   const double dense_items = std::ceil(static_cast<double>(p.desc.L) / (32 * waves)) * count_dense_heads(p) * p.desc.B;
   const double dense_rounds = std::ceil(dense_items / (8 / waves * n_cu));
-  if (per_slot > 300.0 && dense_rounds * p.n_k_blocks > 1.3 * per_slot) return 0;
+  // (At D = 128 up to 400 tiles a slot the table is ahead, us, other form / table: 1 dense head of 6 x 30,000: 667 / 575, of 4 x
+  // 31,200: 638 / 559, of 8 x 34,012: 751 / 695, of 2 x 38,400: 764 / 748; above it within 2.6 %.  At D = 64, 66,000: 1,305 / 1,592.)
+  if (per_slot > (p.desc.D == 128 ? 400.0 : 300.0) && dense_rounds * p.n_k_blocks > 1.3 * per_slot) return 0;
   return waves;
 }
 

@@ -101,7 +101,8 @@ def test_which_layers_run_from_a_table(replay, tmp_path, shape, waves):
     ((64, 2, 3, 1, 1, 1000, 20), True),      # long items three quarters of the layer, a quarter above the share: halved
     ((64, 1, 8, 4, 4, 1000, 20), False),     # two fifths: whole
     ((64, 2, 3, 1, 1, 600, 20), False),      # under 100 tiles a slot: whole up to twice the share
-    ((128, 2, 3, 1, 1, 1000, 20), True)])
+    ((128, 2, 3, 1, 1, 1000, 20), True),
+    ((128, 1, 3, 1, 1, 1500, 20), False)])   # two thirds: whole, though 1.5 times the share
 def test_which_long_items_are_halved(replay, tmp_path, shape, cut):
     """Both sides of the rule that cuts items above an even share, with 256 compute units."""
     res = run(replay, tmp_path, [layer_text(mixed_layer(*shape), 0, rounds=1, tensors=0)])
