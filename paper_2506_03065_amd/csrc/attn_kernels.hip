@@ -694,7 +694,29 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
   // instruction writes 16 bytes to each of 32 rows, 5,000 cycles at the end of an item.  Through LDS (the tiles are done
   // with: every stage ends with a barrier), 64 d of the wave's rows at a time, it writes 128 bytes to each of eight.
   // 24 heads x 1,998, D = 128, dense: 57.8 -> 55.9 us, 200 columns: 16.6 -> 15.4; 36 heads x 7,560: 155 -> 149; 42 heads x
-  // 32,760: 2,536 -> 2,499. ----
+  // 32,760: 2,536 -> 2,499.  Eight waves at D = 128, those of long items, store from the registers (40 heads x 75,600, 8 dense: 22.31 ms
+  // through LDS, 22.13 so; D = 64 the other way: 37 heads x 87,747: 23.74 / 23.89). ----
+  if constexpr (NW == 8 && D == 128) {
+    static_assert(QB == 1, "one 32-row block per wave");
+    const float inv = 1.0f / l4[0][0];   // every lane holds the complete sum of its query
+    const int row = q0 + l32;
+    if (row < L) {
+      __bf16* dst = O + (int64_t)(MODE == MODE_PBAND ? cols[row] : row) * p.stride_l;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x2 a01 = {o[db][0][g * 4 + 0] * inv, o[db][0][g * 4 + 1] * inv};
+          const f32x2 a23 = {o[db][0][g * 4 + 2] * inv, o[db][0][g * 4 + 3] * inv};
+          const bf16x2 b01 = __builtin_convertvector(a01, bf16x2);
+          const bf16x2 b23 = __builtin_convertvector(a23, bf16x2);
+          const bf16x4 out4 = {b01[0], b01[1], b23[0], b23[1]};
+          *reinterpret_cast<bf16x4*>(dst + db * 32 + g * 8 + half * 4) = out4;
+        }
+      }
+    }
+    return;
+  }
   unsigned char* const stage_out = (wave * 4096 < TILE_BYTES ? k0 + wave * 4096 : k1 + (wave * 4096 - TILE_BYTES));
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
