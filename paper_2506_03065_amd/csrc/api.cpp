@@ -245,8 +245,9 @@ int stripe_gather_pad(const Plan& p) {
 //   830 to 1,700 of 1,000 to 1,950 (0.58 to 0.92)        0.95 to 1.03, most of them 0.96 to 0.98
 // Whole dense items that do not come out even keep a few slots busy after all others have finished, which the split of
 // the dense heads in a launch per group or the larger units of the layer kernel avoid: 4 heads with one dense,
-// D = 64, 66,000 tokens (258 items in 256 slots, 1.6 times the even load) 1,324 / 1,535; D = 128, 38,400 tokens (300 in
-// 512, 1.3 times) 853 / 964.  At 233 tiles per slot and 1.4 times the load the table still wins (481 / 435).  Long
+// D = 64, 66,000 tokens (258 items in 256 slots, 1.6 times the even load) 1,305 / 1,592.  Where such items are most of the
+// layer the table halves them (pattern_compiler.cpp), which made D = 128, 38,400 tokens (300 in 512, 455 tiles per slot) even,
+// 838 to 853 / 832 to 842.  At 233 tiles per slot and 1.4 times the load the table wins (481 / 435).  Long
 // D = 64 layers take the large tile (a K/V tile in LDS serves twice the rows, 3-4 % a tile) unless its lists, which
 // follow the bands less closely, hold more than that on top; the longest stay in groups, whose launches and tails no
 // longer count.
