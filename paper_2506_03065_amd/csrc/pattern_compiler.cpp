@@ -528,32 +528,46 @@ bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_strip
   // have finished: it is cut into chunks.  Not below 1.6 times the share: a chunk's partial results
   // (64 KB) and the merge pass (5 us) cost more than the shorter tail gives (24 heads x 2,352 tokens,
   // D = 128: 83 us at 0.5, 52 at 1.2, 45 at 1.6, 58 uncut).
-  // Long lists carry more chunks, and where the long items are most of the layer, nothing else is left to fill the slots
-  // beside them: items above the share are then halved.  us, uncut / halved, by what the long items are of the layer:
-  // 0.75 (2 dense heads x 20,000, D = 64): 271 / 251, FP8 193 / 177; 0.77 (1 x 34,012, FP8, D = 128): 472 / 409; 0.78
-  // (2 x 20,000, D = 128): 484 / 441, FP8 284 / 262; but 0.67 (1 x 30,000, D = 128): 646 / 648, FP8 320 / 340; 0.37 to 0.48: 3 to
-  // 5 % slower; below 100 tiles a slot 2 to 10 % slower.  (At most 1.5 chunks a slot: 50 MB of partial results.)
-  const double share = total / slots;
+  // Two work-groups share a compute unit.  Long items that can have a unit each run at nearly its full rate once the short
+  // items beside them are done; as soon as they are more (an XCD deals them to its 32 units; from 30 on some share), two
+  // of them on one unit take twice as long.  Where they are most of a layer of long lists, such pieces are halved, if they are
+  // longer than a slot's share by more than what a cut costs (less at D = 64, with half the partial results an item).
+  // us, whole / halved:
+  //   D = 128, pieces of 1.04 to 1.20 shares      253 / 274, 591 / 618, 345 / 356 (FP8), 278 / 300 (0.85 to 1.02 times as fast)
+  //     1.23 to 1.5 shares                        492 / 464, 238 / 230, 303 / 285 (FP8), 388 / 353 (1.02 to 1.11)
+  //     1.5 to 1.9 shares, over 232 items         666 / 539, 391 / 309 (FP8), 318 / 238 (1.24 to 1.4)
+  //                        under 232              416 / 404, 131 / 158 (FP8), 215 / 220, 263 / 270 (FP8) (0.83 to 1.03)
+  //     2.0 to 2.3 shares, 2 pieces / 4           360 / 373, 338 / 342; 3 pieces: 370, 349
+  //     2.4 to 2.9 shares, 2 pieces / 4           302 / 283, 162 / 149 (FP8), 249 / 231; 3 pieces at 2.40: 280 / 288
+  //   D = 64, pieces of 1.05 shares               295 / 305; 1.1 to 1.25: 306 / 301, 272 / 255, 225 / 194 (FP8); 1.3 to 1.7: 551 / 497,
+  //                                               452 / 401, 372 / 297
+  // With less than 0.72 of the layer in long items, or less than 100 tiles a slot, most layers lose 2 to 10 % (other items
+  // fill the slots beside the long ones; the merge pass weighs more).  At most 1.5 halves a slot: 52 MB of partial results.
+  const double share = total / slots, longest = std::max(2.0, 1.6 * share);
+  const double worth = (d.D == 128 ? 1.22 : 1.11) * share;   // shorter pieces are not halved
+  const auto pieces_of = [&](const Rec& r) -> int32_t {
+    if (r.w[0] == SEG_PBAND || r.w[0] == SEG_ZERO || r.w[4] <= 1.25 * longest) return 1;
+    return std::min(static_cast<int32_t>(std::ceil(r.w[4] / longest)), kGridMaxChunks);
+  };
+  const auto long_pieces = [&](const Rec& r) { return r.w[0] != SEG_PBAND && r.w[0] != SEG_ZERO && r.w[4] > worth * pieces_of(r); };
   double long_cost = 0.0;
-  int64_t halves = 0;
+  int64_t n_long = 0;   // pieces that are longer than worth
   for (const Segment& s : segs)
     for (const Rec& r : s.recs)
-      if (s.longest > share && r.w[0] != SEG_PBAND && r.cost() > share) {
+      if (s.longest > worth && long_pieces(r)) {
         long_cost += r.cost();
-        halves += 2;
+        n_long += pieces_of(r);
       }
-  const bool halve = share > 100.0 && long_cost > 0.72 * total && 2 * halves <= 3 * slots;
-  const double longest = std::max(2.0, (halve ? 0.8 : 1.6) * share);
+  const bool halve = share > 100.0 && long_cost > 0.72 * total && 64 * n_long > 29 * static_cast<int64_t>(slots) &&
+                     4 * n_long <= 3 * static_cast<int64_t>(slots);
   std::vector<int32_t> merges;
   int64_t n_slots = 0;
   for (Segment& s : segs) {
-    if (s.longest <= 1.25 * longest + kGridItemCost) continue;
+    if (s.longest <= (halve ? worth : 1.25 * longest + kGridItemCost)) continue;
     std::vector<Rec> cut;
     for (const Rec& r : s.recs) {
       const int32_t n = r.w[4];
-      int32_t pieces = r.w[0] == SEG_PBAND || r.w[0] == SEG_ZERO || n <= 1.25 * longest
-                           ? 1 : static_cast<int32_t>(std::ceil(n / longest));
-      if (pieces > kGridMaxChunks) pieces = kGridMaxChunks;
+      const int32_t pieces = std::min(pieces_of(r) * (halve && long_pieces(r) ? 2 : 1), kGridMaxChunks);
       if (pieces <= 1) {
         cut.push_back(r);
         continue;

@@ -55,7 +55,10 @@ hipError_t launch_grid_fp8(const Fp8Launch& f, const GridLaunch& g, hipStream_t 
 
 static void walk(const GridLaunch& g, const Fp8Launch* f8, hipStream_t stream) {
   stub::note_launch(stream, "attn_grid_kernel");
-  std::printf("grid: waves %d records %d merges %d fp8 %d\n", g.waves, g.n_blocks, g.n_merges, f8 ? 1 : 0);
+  need(g.a.ws + g.merge_table, (size_t)g.n_merges * kGridWords * 4, "merge records");
+  int chunks = 0;
+  for (int i = 0; i < g.n_merges; ++i) chunks += g.a.ws[g.merge_table + (size_t)i * kGridWords + 3];
+  std::printf("grid: waves %d records %d merges %d fp8 %d chunks %d\n", g.waves, g.n_blocks, g.n_merges, f8 ? 1 : 0, chunks);
   if (g.n_merges > 0) stub::note_launch(stream, "merge_chunks_kernel");
   const int BR = g.waves * 32, BC = g.a.D == 128 ? Tile128::BC : Tile64::BC;
   const size_t slot_floats = grid_slot_floats(g.a.D, g.waves);
@@ -112,7 +115,6 @@ static void walk(const GridLaunch& g, const Fp8Launch* f8, hipStream_t stream) {
       std::memset(g.partial + (size_t)r[7] * slot_floats, 0x22, slot_floats * sizeof(float));
     }
   }
-  need(g.a.ws + g.merge_table, (size_t)g.n_merges * kGridWords * 4, "merge records");
   size_t merged = 0;
   for (int i = 0; i < g.n_merges; ++i) {
     const int* r = g.a.ws + g.merge_table + (size_t)i * kGridWords;
