@@ -150,10 +150,10 @@ __device__ __forceinline__ unsigned char* lds_part() {
 }
 
 // Everything a work-group does between picking the item and storing its rows.  K, V: first rows
-// of the item's head (or of its gathered arrays).  Every wave of the work-group calls it
+// of the item's head (or of its gathered arrays).  CALLEE: part of the layer kernel.  Every wave of the work-group calls it
 // with the same item; a return leaves no wave behind at a barrier (all returns are
 // work-group uniform).
-template <int D, int NW, int QB, int BC, int OCC, int MODE>
+template <int D, int NW, int QB, int BC, int OCC, int MODE, bool CALLEE>
 __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, const __bf16* const K, const __bf16* const V,
                                           unsigned char* const k0, unsigned char* const k1, unsigned char* const v0,
                                           unsigned char* const v1, unsigned char* const sI) {
@@ -694,9 +694,12 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
   // instruction writes 16 bytes to each of 32 rows, 5,000 cycles at the end of an item.  Through LDS (the tiles are done
   // with: every stage ends with a barrier), 64 d of the wave's rows at a time, it writes 128 bytes to each of eight.
   // 24 heads x 1,998, D = 128, dense: 57.8 -> 55.9 us, 200 columns: 16.6 -> 15.4; 36 heads x 7,560: 155 -> 149; 42 heads x
-  // 32,760: 2,536 -> 2,499.  Eight waves at D = 128, those of long items, store from the registers (40 heads x 75,600, 8 dense: 22.31 ms
-  // through LDS, 22.13 so; D = 64 the other way: 37 heads x 87,747: 23.74 / 23.89). ----
-  if constexpr (NW == 8 && D == 128) {
+  // 32,760: 2,536 -> 2,499.  Eight waves at D = 128 store from the registers in the layer kernel (40 heads x 75,600, 8 dense: 22.31 ms
+  // through LDS, 22.13 so; D = 64 the other way: 37 heads x 87,747: 23.74 / 23.89) and in launches of dense heads or gathered columns
+  // (10 dense heads x 18,900: 1,491 us through LDS, 1,425 so), but not in those of band lists, which spill four times as many registers
+  // then (20 heads x 18,900, bands: 1,007 us through LDS, 1,060 from the registers; with text borders, 16 x 33,016: 1,077 / 1,174; windows
+  // of 8 heads x 37,800: 310 / 324). ----
+  if constexpr (NW == 8 && D == 128 && (CALLEE || !kBand)) {
     static_assert(QB == 1, "one 32-row block per wave");
     const float inv = 1.0f / l4[0][0];   // every lane holds the complete sum of its query
     const int row = q0 + l32;
@@ -758,7 +761,7 @@ __device__ __forceinline__ void attn_body_callee(const AttnLaunch& p, const Item
                                                  const __bf16* __restrict__ const V, unsigned char* __restrict__ const k0,
                                                  unsigned char* __restrict__ const k1, unsigned char* __restrict__ const v0,
                                                  unsigned char* __restrict__ const v1, unsigned char* __restrict__ const sI) {
-  attn_body<D, NW, QB, BC, OCC, MODE>(p, it, K, V, k0, k1, v0, v1, sI);
+  attn_body<D, NW, QB, BC, OCC, MODE, true>(p, it, K, V, k0, k1, v0, v1, sI);
 }
 
 template <int D, int NW, int QB, int BC, int OCC, int MODE, bool CALLEE = false>
@@ -772,7 +775,7 @@ __device__ __forceinline__ void attn_run(const AttnLaunch& p, const Item& it) {
   unsigned char* const v1 = lds_part<D, BC, LDS_V1>();
   unsigned char* const sI = lds_part<D, BC, LDS_INDEX>();
   if (CALLEE) attn_body_callee<D, NW, QB, BC, OCC, MODE>(p, it, K, V, k0, k1, v0, v1, sI);
-  else attn_body<D, NW, QB, BC, OCC, MODE>(p, it, K, V, k0, k1, v0, v1, sI);
+  else attn_body<D, NW, QB, BC, OCC, MODE, false>(p, it, K, V, k0, k1, v0, v1, sI);
 }
 
 // The item `item` of a launch over one group of heads (or of a segment of the layer
