@@ -173,10 +173,10 @@ class _Marshalled:
         # Heads often share a list, or the whole dict: by object, each held until the end.
         pattern_params = list(pattern_params)
         heads = {id(p): p for p in pattern_params}
-        lists, parts, total, given = {id(None): (0, 0, None)}, [], 0, {}
+        lists, parts, total, given = {id(()): (0, 0, ())}, [], 0, {}
         for key, p in heads.items():
             if p:
-                pair = given[key] = (p.get("offsets"), p.get("cols"))
+                pair = given[key] = (p.get("offsets", ()), p.get("cols", ()))
                 for x in pair:
                     if id(x) not in lists:
                         arr = _i32(x)

@@ -452,3 +452,11 @@ def test_marshalled_parameters_word_for_word():
     assert got == want and not any(bool(p.offsets) != (p.n_offsets > 0) or bool(p.cols) != (p.n_cols > 0) for p in m.params)
     with pytest.raises(ValueError):
         svd._Marshalled([1, 2], [{}])
+
+
+@pytest.mark.parametrize("p", [{"offsets": None}, {"cols": None}, {"half_width": 3, "offsets": None, "cols": [1]}, {"offsets": "x"},
+                               {"half_width": None}])
+def test_parameters_that_are_no_numbers_are_refused(p):
+    """A list given as None is not an absent one."""
+    with pytest.raises((TypeError, ValueError)):
+        svd._Marshalled([2, 2], [{"half_width": 1}, p])
