@@ -300,7 +300,14 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
   };
   // kIndirect: byte offsets of the slabs' rows in the tile whose K was requested last, kept for its V in the next stage (both
   // formed from the ring: 24 heads x 1,998, 200 columns, D = 128: 17.5 -> 16.2 us; window of 8 heads x 75,600: 596 -> 584)
+  // V(t + 1) is therefore requested before K(t + 2), or with a copy of them.
   unsigned row_at[LPT];
+  // kIndirect: the request of a wave's slabs whose rows start at these offsets, at these of their chunks
+  auto request_rows = [&](const __amdgpu_buffer_rsrc_t rsrc, unsigned char* const dst, const unsigned (&rows)[LPT], const unsigned (&chunk)[LPT]) {
+#pragma unroll
+    for (int u = 0; u < LPT; ++u)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr)(dst + u * 1024), 16, (int)(rows[u] + chunk[u]), 0, 0, 0);
+  };
   // FIRST: the prologue's loads, whose indices are read from memory
   auto load_tile = [&](auto is_k_tag, const int buf, const int t, auto first_tag) {
     constexpr bool IS_K = decltype(is_k_tag)::value != 0;
@@ -317,9 +324,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
 #pragma unroll
         for (int u = 0; u < LPT; ++u) row_at[u] = c[u] < 0 ? 0xffffff00u : __umul24((unsigned)c[u], stride_bytes);
       }
-#pragma unroll
-      for (int u = 0; u < LPT; ++u)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr)(dst + u * 1024), 16, (int)(row_at[u] + (IS_K ? g_k[u] : g_v[u])), 0, 0, 0);
+      request_rows(rsrc, dst, row_at, IS_K ? g_k : g_v);
     } else {
       const int row0 = (kBand ? entries[t].x : t + t_base) * BC;
 #pragma unroll
@@ -599,10 +604,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
     settle_max(s_cur);
     if (kLoadsInside) request();
     if (kRowsInside) {
-#pragma unroll
-      for (int u = 0; u < LPT; ++u)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_v, (lds_ptr)(sV[PAR ^ 1] + wave * (LPT * 1024) + u * 1024), 16,
-                                                 (int)(v_rows[u] + g_v[u]), 0, 0, 0);
+      request_rows(rsrc_v, sV[PAR ^ 1] + wave * (LPT * 1024), v_rows, g_v);
     }
     bf16x8 pf[KB2][2][QB];
     if (has1) scores(Int<PAR ^ 1>{}, s_next);
@@ -649,7 +651,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) asm volatile("" : "+v"(mx_raw[qb]));
     }
-    // the loads issued at the top of the stage must have landed before anyone reads them
+    // the loads that this stage has requested must have landed before anyone reads them
     __syncthreads();
   };
 
