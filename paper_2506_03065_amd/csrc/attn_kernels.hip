@@ -149,6 +149,14 @@ __device__ __forceinline__ unsigned char* lds_part() {
   return part;
 }
 
+// Orders a wave's LDS accesses across its lanes: what any lane has written is there for the others.  The LDS serves one wave's
+// accesses in order, so this emits nothing; it keeps the compiler, which sees single lanes, from moving one past the other.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Everything a work-group does between picking the item and storing its rows.  K, V: first rows
 // of the item's head (or of its gathered arrays).  CALLEE: part of the layer kernel.  Every wave of the work-group calls it
 // with the same item; a return leaves no wave behind at a barrier (all returns are
@@ -722,6 +730,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
     }
     return;
   }
+  static_assert(NW * 4096 <= 2 * TILE_BYTES && TILE_BYTES % 4096 == 0, "a wave's 32 rows x 64 d lie inside one K tile");
   unsigned char* const stage_out = (wave * 4096 < TILE_BYTES ? k0 + wave * 4096 : k1 + (wave * 4096 - TILE_BYTES));
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
@@ -746,12 +755,14 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
           *reinterpret_cast<bf16x4*>(stage_out + l32 * 128 + ((((db - d0) * 4 + g) ^ (l32 & 7)) << 4) + half * 8) = out4;
         }
       }
+      wave_lds_order();
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int r = j * 8 + (lane >> 3);
         const u32x4 piece = *reinterpret_cast<const u32x4*>(stage_out + r * 128 + (((lane & 7) ^ (r & 7)) << 4));
         if (q0 + qb * 32 + r < L) *reinterpret_cast<u32x4*>(O + (int64_t)to[j] * p.stride_l + d0 * 32 + (lane & 7) * 8) = piece;
       }
+      wave_lds_order();
     }
   }
 }

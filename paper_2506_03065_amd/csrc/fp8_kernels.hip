@@ -209,6 +209,14 @@ struct Fp8Item {
   float* partial;           // split item: where its unnormalised result goes, else nullptr
 };
 
+// Orders a wave's LDS accesses across its lanes: what any lane has written is there for the others.  The LDS serves one wave's
+// accesses in order, so this emits nothing; it keeps the compiler, which sees single lanes, from moving one past the other.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // smem: 4 * BC * D bytes of LDS, 16-byte aligned.
 template <int D, int NW, int BC, int MODE>
 __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it, unsigned char* const smem) {
@@ -672,12 +680,14 @@ __device__ __forceinline__ void fp8_body(const Fp8Launch& pp, const Fp8Item& it,
         *reinterpret_cast<bf16x4*>(stage_out + l32 * (2 * PD) + ((((db - d0) * 4 + g) ^ (l32 % PC)) << 4) + half * 8) = out4;
       }
     }
+    wave_lds_order();
 #pragma unroll
     for (int j = 0; j < 32 / PR; ++j) {
       const int r = j * PR + lane / PC;
       const u32x4 piece = *reinterpret_cast<const u32x4*>(stage_out + r * (2 * PD) + (((lane % PC) ^ (r % PC)) << 4));
       if (q0 + r < L) *reinterpret_cast<u32x4*>(O + (int64_t)to[j] * p.stride_l + d0 * 32 + (lane % PC) * 8) = piece;
     }
+    wave_lds_order();
   }
 }
 
