@@ -307,7 +307,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
                                                lane * 4 + wave * 256, index_base(t) * 4, 0, 0);
   };
   // kIndirect: byte offsets of the slabs' rows in the tile whose K was requested last, kept for its V in the next stage (both
-  // formed from the ring: 24 heads x 1,998, 200 columns, D = 128: 17.5 -> 16.2 us; window of 8 heads x 75,600: 596 -> 584)
+  // formed from the ring: 24 heads x 1,998, 200 columns, D = 128: 17.5 -> 16.2 us; window of 8 heads x 75,600: 596 -> 584).
   // V(t + 1) is therefore requested before K(t + 2), or with a copy of them.
   unsigned row_at[LPT];
   // kIndirect: the request of a wave's slabs whose rows start at these offsets, at these of their chunks
@@ -709,6 +709,13 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
   // (10 dense heads x 18,900: 1,491 us through LDS, 1,425 so), but not in those of band lists, which spill four times as many registers
   // then (20 heads x 18,900, bands: 1,007 us through LDS, 1,060 from the registers; with text borders, 16 x 33,016: 1,077 / 1,174; windows
   // of 8 heads x 37,800: 310 / 324). ----
+  auto four = [](const f32x16& x, const int g, const float inv) -> bf16x4 {   // d of group g of a 32-row block
+    const f32x2 a01 = {x[g * 4 + 0] * inv, x[g * 4 + 1] * inv};
+    const f32x2 a23 = {x[g * 4 + 2] * inv, x[g * 4 + 3] * inv};
+    const bf16x2 b01 = __builtin_convertvector(a01, bf16x2);
+    const bf16x2 b23 = __builtin_convertvector(a23, bf16x2);
+    return {b01[0], b01[1], b23[0], b23[1]};
+  };
   if constexpr (NW == 8 && D == 128 && (CALLEE || !kBand)) {
     static_assert(QB == 1, "one 32-row block per wave");
     const float inv = 1.0f / l4[0][0];   // every lane holds the complete sum of its query
@@ -719,12 +726,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
       for (int db = 0; db < DB; ++db) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const f32x2 a01 = {o[db][0][g * 4 + 0] * inv, o[db][0][g * 4 + 1] * inv};
-          const f32x2 a23 = {o[db][0][g * 4 + 2] * inv, o[db][0][g * 4 + 3] * inv};
-          const bf16x2 b01 = __builtin_convertvector(a01, bf16x2);
-          const bf16x2 b23 = __builtin_convertvector(a23, bf16x2);
-          const bf16x4 out4 = {b01[0], b01[1], b23[0], b23[1]};
-          *reinterpret_cast<bf16x4*>(dst + db * 32 + g * 8 + half * 4) = out4;
+          *reinterpret_cast<bf16x4*>(dst + db * 32 + g * 8 + half * 4) = four(o[db][0], g, inv);
         }
       }
     }
@@ -747,12 +749,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
       for (int db = d0; db < d0 + 2; ++db) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const f32x2 a01 = {o[db][qb][g * 4 + 0] * inv, o[db][qb][g * 4 + 1] * inv};
-          const f32x2 a23 = {o[db][qb][g * 4 + 2] * inv, o[db][qb][g * 4 + 3] * inv};
-          const bf16x2 b01 = __builtin_convertvector(a01, bf16x2);
-          const bf16x2 b23 = __builtin_convertvector(a23, bf16x2);
-          const bf16x4 out4 = {b01[0], b01[1], b23[0], b23[1]};
-          *reinterpret_cast<bf16x4*>(stage_out + l32 * 128 + ((((db - d0) * 4 + g) ^ (l32 & 7)) << 4) + half * 8) = out4;
+          *reinterpret_cast<bf16x4*>(stage_out + l32 * 128 + ((((db - d0) * 4 + g) ^ (l32 & 7)) << 4) + half * 8) = four(o[db][qb], g, inv);
         }
       }
       wave_lds_order();
