@@ -293,7 +293,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
   // Key rows through an index list.  An index read in the loop from memory would hold up
   // the tile load that needs it by a whole trip (and wait, in order, for every load in
   // flight); so the indices of a tile travel to LDS one stage ahead of its K.  -1 =
-  // padding: an offset past the buffer's range, for which the hardware delivers zeros.
+  // padding (request_rows below).
   // Rearranged window of 8 heads x 75,600, D = 128: 632 us with the indices read from
   // memory, 618 with the ring.  Column lists read this way cost the loop nothing
   // measurable and save the pre-pass that gathers K and V rows (5-8 us ahead of the layer:
@@ -310,11 +310,16 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
   // formed from the ring: 24 heads x 1,998, 200 columns, D = 128: 17.5 -> 16.2 us; window of 8 heads x 75,600: 596 -> 584).
   // V(t + 1) is therefore requested before K(t + 2), or with a copy of them.
   unsigned row_at[LPT];
-  // kIndirect: the request of a wave's slabs whose rows start at these offsets, at these of their chunks
-  auto request_rows = [&](const __amdgpu_buffer_rsrc_t rsrc, unsigned char* const dst, const unsigned (&rows)[LPT], const unsigned (&chunk)[LPT]) {
+  // kIndirect: the request of a wave's slabs whose rows start at these offsets, at these of their chunks.  Padding starts at
+  // 2^32 - 16, past every head's end, and the sum with the chunk wraps.  For V the larger of the two is taken: zeros (P is 0 there,
+  // but the memory may hold infinities).  For K it may read the head's first row: those scores are masked.  (A start 256 bytes
+  // lower, without the maximum, lies inside the last row of heads that end there; the maximum for K as well: 24 heads x 1,998, 200
+  // columns, D = 128, 15.5 -> 15.9 us.)
+  auto request_rows = [&](auto is_k_tag, const __amdgpu_buffer_rsrc_t rsrc, unsigned char* const dst, const unsigned (&rows)[LPT],
+                          const unsigned (&chunk)[LPT]) {
 #pragma unroll
     for (int u = 0; u < LPT; ++u)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr)(dst + u * 1024), 16, (int)(rows[u] + chunk[u]), 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr)(dst + u * 1024), 16, (int)(decltype(is_k_tag)::value ? rows[u] + chunk[u] : max(rows[u], rows[u] + chunk[u])), 0, 0, 0);
   };
   // FIRST: the prologue's loads, whose indices are read from memory
   auto load_tile = [&](auto is_k_tag, const int buf, const int t, auto first_tag) {
@@ -330,9 +335,9 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
           c[u] = FIRST ? *reinterpret_cast<const int*>(reinterpret_cast<const char*>(cols + index_base(t)) + g_r[u])
                        : *reinterpret_cast<const int*>(sI + (t & 3) * (BC * 4) + g_r[u]);
 #pragma unroll
-        for (int u = 0; u < LPT; ++u) row_at[u] = c[u] < 0 ? 0xffffff00u : __umul24((unsigned)c[u], stride_bytes);
+        for (int u = 0; u < LPT; ++u) row_at[u] = c[u] < 0 ? 0xfffffff0u : __umul24((unsigned)c[u], stride_bytes);
       }
-      request_rows(rsrc, dst, row_at, IS_K ? g_k : g_v);
+      request_rows(is_k_tag, rsrc, dst, row_at, IS_K ? g_k : g_v);
     } else {
       const int row0 = (kBand ? entries[t].x : t + t_base) * BC;
 #pragma unroll
@@ -612,7 +617,7 @@ __device__ __forceinline__ void attn_body(const AttnLaunch& p, const Item& it, c
     settle_max(s_cur);
     if (kLoadsInside) request();
     if (kRowsInside) {
-      request_rows(rsrc_v, sV[PAR ^ 1] + wave * (LPT * 1024), v_rows, g_v);
+      request_rows(Int<0>{}, rsrc_v, sV[PAR ^ 1] + wave * (LPT * 1024), v_rows, g_v);
     }
     bf16x8 pf[KB2][2][QB];
     if (has1) scores(Int<PAR ^ 1>{}, s_next);

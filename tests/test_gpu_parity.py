@@ -259,6 +259,35 @@ def test_rows_behind_the_last_one_past_32_bits(D, options):
     del store
 
 
+@pytest.mark.parametrize("L,stride,D", [(9256395, 232, 128), (10737418, 200, 128), (16777215, 128, 64)])
+def test_padding_of_a_column_list_when_the_head_ends_close_to_32_bits(L, stride, D):
+    """Two heads whose last row ends within 256 bytes of byte 2^32, and the longest of contiguous rows at D = 64: the padding of
+    a column list must not reach into that row, whose V is not finite here."""
+    assert D == 64 or 2 ** 32 - 256 < (L - 1) * stride * 2 + D * 2 < 2 ** 32
+    cols = np.unique(np.random.default_rng(7).integers(0, L - 1, 70)).astype(np.int32)
+    table, params = np.asarray([W.VSTRIPE], dtype=np.int32), [{"cols": cols}]
+    q, v, out = (torch.as_strided(torch.empty(L * stride, dtype=torch.bfloat16, device=DEV), (1, 1, L, D), (L * stride, L * stride, stride, 1))
+                 for _ in range(3))
+    gen = torch.Generator(device=DEV).manual_seed(59)
+    for t in (q, v):
+        t.normal_(generator=gen)
+    v[:, :, L - 1] = float("inf")
+    out.fill_(float("nan"))
+    desc = svd.desc_of(q)
+    ws = torch.empty(svd.svd_plan_workspace_bytes(desc, table, params), dtype=torch.uint8, device=DEV)
+    plan = svd.svd_plan_create(desc, table, params, workspace=ws)
+    assert plan.table()["bf16"] == 4   # columns are read through their list
+    svd.svd_attn_forward_planned(plan, q, q, v, out)
+    torch.cuda.synchronize()
+    plan.close()
+    rows, idx = [0, 1, 127, 128, L // 2, L - 2, L - 1], torch.as_tensor(cols.astype(np.int64), device=DEV)
+    assert torch.isfinite(out[0, 0, :: 4099]).all() and torch.isfinite(out[0, 0, -300:]).all()
+    s = q[0, 0, rows].double() @ q[0, 0, idx].double().T / D ** 0.5
+    want = torch.softmax(s, 1) @ v[0, 0, idx].double()
+    for i, r in enumerate(rows):
+        assert_close(f64(out[0, 0, r: r + 1]), f64(want[i: i + 1]), f"row {r}")
+
+
 @pytest.mark.parametrize("L,D,split", [(1000, 64, 2), (1000, 64, 3), (1000, 128, 5), (777, 128, 8), (130, 64, 8),
                                        (60, 128, 4)])
 def test_dense_key_range_split(L, D, split):
