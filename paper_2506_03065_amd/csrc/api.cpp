@@ -251,7 +251,9 @@ int stripe_gather_pad(const Plan& p) {
 // D = 64 layers take the large tile (a K/V tile in LDS serves twice the rows, 3-4 % a tile) unless its lists, which
 // follow the bands less closely, hold more than that on top; the longest stay in groups, whose launches and tails no
 // longer count.
-int grid_waves(const Plan& p, const svd_plan_options* opt, int form, int n_cu) {
+// only_halved: the table is ahead only if it halves its long items.
+int grid_waves(const Plan& p, const svd_plan_options* opt, int form, int n_cu, bool* only_halved) {
+  *only_halved = false;
   if (n_cu < 1) return 0;
   if (opt && (opt->block_q || opt->block_k || opt->dense_split || opt->single_launch)) return 0;
   const int small_q = svd::kernel_small_block_q(p.desc.D);
@@ -263,9 +265,15 @@ int grid_waves(const Plan& p, const svd_plan_options* opt, int form, int n_cu) {
   const int waves = p.desc.D == 64 && per_slot > 400.0 && 2.0 * svd::grid_tiles(p, p.block_q) < 1.03 * small ? 8 : 4;
   const double dense_items = std::ceil(static_cast<double>(p.desc.L) / (32 * waves)) * count_dense_heads(p) * p.desc.B;
   const double dense_rounds = std::ceil(dense_items / (8 / waves * n_cu));
-  // (At D = 128 up to 400 tiles a slot the table is ahead, us, other form / table: 1 dense head of 6 x 30,000: 667 / 575, of 4 x
-  // 31,200: 638 / 559, of 8 x 34,012: 751 / 695, of 2 x 38,400: 764 / 748; above it within 2.6 %.  At D = 64, 66,000: 1,305 / 1,592.)
-  if (per_slot > (p.desc.D == 128 ? 400.0 : 300.0) && dense_rounds * p.n_k_blocks > 1.3 * per_slot) return 0;
+  // At D = 128 up to 400 tiles a slot the table is ahead where it halves such items, or where there are at most 30 to an XCD, a
+  // compute unit for nearly each.  us, layer kernel / table, one dense head: 6 x 30,720 (240 items, 0.70 of the layer) 669 / 560,
+  // 6 x 30,460 at 365 tiles 695 / 652; halved: 4 x 31,200 (0.76) 664 / 541, 3 x 33,000 (0.76) 704 / 669, 8 x 34,008 (0.81) 738 / 678,
+  // 2 x 38,400 814 / 756; whole and over 240: 4 x 31,200 (0.69) 648 / 699, 8 x 34,012 (0.70) 745 / 810, 3 x 33,000 (0.66) 717 / 767.
+  // Above 400 within 2.6 %.  At D = 64, 66,000: 1,305 / 1,592.
+  if (per_slot > 300.0 && dense_rounds * p.n_k_blocks > 1.3 * per_slot) {
+    if (p.desc.D != 128 || per_slot > 400.0) return 0;
+    *only_halved = 32.0 * dense_items > 30.0 * n_cu;
+  }
   return waves;
 }
 
@@ -298,8 +306,9 @@ struct GridTables {
 };
 GridTables add_grid_tables(Plan* p, const svd_plan_options* opt, int form, int n_cu, bool fp8) {
   GridTables g;
-  g.waves = grid_waves(*p, opt, form, n_cu);
-  if (g.waves) g.bf16 = svd::build_grid_table(p, g.waves * 32, 8 / g.waves * n_cu, true, &g.table);
+  bool only_halved = false;
+  g.waves = grid_waves(*p, opt, form, n_cu, &only_halved);
+  if (g.waves) g.bf16 = svd::build_grid_table(p, g.waves * 32, 8 / g.waves * n_cu, true, &g.table, only_halved);
   if (fp8 && grid_fp8(*p, opt, n_cu, &g.fp8_optional)) {
     bool stripes = false;
     for (const svd::Group& gr : p->groups) stripes = stripes || gr.mode == SVD_VSTRIPE;

@@ -441,7 +441,7 @@ struct TableRollback {
 };
 }  // namespace
 
-bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_stripes, GridTable* out) {
+bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_stripes, GridTable* out, bool only_halved) {
   TableRollback rollback(plan);
   const svd_tensor_desc& d = plan->desc;
   const int64_t L = d.L, bk = plan->block_k;
@@ -560,6 +560,7 @@ bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_strip
       }
   const bool halve = share > 100.0 && long_cost > 0.72 * total && 64 * n_long > 29 * static_cast<int64_t>(slots) &&
                      4 * n_long <= 3 * static_cast<int64_t>(slots);
+  if (only_halved && !halve) return false;
   std::vector<int32_t> merges;
   int64_t n_slots = 0;
   for (Segment& s : segs) {

@@ -125,10 +125,10 @@ const std::vector<BandList>* bands_on(const Group& g, int32_t block_q);
 // Key tiles that a launch of the whole layer on query tiles of block_q rows walks; *dense: those of the dense heads.
 double grid_tiles(const Plan& plan, int32_t block_q, double* dense = nullptr);
 // Appends the records to plan->ws_image.  slots: work-groups that the device runs at a time.  False: an index
-// would not fit, and the plan is as it was.
+// would not fit, or only_halved is asked for and the long items stay whole; the plan is as it was.
 // text_of_stripes = false: the text rows of vertical-stripe heads are left out (the FP8 variant, whose arrays of such
 // a head hold its columns only, computes them in a launch of their own).
-bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_stripes, GridTable* out);
+bool build_grid_table(Plan* plan, int32_t block_q, int slots, bool text_of_stripes, GridTable* out, bool only_halved = false);
 
 svd_status validate_desc(const svd_tensor_desc* desc);
 

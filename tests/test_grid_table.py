@@ -118,6 +118,22 @@ def test_which_long_items_are_halved(replay, tmp_path, shape, items, chunks):
     assert int(first[10]) <= 1.5 * 512
 
 
+@pytest.mark.parametrize("shape,waves,items", [
+    ((128, 1, 3, 0, 0, 1560, 20), 4, 244),   # three quarters of the layer in 244 long dense items of 1.6 shares: halved
+    ((128, 1, 4, 0, 0, 1560, 20), 0, 0),     # 0.7 of it: they would stay whole, more than 30 to an XCD
+    ((128, 1, 4, 0, 0, 1536, 20), 4, 0),     # 240 items, 30 to an XCD: whole
+    ((128, 1, 2, 0, 0, 1920, 20), 0, 0),     # over 400 tiles a slot
+    ((128, 1, 3, 0, 0, 1500, 20), 4, 235)])  # under 300
+def test_long_uneven_dense_items_are_halved_or_leave_the_table(replay, tmp_path, shape, waves, items):
+    """Both sides of each line of the rule at D = 128 between 300 and 400 tiles a slot, with 256 compute units."""
+    res = run(replay, tmp_path, [layer_text(mixed_layer(*shape), 0, rounds=1, tensors=0)])
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+    assert f"layer mixed: table waves {waves}," in res.stdout, res.stdout
+    if waves:
+        first = next(line.split() for line in res.stdout.splitlines() if line.startswith("grid:"))
+        assert (int(first[6]), int(first[10])) == (items, 2 * items), res.stdout
+
+
 def test_a_table_that_cannot_be_built_leaves_no_trace(tmp_path):
     exe = str(tmp_path / "grid_table_fails")
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", STUB, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
