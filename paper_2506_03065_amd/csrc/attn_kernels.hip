@@ -141,7 +141,9 @@ struct Item {
 // can tell a transposing read of one V tile from the tile loads into the other buffers: out of
 // one array every stage waited, before the first of its V reads, after a third of its MFMAs, for the
 // loads that it had requested itself.  (42 heads x 32,760, D = 128: 2,596 -> 2,551 us; 40 heads x
-// 75,600, 18 of them dense, layer kernel: 43.56 -> 42.90 ms; short layers the same.)
+// 75,600, 18 of them dense, layer kernel: 43.56 -> 42.90 ms; short layers the same.  Whole dense items two to a
+// unit while other units idle, where power is no limit, lose by it: one dense head and ten sparse ones x 30,156, D = 64, 359 ->
+// 377; three and six x 15,626, D = 128, 394 -> 402.)
 enum { LDS_K0, LDS_K1, LDS_V0, LDS_V1, LDS_INDEX };
 template <int D, int BC, int PART>
 __device__ __forceinline__ unsigned char* lds_part() {
