@@ -69,13 +69,27 @@ def test_random_layer(seed):
             assert not out[:, h].view(torch.int16).any() and not out8[:, h].view(torch.int16).any()
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("step,w", [(17, 3), (9, 2), (33, 0), (64, 31), (5, 2)])
+def test_several_runs_in_one_tile(D, step, w):
+    """Seven bands `step` apart: a key tile is crossed by up to seven runs (step 5 merges all into one), with their edges
+    in every place of a lane's elements and past both ends of the sequence, in bf16 and FP8."""
+    L = 777
+    params = {"half_width": w, "offsets": tuple(i * step for i in range(-3, 4))}
+    wl = W.Workload("runs", -1, 1, 2, L, D, 111, 7, 0, np.full(2, W.MULTIDIAG, dtype=np.int32), [params, dict(params)], 97)
+    q, k, v = (t.to(DEV) for t in W.make_qkv(wl))
+    check_layer(wl, q, k, v, run_planned(wl, q, k, v))
+    out8, _ = run_fp8(wl, q, k, v)
+    check_layer_fp8(wl, q, k, v, out8)
+
+
 FORMS = {"table": {}, "layer": {"single_launch": 1}, "groups": {"single_launch": 2}, "groups-large": {"single_launch": 2, "block_q": 256}}
 
 
 @pytest.mark.parametrize("form", list(FORMS))
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("step,w", [(17, 3), (9, 2), (33, 0), (64, 31), (5, 2)])
-def test_several_runs_in_one_tile(D, step, w, form):
+def test_several_runs_in_one_tile_in_every_launch_form(D, step, w, form):
     """Seven bands `step` apart: a key tile is crossed by up to seven runs (step 5 merges all into one), with their edges
     in every place of a lane's elements and past both ends of the sequence, and a band over positions in any frames; in bf16
     from the table (four waves), the layer kernel and a launch per group on either query tile, and in FP8 from the table and

@@ -97,6 +97,20 @@ def test_which_layers_run_from_a_table(replay, tmp_path, shape, waves):
     assert f"layer mixed: table waves {waves}," in res.stdout, res.stdout
 
 
+@pytest.mark.parametrize("shape,cut", [
+    ((64, 2, 3, 1, 1, 1000, 20), True),      # long items three quarters of the layer, a quarter above the share: halved
+    ((64, 1, 8, 4, 4, 1000, 20), False),     # two fifths: whole
+    ((64, 2, 3, 1, 1, 600, 20), False),      # under 100 tiles a slot: whole up to twice the share
+    ((128, 2, 3, 1, 1, 1000, 20), True),
+    ((128, 1, 3, 1, 1, 1500, 20), False)])   # two thirds: whole, though 1.5 times the share
+def test_which_long_items_are_halved(replay, tmp_path, shape, cut):
+    """Both sides of the rule that cuts items above an even share, with 256 compute units."""
+    res = run(replay, tmp_path, [layer_text(mixed_layer(*shape), 0, rounds=1, tensors=0)])
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+    first = next(line.split() for line in res.stdout.splitlines() if line.startswith("grid:"))   # (the last one is of a rotated table)
+    assert (int(first[2]), int(first[6]) > 0) == (4, cut), res.stdout
+
+
 @pytest.mark.parametrize("shape,items,chunks", [
     ((64, 2, 3, 1, 1, 1000, 20), 314, 2),     # long items of 1.3 shares, three quarters of the layer: halved
     ((128, 2, 3, 1, 1, 1000, 20), 314, 2),
@@ -109,7 +123,7 @@ def test_which_layers_run_from_a_table(replay, tmp_path, shape, waves):
     ((128, 1, 2, 0, 0, 1200, 20), 188, 2),    # 2.2 shares: two pieces of 1.1, as without the rule
     ((128, 1, 1, 0, 0, 1100, 20), 172, 4),    # 2.6 shares: the two pieces of 1.3 halved
     ((128, 1, 2, 0, 0, 1550, 20), 243, 2)])   # 1.7 shares, 243 items
-def test_which_long_items_are_halved(replay, tmp_path, shape, items, chunks):
+def test_into_how_many_pieces_long_items_are_cut(replay, tmp_path, shape, items, chunks):
     """Both sides of the rule that halves long items, with 256 compute units: how many are cut, and into how many pieces."""
     res = run(replay, tmp_path, [layer_text(mixed_layer(*shape), 0, rounds=1, tensors=0)])
     assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
